@@ -14,7 +14,8 @@
  * attention entries also take 2 and 3: the tuned kernels with a choice they
  * normally make from the shape fixed, so that tests reach both variants on any
  * shape -- GEMM: 2 = full 256 x 256 tiles only, 3 = half-height tiles only, 4 (stage_kernel_gemm, forward and
- * input-gradient layouts) = 128 x 128 tiles only;
+ * input-gradient layouts) = 128 x 128 tiles only; in fp32 2 / 3 / 4 = tiles of 64 x 64 / 32 x 32 / 16 x 16 (weight gradients:
+ * 32 x 32 for 4 as well) for the products and the two fused-activation entries;
  * attention: 2 / 3 = forward and dQ workgroups of 8 / 4 wavefronts (dK/dV workgroups of 128 keys), 4 = forward and dQ
  * workgroups of 64 queries whose two wavefronts per query block each take half of the keys, dK/dV workgroups of 64 keys.
  * Return: 0, or STAGE_E_INVAL for
@@ -40,16 +41,16 @@ int stage_kernel_gemm(int dtype, int mode, int M, int N, int K, const void* A, i
 /* The forward FFN-in product with its activation (paper section 3.1: part of a chunk's F block): Z = A.B with B [K, f]
  * (GELU) or [K, 2f] (SwiGLU, columns gate | up), and Aout [M, f] = gelu(Z) or silu(Z[:, :f]) * Z[:, f:].  The tuned kernel
  * forms the activation from the fp32 accumulators in the product's epilogue (one rounding less than reading Z back, and Z
- * is not re-read); the plain kernels (kernel_set 1, or fp32) run the product and then the activation kernel on the stored
- * Z, which needs ldz = f or 2f and lda_out = f.  kernel_set 2 / 3 as for stage_kernel_gemm. */
+ * is not re-read; in fp32 rows must be dense, ldz = f or 2f and lda_out = f); the plain kernels (kernel_set 1) run the
+ * product and then the activation kernel on the stored Z, dense rows only.  kernel_set 2 / 3 as for stage_kernel_gemm. */
 int stage_kernel_gemm_act(int dtype, int act, int M, int f, int K, const void* A, int64_t lda, const void* B, int64_t ldb,
                           void* Z, int64_t ldz, void* Aout, int64_t lda_out, int kernel_set, void* hip_stream);
 
 /* The input-gradient product of the FFN-out map with the activation backward (part of a chunk's B block): da = dY.W^T with
  * W [f, K] (the map's weight, [in, out]), then Z [M, f] (GELU) or [M, 2f] (SwiGLU, gate | up) is overwritten by
  * dZ = da * gelu'(Z), or dgate = da * up * silu'(gate), dup = da * silu(gate).  The tuned kernel does this in the
- * product's epilogue on the fp32 accumulators (da is never stored; da_scratch may be NULL); the plain kernels (kernel_set
- * 1, or fp32) store da [M, f] in da_scratch and run the activation kernel, which needs ldz = f or 2f. */
+ * product's epilogue on the fp32 accumulators (bf16: da is never stored and da_scratch may be NULL); fp32 and the plain
+ * kernels (kernel_set 1) store da [M, f] in da_scratch as well and need ldz = f or 2f. */
 int stage_kernel_gemm_act_bwd(int dtype, int act, int M, int f, int K, const void* dY, int64_t ldy, const void* W, int64_t ldw,
                               void* Z, int64_t ldz, void* da_scratch, int kernel_set, void* hip_stream);
 

@@ -125,6 +125,16 @@ bool attn_mfma_supported(const AttnArgs& a);
 hipError_t attn_fwd_mfma(const AttnArgs& a, hipStream_t s);
 hipError_t attn_bwd_mfma(const AttnArgs& a, hipStream_t s);
 
+// fp32 path: matrix products and attention on the fp32 matrix cores.  shape: 0 = chosen from the sizes; 1, 2, 3 = 64 x 64,
+// 32 x 32, 16 x 16 tiles (weight gradients: 2 and 3 are the same).  With act_bwd, a non-null C receives da as well.
+bool gemm32_supported(const GemmArgs& g);
+hipError_t gemm32(const GemmArgs& g, hipStream_t s, int shape = 0);
+bool wgrad32_group_supported(const GemmArgs* list, int n, int nseg, const int64_t* seg_delta);
+hipError_t wgrad32_group(const GemmArgs* list, int n, int nseg, const int64_t* seg_delta, hipStream_t s, int shape = 0);
+bool attn32_supported(const AttnArgs& a);
+hipError_t attn32_fwd(const AttnArgs& a, hipStream_t s);
+hipError_t attn32_bwd(const AttnArgs& a, hipStream_t s);
+
 // scalar conversions
 __device__ __forceinline__ float to_f32(float v) { return v; }
 __device__ __forceinline__ float to_f32(bf16 v) { return (float)v; }

@@ -1,7 +1,6 @@
 // Plain reference HIP kernels: one kernel per mathematical step, fp32 arithmetic,
-// any storage dtype.  They are the compute path of the fp32 configuration (whose
-// shapes are launch-bound, not roofline-bound) and an A/B baseline for the tuned
-// bf16 kernels.  Definitions follow the split of a linear layer's backward into
+// any storage dtype.  They take what the tuned kernels do not (unaligned operands, odd
+// widths) and are an A/B baseline for them.  Definitions follow the split of a linear layer's backward into
 // input-gradient and weight-gradient products (paper Appendix B).
 #include "common.h"
 

@@ -298,6 +298,7 @@ int do_gemm(stage* st, int mode, int M, int N, int K, const void* A, int64_t lda
   g.bias = bias;
   ProfScope ps(st, STAGE_K_GEMM_NN + mode, 2.0 * M * N * K);
   if (st->kernel_set == 0 && st->dt == DT_BF16 && gemm_mfma_supported(g)) HIPCHK(gemm_mfma(g, st->stream));
+  else if (st->kernel_set == 0 && st->dt == DT_F32 && gemm32_supported(g)) HIPCHK(gemm32(g, st->stream));
   else HIPCHK(gemm_ref(st->dt, g, st->stream));
   return STAGE_OK;
 }
@@ -309,10 +310,10 @@ bool try_gemm_act(stage* st, int* rc, int M, int f, int K, const void* A, const 
   const int fin = st->cfg.act == STAGE_ACT_SWIGLU ? 2 * f : f;
   GemmArgs g{GEMM_NN, M, fin, K, A, (int64_t)K, W, (int64_t)fin, z, (int64_t)fin, nullptr, 0, 0, 0, 0};
   g.act = st->cfg.act == STAGE_ACT_SWIGLU ? 2 : 1; g.C2 = a; g.ldc2 = f; g.bias = bias;
-  if (st->kernel_set != 0 || st->dt != DT_BF16 || !gemm_mfma_supported(g)) return false;
+  if (st->kernel_set != 0 || !(st->dt == DT_BF16 ? gemm_mfma_supported(g) : gemm32_supported(g))) return false;
   ProfScope ps(st, STAGE_K_GEMM_NN, 2.0 * M * fin * K);
   *rc = STAGE_OK;
-  if (gemm_mfma(g, st->stream) != hipSuccess) { st->sticky = STAGE_E_HIP; *rc = STAGE_E_HIP; }
+  if ((st->dt == DT_BF16 ? gemm_mfma(g, st->stream) : gemm32(g, st->stream)) != hipSuccess) { st->sticky = STAGE_E_HIP; *rc = STAGE_E_HIP; }
   return true;
 }
 
@@ -322,10 +323,10 @@ bool try_gemm_act_bwd(stage* st, int* rc, int M, int f, int K, const void* dy, c
   const int nop = st->cfg.act == STAGE_ACT_SWIGLU ? 2 : 1;
   GemmArgs g{GEMM_NT, M, f, K, dy, (int64_t)K, W, (int64_t)K, nullptr, (int64_t)f, nullptr, 0, 0, 0, 0};
   g.act_bwd = nop; g.Z = z; g.ldz = (int64_t)nop * f;
-  if (st->kernel_set != 0 || st->dt != DT_BF16 || !gemm_mfma_supported(g)) return false;
+  if (st->kernel_set != 0 || !(st->dt == DT_BF16 ? gemm_mfma_supported(g) : gemm32_supported(g))) return false;
   ProfScope ps(st, STAGE_K_GEMM_NT, 2.0 * M * f * K);
   *rc = STAGE_OK;
-  if (gemm_mfma(g, st->stream) != hipSuccess) { st->sticky = STAGE_E_HIP; *rc = STAGE_E_HIP; }
+  if ((st->dt == DT_BF16 ? gemm_mfma(g, st->stream) : gemm32(g, st->stream)) != hipSuccess) { st->sticky = STAGE_E_HIP; *rc = STAGE_E_HIP; }
   return true;
 }
 
@@ -385,6 +386,7 @@ int forward_layer(stage* st, int l, const LayerBuf& o, void* y_l, bool y_lp) {
   {
     ProfScope ps(st, STAGE_K_ATTN_FWD, attn_flops(st, false));
     if (st->kernel_set == 0 && st->dt == DT_BF16 && attn_mfma_supported(a)) HIPCHK(attn_fwd_mfma(a, st->stream));
+    else if (st->kernel_set == 0 && st->dt == DT_F32 && attn32_supported(a)) HIPCHK(attn32_fwd(a, st->stream));
     else HIPCHK(attn_fwd_ref(st->dt, a, st->stream));
   }
   rc = do_gemm(st, GEMM_NN, D.T, D.d, D.da, o.o, D.da, W.wo, D.d, o.x1, D.d, o.x, D.d, 0, 1, 1, W.bo);
@@ -477,6 +479,7 @@ int exec_backward_input(stage* st, int mb, const void* dy, void* dx, int l0, int
     {
       ProfScope ps(st, STAGE_K_ATTN_BWD, attn_flops(st, true));
       if (st->kernel_set == 0 && st->dt == DT_BF16 && attn_mfma_supported(a)) HIPCHK(attn_bwd_mfma(a, st->stream));
+      else if (st->kernel_set == 0 && st->dt == DT_F32 && attn32_supported(a)) HIPCHK(attn32_bwd(a, st->stream));
       else HIPCHK(attn_bwd_ref(st->dt, a, st->stream));
     }
     if (D.rope) {    // gradients with respect to the unrotated q and k: the transposed rotation
@@ -504,11 +507,15 @@ hipError_t wgrad_list(DType dt, int kernel_set, const GemmArgs* list, int n, int
   if (n == 0) return hipSuccess;
   if (kernel_set == 0 && dt == DT_BF16 && gemm_mfma_wgrad_group_supported(list, n, nseg, seg_delta))
     return gemm_mfma_wgrad_group(list, n, nseg, seg_delta, s);
+  if (kernel_set == 0 && dt == DT_F32 && wgrad32_group_supported(list, n, nseg, seg_delta))
+    return wgrad32_group(list, n, nseg, seg_delta, s);
   for (int sg = 0; sg < nseg; ++sg)
     for (int i = 0; i < n; ++i) {
       GemmArgs g = list[i];
       if (sg > 0) { g.A = (const char*)g.A + seg_delta[sg]; g.B = (const char*)g.B + seg_delta[sg]; }
-      hipError_t e = (kernel_set == 0 && dt == DT_BF16 && gemm_mfma_supported(g)) ? gemm_mfma(g, s) : gemm_ref(dt, g, s);
+      const hipError_t e = (kernel_set == 0 && dt == DT_BF16 && gemm_mfma_supported(g)) ? gemm_mfma(g, s)
+                           : (kernel_set == 0 && dt == DT_F32 && gemm32_supported(g))   ? gemm32(g, s)
+                                                                                        : gemm_ref(dt, g, s);
       if (e != hipSuccess) return e;
     }
   return hipSuccess;
@@ -963,6 +970,7 @@ const char* stage_strerror(int code) {
 extern "C" {
 
 static int hip_rc(hipError_t e) { return e == hipSuccess ? STAGE_OK : (e == hipErrorInvalidValue ? STAGE_E_INVAL : STAGE_E_HIP); }
+static int shape32(int kernel_set) { return kernel_set >= 2 && kernel_set <= 4 ? kernel_set - 1 : 0; }
 static bool dtype_ok(int dt) { return dt == STAGE_DTYPE_FP32 || dt == STAGE_DTYPE_BF16; }
 
 int stage_kernel_gemm(int dtype, int mode, int M, int N, int K, const void* A, int64_t lda, const void* B, int64_t ldb,
@@ -972,6 +980,7 @@ int stage_kernel_gemm(int dtype, int mode, int M, int N, int K, const void* A, i
   GemmArgs g{mode, M, N, K, A, lda, B, ldb, C, ldc, R, ldr, acc_f32};
   if (kernel_set != 1 && dtype == STAGE_DTYPE_BF16 && gemm_mfma_supported(g))
     return hip_rc(gemm_mfma(g, (hipStream_t)hip_stream, kernel_set == 2 ? 1 : kernel_set == 3 ? 2 : kernel_set == 4 ? 3 : 0));
+  if (kernel_set != 1 && dtype == STAGE_DTYPE_FP32 && gemm32_supported(g)) return hip_rc(gemm32(g, (hipStream_t)hip_stream, shape32(kernel_set)));
   return hip_rc(gemm_ref((DType)dtype, g, (hipStream_t)hip_stream));
 }
 
@@ -985,8 +994,9 @@ int stage_kernel_gemm_act(int dtype, int act, int M, int f, int K, const void* A
   g.act = act == STAGE_ACT_SWIGLU ? 2 : 1; g.C2 = Aout; g.ldc2 = lda_out;
   if (kernel_set != 1 && dtype == STAGE_DTYPE_BF16 && gemm_mfma_supported(g))
     return hip_rc(gemm_mfma(g, (hipStream_t)hip_stream, kernel_set == 2 ? 1 : kernel_set == 3 ? 2 : 0));
-  // plain kernels: the product, then the activation from the stored z (needs dense rows)
+  // fp32, and the plain kernels (the product, then the activation from the stored z): dense rows
   if (ldz != fin || lda_out != f) return STAGE_E_INVAL;
+  if (kernel_set != 1 && dtype == STAGE_DTYPE_FP32 && gemm32_supported(g)) return hip_rc(gemm32(g, (hipStream_t)hip_stream, shape32(kernel_set)));
   g.act = 0; g.C2 = nullptr;
   const hipError_t e = gemm_ref((DType)dtype, g, (hipStream_t)hip_stream);
   if (e != hipSuccess) return hip_rc(e);
@@ -1004,9 +1014,11 @@ int stage_kernel_gemm_act_bwd(int dtype, int act, int M, int f, int K, const voi
   g.act_bwd = nop; g.Z = Z; g.ldz = ldz;
   if (kernel_set != 1 && dtype == STAGE_DTYPE_BF16 && gemm_mfma_supported(g))
     return hip_rc(gemm_mfma(g, (hipStream_t)hip_stream, kernel_set == 2 ? 1 : kernel_set == 3 ? 2 : 0));
-  // plain kernels: the product into the scratch, then the activation backward kernel (dense z rows)
+  // fp32, and the plain kernels (the product into the scratch, then the activation backward kernel): dense z rows
   if (!da_scratch || ldz != (int64_t)nop * f) return STAGE_E_INVAL;
-  g.act_bwd = 0; g.Z = nullptr; g.C = da_scratch;
+  g.C = da_scratch;
+  if (kernel_set != 1 && dtype == STAGE_DTYPE_FP32 && gemm32_supported(g)) return hip_rc(gemm32(g, (hipStream_t)hip_stream, shape32(kernel_set)));
+  g.act_bwd = 0; g.Z = nullptr;
   const hipError_t e = gemm_ref((DType)dtype, g, (hipStream_t)hip_stream);
   if (e != hipSuccess) return hip_rc(e);
   ActArgs ac{}; ac.kind = act; ac.rows = M; ac.f = f; ac.z = Z; ac.da = da_scratch;
@@ -1039,6 +1051,7 @@ int stage_kernel_attention_fwd(int dtype, int b, int s, int h, int hkv, int hd, 
   a.qkv = qkv; a.ld = (int64_t)(h + 2 * hkv) * hd; a.o = o; a.lse = lse;
   a.width = kernel_set == 2 ? 1 : kernel_set == 3 ? 2 : kernel_set == 4 ? 3 : 0;
   if (kernel_set != 1 && dtype == STAGE_DTYPE_BF16 && attn_mfma_supported(a)) return hip_rc(attn_fwd_mfma(a, (hipStream_t)hip_stream));
+  if (kernel_set != 1 && dtype == STAGE_DTYPE_FP32 && attn32_supported(a)) return hip_rc(attn32_fwd(a, (hipStream_t)hip_stream));
   return hip_rc(attn_fwd_ref((DType)dtype, a, (hipStream_t)hip_stream));
 }
 
@@ -1077,6 +1090,7 @@ int stage_kernel_attention_bwd_ws(int dtype, int b, int s, int h, int hkv, int h
   a.dkv_part = attn_bwd_part_bytes(b, s, h, hkv, hd) ? (float*)scratch : nullptr;
   a.width = kernel_set == 2 ? 1 : kernel_set == 3 ? 2 : kernel_set == 4 ? 3 : 0;
   if (kernel_set != 1 && dtype == STAGE_DTYPE_BF16 && attn_mfma_supported(a)) return hip_rc(attn_bwd_mfma(a, (hipStream_t)hip_stream));
+  if (kernel_set != 1 && dtype == STAGE_DTYPE_FP32 && attn32_supported(a)) return hip_rc(attn32_bwd(a, (hipStream_t)hip_stream));
   return hip_rc(attn_bwd_ref((DType)dtype, a, (hipStream_t)hip_stream));
 }
 

@@ -1,0 +1,94 @@
+"""The fp32 matrix-core kernels at the edges of their tiles, every tile shape forced, against 64-bit products.
+
+Tolerance: a product over K terms of unit-variance operands, summed in fp32 in any order, is off by at most about
+eps * sqrt(K) of its own spread sqrt(K) per rounding, i.e. a few times 2^-24 * sqrt(K) relative to the largest element;
+2e-5 leaves that a factor of ten at the largest K here.
+"""
+import numpy as np
+import pytest
+
+from oracle import stage_oracle as so
+from paper_2507_00217_amd import synth
+from tests.gpu_util import to_dev, to_np
+from tests.test_gpu_kernels import L, P
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-5
+
+# one tile and less, one past a tile edge in M, reductions below / at / past a 16-deep slice, W slices and their double buffer
+SHAPES = [(1, 4, 4), (16, 16, 16), (17, 20, 20), (33, 36, 132), (65, 68, 260), (63, 64, 1028), (130, 196, 524)]
+
+
+@pytest.mark.parametrize("shape", [0, 2, 3, 4])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_products(mode, shape, M, N, K):
+    import torch
+    if mode == 2:
+        M = (M + 3) // 4 * 4
+        K = K + 1                                   # a slow reduction index has no alignment
+    A = synth.normal(31, 1, (K, M) if mode == 2 else (M, K)); B = synth.normal(31, 2, (N, K) if mode == 1 else (K, N))
+    C0 = synth.normal(31, 3, (M, N))
+    ref = (A.astype(np.float64).T if mode == 2 else A.astype(np.float64)) @ (B.astype(np.float64).T if mode == 1 else B.astype(np.float64))
+    Ad, Bd, Rd = to_dev(A, "fp32"), to_dev(B, "fp32"), to_dev(C0, "fp32")
+    if mode == 2:
+        Cd = Rd.clone()
+        rc = L().stage_kernel_gemm(0, 2, M, N, K, P(Ad), M, P(Bd), N, P(Cd), N, None, 0, 1, shape, None)
+    else:
+        Cd = torch.full((M, N), float("nan"), device="cuda:0")
+        rc = L().stage_kernel_gemm(0, mode, M, N, K, P(Ad), K, P(Bd), Bd.shape[1], P(Cd), N, P(Rd), N, 0, shape, None)
+    assert rc == 0
+    assert so.max_rel_err(to_np(Cd), ref + C0) <= TOL
+
+
+@pytest.mark.parametrize("shape", [0, 2, 3, 4])
+@pytest.mark.parametrize("act", [0, 1])
+@pytest.mark.parametrize("M,f,K", [(1, 4, 4), (17, 20, 36), (65, 36, 132), (130, 100, 524)])
+def test_fused_activations(act, shape, M, f, K):
+    """FFN-in with its activation, FFN-out's input gradient with the activation backward (da is kept in the scratch too)."""
+    import torch
+    fin = (1 + act) * f
+    sh = so.Shape(1, 64, 1, 1, f, 1, 1, act="swiglu" if act else "gelu")
+    X, W = synth.normal(32, 1, (M, K)), synth.normal(32, 2, (K, fin), std=K ** -0.5)
+    dY, V = synth.normal(32, 3, (M, K)), synth.normal(32, 4, (f, K), std=K ** -0.5)
+    z = X.astype(np.float64) @ W.astype(np.float64)
+    a = z[:, :f] * so.sigmoid(z[:, :f]) * z[:, f:] if act else so.gelu(z)
+    da = dY.astype(np.float64) @ V.astype(np.float64).T
+    Zd, Aout, DA = (torch.full((M, n), float("nan"), device="cuda:0") for n in (fin, f, f))
+    Xd, Wd, dYd, Vd = (to_dev(t, "fp32") for t in (X, W, dY, V))
+    assert L().stage_kernel_gemm_act(0, act, M, f, K, P(Xd), K, P(Wd), fin, P(Zd), fin, P(Aout), f, shape, None) == 0
+    assert so.max_rel_err(to_np(Zd), z) <= TOL and so.max_rel_err(to_np(Aout), a) <= TOL
+    assert L().stage_kernel_gemm_act_bwd(0, act, M, f, K, P(dYd), K, P(Vd), K, P(Zd), fin, P(DA), shape, None) == 0
+    assert so.max_rel_err(to_np(DA), da) <= TOL
+    assert so.max_rel_err(to_np(Zd), so.act_backward(sh, z, da)) <= TOL
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("b,s,h,hkv,hd", [(1, 1, 1, 1, 64), (2, 16, 2, 1, 128), (1, 17, 3, 3, 64), (2, 129, 4, 2, 128), (1, 275, 6, 2, 64)])
+def test_attention_against_64_bits(b, s, h, hkv, hd, causal):
+    """Blocks of 16 queries and keys, eight wavefronts over them: one block, one past it, one past a full round of wavefronts."""
+    import torch
+    width = (h + 2 * hkv) * hd
+    g = torch.Generator().manual_seed(33)
+    qkv, do = torch.randn((b * s, width), generator=g), torch.randn((b * s, h * hd), generator=g)
+    x = qkv.double().requires_grad_()
+    outs, lses = [], []
+    for t in x.split(s, 0):
+        for j in range(h):
+            q, k, v = (t[:, o * hd:(o + 1) * hd] for o in (j, h + j // (h // hkv), h + hkv + j // (h // hkv)))
+            sc = q @ k.t() / hd ** 0.5
+            if causal:
+                sc = sc.masked_fill(torch.ones_like(sc, dtype=torch.bool).triu(1), -float("inf"))
+            lse = torch.logsumexp(sc, -1)
+            outs.append(torch.exp(sc - lse[:, None]) @ v); lses.append(lse)
+    o = torch.stack([torch.cat(outs[i * h:(i + 1) * h], 1) for i in range(b)]).view(b * s, h * hd)
+    o.backward(do.double())
+    dev = lambda t: t.to("cuda:0")
+    qkvd, dod = dev(qkv), dev(do)
+    od, dqkv = torch.full_like(dod, float("nan")), torch.full_like(qkvd, float("nan"))
+    lse, delta = (torch.full((b, h, s), float("nan"), device="cuda:0") for _ in range(2))
+    assert L().stage_kernel_attention_fwd(0, b, s, h, hkv, hd, causal, P(qkvd), P(od), P(lse), 0, None) == 0
+    assert L().stage_kernel_attention_bwd(0, b, s, h, hkv, hd, causal, P(qkvd), P(od), P(lse), P(dod), P(dqkv), P(delta), 0, None) == 0
+    assert so.max_rel_err(to_np(od), o.detach().numpy()) <= TOL
+    assert so.max_rel_err(to_np(lse), torch.stack(lses).view(b, h, s).detach().numpy()) <= TOL
+    assert so.max_rel_err(to_np(dqkv), x.grad.numpy()) <= TOL
