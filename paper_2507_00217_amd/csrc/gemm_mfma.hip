@@ -197,6 +197,23 @@ __device__ __forceinline__ bf16x8 frag(lds_char* const (&pt)[NB], int b, int ks)
   }
 }
 
+// the activation backward of four elements: da in fp32, the stashed pre-activation(s) in bf16
+__device__ __forceinline__ bf16x4 dgelu4(f32x4 da, bf16x4 z) {
+  bf16x4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = (bf16)(da[e] * dgelu_f32((float)z[e]));
+  return o;
+}
+__device__ __forceinline__ void dswiglu4(f32x4 da, bf16x4 gt, bf16x4 up, bf16x4& og, bf16x4& ou) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float gv = (float)gt[e], uv = (float)up[e], d = da[e];
+    const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-gv));
+    og[e] = (bf16)(d * uv * (sg + gv * sg * (1.f - sg)));
+    ou[e] = (bf16)(d * gv * sg);
+  }
+}
+
 // TN = 32-column groups per wavefront: 2 -> 8 wavefronts of 128x64 (two per SIMD, 128 accumulator registers each),
 // 4 -> 4 wavefronts of 128x128 (one per SIMD, 256 accumulator registers, a third less LDS read traffic)
 // K segments: the reduction may run over `nseg` operand pairs of equal shape, pair s being (A, B) moved by
@@ -204,14 +221,13 @@ __device__ __forceinline__ bf16x8 frag(lds_char* const (&pt)[NB], int b, int ks)
 // pass over K then does the work of nseg launches with a single read-modify-write of C, and -- fp32 accumulators
 // written to and read back from fp32 memory unchanged -- gives the same bits as those launches one after another.
 // WR, WC = rows and columns of 128 in the tile: (2, 2) -> 256 x 256 (wave grid 2 x WGN); (1, 2) -> 128 x 256 (wave grid
-// 1 x WGN, half the wavefronts); (1, 1) -> 128 x 128 (four wavefronts of 64 x 64); A must be a [row][k] operand unless
-// the tile is a full one.  The smaller tiles exist for the work a grid of full tiles would leave to a fraction of the
+// 1 x WGN, half the wavefronts; A must be a [row][k] operand); (1, 1) -> 128 x 128 (four wavefronts of 64 x 64).  The smaller tiles exist for the work a grid of full tiles would leave to a fraction of the
 // CUs: the last, partly filled round of a product, and products with few tiles.
-template <bool AKC, bool BKC, int EPI, int TN, int WR = 2, int WC = 2>
+template <bool AKC, bool BKC, int EPI, int TN, int WR = 2, int WC = 2, int SMALL_DEPTH = 4>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds_char* smem, int nseg = 1,
                                           const int64_t* seg_delta = nullptr) {
-  static_assert(WR == 2 || (WR == 1 && AKC), "the smaller tiles take a [row][k] A operand");
-  static_assert(WC == 2 || (WR == 1 && TN == 2 && (EPI == EPI_STORE || EPI == EPI_RESID)), "the 128 x 128 tile: plain epilogues only");
+  static_assert(WR == 2 || AKC || WC == 1, "the half-height tile takes a [row][k] A operand");
+  static_assert(WC == 2 || (WR == 1 && TN == 2), "the 128 x 128 tile: four wavefronts of 64 x 64");
   constexpr bool GLU = EPI == EPI_SWIGLU;
   static_assert(!GLU || (TN == 2 && !BKC), "gate and up blocks are the two halves of a wavefront's columns");
   constexpr int BMV = WR * 128, BNV = WC * 128;                                    // tile: BMV rows, BNV columns
@@ -219,6 +235,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   constexpr int WGN = BNV / (TN * 32), WAVES = (BMV / RW) * WGN;
   constexpr int A_BYTES = BMV * BK * 2, B_BYTES = BNV * BK * 2;
   constexpr int PCS = BNV / 8;                                                     // 16-byte pieces per row of C / per reduction row of a [k][row] B tile
+  constexpr int PCA = BMV / 8;                                                     // ... of a [k][row] A tile
   constexpr int CHA = (A_BYTES / 16) / (WAVES * 64), CHB = (B_BYTES / 16) / (WAVES * 64); // loads per thread and K tile
   constexpr int NI = RW / 16, NJ = 2 * TN;                                         // 16 x 16 accumulator blocks per wavefront
   // The ring of operand tiles (see below): DEPTH K tiles ahead of the one being multiplied, 2 * DEPTH + 1 slots.  The
@@ -227,7 +244,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   // that come from HBM rather than from a cache arrive late, and products of this tile ran a quarter to a third slower
   // on cold operands than on warm ones.
   constexpr bool SMALL = WR == 1 && WC == 1;
-  constexpr int SLOT = SMALL ? TILE_BYTES / 2 : TILE_BYTES, DEPTH = SMALL ? 4 : 2, NSLOT = 2 * DEPTH + 1;
+  constexpr int SLOT = SMALL ? TILE_BYTES / 2 : TILE_BYTES, DEPTH = SMALL ? SMALL_DEPTH : 2, NSLOT = 2 * DEPTH + 1;
   static_assert(A_BYTES <= SLOT && B_BYTES <= SLOT && (size_t)NSLOT * SLOT <= LDS_BYTES, "ring fits");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -238,7 +255,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   const unsigned bytesB = (unsigned)(((int64_t)((BKC ? g.N : g.K) - 1) * g.ldb + (BKC ? g.K : g.N)) * 2);
   rsrc_words rsA = raw_rsrc(g.A, bytesA), rsB = raw_rsrc(g.B, bytesB);
   unsigned offa[CHA], offb[CHB];
-  tile_offsets<AKC, WAVES, CHA>(offa, g.lda, m0, g.M, wave, lane);
+  tile_offsets<AKC, WAVES, CHA, AKC ? 32 : PCA>(offa, g.lda, m0, g.M, wave, lane);
   tile_offsets<BKC, WAVES, CHB, PCS>(offb, g.ldb, n0, g.N, wave, lane, GLU ? g.N / 2 : 0);
 
   // LDS map: a ring of NSLOT slots of one operand tile each; the operand tiles of the reduction take the slots in the
@@ -305,7 +322,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   lds_char *pa[NPA], *pb[NPB];
   {
     unsigned ada[NPA], adb[NPB];
-    frag_offsets<AKC, NPA>(ada, wm, lane);
+    frag_offsets<AKC, NPA, PCA>(ada, wm, lane);
     frag_offsets<BKC, NPB, PCS>(adb, wn, lane);
 #pragma unroll
     for (int x = 0; x < NPA; ++x) pa[x] = smem + ada[x];
@@ -346,7 +363,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
         if (n % 2 == 0 && n / 2 < NFRAG) {
           const int f = n / 2;
           if (f < NJ) fb[cur ^ 1][f] = frag<BKC, NPB, PCS>(pb, f, ks_next);
-          else fa[cur ^ 1][f - NJ] = frag<AKC, NPA>(pa, f - NJ, ks_next);
+          else fa[cur ^ 1][f - NJ] = frag<AKC, NPA, PCA>(pa, f - NJ, ks_next);
         }
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (do_load) if (n % GAP == GAP - 1) {
@@ -364,7 +381,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
 #pragma unroll
   for (int j = 0; j < NJ; ++j) fb[0][j] = frag<BKC, NPB, PCS>(pb, j, 0);
 #pragma unroll
-  for (int i = 0; i < NI; ++i) fa[0][i] = frag<AKC, NPA>(pa, i, 0);
+  for (int i = 0; i < NI; ++i) fa[0][i] = frag<AKC, NPA, PCA>(pa, i, 0);
   int kt = 0;
   auto trip = [&](auto tail_c) __attribute__((always_inline)) {
     constexpr bool tail = decltype(tail_c)::value;
@@ -417,7 +434,37 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
     }
   }
   const int sub_b = (col_l & 4) * 2;      // byte inside a 16-byte piece at which this lane's 4 columns start
-  if constexpr (EPI == EPI_DGELU || EPI == EPI_DSWIGLU) {
+  if constexpr ((EPI == EPI_DGELU || EPI == EPI_DSWIGLU) && SMALL) {
+    // Activation backward on a 128 x 128 tile: z is read and rewritten where the accumulators lie, 4 columns of a row at a
+    // time.  The rows go through L2 in 32-byte pieces, which a tile this size does not notice; all reads of a block row are
+    // in flight at once.
+    const int f = g.N;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int m = m0 + wm + i * 16 + row_l;
+      bf16* zr = (bf16*)g.Z + (int64_t)min(m, g.M - 1) * g.ldz;
+      bf16x4 gt[NJ], up[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int n = min(n0 + wn + j * 16 + col_l, f - 4);
+        gt[j] = *reinterpret_cast<const bf16x4*>(zr + n);
+        if (EPI == EPI_DSWIGLU) up[j] = *reinterpret_cast<const bf16x4*>(zr + f + n);
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int n = n0 + wn + j * 16 + col_l;
+        if (m >= g.M || n >= f) continue;
+        if (EPI == EPI_DGELU) *reinterpret_cast<bf16x4*>(zr + n) = dgelu4(acc[i][j], gt[j]);
+        else {
+          bf16x4 og, ou;
+          dswiglu4(acc[i][j], gt[j], up[j], og, ou);
+          *reinterpret_cast<bf16x4*>(zr + n) = og;
+          *reinterpret_cast<bf16x4*>(zr + f + n) = ou;
+        }
+      }
+    }
+    return;
+  } else if constexpr (EPI == EPI_DGELU || EPI == EPI_DSWIGLU) {
     // Activation backward on the fp32 accumulators (da), in place over the stashed z, in four quarters of the tile: a
     // quarter takes 32 rows from each 128-row half, so that every wavefront owns two of its accumulator block rows in
     // it.  The quarter's z columns (gate, and for SwiGLU up) come global -> LDS directly, whole rows (row r's piece p at
@@ -461,23 +508,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
           const int p = (wn + j * 16 + col_l) >> 3;
           lds_char* at = buf + sr * 512 + ((p ^ (sr & 31)) << 4) + sub_b;
           if (EPI == EPI_DGELU) {
-            bf16x4 u = *(lds_b4)at, o4;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float uv = (float)u[e];
-              o4[e] = (bf16)(acc[i][j][e] * dgelu_f32(uv));
-            }
-            *(lds_b4)at = o4;
+            *(lds_b4)at = dgelu4(acc[i][j], *(lds_b4)at);
             __builtin_amdgcn_sched_barrier(0);
           } else {
-            bf16x4 gt = *(lds_b4)at, up = *(lds_b4)(at + OPB), og, ou;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float gv = (float)gt[e], uv = (float)up[e], d = acc[i][j][e];
-              const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-gv));
-              og[e] = (bf16)(d * uv * (sg + gv * sg * (1.f - sg)));
-              ou[e] = (bf16)(d * gv * sg);
-            }
+            bf16x4 og, ou;
+            dswiglu4(acc[i][j], *(lds_b4)at, *(lds_b4)(at + OPB), og, ou);
             *(lds_b4)at = og;
             *(lds_b4)(at + OPB) = ou;
           }
@@ -507,8 +542,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
     // 16 rows.  Row r's 16-byte piece p (of PCS) sits at r*PCS*16 + ((p ^ (r % PCS)) << 4): the fragment writes of 16
     // rows spread over all banks and a row is read back as a permutation of itself.  No loads are in flight here (none is issued past the last K tile); the barrier waits
     // for the other wavefronts' last fragment reads.
-    // EPI_SWIGLU: pieces 0..15 of a staged row are the tile's 128 gate columns, pieces 16..31 its 128 up columns (two
-    // 256-byte runs of the output row).
+    // EPI_SWIGLU: the lower half of a staged row's pieces are the tile's gate columns, the upper half its up columns (two
+    // runs of the output row).
     const int glu_f = g.N / 2;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -518,7 +553,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
         const int r = wm + i * 16 + row_l;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-          const int p = GLU ? (j >> 1) * 16 + (wn >> 6) * 4 + (j & 1) * 2 + (col_l >> 3) : (wn + j * 16 + col_l) >> 3;
+          const int p = GLU ? (j >> 1) * (PCS / 2) + (wn >> 6) * 4 + (j & 1) * 2 + (col_l >> 3) : (wn + j * 16 + col_l) >> 3;
           bf16x4 o;
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[e] = (bf16)fn(acc[i][j][e]);
@@ -532,7 +567,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
       const int p = lane & (PCS - 1);
       int n = n0 + p * 8;
       bool n_ok = n < g.N;
-      if (GLU) { const int feat = n0 + (p & 15) * 8; n_ok = feat < glu_f; n = (p >> 4) ? glu_f + feat : feat; }
+      if (GLU) { const int feat = n0 + (p & (PCS / 2 - 1)) * 8; n_ok = feat < glu_f; n = p >= PCS / 2 ? glu_f + feat : feat; }
 #pragma unroll
       for (int t = 0; t < BMV / WAVES / RPI; ++t) {
         const int r = wave * (BMV / WAVES) + RPI * t + lane / PCS, m = m0 + r;
@@ -569,10 +604,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
         }
       }
       __syncthreads();
-      const int pc = lane & 15, feat = n0 + pc * 8;
+      constexpr int PA = PCS / 2, RPA = 64 / PA;         // 16-byte pieces per row of a, rows per instruction
+      const int pc = lane & (PA - 1), feat = n0 + pc * 8;
 #pragma unroll
-      for (int t = 0; t < BMV / WAVES / 4; ++t) {
-        const int r = wave * (BMV / WAVES) + 4 * t + (lane >> 4), m = m0 + r;
+      for (int t = 0; t < BMV / WAVES / RPA; ++t) {
+        const int r = wave * (BMV / WAVES) + RPA * t + lane / PA, m = m0 + r;
         const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) const u32x4*>(smem + r * 512 + ((((r & 16) | pc) ^ (r & 15)) << 4));
         if (m < g.M && feat < glu_f) *reinterpret_cast<u32x4*>((bf16*)g.C2 + (int64_t)m * g.ldc2 + feat) = v;
       }
@@ -680,8 +716,9 @@ __global__ __launch_bounds__(256, 2) void gemm_quarter_kernel(   // (register bu
   }
   int tile_m, tile_n;
   tile_of(first + (bid >> 2), tiles_m, tiles_n, tile_m, tile_n);
-  const int m0 = tile_m * BM + (bid & 1) * 128, n0 = tile_n * BN + ((bid >> 1) & 1) * 128;
-  if (m0 >= g.M || n0 >= g.N) return;                  // the same for the whole workgroup
+  constexpr int TB = EPI == EPI_SWIGLU ? GLU_BN : BN;
+  const int m0 = tile_m * BM + (bid & 1) * 128, n0 = tile_n * TB + ((bid >> 1) & 1) * (TB / 2);
+  if (m0 >= g.M || n0 >= (EPI == EPI_SWIGLU ? g.N / 2 : g.N)) return;                  // the same for the whole workgroup
   gemm_tile<AKC, BKC, EPI, 2, 1, 1>(g, m0, n0, (lds_char*)smem_raw);
 }
 
@@ -717,6 +754,26 @@ __global__ __launch_bounds__(1024 / TN) void gemm_wgrad_group_kernel(GemmGroup g
   }
 }
 
+// The same products in 128 x 128 tiles, one workgroup each: workgroup `bid` takes quadrant bid % 4 of tile number first + bid / 4.
+template <int DEPTH>
+__global__ __launch_bounds__(256, 2) void gemm_wgrad_quarter_kernel(GemmGroup gg, int first) {
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  int bid = blockIdx.x;
+  {
+    const int per = (int)gridDim.x >> 3, main = per << 3;
+    if (bid < main) bid = (bid & 7) * per + (bid >> 3);
+  }
+  const int t = first + (bid >> 2);
+  int pi = 0;
+  while (pi + 1 < gg.n && t >= gg.first_tile[pi + 1]) ++pi;
+  const GemmArgs& g = gg.p[pi];
+  int tile_m, tile_n;
+  tile_of(t - gg.first_tile[pi], (g.M + BM - 1) / BM, (g.N + BN - 1) / BN, tile_m, tile_n);
+  const int m0 = tile_m * BM + (bid & 1) * 128, n0 = tile_n * BN + ((bid >> 1) & 1) * 128;
+  if (m0 >= g.M || n0 >= g.N) return;
+  gemm_tile<false, false, EPI_ACC32, 2, 1, 1, DEPTH>(g, m0, n0, (lds_char*)smem_raw, gg.nseg, gg.seg_delta);
+}
+
 // Eight wavefronts of 128x64 or four of 128x128 per tile: the wider ones read a third less from LDS and are ahead on
 // weight gradients (+2..4 %) and on input gradients with a long reduction (+7 % at K = 22016), the narrower ones on
 // short reductions (an epilogue without spills, two wavefronts per SIMD to cover it); the fused SwiGLU epilogue and the
@@ -747,16 +804,25 @@ hipError_t launch_tiles(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles
   return hipGetLastError();
 }
 
+template <int DEPTH>
+hipError_t launch_wgrad_quarter(const GemmGroup& gg, int first, int n, hipStream_t s) {
+  constexpr size_t LDS = (size_t)(2 * DEPTH + 1) * (TILE_BYTES / 2);
+  auto kern = gemm_wgrad_quarter_kernel<DEPTH>;
+  static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(kern, dim3(4 * n), dim3(256), LDS, s, gg, first);
+  return hipGetLastError();
+}
+
 // Full tiles for every complete round of one tile per CU; what is left over -- a last round that would keep at most
 // half of the CUs busy, or a whole product with that few tiles -- goes out as twice as many half-height tiles, which
-// take about two thirds as long each, or, if that would still leave half of the CUs idle and the epilogue is a plain
-// one, as four times as many 128 x 128 tiles (two fifths as long each).  `shape`: 0 = this rule, 1 = full tiles only,
+// take about two thirds as long each, or, if that would still leave half of the CUs idle, as four times as many 128 x 128 tiles (two fifths as long each).  `shape`: 0 = this rule, 1 = full tiles only,
 // 2 = half-height tiles only, 3 = 128 x 128 tiles only (where there are none: the rule).
 template <bool AKC, bool BKC, int EPI>
 hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   const int tiles_m = (g.M + BM - 1) / BM;
   const int tiles_n = EPI == EPI_SWIGLU ? (g.N / 2 + GLU_BN - 1) / GLU_BN : (g.N + BN - 1) / BN, total = tiles_m * tiles_n;
-  constexpr bool QUARTERS = AKC && (EPI == EPI_STORE || EPI == EPI_RESID);
+  constexpr bool QUARTERS = AKC;
   int n_half = 0, n_quarter = 0;          // full tiles at the end of the walk order that are split in two / in four
   if constexpr (AKC) {
     const int n_cu = cu_count(), tail = total % n_cu;
@@ -828,7 +894,7 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t s, int tile_shape) {
       if (g.act_bwd == 1) return launch<true, true, EPI_DGELU>(g, s, tile_shape);
       if (g.act_bwd == 2) return launch<true, true, EPI_DSWIGLU>(g, s, tile_shape);
       return launch<true, true, EPI_STORE>(g, s, tile_shape);
-    case GEMM_TN: return launch<false, false, EPI_ACC32>(g, s, tile_shape);
+    case GEMM_TN: return tile_shape == 0 ? gemm_mfma_wgrad_group(&g, 1, 1, nullptr, s) : launch<false, false, EPI_ACC32>(g, s, tile_shape);
   }
   return hipErrorInvalidValue;
 }
@@ -859,11 +925,24 @@ hipError_t gemm_mfma_wgrad_group(const GemmArgs* list, int n, int nseg, const in
       total += ((gg.p[i].M + BM - 1) / BM) * ((gg.p[i].N + BN - 1) / BN);
     }
     for (int i = gg.n; i <= GROUP_MAX; ++i) gg.first_tile[i] = total;
-    gg.total_tiles = total;
-    const int grid = total < n_cu ? total : n_cu;       // one workgroup per CU (128 KiB of LDS each)
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(1024 / WAVE_COLS_WGRAD), LDS_BYTES, s, gg);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    // Complete rounds of full tiles; a last round (or a whole list) of at most half a tile per CU goes out as 128 x 128 tiles,
+    // which spread its reads and writes of C -- 512 KiB per full tile, 18 us whatever the reduction length -- over four
+    // times as many CUs.  Lists that leave every CU at most one such tile take the deep operand ring, others the shallow one
+    // that lets two workgroups share a CU.  Measured (us, full tiles against this rule's): 48 tiles, K 128: 22.5 / 9.7;
+    // 75 tiles, K 400: 28.9 / 17.7; 64 tiles, K 4096: 91.7 / 42.4; 128 tiles, K 8192: 172 / 159; on fuller rounds the doubled
+    // operand traffic loses (196 tiles, K 3000: 86 / 113).
+    const int tail = total % n_cu, n_quarter = 2 * tail <= n_cu ? tail : 0, n_full = total - n_quarter;
+    if (n_full) {
+      const int grid = n_full < n_cu ? n_full : n_cu;       // one workgroup per CU (160 KiB of LDS each)
+      gg.total_tiles = n_full;
+      hipLaunchKernelGGL(kern, dim3(grid), dim3(1024 / WAVE_COLS_WGRAD), LDS_BYTES, s, gg);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    if (n_quarter) {
+      const hipError_t e = 4 * n_quarter <= n_cu ? launch_wgrad_quarter<4>(gg, n_full, n_quarter, s) : launch_wgrad_quarter<2>(gg, n_full, n_quarter, s);
+      if (e != hipSuccess) return e;
+    }
   }
   return hipSuccess;
 }

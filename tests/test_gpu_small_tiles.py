@@ -1,0 +1,77 @@
+"""The 128 x 128 tiles of the fused-activation and weight-gradient products at their edges."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from oracle import stage_oracle as so
+from paper_2507_00217_amd import synth
+from tests.gpu_util import rnd, to_dev, to_np
+from tests.test_gpu_kernels import KTOL, L, P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("act", [0, 1])
+@pytest.mark.parametrize("M,f,K", [(1, 8, 64), (127, 64, 64), (129, 72, 128), (128, 136, 320), (257, 200, 384)])
+def test_fused_activations_on_small_products(act, M, f, K):
+    """Products this small take 128 x 128 tiles (64 features for SwiGLU): one row, one past a tile in each dimension, ring
+    depths from one K tile to two past the ring.  Tolerance: one bf16 rounding of the output and of z, as for the larger tiles."""
+    import torch
+    fin = (1 + act) * f
+    sh = so.Shape(1, 64, 1, 1, f, 1, 1, act="swiglu" if act else "gelu")
+    X, W = rnd(synth.normal(41, 1, (M, K)), "bf16"), rnd(synth.normal(41, 2, (K, fin), std=1.5 * K ** -0.5), "bf16")
+    dY, V = rnd(synth.normal(41, 3, (M, K)), "bf16"), rnd(synth.normal(41, 4, (f, K), std=1.5 * K ** -0.5), "bf16")
+    z = X.astype(np.float64) @ W.astype(np.float64)
+    a = z[:, :f] * so.sigmoid(z[:, :f]) * z[:, f:] if act else so.gelu(z)
+    Xd, Wd, dYd, Vd = (to_dev(t, "bf16") for t in (X, W, dY, V))
+    Zd, Aout = (torch.full((M, n), float("nan"), dtype=torch.bfloat16, device="cuda:0") for n in (fin, f))
+    assert L().stage_kernel_gemm_act(1, act, M, f, K, P(Xd), K, P(Wd), fin, P(Zd), fin, P(Aout), f, 0, None) == 0
+    assert so.max_rel_err(to_np(Zd), z) <= KTOL["bf16"] and so.max_rel_err(to_np(Aout), a) <= KTOL["bf16"]
+    zr = to_np(Zd)
+    da = dY.astype(np.float64) @ V.astype(np.float64).T
+    assert L().stage_kernel_gemm_act_bwd(1, act, M, f, K, P(dYd), K, P(Vd), K, P(Zd), fin, None, 0, None) == 0
+    assert so.max_rel_err(to_np(Zd), so.act_backward(sh, zr, da)) <= KTOL["bf16"]
+
+
+def test_gelu_keeps_its_digits_in_the_tail():
+    """GELU and its derivative from Phi(u), element by element: bf16 outputs of exact inputs within one rounding (2^-8) plus
+    the rounding of z for u in [-6, 6], where 1 + erf would have lost every digit below -5."""
+    import torch
+    u = synth.round_bf16(np.linspace(-6, 6, 64 * 64, dtype=np.float32)).reshape(64, 64)
+    eye = np.eye(64, dtype=np.float32)
+    Zd, Aout = (torch.empty((64, 64), dtype=torch.bfloat16, device="cuda:0") for _ in range(2))
+    ud, ed = to_dev(u, "bf16"), to_dev(eye, "bf16")
+    assert L().stage_kernel_gemm_act(1, 0, 64, 64, 64, P(ud), 64, P(ed), 64, P(Zd), 64, P(Aout), 64, 0, None) == 0
+    x = torch.from_numpy(u).double()
+    ref = (x * torch.special.ndtr(x)).numpy()
+    assert np.array_equal(to_np(Zd), u)
+    assert np.max(np.abs(to_np(Aout) - ref) / np.maximum(np.abs(ref), 1e-12)) <= 2.0 ** -8
+    ones = to_dev(np.eye(64, dtype=np.float32), "bf16")
+    dy = to_dev(np.ones((64, 64), np.float32), "bf16")
+    assert L().stage_kernel_gemm_act_bwd(1, 0, 64, 64, 64, P(dy), 64, P(ones), 64, P(Zd), 64, None, 0, None) == 0
+    dref = (torch.special.ndtr(x) + x * torch.exp(-0.5 * x * x) / (2 * np.pi) ** 0.5).numpy()
+    assert np.max(np.abs(to_np(Zd) - dref)) <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("shapes", [[(8, 8, 1)], [(128, 136, 65)], [(264, 520, 200), (136, 8, 64)],
+                                    [(4096, 4096, 72), (2560, 264, 320), (520, 1032, 129)],                 # 256 full tiles and a tail
+                                    [(2048, 4104, 40), (1032, 520, 136)]])                                  # a tail of more than 64
+def test_weight_gradients_of_a_short_last_round(shapes):
+    """Lists whose last round keeps at most half of the CUs busy go out (partly) as 128 x 128 tiles: the same bits as full tiles."""
+    import torch
+    n = len(shapes)
+    g = torch.Generator().manual_seed(42)
+    A, B, Cs = [], [], []
+    for M, N, K in shapes:
+        A.append(torch.randn((K, M), generator=g).bfloat16().to("cuda:0")); B.append(torch.randn((K, N), generator=g).bfloat16().to("cuda:0"))
+        Cs.append(torch.randn((M, N), generator=g).to("cuda:0"))
+    full = [c.clone() for c in Cs]
+    Ms, Ns, Ks = zip(*shapes)
+    ia, la, pa = (lambda v: (C.c_int * n)(*v)), (lambda v: (C.c_int64 * n)(*v)), (lambda t: (C.c_void_p * n)(*[u.data_ptr() for u in t]))
+    assert L().stage_kernel_wgrad_group(1, n, ia(Ms), ia(Ns), ia(Ks), pa(A), la(Ms), pa(B), la(Ns), pa(Cs), la(Ns), 0, None) == 0
+    for (M, N, K), a, b, c in zip(shapes, A, B, full):
+        ref = c.double() + a.double().t() @ b.double()
+        assert L().stage_kernel_gemm(1, 2, M, N, K, P(a), M, P(b), N, P(c), N, None, 0, 1, 2, None) == 0
+        assert ((c.double() - ref).abs().max() / ref.abs().max()).item() <= 1e-5 * max(1.0, K ** 0.5)
+    assert all(torch.equal(x, y) for x, y in zip(Cs, full))
