@@ -53,7 +53,7 @@ __device__ __forceinline__ void st_row(void* base, int64_t off, const float (&sr
 
 constexpr int NORM_THREADS = 256;
 constexpr int NORM_MAXCH = 4;          // 16-byte chunks per thread: d <= 256*4*(16/sizeof(T))
-constexpr int NORM_PARTIAL_ROWS = 512;   // multiple of 4; two workgroups per CU keep more rows in flight
+constexpr int NORM_PARTIAL_ROWS = 512;   // backward: at most two workgroups per CU
 int norm_partial_rows() { return NORM_PARTIAL_ROWS; }
 
 __device__ __forceinline__ float wg_sum(float v, float* red) {
@@ -64,7 +64,7 @@ __device__ __forceinline__ float wg_sum(float v, float* red) {
   return red[0] + red[1] + red[2] + red[3];
 }
 
-// out = (x - mean) * rstd * gamma + beta   |   out = x * rstd * gamma
+// out = (x - mean) * rstd * gamma + beta   |   out = x * rstd * gamma; x_wide, if given, receives x in fp32 on the way
 template <typename T, int KIND>
 __global__ __launch_bounds__(NORM_THREADS) void norm_fwd_kernel(NormArgs n) {
   constexpr int V = Vec<T>::N;
@@ -80,6 +80,7 @@ __global__ __launch_bounds__(NORM_THREADS) void norm_fwd_kernel(NormArgs n) {
     const int vi = threadIdx.x + c * NORM_THREADS;
     if (vi < nvec) {
       ld_row<T>(xv[c], n.x, roff + vi * V, n.x_f32);
+      if (n.x_wide) st_row<T>(n.x_wide, roff + vi * V, xv[c], true);
 #pragma unroll
       for (int e = 0; e < V; ++e) s += (KIND == 0) ? xv[c][e] : xv[c][e] * xv[c][e];
     }
@@ -119,116 +120,200 @@ __global__ __launch_bounds__(NORM_THREADS) void norm_fwd_kernel(NormArgs n) {
 // dx = resid + rstd * (dxhat - mean(dxhat) - xhat * mean(dxhat * xhat)),  dxhat = dout * gamma
 // (the mean(dxhat) term is absent for RMSNorm); per-workgroup partial sums of
 // dgamma = sum_rows dout * xhat and dbeta = sum_rows dout go to n.partial.
-template <typename T, int KIND>
-__global__ __launch_bounds__(NORM_THREADS) void norm_bwd_kernel(NormArgs n) {
+//
+// Bound by HBM, 8 bytes per element (16 with an fp32 residual stream), as long as enough rows are in flight.  A row takes
+// tpr threads (whole wavefronts) with at most NB_CH 16-byte pieces each, so that widths that are not a power of two leave few
+// threads idle (5120: 5 wavefronts x 2 pieces; one fixed workgroup of 256 threads needed 3 pieces, half of the last unused,
+// and registers for 4); a workgroup holds as many rows side by side as fit in 256 threads.  The next row's loads are
+// issued before this one is reduced, both row sums cross the workgroup in one exchange, and xhat and dxhat are formed again
+// from the raw row rather than kept.  4096 x 5120 in bf16: 49 -> 45 us (3.8 TB/s,
+// partial sums not counted; a large copy reaches 4.8); 2048 x 2048 with an fp32 residual stream: 20.5 -> 16-18.
+constexpr int NB_CH = 2;
+template <typename T, bool WIDE> struct RowPiece { static constexpr int W = WIDE ? Vec<T>::N / 4 : 1; uint4 v[W]; };
+template <typename T, bool WIDE>
+__device__ __forceinline__ RowPiece<T, WIDE> ld_piece(const void* base, int64_t off) {
+  RowPiece<T, WIDE> r;
+  const uint4* p = reinterpret_cast<const uint4*>((const char*)base + off * (WIDE ? 4 : sizeof(T)));
+#pragma unroll
+  for (int q = 0; q < RowPiece<T, WIDE>::W; ++q) r.v[q] = p[q];
+  return r;
+}
+template <typename T, bool WIDE> __device__ __forceinline__ float at_piece(const RowPiece<T, WIDE>& r, int e) {
+  if constexpr (WIDE || sizeof(T) == 4) {
+    const uint4 q = r.v[WIDE ? e / 4 : 0];
+    return __uint_as_float((e & 3) == 0 ? q.x : (e & 3) == 1 ? q.y : (e & 3) == 2 ? q.z : q.w);
+  } else {
+    Vec<T> t; t.raw = r.v[0];
+    return to_f32(t.v[e]);
+  }
+}
+
+// XW / RW: x / resid is stored in fp32 although T is not
+template <typename T, int KIND, bool XW, bool RW>
+__global__ __launch_bounds__(512) void norm_bwd_kernel(NormArgs n, int tpr) {
   constexpr int V = Vec<T>::N;
-  __shared__ float red[4];
-  const int nvec = n.d / V;
-  float gam[NORM_MAXCH][V], dg[NORM_MAXCH][V], db[NORM_MAXCH][V];
+  extern __shared__ float col_sums[];                    // [row groups][2][d], only with several row groups
+  __shared__ float red[2][16][2];
+  const int nvec = n.d / V, ngrp = blockDim.x / tpr, wpr = tpr >> 6;
+  const int grp = threadIdx.x / tpr, t = threadIdx.x % tpr, wave = threadIdx.x >> 6;
+  float dg[NB_CH][V], db[NB_CH][V];
+  Vec<T> gam[NB_CH];
 #pragma unroll
-  for (int c = 0; c < NORM_MAXCH; ++c) {
-    const int vi = threadIdx.x + c * NORM_THREADS;
-    Vec<T> g;
-    if (vi < nvec) g = ldv((const T*)n.gamma + vi * V);
+  for (int c = 0; c < NB_CH; ++c) {
+    const int vi = t + c * tpr;
+    gam[c] = ldv((const T*)n.gamma + (vi < nvec ? vi : 0) * V);
 #pragma unroll
-    for (int e = 0; e < V; ++e) { gam[c][e] = vi < nvec ? to_f32(g.v[e]) : 0.f; dg[c][e] = 0.f; db[c][e] = 0.f; }
+    for (int e = 0; e < V; ++e) dg[c][e] = db[c][e] = 0.f;
   }
   const float inv_d = 1.f / (float)n.d;
-  for (int row = blockIdx.x; row < n.rows; row += gridDim.x) {
-    const int64_t roff = (int64_t)row * n.d;
-    const T* dout = (const T*)n.dout + roff;
-    const float mean = n.stats[2 * row], rstd = n.stats[2 * row + 1];
-    float xh[NORM_MAXCH][V], dxh[NORM_MAXCH][V], res[NORM_MAXCH][V];
+  RowPiece<T, XW> x[NB_CH], xn[NB_CH];
+  RowPiece<T, RW> rs[NB_CH], rsn[NB_CH];
+  Vec<T> dv[NB_CH], dvn[NB_CH];
+  float mean = 0.f, rstd = 0.f, mean_n = 0.f, rstd_n = 0.f;
+  // rows past the end are read as the last one and leave no trace
+  auto load = [&](int row) __attribute__((always_inline)) {
+    const int r = min(row, n.rows - 1);
+    const int64_t roff = (int64_t)r * n.d;
+    mean_n = n.stats[2 * r]; rstd_n = n.stats[2 * r + 1];
+#pragma unroll
+    for (int c = 0; c < NB_CH; ++c) {
+      const int vi = t + c * tpr;
+      const int64_t off = roff + (vi < nvec ? vi : 0) * V;
+      xn[c] = ld_piece<T, XW>(n.x, off);
+      dvn[c] = ldv((const T*)n.dout + off);
+      if (n.resid) rsn[c] = ld_piece<T, RW>(n.resid, off);
+    }
+  };
+  const int step = gridDim.x * ngrp;
+  int row0 = blockIdx.x * ngrp;
+  load(row0 + grp);
+  for (int it = 0; row0 < n.rows; row0 += step, ++it) {
+    const int row = row0 + grp;
+    mean = mean_n; rstd = rstd_n;
+#pragma unroll
+    for (int c = 0; c < NB_CH; ++c) { x[c] = xn[c]; dv[c] = dvn[c]; rs[c] = rsn[c]; }
+    if (row0 + step < n.rows) load(row + step);
+    const bool live = row < n.rows;
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-    for (int c = 0; c < NORM_MAXCH; ++c) {
-      const int vi = threadIdx.x + c * NORM_THREADS;
-      if (vi < nvec) {
-        float tx[V];
-        ld_row<T>(tx, n.x, roff + vi * V, n.x_f32);
-        Vec<T> td = ldv(dout + vi * V);
-        if (n.resid) ld_row<T>(res[c], n.resid, roff + vi * V, n.resid_f32);     // in flight during the row reductions
+    for (int c = 0; c < NB_CH; ++c)
+      if (live && t + c * tpr < nvec) {
 #pragma unroll
         for (int e = 0; e < V; ++e) {
-          const float xhat = (tx[e] - mean) * rstd;
-          const float dv = to_f32(td.v[e]);
-          xh[c][e] = xhat;
-          dxh[c][e] = dv * gam[c][e];
-          dg[c][e] += dv * xhat;
-          if (KIND == 0) db[c][e] += dv;
-          s1 += dxh[c][e];
-          s2 += dxh[c][e] * xhat;
+          const float xhat = (at_piece<T, XW>(x[c], e) - mean) * rstd, d = to_f32(dv[c].v[e]), dx = d * to_f32(gam[c].v[e]);
+          dg[c][e] += d * xhat;
+          if (KIND == 0) { db[c][e] += d; s1 += dx; }
+          s2 += dx * xhat;
         }
       }
+    for (int o = 32; o > 0; o >>= 1) {
+      if (KIND == 0) s1 += __shfl_xor(s1, o, 64);
+      s2 += __shfl_xor(s2, o, 64);
     }
-    float m1 = 0.f;
-    if (KIND == 0) m1 = wg_sum(s1, red) * inv_d;
-    const float m2 = wg_sum(s2, red) * inv_d;
+    if (wpr > 1) {                                       // two sets of slots in turn: one barrier per row
+      if ((threadIdx.x & 63) == 0) { red[it & 1][wave][0] = s1; red[it & 1][wave][1] = s2; }
+      __syncthreads();
+      s1 = s2 = 0.f;
+      for (int k = 0; k < wpr; ++k) { s1 += red[it & 1][grp * wpr + k][0]; s2 += red[it & 1][grp * wpr + k][1]; }
+    }
+    const float m1 = s1 * inv_d, m2 = s2 * inv_d;
 #pragma unroll
-    for (int c = 0; c < NORM_MAXCH; ++c) {
-      const int vi = threadIdx.x + c * NORM_THREADS;
-      if (vi < nvec) {
+    for (int c = 0; c < NB_CH; ++c) {
+      const int vi = t + c * tpr;
+      if (live && vi < nvec) {
+        const int64_t off = (int64_t)row * n.d + vi * V;
         float o[V];
 #pragma unroll
         for (int e = 0; e < V; ++e) {
-          float v = (dxh[c][e] - m1 - xh[c][e] * m2) * rstd;
-          if (n.resid) v += res[c][e];
-          o[e] = v;
+          const float xhat = (at_piece<T, XW>(x[c], e) - mean) * rstd;
+          o[e] = (to_f32(dv[c].v[e]) * to_f32(gam[c].v[e]) - m1 - xhat * m2) * rstd;
+          if (n.resid) o[e] += at_piece<T, RW>(rs[c], e);
         }
-        st_row<T>(n.out, roff + vi * V, o, n.out_f32);
-        if (n.out_lp) st_row<T>(n.out_lp, roff + vi * V, o, false);
+        st_row<T>(n.out, off, o, n.out_f32);
+        if (n.out_lp) st_row<T>(n.out_lp, off, o, false);
+        if (!RW && n.resid_copy) *reinterpret_cast<uint4*>((T*)n.resid_copy + off) = rs[c].v[0];
       }
+    }
+  }
+  if (ngrp > 1) {                                        // the row groups' column sums, in order
+    float* cs = col_sums + (int64_t)grp * 2 * n.d;
+#pragma unroll
+    for (int c = 0; c < NB_CH; ++c) {
+      const int vi = t + c * tpr;
+      if (vi < nvec)
+#pragma unroll
+        for (int e = 0; e < V; ++e) { cs[vi * V + e] = dg[c][e]; if (KIND == 0) cs[n.d + vi * V + e] = db[c][e]; }
+    }
+    __syncthreads();
+    if (grp != 0) return;
+#pragma unroll
+    for (int c = 0; c < NB_CH; ++c) {
+      const int vi = t + c * tpr;
+      if (vi < nvec)
+        for (int g = 1; g < ngrp; ++g)
+#pragma unroll
+          for (int e = 0; e < V; ++e) {
+            dg[c][e] += col_sums[(int64_t)g * 2 * n.d + vi * V + e];
+            if (KIND == 0) db[c][e] += col_sums[(int64_t)g * 2 * n.d + n.d + vi * V + e];
+          }
     }
   }
   float* pg = n.partial + (int64_t)blockIdx.x * 2 * n.d;
   float* pb = pg + n.d;
 #pragma unroll
-  for (int c = 0; c < NORM_MAXCH; ++c) {
-    const int vi = threadIdx.x + c * NORM_THREADS;
+  for (int c = 0; c < NB_CH; ++c) {
+    const int vi = t + c * tpr;
     if (vi < nvec)
 #pragma unroll
-      for (int e = 0; e < V; ++e) {
-        pg[vi * V + e] = dg[c][e];
-        if (KIND == 0) pb[vi * V + e] = db[c][e];
+      for (int q = 0; q < V / 4; ++q) {
+        *reinterpret_cast<float4*>(pg + vi * V + 4 * q) = make_float4(dg[c][4 * q], dg[c][4 * q + 1], dg[c][4 * q + 2], dg[c][4 * q + 3]);
+        if (KIND == 0) *reinterpret_cast<float4*>(pb + vi * V + 4 * q) = make_float4(db[c][4 * q], db[c][4 * q + 1], db[c][4 * q + 2], db[c][4 * q + 3]);
       }
   }
 }
 
-// grads += sum over workgroup partials, in a fixed order: 64 columns per workgroup, FIN_WAVES wavefronts each summing
-// an equal share of the partial rows (coalesced 256-byte reads, all of a wavefront's loads in flight at once: the kernel
-// is a few microseconds of memory latency, not bandwidth), then wavefront 0 adds the shares in order
-constexpr int FIN_WAVES = 16;
-static_assert(NORM_PARTIAL_ROWS % FIN_WAVES == 0, "equal shares");
-template <int KIND>
-__global__ __launch_bounds__(FIN_WAVES * 64) void norm_bwd_finalize_kernel(NormArgs n, int nparts) {
-  __shared__ float sg[FIN_WAVES][64], sb[FIN_WAVES][64];
+// dst[col] += sum over a job's partial rows, in a fixed order, for all jobs of the list (norm-parameter and bias gradients of a
+// layer) in one launch: 64 columns per workgroup, SUM_WAVES wavefronts that take every SUM_WAVES-th partial row (coalesced
+// 256-byte reads, 16 of a wavefront's loads in flight at once: a few microseconds of memory latency, not bandwidth), then
+// wavefront 0 adds the shares in order.
+constexpr int SUM_WAVES = 16;
+__global__ __launch_bounds__(SUM_WAVES * 64) void col_sum_kernel(ColSumList l) {
+  __shared__ float sums[SUM_WAVES][64];
+  int ji = 0;
+  while (ji + 1 < l.n && (int)blockIdx.x >= l.first[ji + 1]) ++ji;
+  const ColSum j = l.j[ji];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int col = blockIdx.x * 64 + lane;
-  float g = 0.f, b = 0.f;
-  if (col < n.d) {
-    constexpr int PER = NORM_PARTIAL_ROWS / FIN_WAVES;
-    const float* p0 = n.partial + (int64_t)w * PER * 2 * n.d + col;
-    float vg[PER], vb[PER];
+  const int col = ((int)blockIdx.x - l.first[ji]) * 64 + lane;
+  float s = 0.f;
+  if (col < j.cols) {
+    constexpr int U = 16;
+    for (int p0 = w; p0 < j.parts; p0 += SUM_WAVES * U) {
+      float v[U];
 #pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      vg[p] = p0[(int64_t)p * 2 * n.d];
-      if (KIND == 0) vb[p] = p0[(int64_t)p * 2 * n.d + n.d];
-    }
+      for (int u = 0; u < U; ++u) {
+        const int p = p0 + u * SUM_WAVES;
+        v[u] = p < j.parts ? j.part[(int64_t)p * j.stride + col] : 0.f;
+      }
 #pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      g += vg[p];
-      if (KIND == 0) b += vb[p];
+      for (int u = 0; u < U; ++u) s += v[u];
     }
   }
-  sg[w][lane] = g; sb[w][lane] = b;
+  sums[w][lane] = s;
   __syncthreads();
-  if (w == 0 && col < n.d) {
-    float tg = sg[0][lane], tb = sb[0][lane];
+  if (w == 0 && col < j.cols) {
+    float r = sums[0][lane];
 #pragma unroll
-    for (int k = 1; k < FIN_WAVES; ++k) { tg += sg[k][lane]; tb += sb[k][lane]; }
-    n.dgamma[col] += tg;
-    if (KIND == 0) n.dbeta[col] += tb;
+    for (int k = 1; k < SUM_WAVES; ++k) r += sums[k][lane];
+    j.dst[col] += r;
   }
+}
+
+hipError_t col_sums_add(ColSumList& l, hipStream_t s) {
+  if (l.n == 0) return hipSuccess;
+  int total = 0;
+  for (int i = 0; i < l.n; ++i) { l.first[i] = total; total += (l.j[i].cols + 63) / 64; }
+  hipLaunchKernelGGL(col_sum_kernel, dim3(total), dim3(SUM_WAVES * 64), 0, s, l);
+  return hipGetLastError();
 }
 
 template <typename T>
@@ -245,26 +330,47 @@ static hipError_t norm_fwd_t(const NormArgs& n, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T>
-static hipError_t norm_bwd_t(const NormArgs& n, hipStream_t s) {
-  if (!norm_shape_ok<T>(n)) return hipErrorInvalidValue;
-  const int parts = NORM_PARTIAL_ROWS;
-  const int fb = (n.d + 63) / 64;
-  if (n.kind == 0) {
-    hipLaunchKernelGGL((norm_bwd_kernel<T, 0>), dim3(parts), dim3(NORM_THREADS), 0, s, n);
-    hipLaunchKernelGGL((norm_bwd_finalize_kernel<0>), dim3(fb), dim3(FIN_WAVES * 64), 0, s, n, parts);
-  } else {
-    hipLaunchKernelGGL((norm_bwd_kernel<T, 1>), dim3(parts), dim3(NORM_THREADS), 0, s, n);
-    hipLaunchKernelGGL((norm_bwd_finalize_kernel<1>), dim3(fb), dim3(FIN_WAVES * 64), 0, s, n, parts);
-  }
+template <typename T, int KIND, bool XW, bool RW>
+static hipError_t norm_bwd_launch(const NormArgs& n, hipStream_t s, int* parts) {
+  const int nvec = n.d / Vec<T>::N, tpr = nvec <= 64 ? 64 : ((nvec + NB_CH - 1) / NB_CH + 63) / 64 * 64;
+  const int ngrp = tpr >= 256 ? 1 : 256 / tpr, want = (n.rows + ngrp - 1) / ngrp;
+  *parts = want < NORM_PARTIAL_ROWS ? want : NORM_PARTIAL_ROWS;
+  const size_t lds = ngrp > 1 ? (size_t)ngrp * 2 * n.d * sizeof(float) : 0;      // at most 32 KiB: d <= 128 * V with 4 groups
+  hipLaunchKernelGGL((norm_bwd_kernel<T, KIND, XW, RW>), dim3(*parts), dim3(ngrp * tpr), lds, s, n, tpr);
   return hipGetLastError();
+}
+template <typename T, int KIND>
+static hipError_t norm_bwd_pick(const NormArgs& n, hipStream_t s, int* parts) {
+  if constexpr (sizeof(T) == 2) {
+    if (n.x_f32 && n.resid_f32 && n.resid) return norm_bwd_launch<T, KIND, true, true>(n, s, parts);
+    if (n.x_f32) return norm_bwd_launch<T, KIND, true, false>(n, s, parts);
+    if (n.resid_f32 && n.resid) return norm_bwd_launch<T, KIND, false, true>(n, s, parts);
+  }
+  return norm_bwd_launch<T, KIND, false, false>(n, s, parts);
+}
+template <typename T>
+static hipError_t norm_bwd_t(const NormArgs& n, hipStream_t s, int* parts) {
+  if (!norm_shape_ok<T>(n)) return hipErrorInvalidValue;
+  return n.kind == 0 ? norm_bwd_pick<T, 0>(n, s, parts) : norm_bwd_pick<T, 1>(n, s, parts);
 }
 
 hipError_t norm_fwd(DType dt, const NormArgs& n, hipStream_t s) {
   return dt == DT_F32 ? norm_fwd_t<float>(n, s) : norm_fwd_t<bf16>(n, s);
 }
+hipError_t norm_bwd_rows(DType dt, const NormArgs& n, hipStream_t s, int* parts) {
+  return dt == DT_F32 ? norm_bwd_t<float>(n, s, parts) : norm_bwd_t<bf16>(n, s, parts);
+}
+void norm_col_sums(const NormArgs& n, int parts, ColSumList* l) {
+  l->j[l->n++] = ColSum{n.partial, (int64_t)2 * n.d, n.d, parts, n.dgamma};
+  if (n.kind == 0) l->j[l->n++] = ColSum{n.partial + n.d, (int64_t)2 * n.d, n.d, parts, n.dbeta};
+}
 hipError_t norm_bwd(DType dt, const NormArgs& n, hipStream_t s) {
-  return dt == DT_F32 ? norm_bwd_t<float>(n, s) : norm_bwd_t<bf16>(n, s);
+  int parts = 0;
+  const hipError_t e = norm_bwd_rows(dt, n, s, &parts);
+  if (e != hipSuccess) return e;
+  ColSumList l{};
+  norm_col_sums(n, parts, &l);
+  return col_sums_add(l, s);
 }
 
 // Norm backward for callers that cannot allocate device memory: the per-workgroup partial sums of dgamma / dbeta go to
@@ -307,59 +413,70 @@ hipError_t norm_bwd_noalloc(DType dt, const NormArgs& n, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // Gradient of a linear map's bias: the column sums of its dZ, added to the fp32 accumulator.  Two steps with a fixed
 // summation order (no atomics): BIAS_PARTS row ranges are summed by one workgroup each per 32 x (16 / sizeof(T))
-// columns -- 8 row lanes per column group, combined through LDS in lane order -- then one thread per column adds the
-// parts in order.
+// columns -- 8 row lanes per column group, combined through LDS in lane order -- then col_sum_kernel adds the parts.  The
+// four maps of a layer go out together: at 400 tokens each of the two steps is launch latency, 3-5 us, eight times over.
 // ---------------------------------------------------------------------------
 constexpr int BIAS_PARTS = 64;
 size_t bias_grad_partial_bytes(int n) { return n > 0 ? (size_t)BIAS_PARTS * n * sizeof(float) : 0; }
 
 template <typename T>
-__global__ __launch_bounds__(256) void bias_grad_partial_kernel(const T* dz, int64_t ld, int rows, int n, float* partial) {
+__global__ __launch_bounds__(256) void bias_grad_partial_kernel(BiasGradList l) {
   constexpr int V = Vec<T>::N;
   __shared__ float red[8][32 * V];
+  int ji = 0;
+  while (ji + 1 < l.n && (int)blockIdx.x >= l.first[ji + 1]) ++ji;
+  const BiasGrad j = l.j[ji];
+  const T* dz = (const T*)j.dz;
   const int cg = threadIdx.x & 31, rl = threadIdx.x >> 5;
-  const int col = (blockIdx.x * 32 + cg) * V;
-  const int per = (rows + BIAS_PARTS - 1) / BIAS_PARTS;
-  const int r0 = blockIdx.y * per, r1 = min(rows, r0 + per);
+  const int col = (((int)blockIdx.x - l.first[ji]) * 32 + cg) * V;
+  const int per = (l.rows + BIAS_PARTS - 1) / BIAS_PARTS;
+  const int r0 = blockIdx.y * per, r1 = min(l.rows, r0 + per);
   float acc[V];
 #pragma unroll
   for (int e = 0; e < V; ++e) acc[e] = 0.f;
-  if (col < n)
+  if (col < j.cols)
     for (int r = r0 + rl; r < r1; r += 8) {
-      Vec<T> v = ldv(dz + (int64_t)r * ld + col);
+      Vec<T> v = ldv(dz + (int64_t)r * j.ld + col);
 #pragma unroll
       for (int e = 0; e < V; ++e) acc[e] += to_f32(v.v[e]);
     }
 #pragma unroll
   for (int e = 0; e < V; ++e) red[rl][cg * V + e] = acc[e];
   __syncthreads();
-  if (rl == 0 && col < n) {
+  if (rl == 0 && col < j.cols) {
 #pragma unroll
     for (int e = 0; e < V; ++e) {
       float s = red[0][cg * V + e];
 #pragma unroll
       for (int k = 1; k < 8; ++k) s += red[k][cg * V + e];
-      partial[(int64_t)blockIdx.y * n + col + e] = s;
+      j.part[(int64_t)blockIdx.y * j.cols + col + e] = s;
     }
   }
 }
 
-__global__ __launch_bounds__(256) void bias_grad_finalize_kernel(const float* partial, int n, float* dbias) {
-  const int col = blockIdx.x * 256 + threadIdx.x;
-  if (col >= n) return;
-  float s = partial[col];
-  for (int p = 1; p < BIAS_PARTS; ++p) s += partial[(int64_t)p * n + col];
-  dbias[col] += s;
+hipError_t bias_grad_rows(DType dt, BiasGradList& l, ColSumList* sums, hipStream_t s) {
+  const int V = dt == DT_F32 ? 4 : 8;
+  if (l.n == 0) return hipSuccess;
+  int total = 0;
+  for (int i = 0; i < l.n; ++i) {
+    const BiasGrad& j = l.j[i];
+    if (l.rows < 1 || j.cols < 1 || j.cols % V || j.ld % V || !j.dz || !j.part || !j.dbias || ((uintptr_t)j.dz & 15)) return hipErrorInvalidValue;
+    l.first[i] = total;
+    total += (j.cols / V + 31) / 32;
+    sums->j[sums->n++] = ColSum{j.part, j.cols, j.cols, BIAS_PARTS, j.dbias};
+  }
+  const dim3 grid(total, BIAS_PARTS);
+  if (dt == DT_F32) hipLaunchKernelGGL((bias_grad_partial_kernel<float>), grid, dim3(256), 0, s, l);
+  else hipLaunchKernelGGL((bias_grad_partial_kernel<bf16>), grid, dim3(256), 0, s, l);
+  return hipGetLastError();
 }
 
 hipError_t bias_grad(DType dt, const void* dz, int64_t ld, int rows, int n, float* partial, float* dbias, hipStream_t s) {
-  const int V = dt == DT_F32 ? 4 : 8;
-  if (rows < 1 || n < 1 || n % V || ld % V || !dz || !partial || !dbias || ((uintptr_t)dz & 15)) return hipErrorInvalidValue;
-  const dim3 grid((n / V + 31) / 32, BIAS_PARTS);
-  if (dt == DT_F32) hipLaunchKernelGGL((bias_grad_partial_kernel<float>), grid, dim3(256), 0, s, (const float*)dz, ld, rows, n, partial);
-  else hipLaunchKernelGGL((bias_grad_partial_kernel<bf16>), grid, dim3(256), 0, s, (const bf16*)dz, ld, rows, n, partial);
-  hipLaunchKernelGGL(bias_grad_finalize_kernel, dim3((n + 255) / 256), dim3(256), 0, s, partial, n, dbias);
-  return hipGetLastError();
+  BiasGradList l{};
+  l.rows = rows; l.n = 1; l.j[0] = BiasGrad{dz, ld, n, partial, dbias};
+  ColSumList sums{};
+  const hipError_t e = bias_grad_rows(dt, l, &sums, s);
+  return e != hipSuccess ? e : col_sums_add(sums, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -470,27 +587,6 @@ hipError_t fill_zero_f32(float* p, size_t n, hipStream_t s) {
 
 __global__ __launch_bounds__(256) void copy_kernel(uint4* dst, const uint4* src, size_t nvec) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < nvec; i += (size_t)gridDim.x * 256) dst[i] = src[i];
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void widen_kernel(float* dst, const T* src, size_t nvec) {
-  constexpr int V = Vec<T>::N;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < nvec; i += (size_t)gridDim.x * 256) {
-    float v[V];
-    ld_row<T>(v, src, (int64_t)i * V, false);
-    st_row<T>(dst, (int64_t)i * V, v, true);
-  }
-}
-
-hipError_t widen_to_f32(DType dt, float* dst, const void* src, size_t n, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  const size_t V = dt == DT_F32 ? 4 : 8;
-  if (n % V) return hipErrorInvalidValue;
-  const size_t nvec = n / V, want = (nvec + 255) / 256;
-  const int grid = (int)(want > 16384 ? 16384 : want);
-  if (dt == DT_F32) hipLaunchKernelGGL((widen_kernel<float>), dim3(grid), dim3(256), 0, s, dst, (const float*)src, nvec);
-  else hipLaunchKernelGGL((widen_kernel<bf16>), dim3(grid), dim3(256), 0, s, dst, (const bf16*)src, nvec);
-  return hipGetLastError();
 }
 
 hipError_t copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t s) {

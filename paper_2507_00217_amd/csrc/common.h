@@ -74,6 +74,8 @@ struct NormArgs {
   int x_f32;                     // x is fp32
   int resid_f32;                 // resid is fp32
   int out_f32;                   // backward: dx is stored as fp32
+  void* x_wide;                  // forward, optional: receives x in fp32
+  void* resid_copy;              // backward, optional (resid in the compute dtype): receives a copy of resid
   void* out_lp;                  // backward, optional: second copy of dx in the compute dtype (a GEMM operand)
 };
 
@@ -87,6 +89,14 @@ struct ActArgs {
 
 int norm_partial_rows();
 
+// Column sums of fp32 partial rows, added to dst: the last step of every parameter gradient that is a sum over rows
+struct ColSum { const float* part; int64_t stride; int cols, parts; float* dst; };
+constexpr int COL_SUM_MAX = 8;       // two norms' gamma and beta, four biases
+struct ColSumList { int n; int first[COL_SUM_MAX]; ColSum j[COL_SUM_MAX]; };
+// Bias gradients of several maps over the same rows; part: bias_grad_partial_bytes(cols) bytes each
+struct BiasGrad { const void* dz; int64_t ld; int cols; float* part; float* dbias; };
+struct BiasGradList { int n, rows; int first[4]; BiasGrad j[4]; };
+
 // plain reference kernels (any dtype); one kernel per mathematical step
 hipError_t gemm_ref(DType dt, const GemmArgs& g, hipStream_t s);
 hipError_t attn_fwd_ref(DType dt, const AttnArgs& a, hipStream_t s);
@@ -95,6 +105,12 @@ hipError_t attn_bwd_ref(DType dt, const AttnArgs& a, hipStream_t s);
 // bandwidth-bound kernels (wavefront reductions, 16-byte accesses)
 hipError_t norm_fwd(DType dt, const NormArgs& n, hipStream_t s);
 hipError_t norm_bwd(DType dt, const NormArgs& n, hipStream_t s);
+// norm_bwd in two steps, so that the second can be shared: dx and the partial sums of dgamma / dbeta (`parts` rows in n.partial),
+// then col_sums_add of what norm_col_sums (and bias_grad_rows) put on a list
+hipError_t norm_bwd_rows(DType dt, const NormArgs& n, hipStream_t s, int* parts);
+void norm_col_sums(const NormArgs& n, int parts, ColSumList* l);
+hipError_t bias_grad_rows(DType dt, BiasGradList& l, ColSumList* sums, hipStream_t s);
+hipError_t col_sums_add(ColSumList& l, hipStream_t s);
 // the same with the partial sums in a fixed device array of the library (n.partial ignored); d <= norm_bwd_noalloc_max_d()
 hipError_t norm_bwd_noalloc(DType dt, const NormArgs& n, hipStream_t s);
 int norm_bwd_noalloc_max_d();
@@ -105,7 +121,6 @@ size_t bias_grad_partial_bytes(int n);
 hipError_t bias_grad(DType dt, const void* dz, int64_t ld, int rows, int n, float* partial, float* dbias, hipStream_t s);
 hipError_t fill_zero_f32(float* p, size_t n, hipStream_t s);
 hipError_t copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t s);
-hipError_t widen_to_f32(DType dt, float* dst, const void* src, size_t n, hipStream_t s);   // dst[i] = (float)src[i]
 // rotary position embedding: table [s][hd/2] of (cos, sin) pairs; rotation in place of the first nh heads of each row
 hipError_t rope_table(float* table, int s, int hd, double theta, hipStream_t st);
 hipError_t rope_apply(DType dt, void* x, int64_t ld, int64_t rows, int s, int nh, int hd, const float* table, int inverse,

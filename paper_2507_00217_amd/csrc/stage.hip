@@ -137,18 +137,19 @@ size_t slot_bytes(const Dims& D) { return (D.recompute ? x_bytes(D) : rec_bytes(
 size_t big_slot_bytes(const Dims& D) { return D.recompute ? rec_bytes(D) * D.L : 0; }
 size_t stash_bytes(const Dims& D) { return slot_bytes(D) * D.cap + big_slot_bytes(D) * D.hcap; }
 
-struct WsOff { size_t da, dn, delta, partial, rec, dkvp, rope, bpart, end; };
+struct WsOff { size_t da, dn, delta, partial, partial2, rec, dkvp, rope, bpart, end; };
 WsOff ws_off(const Dims& D) {
   WsOff w; size_t p = 0;
   auto take = [&](size_t bytes) { size_t r = p; p += up(bytes); return r; };
   w.da = take((size_t)D.T * D.f * D.es);
   w.dn = take((size_t)D.T * (D.d > D.da ? D.d : D.da) * D.es);
   w.delta = take((size_t)D.b * D.h * D.s * sizeof(float));
-  w.partial = take((size_t)norm_partial_rows() * 2 * D.d * sizeof(float));
+  w.partial = take((size_t)norm_partial_rows() * 2 * D.d * sizeof(float));      // the layer's first norm
+  w.partial2 = take((size_t)norm_partial_rows() * 2 * D.d * sizeof(float));     // and its second: both summed at the end of its B
   w.rec = take(D.recompute ? rec_bytes(D) : 0);       // the layer record F works in under recomputation
   w.dkvp = take(D.es == 2 ? attn_bwd_part_bytes(D.b, D.s, D.h, D.hkv, D.hd) : 0);   // grouped-query dK/dV partials
   w.rope = take(D.rope ? (size_t)D.s * (D.hd / 2) * 2 * sizeof(float) : 0);          // (cos, sin) per position and pair
-  w.bpart = take(D.bias ? bias_grad_partial_bytes(D.fin > D.dq ? (D.fin > D.d ? D.fin : D.d) : (D.dq > D.d ? D.dq : D.d)) : 0);
+  w.bpart = take(D.bias ? bias_grad_partial_bytes(D.fin + D.dq + 2 * D.d) : 0);   // the four maps' biases
   w.end = p;
   return w;
 }
@@ -367,15 +368,17 @@ AttnArgs attn_args(const stage* st, const LayerBuf& o, const void* dout, const W
   return a;
 }
 
-// Forward of layer l through the record `o`.  y_l: where the layer's output goes (fp32 unless `y_lp`); nullptr
+// Forward of layer l through the record `o`.  x_in: the caller's input in the compute dtype, which the first norm also widens
+// into the record's x; nullptr: x is already there.  y_l: where the layer's output goes (fp32 unless `y_lp`); nullptr
 // skips the last GEMM, which is what rebuilding a record for B needs.
-int forward_layer(stage* st, int l, const LayerBuf& o, void* y_l, bool y_lp) {
+int forward_layer(stage* st, int l, const LayerBuf& o, const void* x_in, void* y_l, bool y_lp) {
   const Dims& D = st->D;
   const LayerW W = layer_weights(st, l);
   const WsOff w = ws_off(D);
-  NormArgs n{}; n.kind = st->cfg.norm; n.rows = D.T; n.d = D.d; n.eps = st->cfg.norm_eps; n.x_f32 = 1;
-  n.x = o.x; n.gamma = W.g1; n.beta = W.b1; n.out = o.n1; n.stats = o.st1;
-  { ProfScope ps(st, STAGE_K_NORM_FWD, norm_bytes(st, 1, 1)); HIPCHK(norm_fwd(st->dt, n, st->stream)); }
+  NormArgs n{}; n.kind = st->cfg.norm; n.rows = D.T; n.d = D.d; n.eps = st->cfg.norm_eps; n.x_f32 = x_in ? 0 : 1;
+  n.x = x_in ? x_in : o.x; n.x_wide = x_in ? o.x : nullptr; n.gamma = W.g1; n.beta = W.b1; n.out = o.n1; n.stats = o.st1;
+  { ProfScope ps(st, STAGE_K_NORM_FWD, norm_bytes(st, 1, x_in ? 2 : 1)); HIPCHK(norm_fwd(st->dt, n, st->stream)); }
+  n.x_f32 = 1; n.x_wide = nullptr;
   int rc = do_gemm(st, GEMM_NN, D.T, D.dq, D.d, o.n1, D.d, W.wqkv, D.dq, o.qkv, D.dq, nullptr, 0, 0, 0, 0, W.bqkv);
   if (rc) return rc;
   if (D.rope) {      // q and k of the stash are the rotated ones: attention forward and backward both want those
@@ -408,16 +411,11 @@ int forward_layer(stage* st, int l, const LayerBuf& o, void* y_l, bool y_lp) {
 // layers [l0, l1): x is read when l0 == 0, y is written when l1 == L
 int exec_forward(stage* st, int mb, const void* x, void* y, int l0, int l1) {
   const Dims& D = st->D;
-  const size_t n_act = (size_t)D.T * D.d;
-  if (l0 == 0) {
-    ProfScope ps(st, STAGE_K_COPY, (double)n_act * (D.es + sizeof(float)));
-    HIPCHK(widen_to_f32(st->dt, (float*)layer_buf(st, mb, 0, REC_WORKSPACE).x, x, n_act, st->stream));
-  }
   for (int l = l0; l < l1; ++l) {
     const bool last = l + 1 == D.L;
     // the output is the next layer's fp32 x, or the caller's Y
     void* y_l = last ? y : (void*)layer_buf(st, mb, l + 1, REC_WORKSPACE).x;
-    const int rc = forward_layer(st, l, layer_buf(st, mb, l, REC_WORKSPACE), y_l, last);
+    const int rc = forward_layer(st, l, layer_buf(st, mb, l, REC_WORKSPACE), l == 0 ? x : nullptr, y_l, last);
     if (rc) return rc;
   }
   return STAGE_OK;
@@ -427,11 +425,6 @@ int exec_forward(stage* st, int mb, const void* x, void* y, int l0, int l1) {
 int exec_backward_input(stage* st, int mb, const void* dy, void* dx, int l0, int l1) {
   const Dims& D = st->D;
   const WsOff w = ws_off(D);
-  const size_t act_bytes = (size_t)D.T * D.d * D.es;
-  if (l1 == D.L) {
-    ProfScope ps(st, STAGE_K_COPY, 2.0 * act_bytes);
-    HIPCHK(copy_bytes(layer_buf(st, mb, D.L - 1).dyb, dy, act_bytes, st->stream));
-  }
   void* da = st->ws + w.da;
   void* dn = st->ws + w.dn;
   for (int l = l1 - 1; l >= l0; --l) {
@@ -439,20 +432,18 @@ int exec_backward_input(stage* st, int mb, const void* dy, void* dx, int l0, int
     const LayerW W = layer_weights(st, l);
     const bool last = l + 1 == D.L;
     int rc;
-    if (D.recompute && (rc = forward_layer(st, l, o, nullptr, false))) return rc;
+    if (D.recompute && (rc = forward_layer(st, l, o, nullptr, nullptr, false))) return rc;
     // gradient arriving at this layer's output: GEMM operand copy in the compute dtype, and the residual-branch
     // term, which is the fp32 dx the layer above left in its x region (the caller's dY for the last layer)
-    const void* dy_op = o.dyb;
+    // The last layer reads the caller's dY; W needs it later, so the second norm's backward, which adds it, copies it into the
+    // slot as it goes by.  (A dY that the tuned products do not take as an operand is copied first.)
+    const bool in_place = last && ((uintptr_t)dy & 15) == 0;
+    if (last && !in_place) {
+      ProfScope ps(st, STAGE_K_COPY, 2.0 * D.T * D.d * D.es);
+      HIPCHK(copy_bytes(o.dyb, dy, (size_t)D.T * D.d * D.es, st->stream));
+    }
+    const void* dy_op = in_place ? dy : (const void*)o.dyb;
     const void* dy_res = last ? dy_op : (const void*)layer_buf(st, mb, l + 1).x;
-    // bias gradients: column sums of the four dZ tensors, as each becomes available
-    float* bpart = (float*)(st->ws + w.bpart);
-    auto dbias = [&](const void* dz, int n, int pid) -> int {
-      if (!D.bias) return STAGE_OK;
-      ProfScope ps(st, STAGE_K_COPY, (double)D.T * n * D.es);
-      HIPCHK(bias_grad(st->dt, dz, n, D.T, n, bpart, W.G[pid], st->stream));
-      return STAGE_OK;
-    };
-    if ((rc = dbias(dy_op, D.d, STAGE_P_BOUT))) return rc;
     // FFN: da = dy.Wout^T ; dz = act'(z) * da (in place over z) ; dn2 = dz.Win^T
     if (try_gemm_act_bwd(st, &rc, D.T, D.f, D.d, dy_op, W.wout, o.z)) {
       if (rc) return rc;
@@ -462,17 +453,20 @@ int exec_backward_input(stage* st, int mb, const void* dy, void* dx, int l0, int
       ActArgs ac{}; ac.kind = st->cfg.act; ac.rows = D.T; ac.f = D.f; ac.z = o.z; ac.da = da;
       { ProfScope ps(st, STAGE_K_ACT_BWD, (double)D.T * (2.0 * D.fin + D.f) * D.es); HIPCHK(act_bwd(st->dt, ac, st->stream)); }
     }
-    if ((rc = dbias(o.z, D.fin, STAGE_P_BIN))) return rc;
     rc = do_gemm(st, GEMM_NT, D.T, D.d, D.fin, o.z, D.fin, W.win, D.fin, dn, D.d, nullptr, 0, 0);
     if (rc) return rc;
     // dx1 = dy + norm2'(dn2): fp32 in place over x1, plus a compute-dtype copy for the two GEMMs that read it
     NormArgs n{}; n.kind = st->cfg.norm; n.rows = D.T; n.d = D.d; n.eps = st->cfg.norm_eps;
     n.x = o.x1; n.x_f32 = 1; n.gamma = W.g2; n.out = o.x1; n.out_f32 = 1; n.out_lp = o.dx1b;
     n.stats = o.st2; n.dout = dn; n.resid = dy_res; n.resid_f32 = last ? 0 : 1;
-    n.dgamma = W.G[STAGE_P_NORM2_GAMMA]; n.dbeta = W.G[STAGE_P_NORM2_BETA]; n.partial = (float*)(st->ws + w.partial);
-    { ProfScope ps(st, STAGE_K_NORM_BWD, norm_bytes(st, last ? 2 : 3, last ? 3 : 2)); HIPCHK(norm_bwd(st->dt, n, st->stream)); }
+    n.dgamma = W.G[STAGE_P_NORM2_GAMMA]; n.dbeta = W.G[STAGE_P_NORM2_BETA]; n.partial = (float*)(st->ws + w.partial2);
+    n.resid_copy = in_place ? o.dyb : nullptr;
+    ColSumList sums{};
+    int parts = 0;
+    { ProfScope ps(st, STAGE_K_NORM_BWD, norm_bytes(st, last ? 2 : 3, last ? (in_place ? 4 : 3) : 2)); HIPCHK(norm_bwd_rows(st->dt, n, st->stream, &parts)); }
+    norm_col_sums(n, parts, &sums);
+    n.resid_copy = nullptr;
     // attention: do = dx1.Wo^T ; (dq,dk,dv) ; dn1 = dqkv.Wqkv^T
-    if ((rc = dbias(o.dx1b, D.d, STAGE_P_BO))) return rc;
     rc = do_gemm(st, GEMM_NT, D.T, D.da, D.d, o.dx1b, D.d, W.wo, D.d, dn, D.da, nullptr, 0, 0);
     if (rc) return rc;
     AttnArgs a = attn_args(st, o, dn, w);
@@ -486,7 +480,6 @@ int exec_backward_input(stage* st, int mb, const void* dy, void* dx, int l0, int
       ProfScope ps(st, STAGE_K_ROPE, 2.0 * D.T * (D.da + D.dkv) * D.es);
       HIPCHK(rope_apply(st->dt, o.dqkv, D.dq, D.T, D.s, D.h + D.hkv, D.hd, (const float*)(st->ws + w.rope), 1, st->stream));
     }
-    if ((rc = dbias(o.dqkv, D.dq, STAGE_P_BQKV))) return rc;
     rc = do_gemm(st, GEMM_NT, D.T, D.d, D.dq, o.dqkv, D.dq, W.wqkv, D.dq, dn, D.d, nullptr, 0, 0);
     if (rc) return rc;
     // dx = dx1 + norm1'(dn1): layer 0 hands it to the caller; otherwise fp32 in place over x (the residual term of
@@ -495,7 +488,24 @@ int exec_backward_input(stage* st, int mb, const void* dy, void* dx, int l0, int
     n.dgamma = W.G[STAGE_P_NORM1_GAMMA]; n.dbeta = W.G[STAGE_P_NORM1_BETA];
     if (l == 0) { n.out = dx; n.out_f32 = 0; n.out_lp = nullptr; }
     else { n.out = o.x; n.out_f32 = 1; n.out_lp = layer_buf(st, mb, l - 1).dyb; }
-    { ProfScope ps(st, STAGE_K_NORM_BWD, norm_bytes(st, l == 0 ? 2 : 3, 2)); HIPCHK(norm_bwd(st->dt, n, st->stream)); }
+    n.partial = (float*)(st->ws + w.partial);
+    { ProfScope ps(st, STAGE_K_NORM_BWD, norm_bytes(st, l == 0 ? 2 : 3, 2)); HIPCHK(norm_bwd_rows(st->dt, n, st->stream, &parts)); }
+    norm_col_sums(n, parts, &sums);
+    // bias gradients: the column sums of the layer's four dZ tensors, all of which the slot holds until W; then one launch adds
+    // every partial sum of the layer to its parameter's gradient
+    if (D.bias) {
+      BiasGradList bl{};
+      float* bp = (float*)(st->ws + w.bpart);
+      bl.rows = D.T;
+      auto add = [&](const void* dz, int cols, int pid) {
+        bl.j[bl.n++] = BiasGrad{dz, cols, cols, bp, W.G[pid]};
+        bp += bias_grad_partial_bytes(cols) / sizeof(float);
+      };
+      add(o.dyb, D.d, STAGE_P_BOUT); add(o.z, D.fin, STAGE_P_BIN); add(o.dx1b, D.d, STAGE_P_BO); add(o.dqkv, D.dq, STAGE_P_BQKV);
+      ProfScope ps(st, STAGE_K_COPY, (double)D.T * (2 * D.d + D.fin + D.dq) * D.es);
+      HIPCHK(bias_grad_rows(st->dt, bl, &sums, st->stream));
+    }
+    { ProfScope ps(st, STAGE_K_NORM_BWD, 0.0); HIPCHK(col_sums_add(sums, st->stream)); }
   }
   return STAGE_OK;
 }
