@@ -637,34 +637,50 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
     }
     return;
   }
+  if constexpr (EPI == EPI_RESID) {
+    // C = acc (+ R), fp32 or bf16.  R is fetched GR block rows ahead of the one being stored, all of a 128 x 128 tile's at once
+    // and without branches (elements outside the matrix read its last ones): one row at a time the tile waited for memory
+    // once per row, 6 us of a 2048 x 2048 product and 4 of the 12 us of a 400 x 640 one.
+    auto store = [&](int i, int j, f32x4 v) __attribute__((always_inline)) {
+      const int m = m0 + wm + i * 16 + row_l, n = n0 + wn + j * 16 + col_l;
+      if (m >= g.M || n >= g.N) return;          // N % 8 == 0 and n % 4 == 0: the 4 columns are in or out together
+      if (g.c_f32) *reinterpret_cast<f32x4*>((float*)g.C + (int64_t)m * g.ldc + n) = v;
+      else *reinterpret_cast<bf16x4*>((bf16*)g.C + (int64_t)m * g.ldc + n) = bf16x4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
+    };
+    auto add_resid = [&](auto zero) __attribute__((always_inline)) {
+      using RT = decltype(zero);                 // float or bf16
+      typedef RT rvec __attribute__((ext_vector_type(4)));
+      constexpr int GR = SMALL ? NI : 2;
+      rvec r[2][GR][NJ];
+      auto fetch = [&](int set, int i0) __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int m = m0 + wm + i * 16 + row_l;
-    if (m >= g.M) continue;
+        for (int i = 0; i < GR; ++i) {
+          const RT* row = (const RT*)g.R + (int64_t)min(m0 + wm + (i0 + i) * 16 + row_l, g.M - 1) * g.ldr;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int n = n0 + wn + j * 16 + col_l;
-      if (n >= g.N) continue;          // N % 8 == 0 and n % 4 == 0: the 4 columns are in or out together
-      f32x4 v = acc[i][j];
-      {
-        if (EPI == EPI_RESID && g.R) {
-          if (g.r_f32) {
-            v += *reinterpret_cast<const f32x4*>((const float*)g.R + (int64_t)m * g.ldr + n);
-          } else {
-            bf16x4 r = *reinterpret_cast<const bf16x4*>((const bf16*)g.R + (int64_t)m * g.ldr + n);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] += (float)r[e];
-          }
+          for (int j = 0; j < NJ; ++j) r[set][i][j] = *reinterpret_cast<const rvec*>(row + min(n0 + wn + j * 16 + col_l, g.N - 4));
         }
-        if (EPI == EPI_RESID && g.c_f32) {
-          *reinterpret_cast<f32x4*>((float*)g.C + (int64_t)m * g.ldc + n) = v;
-        } else {
-          bf16x4 o;
+      };
+      fetch(0, 0);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = (bf16)v[e];
-          *reinterpret_cast<bf16x4*>((bf16*)g.C + (int64_t)m * g.ldc + n) = o;
-        }
+      for (int i0 = 0; i0 < NI; i0 += GR) {
+        const int set = (i0 / GR) & 1;
+        if (i0 + GR < NI) fetch(set ^ 1, i0 + GR);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < GR; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            store(i0 + i, j, acc[i0 + i][j] + f32x4{(float)r[set][i][j][0], (float)r[set][i][j][1], (float)r[set][i][j][2], (float)r[set][i][j][3]});
+        __builtin_amdgcn_sched_barrier(0);
       }
+    };
+    if (g.R && g.r_f32) add_resid(0.f);
+    else if (g.R) add_resid((bf16)0.f);
+    else {
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) store(i, j, acc[i][j]);
     }
   }
 }
@@ -678,6 +694,18 @@ __device__ __forceinline__ void tile_of(int idx, int tiles_m, int tiles_n, int& 
   const int gsz = min(tiles_m - first_m, GROUP);
   tile_m = first_m + (idx % in_group) % gsz;
   tile_n = (idx % in_group) / gsz;
+}
+
+// Walk order of the smaller tiles, as a permutation of the local index i (n of them) of the full tile they are a part of: an XCD
+// works on 8 (128 x 128 tiles) or 16 (half-height) consecutive ones, which in the order above are one or two columns of 8
+// rows -- 2304 or 2560 operand rows per K tile through its L2.  Exchanging index bits makes that 4 x 2 or 4 x 4 full tiles, 1536
+// or 2048 rows.  (The tail of a product starts somewhere in a column, which costs some of the gain and nothing else.)
+template <int COL_BITS>
+__device__ __forceinline__ int compact(int i, int n) {
+  constexpr int CHUNK = 8 << COL_BITS;
+  if ((i & ~(CHUNK - 1)) + CHUNK > n) return i;
+  const int j = i & (CHUNK - 1), half = j >> (2 + COL_BITS), col = (j >> 2) & ((1 << COL_BITS) - 1);
+  return (i & ~(CHUNK - 1)) | (col << 3) | (half << 2) | (j & 3);
 }
 
 // one workgroup per tile: workgroup `bid` takes the full tile number first + bid of the walk order (WR == 2), or the
@@ -698,7 +726,7 @@ __global__ __launch_bounds__(WR * 512 / TN, WR == 1 ? 2 : 1) void gemm_mfma_kern
     if (bid < main) bid = (bid & 7) * per + (bid >> 3);
   }
   int tile_m, tile_n;
-  tile_of(first + (WR == 2 ? bid : bid >> 1), tiles_m, tiles_n, tile_m, tile_n);
+  tile_of(first + (WR == 2 ? bid : compact<2>(bid >> 1, nb >> 1)), tiles_m, tiles_n, tile_m, tile_n);
   gemm_tile<AKC, BKC, EPI, TN, WR>(g, tile_m * BM + (WR == 2 ? 0 : (bid & 1) * 128), tile_n * (EPI == EPI_SWIGLU ? GLU_BN : BN),
                                    (lds_char*)smem_raw);
 }
@@ -715,7 +743,7 @@ __global__ __launch_bounds__(256, 2) void gemm_quarter_kernel(   // (register bu
     if (bid < main) bid = (bid & 7) * per + (bid >> 3);
   }
   int tile_m, tile_n;
-  tile_of(first + (bid >> 2), tiles_m, tiles_n, tile_m, tile_n);
+  tile_of(first + compact<1>(bid >> 2, (int)gridDim.x >> 2), tiles_m, tiles_n, tile_m, tile_n);
   constexpr int TB = EPI == EPI_SWIGLU ? GLU_BN : BN;
   const int m0 = tile_m * BM + (bid & 1) * 128, n0 = tile_n * TB + ((bid >> 1) & 1) * (TB / 2);
   if (m0 >= g.M || n0 >= (EPI == EPI_SWIGLU ? g.N / 2 : g.N)) return;                  // the same for the whole workgroup
@@ -763,7 +791,7 @@ __global__ __launch_bounds__(256, 2) void gemm_wgrad_quarter_kernel(GemmGroup gg
     const int per = (int)gridDim.x >> 3, main = per << 3;
     if (bid < main) bid = (bid & 7) * per + (bid >> 3);
   }
-  const int t = first + (bid >> 2);
+  const int t = first + compact<1>(bid >> 2, (int)gridDim.x >> 2);
   int pi = 0;
   while (pi + 1 < gg.n && t >= gg.first_tile[pi + 1]) ++pi;
   const GemmArgs& g = gg.p[pi];
