@@ -14,7 +14,7 @@
  * attention entries also take 2 and 3: the tuned kernels with a choice they
  * normally make from the shape fixed, so that tests reach both variants on any
  * shape -- GEMM: 2 = full 256 x 256 tiles only, 3 = half-height tiles only, 4 (stage_kernel_gemm, forward and
- * input-gradient layouts) = 128 x 128 tiles only; in fp32 2 / 3 / 4 = tiles of 64 x 64 / 32 x 32 / 16 x 16 (weight gradients:
+ * input-gradient layouts) = 128 x 128, 5 = 64 x 64, 6 = 128 x 64 tiles only; in fp32 2 / 3 / 4 = tiles of 64 x 64 / 32 x 32 / 16 x 16 (weight gradients:
  * 32 x 32 for 4 as well) for the products and the two fused-activation entries;
  * attention: 2 / 3 = forward and dQ workgroups of 8 / 4 wavefronts (dK/dV workgroups of 128 keys), 4 = forward and dQ
  * workgroups of 64 queries whose two wavefronts per query block each take half of the keys, dK/dV workgroups of 64 keys.

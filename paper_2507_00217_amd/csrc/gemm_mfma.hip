@@ -52,6 +52,7 @@ enum Epi { EPI_STORE = 0, EPI_RESID = 1, EPI_ACC32 = 2, EPI_GELU = 3, EPI_SWIGLU
 // the up columns f + j of the product (even blocks gate, odd blocks up), so that a lane's two accumulator blocks are
 // the gate and the up value of the same 32 features and silu(gate) * up is formed in registers.
 constexpr int GLU_BN = 128;
+constexpr int TINY_DEPTH = 8;       // K tiles ahead of the 64 x 64 tile: 17 slots of 8 KiB
 
 // Phi(u) = the normal distribution function and e = exp(-u^2 / 2), from which GELU u * Phi(u) and its derivative Phi(u) +
 // u * e / sqrt(2 pi) follow.  With a = |u| and t = 1 / (1 + 0.21 a), Phi(-a) * exp(a^2 / 2) = t * P(t), P a polynomial of degree
@@ -99,9 +100,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, un
 // (j*8 + w)*64 .. +63, lane l the l-th of them.  Rows past the end of the matrix fall outside the buffer's range
 // by themselves or are redirected to OOB, which stores zeros.
 // (a [row][k] tile may have any multiple of 8 rows: WAVES * 64 * CH pieces; a [k][row] tile has PCS pieces = 8 * PCS rows
-// per reduction row, 32 or 16, and the same formulas with 32 replaced by PCS)
+// per reduction row, 32, 16 or 8, and the same formulas with 32 replaced by PCS)
 // glu_f > 0 (a [k][row] B tile of EPI_SWIGLU): row0 is the tile's first feature and piece p = 8 columns of block p / 4
 // fetches columns (odd block ? glu_f : 0) + row0 + (p / 8) * 32 + (p % 4) * 8 ..
+// swz of a [k][row] tile with PCS pieces per reduction row; with 8 (128-byte rows) two consecutive rows share a turn of the
+// banks, so bit 1 of k and not bit 0 moves a row by 64 bytes
+template <int PCS> __device__ __forceinline__ int swz(int k) {
+  static_assert(PCS == 8 || PCS == 16 || PCS == 32, "row widths of the tiles");
+  return PCS == 8 ? (((k >> 1) & 1) << 2) | (((k >> 3) & 1) << 1) : ((k & 3) << 2) | (((k >> 3) & 1) << 1);
+}
 template <bool KC, int WAVES, int CH, int PCS = 32>
 __device__ __forceinline__ void tile_offsets(unsigned (&off)[CH], int64_t ld, int row0, int rows, int wave, int lane,
                                              int glu_f = 0) {
@@ -113,7 +120,7 @@ __device__ __forceinline__ void tile_offsets(unsigned (&off)[CH], int64_t ld, in
       const int r = s >> 3, c = (s & 7) ^ ((r >> 1) & 7);
       off[j] = row0 + r < rows ? (unsigned)(((int64_t)(row0 + r) * ld + c * 8) * 2) : OOB;
     } else {
-      const int k = s / PCS, p = (s % PCS) ^ (((k & 3) << 2) | (((k >> 3) & 1) << 1));
+      const int k = s / PCS, p = (s % PCS) ^ swz<PCS>(k);
       int row = row0 + p * 8;
       bool ok = row < rows;
       if (glu_f) {
@@ -172,7 +179,7 @@ __device__ __forceinline__ void frag_offsets(unsigned (&ad)[NB], int row0, int l
   } else {
     const int g = lane >> 4, li = lane & 15;
     const int krow = g * 8 + (li >> 2);
-    const int sw = ((krow & 3) << 2) | (((krow >> 3) & 1) << 1);
+    const int sw = swz<PCS>(krow);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       const int p = ((row0 >> 4) + b) * 2 + ((li & 3) >> 1);                   // 16-byte piece of the reduction row
@@ -221,17 +228,19 @@ __device__ __forceinline__ void dswiglu4(f32x4 da, bf16x4 gt, bf16x4 up, bf16x4&
 // pass over K then does the work of nseg launches with a single read-modify-write of C, and -- fp32 accumulators
 // written to and read back from fp32 memory unchanged -- gives the same bits as those launches one after another.
 // WR, WC = rows and columns of 128 in the tile: (2, 2) -> 256 x 256 (wave grid 2 x WGN); (1, 2) -> 128 x 256 (wave grid
-// 1 x WGN, half the wavefronts; A must be a [row][k] operand); (1, 1) -> 128 x 128 (four wavefronts of 64 x 64).  The smaller tiles exist for the work a grid of full tiles would leave to a fraction of the
+// 1 x WGN, half the wavefronts; A must be a [row][k] operand); (1, 1) -> 128 x 128 (four wavefronts of 64 x 64); (1, 0) -> 128 x
+// 64 (four of 64 x 32, or 32 x 64 for SwiGLU, whose gate and up columns are a wavefront's two halves); (0, 0) -> 64 x 64 (four of 32 x 32).  The smaller tiles exist for the work a grid of full tiles would leave to a fraction of the
 // CUs: the last, partly filled round of a product, and products with few tiles.
 template <bool AKC, bool BKC, int EPI, int TN, int WR = 2, int WC = 2, int SMALL_DEPTH = 4>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds_char* smem, int nseg = 1,
                                           const int64_t* seg_delta = nullptr) {
-  static_assert(WR == 2 || AKC || WC == 1, "the half-height tile takes a [row][k] A operand");
-  static_assert(WC == 2 || (WR == 1 && TN == 2), "the 128 x 128 tile: four wavefronts of 64 x 64");
+  static_assert(WR == 2 || AKC || WC <= 1, "the half-height tile takes a [row][k] A operand");
+  static_assert(WC == 2 || (WR == 1 && WC == 1 && TN == 2) || (WR <= 1 && WC == 0 && TN == 1) || (WR == 1 && WC == 0 && TN == 2),
+                "four wavefronts of 64 x 64, 64 x 32, 32 x 64 or 32 x 32");
   constexpr bool GLU = EPI == EPI_SWIGLU;
   static_assert(!GLU || (TN == 2 && !BKC), "gate and up blocks are the two halves of a wavefront's columns");
-  constexpr int BMV = WR * 128, BNV = WC * 128;                                    // tile: BMV rows, BNV columns
-  constexpr int RW = WC == 1 ? 64 : 128;                                           // rows of a wavefront's sub-tile
+  constexpr int BMV = WR ? WR * 128 : 64, BNV = WC ? WC * 128 : 64;                // tile: BMV rows, BNV columns
+  constexpr int RW = WR == 0 || (WC == 0 && TN == 2) ? 32 : WC <= 1 ? 64 : 128;                                           // rows of a wavefront's sub-tile
   constexpr int WGN = BNV / (TN * 32), WAVES = (BMV / RW) * WGN;
   constexpr int A_BYTES = BMV * BK * 2, B_BYTES = BNV * BK * 2;
   constexpr int PCS = BNV / 8;                                                     // 16-byte pieces per row of C / per reduction row of a [k][row] B tile
@@ -243,8 +252,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   // holds -- and the same lead in time needs -- twice the depth: with a lead of two K tiles (about 1 us here) operands
   // that come from HBM rather than from a cache arrive late, and products of this tile ran a quarter to a third slower
   // on cold operands than on warm ones.
-  constexpr bool SMALL = WR == 1 && WC == 1;
-  constexpr int SLOT = SMALL ? TILE_BYTES / 2 : TILE_BYTES, DEPTH = SMALL ? SMALL_DEPTH : 2, NSLOT = 2 * DEPTH + 1;
+  constexpr bool SMALL = WC <= 1;
+  constexpr int SLOT = WR == 0 ? TILE_BYTES / 4 : SMALL ? TILE_BYTES / 2 : TILE_BYTES, DEPTH = SMALL ? SMALL_DEPTH : 2, NSLOT = 2 * DEPTH + 1;
   static_assert(A_BYTES <= SLOT && B_BYTES <= SLOT && (size_t)NSLOT * SLOT <= LDS_BYTES, "ring fits");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -342,9 +351,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   // to land.  Away from the end of the reduction the loop body has no branches.
   constexpr int NMFMA = NI * NJ;                                // MFMAs per k-step
   constexpr int NFRAG = NI + NJ;                                // fragments per k-step
-  static_assert(NMFMA % CHA == 0 && NMFMA % CHB == 0 && NMFMA >= 2 * NFRAG, "placement of loads and fragment reads");
+  constexpr int EVERY = NMFMA >= 2 * NFRAG ? 2 : 1;             // MFMAs per fragment read
+  static_assert(NMFMA % CHA == 0 && NMFMA % CHB == 0 && NMFMA >= EVERY * NFRAG, "placement of loads and fragment reads");
   bf16x8 fa[2][NI], fb[2][NJ];
-  // one k-step: the MFMAs on fragment set `cur`; after every second MFMA one fragment of `ks_next` into the other set
+  // one k-step: the MFMAs on fragment set `cur`; after every second MFMA (every one on the smallest tile) one fragment of `ks_next` into the other set
   // (B's first: the first MFMAs of the next k-step need all of them); and the loads of operand tile `op` (0 = A, 1 = B)
   // spread between the MFMAs
   auto kstep = [&](auto cur_c, auto ks_c, auto op_c, auto tail_c, lds_char* dst) __attribute__((always_inline)) {
@@ -360,8 +370,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
         acc[i][js] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[cur][js], fa[cur][i], acc[i][js], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         const int n = i * NJ + j;
-        if (n % 2 == 0 && n / 2 < NFRAG) {
-          const int f = n / 2;
+        if (n % EVERY == 0 && n / EVERY < NFRAG) {
+          const int f = n / EVERY;
           if (f < NJ) fb[cur ^ 1][f] = frag<BKC, NPB, PCS>(pb, f, ks_next);
           else fa[cur ^ 1][f - NJ] = frag<AKC, NPA, PCA>(pa, f - NJ, ks_next);
         }
@@ -376,7 +386,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   };
   std::integral_constant<int, 0> c0; std::integral_constant<int, 1> c1;
 
-  __builtin_amdgcn_s_waitcnt(0);   // the start-up tiles (and C for weight gradients) landed
+  auto wait_vm = [](auto n_c) { constexpr int n = decltype(n_c)::value; static_assert(n < 64, "vmcnt is a 6-bit count"); __builtin_amdgcn_s_waitcnt(0x0070 | (n & 15) | ((n >> 4) << 14)); };
+  // the first K tile has landed (with weight gradients, whose C is fetched after the start-up tiles: all of them, and C)
+  if (EPI != EPI_ACC32 && nk >= DEPTH) wait_vm(std::integral_constant<int, (DEPTH - 1) * (CHA + CHB)>{});
+  else __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < NJ; ++j) fb[0][j] = frag<BKC, NPB, PCS>(pb, j, 0);
@@ -393,12 +406,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
     // A(kt+1), B(kt+1) have landed once nothing older than the loads of A(kt+2) ... A(kt+DEPTH) is outstanding (in the
     // last trips: of the tiles that are left beyond kt+1); own LDS reads are done
     constexpr int VM = (DEPTH - 1) * CHA + (DEPTH - 2) * CHB;
-    static_assert(VM < 64, "vmcnt is a 6-bit count");
-    auto wait_vm = [](auto n_c) { constexpr int n = decltype(n_c)::value; __builtin_amdgcn_s_waitcnt(0x0070 | (n & 15) | ((n >> 4) << 14)); };
-    if (!tail) wait_vm(std::integral_constant<int, VM>{});
-    else if (DEPTH == 4 && nk - kt == 4) wait_vm(std::integral_constant<int, DEPTH == 4 ? 2 * (CHA + CHB) : 0>{});
-    else if (DEPTH == 4 && nk - kt == 3) wait_vm(std::integral_constant<int, DEPTH == 4 ? CHA + CHB : 0>{});
-    else __builtin_amdgcn_s_waitcnt(0);
+    if constexpr (!tail) wait_vm(std::integral_constant<int, VM>{});
+    else {
+      auto left = [&](auto n_c) {                     // n K tiles beyond kt + 1 may be outstanding
+        constexpr int n = decltype(n_c)::value;
+        if constexpr (n > 0 && n <= DEPTH - 2) { if (nk - kt == n + 2) { wait_vm(std::integral_constant<int, n * (CHA + CHB)>{}); return true; } }
+        return false;
+      };
+      if (!(left(std::integral_constant<int, 6>{}) || left(std::integral_constant<int, 5>{}) || left(std::integral_constant<int, 4>{}) ||
+            left(std::integral_constant<int, 3>{}) || left(std::integral_constant<int, 2>{}) || left(std::integral_constant<int, 1>{})))
+        __builtin_amdgcn_s_waitcnt(0);
+      static_assert(DEPTH <= 8, "cases above");
+    }
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
     {
@@ -750,6 +769,25 @@ __global__ __launch_bounds__(256, 2) void gemm_quarter_kernel(   // (register bu
   gemm_tile<AKC, BKC, EPI, 2, 1, 1>(g, m0, n0, (lds_char*)smem_raw);
 }
 
+// one workgroup per 64 x 64 (WR == 0) or 128 x 64 tile (WR == 1): workgroup `bid` takes the sixteenth bid % 16 (eighth bid % 8) of full
+// tile number first + bid / 16 (/ 8)
+template <bool AKC, bool BKC, int EPI, int WR>
+__global__ __launch_bounds__(256, 2) void gemm_tiny_kernel(GemmArgs g, int tiles_m, int tiles_n, int first) {
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  int bid = blockIdx.x;
+  {
+    const int per = (int)gridDim.x >> 3, main = per << 3;
+    if (bid < main) bid = (bid & 7) * per + (bid >> 3);
+  }
+  int tile_m, tile_n;
+  constexpr int RB = WR ? 1 : 2;                       // log2 of the tile rows inside a full tile
+  tile_of(first + (bid >> (RB + 2)), tiles_m, tiles_n, tile_m, tile_n);
+  constexpr int TB = EPI == EPI_SWIGLU ? GLU_BN : BN;
+  const int m0 = tile_m * BM + (bid & ((1 << RB) - 1)) * (BM >> RB), n0 = tile_n * TB + ((bid >> RB) & 3) * (TB / 4);
+  if (m0 >= g.M || n0 >= (EPI == EPI_SWIGLU ? g.N / 2 : g.N)) return;
+  gemm_tile<AKC, BKC, EPI, EPI == EPI_SWIGLU ? 2 : 1, WR, 0, WR ? 4 : TINY_DEPTH>(g, m0, n0, (lds_char*)smem_raw);
+}
+
 // Several weight-gradient products C_p += A_p^T . B_p in one launch of persistent workgroups.  Each workgroup
 // takes the tiles  r * gridDim.x + (its slot)  of the concatenated tile list, r = 0, 1, ...: after it has issued a
 // tile's stores it goes straight on to the next tile's C and operand loads, so the read-modify-write of the fp32
@@ -782,24 +820,26 @@ __global__ __launch_bounds__(1024 / TN) void gemm_wgrad_group_kernel(GemmGroup g
   }
 }
 
-// The same products in 128 x 128 tiles, one workgroup each: workgroup `bid` takes quadrant bid % 4 of tile number first + bid / 4.
-template <int DEPTH>
-__global__ __launch_bounds__(256, 2) void gemm_wgrad_quarter_kernel(GemmGroup gg, int first) {
+// The same products in tiles of 128 x 128 (WR, WC = 1, 1), 128 x 64 (1, 0) or 64 x 64 (0, 0), one workgroup each: workgroup `bid` takes part
+// bid % (4, 8, 16) of the full tile number first + bid / (4, 8, 16).
+template <int WR, int WC, int DEPTH>
+__global__ __launch_bounds__(256, 2) void gemm_wgrad_small_kernel(GemmGroup gg, int first) {
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   int bid = blockIdx.x;
   {
     const int per = (int)gridDim.x >> 3, main = per << 3;
     if (bid < main) bid = (bid & 7) * per + (bid >> 3);
   }
-  const int t = first + compact<1>(bid >> 2, (int)gridDim.x >> 2);
+  constexpr int RB = WR ? 1 : 2, CB = WC ? 1 : 2;      // log2 of the tile's rows and columns inside a full tile
+  const int t = first + compact<1>(bid >> (RB + CB), (int)gridDim.x >> (RB + CB));
   int pi = 0;
   while (pi + 1 < gg.n && t >= gg.first_tile[pi + 1]) ++pi;
   const GemmArgs& g = gg.p[pi];
   int tile_m, tile_n;
   tile_of(t - gg.first_tile[pi], (g.M + BM - 1) / BM, (g.N + BN - 1) / BN, tile_m, tile_n);
-  const int m0 = tile_m * BM + (bid & 1) * 128, n0 = tile_n * BN + ((bid >> 1) & 1) * 128;
+  const int m0 = tile_m * BM + (bid & ((1 << RB) - 1)) * (BM >> RB), n0 = tile_n * BN + ((bid >> RB) & ((1 << CB) - 1)) * (BN >> CB);
   if (m0 >= g.M || n0 >= g.N) return;
-  gemm_tile<false, false, EPI_ACC32, 2, 1, 1, DEPTH>(g, m0, n0, (lds_char*)smem_raw, gg.nseg, gg.seg_delta);
+  gemm_tile<false, false, EPI_ACC32, WC ? 2 : 1, WR, WC, DEPTH>(g, m0, n0, (lds_char*)smem_raw, gg.nseg, gg.seg_delta);
 }
 
 // Eight wavefronts of 128x64 or four of 128x128 per tile: the wider ones read a third less from LDS and are ahead on
@@ -832,32 +872,50 @@ hipError_t launch_tiles(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles
   return hipGetLastError();
 }
 
-template <int DEPTH>
-hipError_t launch_wgrad_quarter(const GemmGroup& gg, int first, int n, hipStream_t s) {
-  constexpr size_t LDS = (size_t)(2 * DEPTH + 1) * (TILE_BYTES / 2);
-  auto kern = gemm_wgrad_quarter_kernel<DEPTH>;
+template <int WR, int WC, int DEPTH>
+hipError_t launch_wgrad_small(const GemmGroup& gg, int first, int n, hipStream_t s) {
+  constexpr size_t LDS = (size_t)(2 * DEPTH + 1) * (WR ? TILE_BYTES / 2 : TILE_BYTES / 4);
+  auto kern = gemm_wgrad_small_kernel<WR, WC, DEPTH>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(4 * n), dim3(256), LDS, s, gg, first);
+  hipLaunchKernelGGL(kern, dim3((WC ? 4 : WR ? 8 : 16) * n), dim3(256), LDS, s, gg, first);
   return hipGetLastError();
 }
 
-// Full tiles for every complete round of one tile per CU; what is left over -- a last round that would keep at most
-// half of the CUs busy, or a whole product with that few tiles -- goes out as twice as many half-height tiles, which
-// take about two thirds as long each, or, if that would still leave half of the CUs idle, as four times as many 128 x 128 tiles (two fifths as long each).  `shape`: 0 = this rule, 1 = full tiles only,
-// 2 = half-height tiles only, 3 = 128 x 128 tiles only (where there are none: the rule).
+// Whether what is left over fits one round of `rows` x 64 tiles (counting only those inside the matrix when it is all of it)
+inline bool tiny_fits(const GemmArgs& g, int tail, int total, int n_cu, int rows) {      // (SwiGLU: 32 features, gate and up; N = 2f)
+  return tail > 0 && (tail == total ? (int64_t)((g.M + rows - 1) / rows) * ((g.N + 63) / 64) : tail * (1024 / rows)) <= n_cu;
+}
+template <bool AKC, bool BKC, int EPI, int WR>
+hipError_t launch_tiny(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles_n, int total, int n) {
+  constexpr size_t LDS = WR ? (size_t)9 * (TILE_BYTES / 2) : (size_t)(2 * TINY_DEPTH + 1) * (TILE_BYTES / 4);
+  auto kern = gemm_tiny_kernel<AKC, BKC, EPI, WR>;
+  static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(kern, dim3((WR ? 8 : 16) * n), dim3(256), LDS, s, g, tiles_m, tiles_n, total - n);
+  return hipGetLastError();
+}
+
+// Full tiles for every complete round of one tile per CU; what is left over -- a last round that would keep at most half of
+// the CUs busy, or a whole product with that few tiles -- goes out in smaller tiles, the smallest of which one round is
+// enough: 64 x 64, 128 x 64, 128 x 128, half-height.  A tile's time per K tile is what its CU's LDS and load path take (0.19, 0.28,
+// 0.36 us for the first three while few CUs are busy, 0.5 for the third when all are; half-height 0.75, full 1.05 to 1.4), so
+// a smaller tile always finishes sooner than a larger one, but no two rounds of it do.  Measured (us; 64 x 64 / 128 x 64 / 128 x 128):
+// 400 x 640 x 1728: 8.6 / 9.8 / 13.7; 1000 x 1280 x 5120: 36 / 26 / 34; 2048 x 2048 x 4096: 60 / 41 / 32.  All give the same bits.
+// `shape`: 0 = this rule, else one tile shape for all: 1 = full, 2 = half-height, 3 = 128 x 128, 4 = 64 x 64 (SwiGLU: 128 x 64),
+// 5 = 128 x 64 (weight gradients: always full).
 template <bool AKC, bool BKC, int EPI>
 hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   const int tiles_m = (g.M + BM - 1) / BM;
   const int tiles_n = EPI == EPI_SWIGLU ? (g.N / 2 + GLU_BN - 1) / GLU_BN : (g.N + BN - 1) / BN, total = tiles_m * tiles_n;
-  constexpr bool QUARTERS = AKC;
-  int n_half = 0, n_quarter = 0;          // full tiles at the end of the walk order that are split in two / in four
+  int n_half = 0, n_quarter = 0, n_tiny = 0;          // full tiles at the end of the walk order that are split in 2 / 4 / 16
+  const int n_cu = cu_count(), tail = total % n_cu;
   if constexpr (AKC) {
-    const int n_cu = cu_count(), tail = total % n_cu;
-    if (QUARTERS && (shape == 3 || (shape == 0 && 4 * tail <= n_cu))) n_quarter = shape == 3 ? total : tail;
+    if (shape >= 4 || (shape == 0 && tiny_fits(g, tail, total, n_cu, 128))) n_tiny = shape >= 4 ? total : tail;
+    else if (shape == 3 || (shape == 0 && 4 * tail <= n_cu)) n_quarter = shape == 3 ? total : tail;
     else n_half = shape == 2 ? total : shape == 1 ? 0 : (2 * tail <= n_cu ? tail : 0);
   }
-  const int n_small = n_half + n_quarter;
+  const int n_small = n_half + n_quarter + n_tiny;
   if (total > n_small) {
     hipError_t e;
     if constexpr (AKC && BKC && EPI == EPI_STORE)
@@ -870,7 +928,14 @@ hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   if constexpr (AKC) {
     if (n_half) return launch_tiles<AKC, BKC, EPI, 1>(g, s, tiles_m, tiles_n, total - n_half, 2 * n_half);
   }
-  if constexpr (QUARTERS) {
+  if constexpr (AKC) {
+    if (n_tiny) {
+      if constexpr (EPI != EPI_SWIGLU)
+        if (shape == 4 || (shape == 0 && tiny_fits(g, tail, total, n_cu, 64))) return launch_tiny<AKC, BKC, EPI, 0>(g, s, tiles_m, tiles_n, total, n_tiny);
+      return launch_tiny<AKC, BKC, EPI, 1>(g, s, tiles_m, tiles_n, total, n_tiny);
+    }
+  }
+  if constexpr (AKC) {
     if (n_quarter) {
       auto kern = gemm_quarter_kernel<AKC, BKC, EPI>;
       static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
@@ -956,7 +1021,8 @@ hipError_t gemm_mfma_wgrad_group(const GemmArgs* list, int n, int nseg, const in
     // Complete rounds of full tiles; a last round (or a whole list) of at most half a tile per CU goes out as 128 x 128 tiles,
     // which spread its reads and writes of C -- 512 KiB per full tile, 18 us whatever the reduction length -- over four
     // times as many CUs.  Lists that leave every CU at most one such tile take the deep operand ring, others the shallow one
-    // that lets two workgroups share a CU.  Measured (us, full tiles against this rule's): 48 tiles, K 128: 22.5 / 9.7;
+    // that lets two workgroups share a CU.  Short reductions and very short lists, where the reads and writes of C are most of
+    // the time, take 64 x 64 tiles (75 tiles, K 400: 18.1 / 15.2 us; 9 tiles, K 400: 10.2 / 5.6; but 72 tiles, K 1500: 29 / 33).  Measured (us, full tiles against this rule's): 48 tiles, K 128: 22.5 / 9.7;
     // 75 tiles, K 400: 28.9 / 17.7; 64 tiles, K 4096: 91.7 / 42.4; 128 tiles, K 8192: 172 / 159; on fuller rounds the doubled
     // operand traffic loses (196 tiles, K 3000: 86 / 113).
     const int tail = total % n_cu, n_quarter = 2 * tail <= n_cu ? tail : 0, n_full = total - n_quarter;
@@ -968,7 +1034,11 @@ hipError_t gemm_mfma_wgrad_group(const GemmArgs* list, int n, int nseg, const in
       if (e != hipSuccess) return e;
     }
     if (n_quarter) {
-      const hipError_t e = 4 * n_quarter <= n_cu ? launch_wgrad_quarter<4>(gg, n_full, n_quarter, s) : launch_wgrad_quarter<2>(gg, n_full, n_quarter, s);
+      int kmax = 0;
+      for (int i = 0; i < gg.n; ++i) kmax = gg.p[i].K > kmax ? gg.p[i].K : kmax;
+      const hipError_t e = (kmax * nseg <= 512 || 16 * n_quarter <= 2 * n_cu) ? launch_wgrad_small<0, 0, 2>(gg, n_full, n_quarter, s)
+                           : 4 * n_quarter <= n_cu                            ? launch_wgrad_small<1, 1, 4>(gg, n_full, n_quarter, s)
+                                                                              : launch_wgrad_small<1, 1, 2>(gg, n_full, n_quarter, s);
       if (e != hipSuccess) return e;
     }
   }

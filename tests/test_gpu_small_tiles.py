@@ -1,4 +1,4 @@
-"""The 128 x 128 tiles of the fused-activation and weight-gradient products at their edges."""
+"""The small tiles of the bf16 products at their edges."""
 import ctypes as C
 
 import numpy as np
@@ -12,11 +12,31 @@ from tests.test_gpu_kernels import KTOL, L, P
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (64, 64, 128), (65, 72, 448), (129, 136, 512), (200, 264, 576), (400, 1736, 1088)])
+def test_small_tiles_agree_bitwise(mode, M, N, K):
+    """64 x 64 (5), 128 x 64 (6) and 128 x 128 tiles (4) against full ones (2) and the rule (0): one row, one past a tile, reductions
+    from one K tile over the ring's depth of eight to two rounds of it."""
+    import torch
+    A, Bm = rnd(synth.normal(43, 1, (M, K)), "bf16"), rnd(synth.normal(43, 2, (N, K) if mode else (K, N)), "bf16")
+    R = rnd(synth.normal(43, 3, (M, N)), "bf16")
+    Ad, Bd, Rd = to_dev(A, "bf16"), to_dev(Bm, "bf16"), to_dev(R, "bf16")
+    outs = []
+    for ks in (2, 4, 5, 6, 0):
+        Cd = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        assert L().stage_kernel_gemm(1, mode, M, N, K, P(Ad), K, P(Bd), Bd.shape[1], P(Cd), N, None if mode else P(Rd), N, 0, ks, None) == 0
+        outs.append(Cd)
+    ref = A.astype(np.float64) @ (Bm.astype(np.float64).T if mode else Bm.astype(np.float64)) + (0 if mode else R)
+    assert so.max_rel_err(to_np(outs[0]), ref) <= KTOL["bf16"]
+    assert all(torch.equal(outs[0], o) for o in outs[1:])
+
+
 @pytest.mark.parametrize("act", [0, 1])
-@pytest.mark.parametrize("M,f,K", [(1, 8, 64), (127, 64, 64), (129, 72, 128), (128, 136, 320), (257, 200, 384)])
+@pytest.mark.parametrize("M,f,K", [(1, 8, 64), (127, 64, 64), (129, 72, 128), (128, 136, 320), (257, 200, 384),
+                                   (1100, 72, 128), (300, 2000, 192)])      # beyond one round of 64 x 64 (GELU) / 128 x 64 (SwiGLU)
 def test_fused_activations_on_small_products(act, M, f, K):
-    """Products this small take 128 x 128 tiles (64 features for SwiGLU): one row, one past a tile in each dimension, ring
-    depths from one K tile to two past the ring.  Tolerance: one bf16 rounding of the output and of z, as for the larger tiles."""
+    """Products this small take 64 x 64 or 128 x 64 tiles (SwiGLU: 32 features), the last ones larger ones: one row, one past a tile in
+    each dimension, reductions from one K tile to past the ring.  Tolerance: one bf16 rounding of the output and of z, as for the larger tiles."""
     import torch
     fin = (1 + act) * f
     sh = so.Shape(1, 64, 1, 1, f, 1, 1, act="swiglu" if act else "gelu")
