@@ -367,32 +367,33 @@ bool wgrad32_group_supported(const GemmArgs* list, int n, int nseg, const int64_
   return true;
 }
 
-// Products of one tile shape go out together (GROUP32_MAX at a time); the shape of a product depends on the product alone, so
-// its bits do not depend on what it is grouped with.
+// One tile shape for the whole list, by the rule above on the list's tiles; both shapes split the reduction over four wavefronts
+// in the same slices, so a product's bits depend neither on the shape nor on what it is grouped with.  Four products of 448
+// tokens x 512 .. 2816: 44 us with eight wavefronts per 32 x 32 tile, 41 with four, 46 in 64 x 64 tiles (two to a CU: a round and a
+// half); two layers of 128 tokens x 256 .. 1024: 16.5, 12.0 and 13.5.
 hipError_t wgrad32_group(const GemmArgs* list, int n, int nseg, const int64_t* seg_delta, hipStream_t s, int shape) {
+  int64_t area[2] = {0, 0};
   for (int which = 0; which < 2; ++which) {
     const int t = which == 0 ? 64 : 32;
+    for (int i = 0; i < n; ++i) area[which] += (int64_t)((list[i].M + t - 1) / t) * ((list[i].N + t - 1) / t);
+    area[which] = (area[which] + 255) / 256 * t * t;
+  }
+  const bool wide = shape > 0 ? shape == 1 : (double)area[0] <= 1.2 * (double)area[1];
+  const int t = wide ? 64 : 32;
+  for (int i0 = 0; i0 < n; i0 += GROUP32_MAX) {
     Wgrad32Group gg;
-    gg.n = 0; gg.nseg = nseg;
+    gg.n = n - i0 < GROUP32_MAX ? n - i0 : GROUP32_MAX; gg.nseg = nseg;
     for (int i = 0; i < GEMM_MAX_SEG; ++i) gg.seg_delta[i] = i > 0 && i < nseg ? seg_delta[i] : 0;
     int total = 0;
-    for (int i = 0; i <= n; ++i) {
-      if (i < n) {
-        const int want = shape > 0 ? (shape == 1 ? 0 : 1) : pick32(GEMM_TN, list[i].M, list[i].N, 2);
-        if (want == which) {
-          const GemmArgs& a = list[i];
-          gg.p[gg.n++] = Wgrad32{a.A, a.B, a.C, a.lda, a.ldb, a.ldc, a.M, a.N, a.K, total};
-          total += ((a.M + t - 1) / t) * ((a.N + t - 1) / t);
-        }
-      }
-      if (gg.n == GROUP32_MAX || (i == n && gg.n > 0)) {
-        if (which == 0) hipLaunchKernelGGL((wgrad32_group_kernel<4, 4, 4>), dim3(total), dim3(256), 0, s, gg);
-        else hipLaunchKernelGGL((wgrad32_group_kernel<2, 2, 8>), dim3(total), dim3(512), 0, s, gg);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        gg.n = 0; total = 0;
-      }
+    for (int i = 0; i < gg.n; ++i) {
+      const GemmArgs& a = list[i0 + i];
+      gg.p[i] = Wgrad32{a.A, a.B, a.C, a.lda, a.ldb, a.ldc, a.M, a.N, a.K, total};
+      total += ((a.M + t - 1) / t) * ((a.N + t - 1) / t);
     }
+    if (wide) hipLaunchKernelGGL((wgrad32_group_kernel<4, 4, 4>), dim3(total), dim3(256), 0, s, gg);
+    else hipLaunchKernelGGL((wgrad32_group_kernel<2, 2, 4>), dim3(total), dim3(256), 0, s, gg);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
