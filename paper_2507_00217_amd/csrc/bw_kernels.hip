@@ -124,9 +124,9 @@ __global__ __launch_bounds__(NORM_THREADS) void norm_fwd_kernel(NormArgs n) {
 // Bound by HBM, 8 bytes per element (16 with an fp32 residual stream), as long as enough rows are in flight.  A row takes
 // tpr threads (whole wavefronts) with at most NB_CH 16-byte pieces each, so that widths that are not a power of two leave few
 // threads idle (5120: 5 wavefronts x 2 pieces; one fixed workgroup of 256 threads needed 3 pieces, half of the last unused,
-// and registers for 4); a workgroup holds as many rows side by side as fit in 256 threads.  The next row's loads are
+// and registers for 4); a workgroup holds several rows side by side.  The next row's loads are
 // issued before this one is reduced, both row sums cross the workgroup in one exchange, and xhat and dxhat are formed again
-// from the raw row rather than kept.  4096 x 5120 in bf16: 49 -> 45 us (3.8 TB/s,
+// from the raw row rather than kept.  4096 x 5120 in bf16: 49 -> 37 us (4.5 TB/s,
 // partial sums not counted; a large copy reaches 4.8); 2048 x 2048 with an fp32 residual stream: 20.5 -> 16-18.
 constexpr int NB_CH = 2;
 template <typename T, bool WIDE> struct RowPiece { static constexpr int W = WIDE ? Vec<T>::N / 4 : 1; uint4 v[W]; };
@@ -150,7 +150,7 @@ template <typename T, bool WIDE> __device__ __forceinline__ float at_piece(const
 
 // XW / RW: x / resid is stored in fp32 although T is not
 template <typename T, int KIND, bool XW, bool RW>
-__global__ __launch_bounds__(512) void norm_bwd_kernel(NormArgs n, int tpr) {
+__global__ __launch_bounds__(XW || RW ? 512 : 640) void norm_bwd_kernel(NormArgs n, int tpr) {
   constexpr int V = Vec<T>::N;
   extern __shared__ float col_sums[];                    // [row groups][2][d], only with several row groups
   __shared__ float red[2][16][2];
@@ -333,10 +333,19 @@ static hipError_t norm_fwd_t(const NormArgs& n, hipStream_t s) {
 template <typename T, int KIND, bool XW, bool RW>
 static hipError_t norm_bwd_launch(const NormArgs& n, hipStream_t s, int* parts) {
   const int nvec = n.d / Vec<T>::N, tpr = nvec <= 64 ? 64 : ((nvec + NB_CH - 1) / NB_CH + 63) / 64 * 64;
-  const int ngrp = tpr >= 256 ? 1 : 256 / tpr, want = (n.rows + ngrp - 1) / ngrp;
-  *parts = want < NORM_PARTIAL_ROWS ? want : NORM_PARTIAL_ROWS;
-  const size_t lds = ngrp > 1 ? (size_t)ngrp * 2 * n.d * sizeof(float) : 0;      // at most 32 KiB: d <= 128 * V with 4 groups
-  hipLaunchKernelGGL((norm_bwd_kernel<T, KIND, XW, RW>), dim3(*parts), dim3(ngrp * tpr), lds, s, n, tpr);
+  // With nothing stored in fp32, as many rows side by side as the register budget has wavefronts for, one such workgroup per CU:
+  // half the partial rows -- 42 of 210 MB moved at 4096 x 5120, 45 -> 37 us -- of two workgroups of half the size.  With an fp32
+  // residual stream the smaller workgroups are ahead (4096 x 4096: 46 against 49 us), and so they are on short batches.
+  constexpr int THREADS = XW || RW ? 256 : 640;
+  int ngrp = THREADS >= tpr ? THREADS / tpr : 1;
+  if (ngrp > 1 && n.rows < 256 * ngrp) ngrp = tpr >= 256 ? 1 : 256 / tpr;
+  const int cap = ngrp > 1 && ngrp * tpr > 256 ? NORM_PARTIAL_ROWS / 2 : NORM_PARTIAL_ROWS, want = (n.rows + ngrp - 1) / ngrp;
+  *parts = want < cap ? want : cap;
+  const size_t lds = ngrp > 1 ? (size_t)ngrp * 2 * n.d * sizeof(float) : 0;      // at most 80 KiB: d <= 2 * V * tpr
+  auto kern = norm_bwd_kernel<T, KIND, XW, RW>;
+  static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(kern, dim3(*parts), dim3(ngrp * tpr), lds, s, n, tpr);
   return hipGetLastError();
 }
 template <typename T, int KIND>
