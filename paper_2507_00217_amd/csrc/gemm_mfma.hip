@@ -26,9 +26,10 @@
 // copy.  The MFMA is issued with the operands swapped (computes the transposed
 // 16x16 block), which leaves every lane with 4 consecutive columns of one row:
 // 8-byte bf16 / 16-byte fp32 epilogue accesses.  Workgroup ids are remapped so
-// that each XCD (own L2) works on a compact band of tiles.  A 128x256 half-height
-// tile (4 wavefronts) takes over where full tiles would keep at most half of the
-// CUs busy: the last round of a product, or a product with few tiles.
+// that each XCD (own L2) works on a compact band of tiles.  Smaller tiles (128x128,
+// 128x64, 64x64, four wavefronts each; 128x256 for one epilogue) take over where full
+// tiles would keep at most half of the CUs busy: the last round of a product, or a
+// product with few tiles.
 #include "common.h"
 #include <type_traits>
 
@@ -752,7 +753,7 @@ __global__ __launch_bounds__(WR * 512 / TN, WR == 1 ? 2 : 1) void gemm_mfma_kern
 
 // one workgroup per 128 x 128 tile (four wavefronts of 64 x 64): workgroup `bid` takes quadrant bid % 4 of the full
 // tile number first + bid / 4 of the walk order; a quadrant that lies outside the matrix has nothing to do
-template <bool AKC, bool BKC, int EPI>
+template <bool AKC, bool BKC, int EPI, int DEPTH>
 __global__ __launch_bounds__(256, 2) void gemm_quarter_kernel(   // (register budget: as for the half-height tile)
     GemmArgs g, int tiles_m, int tiles_n, int first) {
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
@@ -766,7 +767,7 @@ __global__ __launch_bounds__(256, 2) void gemm_quarter_kernel(   // (register bu
   constexpr int TB = EPI == EPI_SWIGLU ? GLU_BN : BN;
   const int m0 = tile_m * BM + (bid & 1) * 128, n0 = tile_n * TB + ((bid >> 1) & 1) * (TB / 2);
   if (m0 >= g.M || n0 >= (EPI == EPI_SWIGLU ? g.N / 2 : g.N)) return;                  // the same for the whole workgroup
-  gemm_tile<AKC, BKC, EPI, 2, 1, 1>(g, m0, n0, (lds_char*)smem_raw);
+  gemm_tile<AKC, BKC, EPI, 2, 1, 1, DEPTH>(g, m0, n0, (lds_char*)smem_raw);
 }
 
 // one workgroup per 64 x 64 (WR == 0) or 128 x 64 tile (WR == 1): workgroup `bid` takes the sixteenth bid % 16 (eighth bid % 8) of full
@@ -886,6 +887,15 @@ hipError_t launch_wgrad_small(const GemmGroup& gg, int first, int n, hipStream_t
 inline bool tiny_fits(const GemmArgs& g, int tail, int total, int n_cu, int rows) {      // (SwiGLU: 32 features, gate and up; N = 2f)
   return tail > 0 && (tail == total ? (int64_t)((g.M + rows - 1) / rows) * ((g.N + 63) / 64) : tail * (1024 / rows)) <= n_cu;
 }
+template <bool AKC, bool BKC, int EPI, int DEPTH>
+hipError_t launch_quarter(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles_n, int total, int n) {
+  constexpr size_t LDS = (size_t)(2 * DEPTH + 1) * (TILE_BYTES / 2);
+  auto kern = gemm_quarter_kernel<AKC, BKC, EPI, DEPTH>;
+  static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(kern, dim3(4 * n), dim3(256), LDS, s, g, tiles_m, tiles_n, total - n);
+  return hipGetLastError();
+}
 template <bool AKC, bool BKC, int EPI, int WR>
 hipError_t launch_tiny(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles_n, int total, int n) {
   constexpr size_t LDS = WR ? (size_t)9 * (TILE_BYTES / 2) : (size_t)(2 * TINY_DEPTH + 1) * (TILE_BYTES / 4);
@@ -898,10 +908,14 @@ hipError_t launch_tiny(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles_
 
 // Full tiles for every complete round of one tile per CU; what is left over -- a last round that would keep at most half of
 // the CUs busy, or a whole product with that few tiles -- goes out in smaller tiles, the smallest of which one round is
-// enough: 64 x 64, 128 x 64, 128 x 128, half-height.  A tile's time per K tile is what its CU's LDS and load path take (0.19, 0.28,
-// 0.36 us for the first three while few CUs are busy, 0.5 for the third when all are; half-height 0.75, full 1.05 to 1.4), so
-// a smaller tile always finishes sooner than a larger one, but no two rounds of it do.  Measured (us; 64 x 64 / 128 x 64 / 128 x 128):
-// 400 x 640 x 1728: 8.6 / 9.8 / 13.7; 1000 x 1280 x 5120: 36 / 26 / 34; 2048 x 2048 x 4096: 60 / 41 / 32.  All give the same bits.
+// enough: 64 x 64, 128 x 64, 128 x 128, and beyond that 128 x 128 with a shallow ring, two workgroups to a CU.  A tile's time per K
+// tile is what its CU's LDS and load path take (0.19, 0.28, 0.36 us for the first three while few CUs are busy, 0.5 for the third
+// when all are; full 1.05 to 1.4), so a smaller tile always finishes sooner than a larger one, but no two rounds of it do.
+// Measured (us; 64 x 64 / 128 x 64 / 128 x 128): 400 x 640 x 1728: 8.6 / 9.8 / 13.7; 1000 x 1280 x 5120: 36 / 26 / 34; 2048 x 2048 x
+// 4096: 60 / 41 / 32.  Two 128 x 128 workgroups to a CU against the half-height tiles that used to take such shapes: 1000 x 5120 x
+// 1280: 18.3 / 20.1 (operands from HBM: 22 / 28), 4096 x 1536 x 4096: 51 / 51 (59 / 72), and with more than half a tile per CU
+// against full ones, 2048 x 6144 x 2048: 49 / 48 (60 / 53).  The half-height tile is left to the SwiGLU backward, whose z it
+// rewrites in whole rows through LDS (2048 x 2816 x 2048: 36 / 39).  All give the same bits.
 // `shape`: 0 = this rule, else one tile shape for all: 1 = full, 2 = half-height, 3 = 128 x 128, 4 = 64 x 64 (SwiGLU: 128 x 64),
 // 5 = 128 x 64 (weight gradients: always full).
 template <bool AKC, bool BKC, int EPI>
@@ -911,8 +925,8 @@ hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   int n_half = 0, n_quarter = 0, n_tiny = 0;          // full tiles at the end of the walk order that are split in 2 / 4 / 16
   const int n_cu = cu_count(), tail = total % n_cu;
   if constexpr (AKC) {
-    if (shape >= 4 || (shape == 0 && tiny_fits(g, tail, total, n_cu, 128))) n_tiny = shape >= 4 ? total : tail;
-    else if (shape == 3 || (shape == 0 && 4 * tail <= n_cu)) n_quarter = shape == 3 ? total : tail;
+    if (shape >= 4 || (shape == 0 && tiny_fits(g, tail, total, n_cu, 128))) n_tiny = shape ? total : tail;
+    else if (shape == 3 || (shape == 0 && (EPI == EPI_DSWIGLU ? 4 : 2) * tail <= n_cu)) n_quarter = shape ? total : tail;
     else n_half = shape == 2 ? total : shape == 1 ? 0 : (2 * tail <= n_cu ? tail : 0);
   }
   const int n_small = n_half + n_quarter + n_tiny;
@@ -936,13 +950,7 @@ hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
     }
   }
   if constexpr (AKC) {
-    if (n_quarter) {
-      auto kern = gemm_quarter_kernel<AKC, BKC, EPI>;
-      static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
-      if (attr != hipSuccess) return attr;
-      hipLaunchKernelGGL(kern, dim3(4 * n_quarter), dim3(256), LDS_BYTES, s, g, tiles_m, tiles_n, total - n_quarter);
-      return hipGetLastError();
-    }
+    if (n_quarter) return 4 * n_quarter > n_cu ? launch_quarter<AKC, BKC, EPI, 2>(g, s, tiles_m, tiles_n, total, n_quarter) : launch_quarter<AKC, BKC, EPI, 4>(g, s, tiles_m, tiles_n, total, n_quarter);
   }
   return hipSuccess;
 }
