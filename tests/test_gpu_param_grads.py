@@ -15,7 +15,8 @@ F, B, W = 0, 1, 2
 # one, fewer than the row groups, one past a full round of 512 workgroups
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("norm", ["layernorm", "rmsnorm"])
-@pytest.mark.parametrize("rows,d", [(1, 8), (3, 512), (5, 520), (513, 1032), (2049, 264), (1025, 2056), (515, 2560), (2, 4096)])
+@pytest.mark.parametrize("rows,d", [(1, 8), (3, 512), (5, 520), (513, 1032), (2049, 264), (1025, 2056), (515, 2560), (2, 4096),
+                                    (2561, 512), (1281, 1032), (768, 2568)])      # ten, five and three rows side by side, 80 KiB of column sums
 def test_norm_backward_row_shapes(dtype, norm, rows, d):
     import torch
     kind = {"layernorm": 0, "rmsnorm": 1}[norm]
