@@ -55,30 +55,13 @@ enum Epi { EPI_STORE = 0, EPI_RESID = 1, EPI_ACC32 = 2, EPI_GELU = 3, EPI_SWIGLU
 constexpr int GLU_BN = 128;
 constexpr int TINY_DEPTH = 8;       // K tiles ahead of the 64 x 64 tile: 17 slots of 8 KiB
 
-// Phi(u) = the normal distribution function and e = exp(-u^2 / 2), from which GELU u * Phi(u) and its derivative Phi(u) +
-// u * e / sqrt(2 pi) follow.  With a = |u| and t = 1 / (1 + 0.21 a), Phi(-a) * exp(a^2 / 2) = t * P(t), P a polynomial of degree
-// 8 fitted here to the relative error of that quotient (1.6e-8 for a <= 14; evaluated in fp32 the GELU is within 1e-6
-// relative for u > -5, where 0.5 u (1 + erf(u / sqrt 2)) loses all digits to the cancellation in 1 + erf).  A fused epilogue
-// has 128 accumulators per lane and one or two wavefronts per SIMD to evaluate them, so it is bound by instructions: ~20
-// without branches in place of erf's two-sided branch (2048 x 8192 x 2048, isolated: forward 76 -> 66 us, backward
-// 76 -> 65; the plain product takes 54).
-__device__ __forceinline__ float normal_cdf(float u, float& e) {
-  const float a = __builtin_fabsf(u), t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.21f, a, 1.f));
-  float q = -0.07165794f;
-  q = __builtin_fmaf(q, t, 0.28359659f);
-  q = __builtin_fmaf(q, t, -0.33027027f);
-  q = __builtin_fmaf(q, t, 0.34942083f);
-  q = __builtin_fmaf(q, t, -0.09393938f);
-  q = __builtin_fmaf(q, t, 0.12487904f);
-  q = __builtin_fmaf(q, t, 0.06919046f);
-  q = __builtin_fmaf(q, t, 0.08506911f);
-  q = __builtin_fmaf(q, t, 0.08371156f);
-  e = __builtin_amdgcn_exp2f(u * u * -0.72134752f);      // log2(e) / 2
-  const float tail = q * t * e;
-  return u < 0.f ? tail : 1.f - tail;
+// GELU and its derivative of an fp32 value, in the words of the plain activation kernels: same bits for the same value.  (The
+// normal distribution function from one exponential and a polynomial instead of erf takes 10 of the 76 us of the fused
+// 2048 x 8192 x 2048 forward product, but its fp32 error near zero is 5e-7 relative against erf's 2e-7.)
+__device__ __forceinline__ float gelu_f32(float u) { return 0.5f * u * (1.f + erff(u * 0.70710678118654752f)); }
+__device__ __forceinline__ float dgelu_f32(float u) {
+  return 0.5f * (1.f + erff(u * 0.70710678118654752f)) + u * 0.39894228040143268f * __expf(-0.5f * u * u);
 }
-__device__ __forceinline__ float gelu_f32(float u) { float e; return u * normal_cdf(u, e); }
-__device__ __forceinline__ float dgelu_f32(float u) { float e; const float c = normal_cdf(u, e); return __builtin_fmaf(u * 0.39894228f, e, c); }
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -578,7 +561,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[e] = (bf16)fn(acc[i][j][e]);
           *reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(smem + r * (PCS * 16) + ((p ^ (r & (PCS - 1))) << 4) + sub_b) = o;
-          if (EPI == EPI_GELU) __builtin_amdgcn_sched_barrier(0);      // keeps the expansions of the activation from piling up in registers
+          if (EPI == EPI_GELU) __builtin_amdgcn_sched_barrier(0);      // keeps the erf expansions from piling up in registers
         }
       }
     };
