@@ -335,6 +335,8 @@ bool gemm32_supported(const GemmArgs& g) {
   if (g.mode != GEMM_TN && g.K % 4) return false;
   if (g.mode == GEMM_TN && g.M % 4) return false;
   if ((g.mode == GEMM_TN) != (g.acc_f32 != 0) || (g.acc_f32 && (g.R || g.bias))) return false;
+  // an operand with a slow reduction index relies on its rows past K lying past the end of its buffer: no row may overlap the next
+  if (g.lda < (g.mode == GEMM_TN ? g.M : 0) || g.ldb < (g.mode == GEMM_NT ? 0 : g.N)) return false;
   const int64_t lim = (int64_t)1 << 29;        // byte offsets stay below 2 GiB, slices fetched past the end (less than 2048 rows) included
   const int64_t a_rows = g.mode == GEMM_TN ? g.K + 2048 : g.M, b_rows = g.mode == GEMM_NT ? g.N : (int64_t)g.K + 2048;
   if (a_rows * g.lda >= lim || b_rows * g.ldb >= lim || (g.mode != GEMM_TN && (int64_t)g.K + 2048 >= lim)) return false;

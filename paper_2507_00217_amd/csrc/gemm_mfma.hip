@@ -946,6 +946,8 @@ bool gemm_mfma_supported(const GemmArgs& g) {
   if (!al16(g.A) || !al16(g.B) || (!g.act_bwd && !al16(g.C)) || (g.R && !al16(g.R))) return false;
   if (g.lda % 8 || g.ldb % 8 || g.ldc % 4 || (g.R && g.ldr % 4) || g.N % 8) return false;
   if (!g.acc_f32 && !g.c_f32 && g.ldc % 8) return false;   // bf16 C is stored 16 bytes at a time
+  // weight gradients take any K and rely on the rows past it lying past the end of the buffer: no row may overlap the next
+  if (g.lda < (g.mode == GEMM_TN ? g.M : 0) || g.ldb < (g.mode == GEMM_TN ? g.N : 0)) return false;
   const int64_t lim = (int64_t)1 << 30;   // operand byte offsets are 32-bit buffer offsets below 2 GiB
   const int64_t a_rows = g.mode == GEMM_TN ? g.K : g.M, b_rows = g.mode == GEMM_NT ? g.N : g.K;
   if (a_rows * g.lda >= lim || b_rows * g.ldb >= lim) return false;

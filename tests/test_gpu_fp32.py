@@ -92,3 +92,33 @@ def test_attention_against_64_bits(b, s, h, hkv, hd, causal):
     assert so.max_rel_err(to_np(od), o.detach().numpy()) <= TOL
     assert so.max_rel_err(to_np(lse), torch.stack(lses).view(b, h, s).detach().numpy()) <= TOL
     assert so.max_rel_err(to_np(dqkv), x.grad.numpy()) <= TOL
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("mode,M,N,K,lda,ldb", [(2, 24, 40, 50, 0, 0), (2, 64, 64, 33, 8, 16), (2, 24, 40, 50, 24, 8), (2, 24, 40, 50, -24, -40),
+                                                (0, 24, 40, 64, 64, 0), (0, 24, 40, 64, 8, 8), (0, 24, 40, 64, -64, -40), (1, 24, 40, 64, 0, 64),
+                                                (1, 24, 40, 64, 8, 8), (1, 24, 40, 64, -64, -64)])
+def test_products_of_overlapping_rows(dtype, mode, M, N, K, lda, ldb):
+    """Row strides smaller than a row (a broadcast row, a sliding window) or negative (rows in reverse): the sums of the rows written
+    out.  Tolerance as above; bf16 outputs (modes 0 and 1): one rounding, 2^-8."""
+    import ctypes as C
+    import torch
+    a_shape, b_shape = ((K, M) if mode == 2 else (M, K)), ((N, K) if mode == 1 else (K, N))
+    bufs, ptrs, mats = [], [], []
+    for i, (r, c), ld in ((1, a_shape, lda), (2, b_shape, ldb)):
+        buf = to_dev(synth.normal(34, i, ((r - 1) * abs(ld) + c,)), dtype)
+        first = (r - 1) * -ld if ld < 0 else 0                       # element at which row 0 starts
+        rows = buf.as_strided((r, c), (abs(ld), 1)).double()
+        bufs.append(buf); ptrs.append(P(buf) + first * buf.element_size()); mats.append(rows.flip(0) if ld < 0 else rows)
+    A, B = mats
+    C0 = torch.from_numpy(synth.normal(34, 3, (M, N))).to("cuda:0") if mode == 2 else torch.zeros((M, N), device="cuda:0", dtype=bufs[0].dtype)
+    ref = C0.double() + (A.t() if mode == 2 else A) @ (B.t() if mode == 1 else B)
+    dt, tol = {"fp32": 0, "bf16": 1}[dtype], TOL if dtype == "fp32" or mode == 2 else 2.0 ** -8
+    Cd = C0.clone()
+    assert L().stage_kernel_gemm(dt, mode, M, N, K, ptrs[0], lda, ptrs[1], ldb, P(Cd), N, None, 0, int(mode == 2), 0, None) == 0
+    assert so.max_rel_err(to_np(Cd), ref.cpu().numpy()) <= tol
+    if mode == 2:
+        Cg = C0.clone()
+        i1, l1, p1 = (lambda v: (C.c_int * 1)(v)), (lambda v: (C.c_int64 * 1)(v)), (lambda p: (C.c_void_p * 1)(p))
+        assert L().stage_kernel_wgrad_group(dt, 1, i1(M), i1(N), i1(K), p1(ptrs[0]), l1(lda), p1(ptrs[1]), l1(ldb), p1(P(Cg)), l1(N), 0, None) == 0
+        assert torch.equal(Cg, Cd)
