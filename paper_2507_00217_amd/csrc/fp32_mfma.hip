@@ -17,6 +17,7 @@
 // products ran in 8 workgroups with one thread walking all of K (107 us each, 5 us now); a Llama-style layer of 448 x 512: 4563
 // us before.  Products that fill the chip reach 113-123 of the 152 TFLOP/s a large library product does (1400 x 8192 x 1024).
 #include "common.h"
+#include <type_traits>
 
 namespace stg {
 
@@ -442,6 +443,36 @@ template <int HD> __device__ __forceinline__ int piece_col(int q, int g) {
   constexpr int NT = HD / 16;
   return NT * (4 * g + q / (NT / 4)) + 4 * (q % (NT / 4));
 }
+// A block of rows that some columns see and others do not (keys behind a query, rows past the end) is multiplied with weights that
+// are zero for the pairs that do not count, which is right as long as the rows are finite: zero times an infinity or NaN is
+// NaN.  `mul_seen`: acc += f^T . w with row 4 g + j counted only for the columns with ok[j], one row at a time, each column dropping
+// the products of rows that it does not see.  It is far from the loops over the blocks, which carry no branch for it (a
+// branch there costs the backward 4 %): the forward asks its last block, the only one with such pairs, whether its rows
+// are finite (`odd_rows`) and leaves it for the end if they are not; the backward's wavefronts note on the way whether a score
+// or delta, sums over whole rows, was not finite, and if so walk their blocks again.
+template <int NT> __device__ __forceinline__ bool odd_rows(const float (&f)[4][NT]) {
+  float t = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int i = 0; i < NT; ++i) t = __builtin_fmaf(f[j][i], 0.f, t);            // 0, or NaN
+  return __any(t != 0.f);
+}
+template <int NT> __device__ __forceinline__ void mul_seen(f32x4 (&acc)[NT], const float (&f)[4][NT], const f32x4& w, const bool (&ok)[4], int c, int g) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll 1
+    for (int gg = 0; gg < 4; ++gg) {
+      const bool see = __shfl((int)ok[j], 16 * gg + c, 64) != 0;
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        const f32x4 p = mfma4(g == gg ? f[j][i] : 0.f, g == gg ? w[j] : 0.f, f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][e] += see ? p[e] : 0.f;
+        __builtin_amdgcn_sched_barrier(0);                       // one product at a time: no registers beyond the plain path's
+      }
+    }
+}
 __device__ __forceinline__ float max_g(float v) { v = fmaxf(v, __shfl_xor(v, 16, 64)); return fmaxf(v, __shfl_xor(v, 32, 64)); }
 __device__ __forceinline__ float sum_g(float v) { v += __shfl_xor(v, 16, 64); return v + __shfl_xor(v, 32, 64); }
 
@@ -467,10 +498,12 @@ __global__ __launch_bounds__(AW * 64) void attn32_fwd_kernel(AttnArgs a) {
   float m = -INFINITY, l = 0.f;
   f32x4 kf[NT];
   ld_rows<HD>(kf, kp + (int64_t)min(w * 16 + c, last) * a.ld, g);
+  bool odd = false;                                      // the last block, the only one with keys a query does not see, waits for the end
+  f32x4 sc;
   for (int kb = w; kb < nblk; kb += AW) {
     float vf[4][NT];
     ld_cols<HD>(vf, vp, a.ld, kb * 16, last, c, g);
-    f32x4 sc = {0.f, 0.f, 0.f, 0.f};
+    sc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -494,10 +527,24 @@ __global__ __launch_bounds__(AW * 64) void attn32_fwd_kernel(AttnArgs a) {
     l = l * alpha + ps;
 #pragma unroll
     for (int i = 0; i < NT; ++i) o[i] *= alpha;
+    if (kb == nblk - 1 && (odd = odd_rows(vf))) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) vf[j][i] = 0.f;
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int i = 0; i < NT; ++i) o[i] = mfma4(vf[j][i], sc[j], o[i]);
+  }
+  if (odd) {
+    float vf[4][NT];
+    bool ok[4];
+    ld_cols<HD>(vf, vp, a.ld, (nblk - 1) * 16, last, c, g);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { const int key = (nblk - 1) * 16 + 4 * g + e; ok[e] = key < a.s && (!a.causal || key <= q); }
+    mul_seen(o, vf, sc, ok, c, g);
   }
   l = sum_g(l);
   if (g == 0) { red_m[w][c] = m; red_l[w][c] = l; }
@@ -521,7 +568,7 @@ __global__ __launch_bounds__(AW * 64) void attn32_fwd_kernel(AttnArgs a) {
     for (int k = 1; k < AW; ++k) v += red[(k * NT + p) * 64 + lane] * f[k];
     *reinterpret_cast<f32x4*>((float*)a.o + ((int64_t)ib * a.s + q) * d + head * HD + piece_col<HD>(p, g)) = v * inv;
   }
-  if (w == 0 && g == 0) a.lse[((int64_t)ib * a.h + head) * a.s + q] = mt + logf(lt);
+  if (w == 0 && g == 0) a.lse[((int64_t)ib * a.h + head) * a.s + q] = mt == -INFINITY ? NAN : mt + logf(lt);
 }
 
 // dQ of the 16 queries from q0 on; leaves delta = rowsum(dO * O) as well
@@ -553,31 +600,42 @@ __device__ __forceinline__ void attn32_dq(const AttnArgs& a, int q0, int head, i
   const float lse = a.lse[si];
   const int nblk = ((a.causal ? min(a.s, q0 + 16) : a.s) + 15) / 16;
   f32x4 dq[NT];
+  float odd = 0.f;                                       // becomes NaN with the scores of a key row that holds an infinity or NaN
+  auto walk = [&](auto seen_c) __attribute__((always_inline)) {
+    constexpr bool seen = decltype(seen_c)::value;
 #pragma unroll
-  for (int i = 0; i < NT; ++i) dq[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int kb = w; kb < nblk; kb += AW) {
-    const int64_t kr = (int64_t)min(kb * 16 + c, last) * a.ld;
-    f32x4 kf[NT], vf[NT];
-    float kc[4][NT];
-    ld_rows<HD>(kf, kp + kr, g);
-    ld_rows<HD>(vf, vp + kr, g);
-    ld_cols<HD>(kc, kp, a.ld, kb * 16, last, c, g);
-    f32x4 sc = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < NT; ++i) dq[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int kb = w; kb < nblk; kb += AW) {
+      const int64_t kr = (int64_t)min(kb * 16 + c, last) * a.ld;
+      f32x4 kf[NT], vf[NT];
+      float kc[4][NT];
+      ld_rows<HD>(kf, kp + kr, g);
+      ld_rows<HD>(vf, vp + kr, g);
+      ld_cols<HD>(kc, kp, a.ld, kb * 16, last, c, g);
+      f32x4 sc = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+      for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) { sc = mfma4(kf[t][j], qf[t][j], sc); dp = mfma4(vf[t][j], dof[t][j], dp); }
+        for (int j = 0; j < 4; ++j) { sc = mfma4(kf[t][j], qf[t][j], sc); dp = mfma4(vf[t][j], dof[t][j], dp); }
+      bool ok[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int key = kb * 16 + 4 * g + e;
-      const bool ok = key < a.s && (!a.causal || key <= q);
-      sc[e] = ok ? expf(sc[e] * scale - lse) * (dp[e] - delta) : 0.f;
+      for (int e = 0; e < 4; ++e) {
+        const int key = kb * 16 + 4 * g + e;
+        ok[e] = key < a.s && (!a.causal || key <= q);
+        if (!seen) odd = __builtin_fmaf(sc[e], 0.f, odd);
+        sc[e] = ok[e] ? expf(sc[e] * scale - lse) * (dp[e] - delta) : 0.f;
+      }
+      if (seen) mul_seen(dq, kc, sc, ok, c, g);
+      else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int i = 0; i < NT; ++i) dq[i] = mfma4(kc[j][i], sc[j], dq[i]);
+      }
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int i = 0; i < NT; ++i) dq[i] = mfma4(kc[j][i], sc[j], dq[i]);
-  }
+  };
+  walk(std::false_type{});
+  if (__any(odd != 0.f)) walk(std::true_type{});
 #pragma unroll
   for (int p = 0; p < NT; ++p) red[(w * NT + p) * 64 + lane] = piece<HD>(dq, p);
   __syncthreads();
@@ -614,55 +672,70 @@ __device__ __forceinline__ void attn32_dkv(const AttnArgs& a, int k0, int kvh, i
   }
   __syncthreads();
   f32x4 dk[NT], dv[NT];
-#pragma unroll
-  for (int i = 0; i < NT; ++i) dk[i] = dv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int qb0 = a.causal ? k0 / 16 : 0, nqb = (a.s + 15) / 16 - qb0;
-  for (int it = w; it < grp * nqb; it += AW) {
-    const int head = kvh * grp + it / nqb, q0 = (qb0 + it % nqb) * 16;
-    const float *qh = base + head * HD, *doh = dob + head * HD;
-    const int qr = min(q0 + c, last);
-    f32x4 qf[NT], dof[NT];
-    float qc[4][NT], doc[4][NT];
-    ld_rows<HD>(qf, qh + (int64_t)qr * a.ld, g);
-    ld_rows<HD>(dof, doh + (int64_t)qr * d, g);
-    ld_cols<HD>(doc, doh, d, q0, last, c, g);
-    ld_cols<HD>(qc, qh, a.ld, q0, last, c, g);
-    const float* lse = a.lse + ((int64_t)ib * a.h + head) * a.s;
-    float ls[4], dl[4], dc = 0.f;
-    {
-      f32x4 of[NT];
-      ld_rows<HD>(of, (const float*)a.o + ((int64_t)ib * a.s + qr) * d + head * HD, g);
+  float odd = 0.f;                                       // becomes NaN with the scores or delta of a row of Q or dO that holds an infinity or NaN
+  auto walk = [&](auto seen_c) __attribute__((always_inline)) {
+    constexpr bool seen = decltype(seen_c)::value;
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
+    for (int i = 0; i < NT; ++i) dk[i] = dv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int it = w; it < grp * nqb; it += AW) {
+      const int head = kvh * grp + it / nqb, q0 = (qb0 + it % nqb) * 16;
+      const float *qh = base + head * HD, *doh = dob + head * HD;
+      const int qr = min(q0 + c, last);
+      f32x4 qf[NT], dof[NT];
+      float qc[4][NT], doc[4][NT];
+      ld_rows<HD>(qf, qh + (int64_t)qr * a.ld, g);
+      ld_rows<HD>(dof, doh + (int64_t)qr * d, g);
+      ld_cols<HD>(doc, doh, d, q0, last, c, g);
+      if (!seen) ld_cols<HD>(qc, qh, a.ld, q0, last, c, g);
+      const float* lse = a.lse + ((int64_t)ib * a.h + head) * a.s;
+      float ls[4], dl[4], dc = 0.f;
+      {
+        f32x4 of[NT];
+        ld_rows<HD>(of, (const float*)a.o + ((int64_t)ib * a.s + qr) * d + head * HD, g);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) dc += of[t][e] * dof[t][e];
-      dc = sum_g(dc);                                    // delta of query q0 + c
-    }
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { ls[e] = lse[min(q0 + 4 * g + e, last)]; dl[e] = __shfl(dc, 4 * g + e, 64); }
-    f32x4 sc = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const f32x4 kf = kv[t * 64 + lane], vf = kv[(NT + t) * 64 + lane];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { sc = mfma4(qf[t][j], kf[j], sc); dp = mfma4(dof[t][j], vf[j], dp); }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int q = q0 + 4 * g + e;
-      const bool ok = q < a.s && (!a.causal || key <= q);
-      const float p = ok ? expf(sc[e] * scale - ls[e]) : 0.f;
-      sc[e] = p;
-      dp[e] = ok ? p * (dp[e] - dl[e]) : 0.f;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        dv[i] = mfma4(doc[j][i], sc[j], dv[i]);
-        dk[i] = mfma4(qc[j][i], dp[j], dk[i]);
+          for (int e = 0; e < 4; ++e) dc += of[t][e] * dof[t][e];
+        dc = sum_g(dc);                                    // delta of query q0 + c
       }
-  }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { ls[e] = lse[min(q0 + 4 * g + e, last)]; dl[e] = __shfl(dc, 4 * g + e, 64); }
+      f32x4 sc = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const f32x4 kf = kv[t * 64 + lane], vf = kv[(NT + t) * 64 + lane];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { sc = mfma4(qf[t][j], kf[j], sc); dp = mfma4(dof[t][j], vf[j], dp); }
+      }
+      bool ok[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int q = q0 + 4 * g + e;
+        ok[e] = q < a.s && (!a.causal || key <= q);
+        if (!seen) odd = __builtin_fmaf(sc[e], 0.f, odd);
+        const float p = ok[e] ? expf(sc[e] * scale - ls[e]) : 0.f;
+        sc[e] = p;
+        dp[e] = ok[e] ? p * (dp[e] - dl[e]) : 0.f;
+      }
+      if (seen) {
+        mul_seen(dv, doc, sc, ok, c, g);
+        ld_cols<HD>(qc, qh, a.ld, q0, last, c, g);          // (both at once do not fit the registers)
+        mul_seen(dk, qc, dp, ok, c, g);
+      } else {
+        odd = __builtin_fmaf(dc, 0.f, odd);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int i = 0; i < NT; ++i) {
+            dv[i] = mfma4(doc[j][i], sc[j], dv[i]);
+            dk[i] = mfma4(qc[j][i], dp[j], dk[i]);
+          }
+      }
+    }
+  };
+  walk(std::false_type{});
+  if (__any(odd != 0.f)) walk(std::true_type{});
   // the wavefronts' sums, dK first, then dV
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
@@ -684,7 +757,7 @@ __device__ __forceinline__ void attn32_dkv(const AttnArgs& a, int k0, int kvh, i
 
 // Both halves of the backward in one launch: a grid of dK/dV workgroups (low keys first: they see the most queries), then
 // one of dQ workgroups (late queries first).  Neither half alone fills the chip at the lengths fp32 stages have: two launches
-// took 48 us, one takes 30 (448 positions, 4 heads of 128); 155 and 126 us at 2 x 700, 8 heads of 128.
+// took 48 us, one takes 28 (448 positions, 4 heads of 128); 155 and 126 us at 2 x 700, 8 heads of 128.
 template <int HD>
 __global__ __launch_bounds__(AW * 64) void attn32_bwd_kernel(AttnArgs a) {
   __shared__ f32x4 red[AW * (HD / 16) * 64], kv[2 * (HD / 16) * 64];

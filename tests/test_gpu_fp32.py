@@ -122,3 +122,34 @@ def test_products_of_overlapping_rows(dtype, mode, M, N, K, lda, ldb):
         i1, l1, p1 = (lambda v: (C.c_int * 1)(v)), (lambda v: (C.c_int64 * 1)(v)), (lambda p: (C.c_void_p * 1)(p))
         assert L().stage_kernel_wgrad_group(dt, 1, i1(M), i1(N), i1(K), p1(ptrs[0]), l1(lda), p1(ptrs[1]), l1(ldb), p1(P(Cg)), l1(N), 0, None) == 0
         assert torch.equal(Cg, Cd)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+@pytest.mark.parametrize("part", ["q", "k", "v", "do"])
+@pytest.mark.parametrize("s,hd,causal,at", [(16, 64, 1, 9), (37, 128, 1, 20), (37, 64, 1, 36), (37, 64, 0, 36), (150, 128, 1, 0), (150, 64, 1, 141)])
+def test_attention_keeps_a_position_to_those_that_see_it(part, value, s, hd, causal, at):
+    """An infinity or NaN in q, k, v or dO of one position: what the plain kernels, which never read a key behind its query nor a row
+    past the end, leave finite stays finite and right, and the rest is the same kind of non-finite."""
+    import torch
+    h, hkv = 2, 1
+    g = torch.Generator().manual_seed(35)
+    qkv, do = torch.randn((s, (h + 2 * hkv) * hd), generator=g), torch.randn((s, h * hd), generator=g)
+    if part == "do":
+        do[at, hd + 3] = value
+    else:
+        qkv[at, {"q": hd, "k": h * hd, "v": (h + hkv) * hd}[part] + 5] = value
+    qkv, do = qkv.to("cuda:0"), do.to("cuda:0")
+    outs = []
+    for ks in (0, 1):
+        o, dqkv = torch.zeros_like(do), torch.zeros_like(qkv)
+        lse, delta = (torch.zeros((h, s), device="cuda:0") for _ in range(2))
+        assert L().stage_kernel_attention_fwd(0, 1, s, h, hkv, hd, causal, P(qkv), P(o), P(lse), ks, None) == 0
+        assert L().stage_kernel_attention_bwd(0, 1, s, h, hkv, hd, causal, P(qkv), P(o), P(lse), P(do), P(dqkv), P(delta), ks, None) == 0
+        outs.append((o, lse, delta, dqkv))
+    for name, x, y in zip(("o", "lse", "delta", "dqkv"), *outs):
+        assert torch.equal(torch.isnan(x), torch.isnan(y)), name
+        inf = torch.isinf(y)
+        assert torch.equal(torch.isinf(x), inf) and torch.equal(x[inf], y[inf]), name
+        fin = torch.isfinite(y)
+        if fin.any():
+            assert so.max_rel_err(to_np(x[fin]), to_np(y[fin])) <= TOL, name
