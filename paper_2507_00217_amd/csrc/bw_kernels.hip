@@ -121,14 +121,12 @@ __global__ __launch_bounds__(NORM_THREADS) void norm_fwd_kernel(NormArgs n) {
 // (the mean(dxhat) term is absent for RMSNorm); per-workgroup partial sums of
 // dgamma = sum_rows dout * xhat and dbeta = sum_rows dout go to n.partial.
 //
-// Bound by HBM, 8 bytes per element (16 with an fp32 residual stream), as long as enough rows are in flight.  A row takes
-// tpr threads (whole wavefronts) with at most NB_CH 16-byte pieces each, so that widths that are not a power of two leave few
-// threads idle (5120: 5 wavefronts x 2 pieces; one fixed workgroup of 256 threads needed 3 pieces, half of the last unused,
-// and registers for 4); a workgroup holds several rows side by side.  The next row's loads are
-// issued before this one is reduced, both row sums cross the workgroup in one exchange, and xhat and dxhat are formed again
-// from the raw row rather than kept.  4096 x 5120 in bf16: 49 -> 37 us (4.5 TB/s,
-// partial sums not counted; a large copy reaches 4.8); 2048 x 2048 with an fp32 residual stream: 20.5 -> 16-18.
-constexpr int NB_CH = 2;
+// Bound by HBM, 8 bytes per element (16 with an fp32 residual stream), as long as enough rows are in flight.  A row takes up to
+// four wavefronts, piece c of thread t being 16-byte piece t + 256 c of the row, and CH <= 4 pieces per thread (fewer wavefronts
+// for rows of less than 256 pieces): the row sums are then the same whatever else the workgroup does.  Rows of one piece per
+// thread stand side by side in workgroups of up to eight wavefronts.  Both row sums cross the workgroup in one exchange, xhat and
+// dxhat are formed again from the raw row rather than kept, and where registers allow (PF) the next row's loads are issued before
+// this one is reduced.
 template <typename T, bool WIDE> struct RowPiece { static constexpr int W = WIDE ? Vec<T>::N / 4 : 1; uint4 v[W]; };
 template <typename T, bool WIDE>
 __device__ __forceinline__ RowPiece<T, WIDE> ld_piece(const void* base, int64_t off) {
@@ -148,27 +146,28 @@ template <typename T, bool WIDE> __device__ __forceinline__ float at_piece(const
   }
 }
 
+constexpr int NB_THREADS = 512;
 // XW / RW: x / resid is stored in fp32 although T is not
-template <typename T, int KIND, bool XW, bool RW>
-__global__ __launch_bounds__(XW || RW ? 512 : 640) void norm_bwd_kernel(NormArgs n, int tpr) {
+template <typename T, int KIND, bool XW, bool RW, int CH, bool PF, bool SIDE>
+__global__ __launch_bounds__(SIDE ? NB_THREADS : NORM_THREADS) void norm_bwd_kernel(NormArgs n, int tpr) {
   constexpr int V = Vec<T>::N;
-  extern __shared__ float col_sums[];                    // [row groups][2][d], only with several row groups
-  __shared__ float red[2][16][2];
+  extern __shared__ float col_sums[];                    // [row groups - 1][2][d]: the first group's stay in its registers
+  __shared__ float red[2][NB_THREADS / 64][2];
   const int nvec = n.d / V, ngrp = blockDim.x / tpr, wpr = tpr >> 6;
   const int grp = threadIdx.x / tpr, t = threadIdx.x % tpr, wave = threadIdx.x >> 6;
-  float dg[NB_CH][V], db[NB_CH][V];
-  Vec<T> gam[NB_CH];
+  float dg[CH][V], db[CH][V];
+  Vec<T> gam[CH];
 #pragma unroll
-  for (int c = 0; c < NB_CH; ++c) {
+  for (int c = 0; c < CH; ++c) {
     const int vi = t + c * tpr;
     gam[c] = ldv((const T*)n.gamma + (vi < nvec ? vi : 0) * V);
 #pragma unroll
     for (int e = 0; e < V; ++e) dg[c][e] = db[c][e] = 0.f;
   }
   const float inv_d = 1.f / (float)n.d;
-  RowPiece<T, XW> x[NB_CH], xn[NB_CH];
-  RowPiece<T, RW> rs[NB_CH], rsn[NB_CH];
-  Vec<T> dv[NB_CH], dvn[NB_CH];
+  RowPiece<T, XW> x[CH], xn[CH];
+  RowPiece<T, RW> rs[CH], rsn[CH];
+  Vec<T> dv[CH], dvn[CH];
   float mean = 0.f, rstd = 0.f, mean_n = 0.f, rstd_n = 0.f;
   // rows past the end are read as the last one and leave no trace
   auto load = [&](int row) __attribute__((always_inline)) {
@@ -176,7 +175,7 @@ __global__ __launch_bounds__(XW || RW ? 512 : 640) void norm_bwd_kernel(NormArgs
     const int64_t roff = (int64_t)r * n.d;
     mean_n = n.stats[2 * r]; rstd_n = n.stats[2 * r + 1];
 #pragma unroll
-    for (int c = 0; c < NB_CH; ++c) {
+    for (int c = 0; c < CH; ++c) {
       const int vi = t + c * tpr;
       const int64_t off = roff + (vi < nvec ? vi : 0) * V;
       xn[c] = ld_piece<T, XW>(n.x, off);
@@ -186,17 +185,18 @@ __global__ __launch_bounds__(XW || RW ? 512 : 640) void norm_bwd_kernel(NormArgs
   };
   const int step = gridDim.x * ngrp;
   int row0 = blockIdx.x * ngrp;
-  load(row0 + grp);
+  if (PF) load(row0 + grp);
   for (int it = 0; row0 < n.rows; row0 += step, ++it) {
     const int row = row0 + grp;
+    if (!PF) load(row);
     mean = mean_n; rstd = rstd_n;
 #pragma unroll
-    for (int c = 0; c < NB_CH; ++c) { x[c] = xn[c]; dv[c] = dvn[c]; rs[c] = rsn[c]; }
-    if (row0 + step < n.rows) load(row + step);
+    for (int c = 0; c < CH; ++c) { x[c] = xn[c]; dv[c] = dvn[c]; rs[c] = rsn[c]; }
+    if (PF && row0 + step < n.rows) load(row + step);
     const bool live = row < n.rows;
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-    for (int c = 0; c < NB_CH; ++c)
+    for (int c = 0; c < CH; ++c)
       if (live && t + c * tpr < nvec) {
 #pragma unroll
         for (int e = 0; e < V; ++e) {
@@ -216,9 +216,13 @@ __global__ __launch_bounds__(XW || RW ? 512 : 640) void norm_bwd_kernel(NormArgs
       s1 = s2 = 0.f;
       for (int k = 0; k < wpr; ++k) { s1 += red[it & 1][grp * wpr + k][0]; s2 += red[it & 1][grp * wpr + k][1]; }
     }
-    const float m1 = s1 * inv_d, m2 = s2 * inv_d;
+    float m1, m2;
+    {
+#pragma clang fp contract(off)                           // rounded before they are subtracted
+      m1 = s1 * inv_d; m2 = s2 * inv_d;
+    }
 #pragma unroll
-    for (int c = 0; c < NB_CH; ++c) {
+    for (int c = 0; c < CH; ++c) {
       const int vi = t + c * tpr;
       if (live && vi < nvec) {
         const int64_t off = (int64_t)row * n.d + vi * V;
@@ -226,7 +230,12 @@ __global__ __launch_bounds__(XW || RW ? 512 : 640) void norm_bwd_kernel(NormArgs
 #pragma unroll
         for (int e = 0; e < V; ++e) {
           const float xhat = (at_piece<T, XW>(x[c], e) - mean) * rstd;
-          o[e] = (to_f32(dv[c].v[e]) * to_f32(gam[c].v[e]) - m1 - xhat * m2) * rstd;
+          float dxhat;
+          {
+#pragma clang fp contract(off)                           // the rounded product, as in the sums
+            dxhat = to_f32(dv[c].v[e]) * to_f32(gam[c].v[e]);
+          }
+          o[e] = (dxhat - m1 - xhat * m2) * rstd;
           if (n.resid) o[e] += at_piece<T, RW>(rs[c], e);
         }
         st_row<T>(n.out, off, o, n.out_f32);
@@ -235,33 +244,33 @@ __global__ __launch_bounds__(XW || RW ? 512 : 640) void norm_bwd_kernel(NormArgs
       }
     }
   }
-  if (ngrp > 1) {                                        // the row groups' column sums, in order
-    float* cs = col_sums + (int64_t)grp * 2 * n.d;
+  if (SIDE && ngrp > 1) {                                // the row groups' column sums, in order
+    float* cs = col_sums + (int64_t)(grp - 1) * 2 * n.d;
 #pragma unroll
-    for (int c = 0; c < NB_CH; ++c) {
+    for (int c = 0; c < CH; ++c) {
       const int vi = t + c * tpr;
-      if (vi < nvec)
+      if (grp > 0 && vi < nvec)
 #pragma unroll
         for (int e = 0; e < V; ++e) { cs[vi * V + e] = dg[c][e]; if (KIND == 0) cs[n.d + vi * V + e] = db[c][e]; }
     }
     __syncthreads();
     if (grp != 0) return;
 #pragma unroll
-    for (int c = 0; c < NB_CH; ++c) {
+    for (int c = 0; c < CH; ++c) {
       const int vi = t + c * tpr;
       if (vi < nvec)
         for (int g = 1; g < ngrp; ++g)
 #pragma unroll
           for (int e = 0; e < V; ++e) {
-            dg[c][e] += col_sums[(int64_t)g * 2 * n.d + vi * V + e];
-            if (KIND == 0) db[c][e] += col_sums[(int64_t)g * 2 * n.d + n.d + vi * V + e];
+            dg[c][e] += col_sums[(int64_t)(g - 1) * 2 * n.d + vi * V + e];
+            if (KIND == 0) db[c][e] += col_sums[(int64_t)(g - 1) * 2 * n.d + n.d + vi * V + e];
           }
     }
   }
   float* pg = n.partial + (int64_t)blockIdx.x * 2 * n.d;
   float* pb = pg + n.d;
 #pragma unroll
-  for (int c = 0; c < NB_CH; ++c) {
+  for (int c = 0; c < CH; ++c) {
     const int vi = t + c * tpr;
     if (vi < nvec)
 #pragma unroll
@@ -330,32 +339,42 @@ static hipError_t norm_fwd_t(const NormArgs& n, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, int KIND, bool XW, bool RW>
+// Rows side by side (SIDE): with one piece per thread, and in fp32, whose pieces are half as many elements, as many rows as eight
+// wavefronts hold, one such workgroup per CU -- half the partial rows of two workgroups of half the size (us, two against
+// one; 2048 x 2048 with an fp32 residual stream: 18.6 / 17.8; 4096 x 2048 in bf16: 20.2 / 19.1; 448 x 4096 in fp32: 14.1 / 12.7).
+// Other rows go one to a workgroup, two workgroups per CU (4096 x 4096 in bf16: 35.2, two rows in one workgroup per CU 38.8).
+// Prefetch (PF): in fp32, with one piece, and with two where nothing is stored in fp32 (4096 x 3072: 30.5 / 34.4); beyond that its
+// registers cost more rows in flight than it hides (4096 x 5120 with an fp32 residual stream: 74.8 / 72.4; 2048 x 6144: 52.2 /
+// 50.4; 4096 x 8192 would spill).
+template <typename T, int KIND, bool XW, bool RW, int CH>
 static hipError_t norm_bwd_launch(const NormArgs& n, hipStream_t s, int* parts) {
-  const int nvec = n.d / Vec<T>::N, tpr = nvec <= 64 ? 64 : ((nvec + NB_CH - 1) / NB_CH + 63) / 64 * 64;
-  // With nothing stored in fp32, as many rows side by side as the register budget has wavefronts for, one such workgroup per CU:
-  // half the partial rows -- 42 of 210 MB moved at 4096 x 5120, 45 -> 37 us -- of two workgroups of half the size.  With an fp32
-  // residual stream the smaller workgroups are ahead (4096 x 4096: 46 against 49 us), and so they are on short batches.
-  constexpr int THREADS = XW || RW ? 256 : 640;
-  int ngrp = THREADS >= tpr ? THREADS / tpr : 1;
-  if (ngrp > 1 && n.rows < 256 * ngrp) ngrp = tpr >= 256 ? 1 : 256 / tpr;
-  const int cap = ngrp > 1 && ngrp * tpr > 256 ? NORM_PARTIAL_ROWS / 2 : NORM_PARTIAL_ROWS, want = (n.rows + ngrp - 1) / ngrp;
+  constexpr bool SIDE = CH == 1 || sizeof(T) == 4, PF = SIDE || (CH == 2 && !XW && !RW);
+  const int units = (n.d / Vec<T>::N + 63) / 64, tpr = 64 * (units < 4 ? units : 4);
+  int ngrp = SIDE ? NB_THREADS / tpr : 1;
+  if (ngrp > 1 && n.rows < 256 * ngrp) ngrp = NORM_THREADS / tpr;
+  const int cap = SIDE ? NORM_PARTIAL_ROWS / 2 : NORM_PARTIAL_ROWS, want = (n.rows + ngrp - 1) / ngrp;
   *parts = want < cap ? want : cap;
-  const size_t lds = ngrp > 1 ? (size_t)ngrp * 2 * n.d * sizeof(float) : 0;      // at most 80 KiB: d <= 2 * V * tpr
-  auto kern = norm_bwd_kernel<T, KIND, XW, RW>;
-  static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
-  if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(*parts), dim3(ngrp * tpr), lds, s, n, tpr);
+  const size_t lds = (size_t)(ngrp - 1) * 2 * n.d * sizeof(float);       // at most 32 KiB: ngrp * d <= CH * V * NB_THREADS
+  hipLaunchKernelGGL((norm_bwd_kernel<T, KIND, XW, RW, CH, PF, SIDE>), dim3(*parts), dim3(ngrp * tpr), lds, s, n, tpr);
   return hipGetLastError();
+}
+template <typename T, int KIND, bool XW, bool RW>
+static hipError_t norm_bwd_width(const NormArgs& n, hipStream_t s, int* parts) {
+  switch ((n.d / Vec<T>::N + NORM_THREADS - 1) / NORM_THREADS) {                 // pieces per thread
+    case 1: return norm_bwd_launch<T, KIND, XW, RW, 1>(n, s, parts);
+    case 2: return norm_bwd_launch<T, KIND, XW, RW, 2>(n, s, parts);
+    case 3: return norm_bwd_launch<T, KIND, XW, RW, 3>(n, s, parts);
+    default: return norm_bwd_launch<T, KIND, XW, RW, 4>(n, s, parts);
+  }
 }
 template <typename T, int KIND>
 static hipError_t norm_bwd_pick(const NormArgs& n, hipStream_t s, int* parts) {
   if constexpr (sizeof(T) == 2) {
-    if (n.x_f32 && n.resid_f32 && n.resid) return norm_bwd_launch<T, KIND, true, true>(n, s, parts);
-    if (n.x_f32) return norm_bwd_launch<T, KIND, true, false>(n, s, parts);
-    if (n.resid_f32 && n.resid) return norm_bwd_launch<T, KIND, false, true>(n, s, parts);
+    if (n.x_f32 && n.resid_f32 && n.resid) return norm_bwd_width<T, KIND, true, true>(n, s, parts);
+    if (n.x_f32) return norm_bwd_width<T, KIND, true, false>(n, s, parts);
+    if (n.resid_f32 && n.resid) return norm_bwd_width<T, KIND, false, true>(n, s, parts);
   }
-  return norm_bwd_launch<T, KIND, false, false>(n, s, parts);
+  return norm_bwd_width<T, KIND, false, false>(n, s, parts);
 }
 template <typename T>
 static hipError_t norm_bwd_t(const NormArgs& n, hipStream_t s, int* parts) {

@@ -11,12 +11,12 @@ pytestmark = pytest.mark.gpu
 F, B, W = 0, 1, 2
 
 
-# bf16 widths: one wavefront with 4 / 3 rows side by side, two with 2, three (one row), five, eight; fp32 twice the pieces.  Rows:
-# one, fewer than the row groups, one past a full round of 512 workgroups
+# bf16 widths of one to four wavefronts with up to eight rows side by side, two and more pieces per thread (one row); fp32 twice the
+# pieces.  Rows: one, fewer than the row groups, one past a full round of the workgroups
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("norm", ["layernorm", "rmsnorm"])
 @pytest.mark.parametrize("rows,d", [(1, 8), (3, 512), (5, 520), (513, 1032), (2049, 264), (1025, 2056), (515, 2560), (2, 4096),
-                                    (2561, 512), (1281, 1032), (768, 2568)])      # ten, five and three rows side by side, 80 KiB of column sums
+                                    (2561, 512), (1281, 1032), (768, 2568), (514, 2048), (130, 64)])      # two to eight rows side by side, 32 KiB of column sums
 def test_norm_backward_row_shapes(dtype, norm, rows, d):
     import torch
     kind = {"layernorm": 0, "rmsnorm": 1}[norm]
@@ -35,6 +35,38 @@ def test_norm_backward_row_shapes(dtype, norm, rows, d):
     assert so.max_rel_err(to_np(dg), dg_ref) <= 2e-5
     if norm == "layernorm":
         assert so.max_rel_err(to_np(db), db_ref) <= 1e-5
+
+
+@pytest.mark.parametrize("rows", [3, 700])
+@pytest.mark.parametrize("d", [64, 520, 1024, 2052, 3000, 4096])
+def test_norm_backward_row_sum_order(rows, d):
+    """dx from a row sum taken in one order whatever shape the workgroups have: 256 threads of 4 elements at a time, one running sum each, a
+    butterfly over 64 threads, then the four 64s.  Emulated in fp32; a sum in another order changes a tenth of the elements, the
+    emulation itself (fused multiply-adds rounded twice) next to none."""
+    import torch
+    f32 = np.float32
+    fma = lambda a, b, c: (a.astype(np.float64) * b + c).astype(f32)
+    x, dout = synth.normal(52, 1, (rows, d)), synth.normal(52, 2, (rows, d))
+    gamma = synth.normal(52, 3, (d,), mean=1.0, std=0.1)
+    rstd = (1.0 / np.sqrt((x.astype(np.float64) ** 2).mean(1, keepdims=True) + 1e-5)).astype(f32)
+    xhat, dxhat = x * rstd, dout * gamma
+    pad = lambda v: np.pad(v, ((0, 0), (0, 4096 - d))).reshape(rows, 4, 256, 4)
+    px, pd, s = pad(xhat), pad(dxhat), np.zeros((rows, 256), f32)
+    for c in range(4):
+        for e in range(4):
+            s = fma(pd[:, c, :, e], px[:, c, :, e], s)
+    s = s.reshape(rows, 4, 64)
+    for o in (32, 16, 8, 4, 2, 1):
+        s = s + s[:, :, np.arange(64) ^ o]
+    tot = ((s[:, 0, 0] + s[:, 1, 0]) + s[:, 2, 0]) + s[:, 3, 0]
+    m2 = (tot * f32(1.0 / d))[:, None]
+    ref = fma(-xhat, m2, dxhat) * rstd
+    xd, dd, gd = (torch.from_numpy(v).to("cuda:0") for v in (x, dout, gamma))
+    st = torch.from_numpy(np.concatenate([np.zeros_like(rstd), rstd], 1)).to("cuda:0")
+    dx, dg = torch.empty_like(xd), torch.zeros(d, device="cuda:0")
+    part = torch.empty(L().stage_kernel_norm_partial_bytes(d) // 4, device="cuda:0")
+    assert L().stage_kernel_norm_bwd(0, 1, rows, d, P(xd), P(st), P(gd), P(dd), None, P(dx), P(dg), None, P(part), None) == 0
+    assert np.mean(dx.cpu().numpy() != ref) <= 1e-3
 
 
 def test_unaligned_gradient_input():
