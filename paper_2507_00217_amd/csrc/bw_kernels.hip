@@ -53,7 +53,7 @@ __device__ __forceinline__ void st_row(void* base, int64_t off, const float (&sr
 
 constexpr int NORM_THREADS = 256;
 constexpr int NORM_MAXCH = 4;          // 16-byte chunks per thread: d <= 256*4*(16/sizeof(T))
-constexpr int NORM_PARTIAL_ROWS = 512;   // backward: at most two workgroups per CU
+constexpr int NORM_PARTIAL_ROWS = 512;   // backward: partial rows the caller's scratch holds, at most this many workgroups
 int norm_partial_rows() { return NORM_PARTIAL_ROWS; }
 
 __device__ __forceinline__ float wg_sum(float v, float* red) {
@@ -351,8 +351,9 @@ static hipError_t norm_bwd_launch(const NormArgs& n, hipStream_t s, int* parts) 
   constexpr bool SIDE = CH == 1 || sizeof(T) == 4, PF = SIDE || (CH == 2 && !XW && !RW);
   const int units = (n.d / Vec<T>::N + 63) / 64, tpr = 64 * (units < 4 ? units : 4);
   int ngrp = SIDE ? NB_THREADS / tpr : 1;
-  if (ngrp > 1 && n.rows < 256 * ngrp) ngrp = NORM_THREADS / tpr;
-  const int cap = SIDE ? NORM_PARTIAL_ROWS / 2 : NORM_PARTIAL_ROWS, want = (n.rows + ngrp - 1) / ngrp;
+  const int n_cu = cu_count();
+  if (ngrp > 1 && n.rows < n_cu * ngrp) ngrp = NORM_THREADS / tpr;
+  const int fill = SIDE ? n_cu : 2 * n_cu, cap = fill < NORM_PARTIAL_ROWS ? fill : NORM_PARTIAL_ROWS, want = (n.rows + ngrp - 1) / ngrp;
   *parts = want < cap ? want : cap;
   const size_t lds = (size_t)(ngrp - 1) * 2 * n.d * sizeof(float);       // at most 32 KiB: ngrp * d <= CH * V * NB_THREADS
   hipLaunchKernelGGL((norm_bwd_kernel<T, KIND, XW, RW, CH, PF, SIDE>), dim3(*parts), dim3(ngrp * tpr), lds, s, n, tpr);

@@ -88,6 +88,7 @@ struct ActArgs {
 };
 
 int norm_partial_rows();
+int cu_count();                      // compute units of the device that is current at the first call
 
 // Column sums of fp32 partial rows, added to dst: the last step of every parameter gradient that is a sum over rows
 struct ColSum { const float* part; int64_t stride; int cols, parts; float* dst; };

@@ -300,11 +300,12 @@ __global__ __launch_bounds__(W * 64) void wgrad32_group_kernel(Wgrad32Group gg) 
 int pick32(int mode, int M, int N, int n_shapes) {
   static const int tile[3] = {64, 32, 16};
   static const double loss[2][3] = {{1., 1.2, 2.4}, {1., 1.45, 2.8}};
+  const int n_cu = cu_count();
   int best = 0;
   double bt = 0.;
   for (int i = 0; i < n_shapes; ++i) {
     const int64_t tiles = (int64_t)((M + tile[i] - 1) / tile[i]) * ((N + tile[i] - 1) / tile[i]);
-    const double t = (double)((tiles + 255) / 256) * tile[i] * tile[i] * loss[mode == GEMM_NT][i];
+    const double t = (double)((tiles + n_cu - 1) / n_cu) * tile[i] * tile[i] * loss[mode == GEMM_NT][i];
     if (i == 0 || t < bt) { best = i; bt = t; }
   }
   return best;
@@ -375,11 +376,12 @@ bool wgrad32_group_supported(const GemmArgs* list, int n, int nseg, const int64_
 // tokens x 512 .. 2816: 44 us with eight wavefronts per 32 x 32 tile, 41 with four, 46 in 64 x 64 tiles (two to a CU: a round and a
 // half); two layers of 128 tokens x 256 .. 1024: 16.5, 12.0 and 13.5.
 hipError_t wgrad32_group(const GemmArgs* list, int n, int nseg, const int64_t* seg_delta, hipStream_t s, int shape) {
+  const int n_cu = cu_count();
   int64_t area[2] = {0, 0};
   for (int which = 0; which < 2; ++which) {
     const int t = which == 0 ? 64 : 32;
     for (int i = 0; i < n; ++i) area[which] += (int64_t)((list[i].M + t - 1) / t) * ((list[i].N + t - 1) / t);
-    area[which] = (area[which] + 255) / 256 * t * t;
+    area[which] = (area[which] + n_cu - 1) / n_cu * t * t;
   }
   const bool wide = shape > 0 ? shape == 1 : (double)area[0] <= 1.2 * (double)area[1];
   const int t = wide ? 64 : 32;

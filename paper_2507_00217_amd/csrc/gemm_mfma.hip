@@ -35,6 +35,15 @@
 
 namespace stg {
 
+int cu_count() {
+  static const int n_cu = [] {
+    int dev = 0, n = 0;
+    return (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) ? n : 256;
+  }();
+  return n_cu;
+}
+
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -834,17 +843,8 @@ __global__ __launch_bounds__(256, 2) void gemm_wgrad_small_kernel(GemmGroup gg, 
 constexpr int WAVE_COLS = 2, WAVE_COLS_WGRAD = 4;
 constexpr int WIDE_MIN_K = 8192;       // input gradients: four wavefronts from this reduction length on
 
-// One-time set-up (CU count, a kernel's LDS limit) sits in function-local statics, whose initialisation the language
+// One-time set-up (a kernel's LDS limit, like the CU count) sits in function-local statics, whose initialisation the language
 // makes thread-safe: concurrent first calls from several threads run it once.
-int cu_count() {
-  static const int n_cu = [] {
-    int dev = 0, n = 0;
-    return (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) ? n : 256;
-  }();
-  return n_cu;
-}
-
 template <bool AKC, bool BKC, int EPI, int WR, int TN = WAVE_COLS>
 hipError_t launch_tiles(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles_n, int first, int n_wg) {
   // the ring of operand tiles; every epilogue's staging (at most 128 KiB) fits inside it
