@@ -10,12 +10,12 @@
  * allocated, work is enqueued on `hip_stream` (hipStream_t, NULL = default
  * stream) without synchronising.  dtype / norm / act codes are the STAGE_*
  * enums of stage.h.  kernel_set: 0 = tuned gfx950 kernels where one exists for
- * the shape, 1 = plain reference HIP kernels.  stage_kernel_gemm and the
- * attention entries also take 2 and 3: the tuned kernels with a choice they
- * normally make from the shape fixed, so that tests reach both variants on any
- * shape -- GEMM: 2 = full 256 x 256 tiles only, 3 = half-height tiles only, 4 (stage_kernel_gemm, forward and
- * input-gradient layouts) = 128 x 128, 5 = 64 x 64, 6 = 128 x 64 tiles only; in fp32 2 / 3 / 4 = tiles of 64 x 64 / 32 x 32 / 16 x 16 (weight gradients:
- * 32 x 32 for 4 as well) for the products and the two fused-activation entries;
+ * the shape, 1 = plain reference HIP kernels.  The products and the attention
+ * entries also take higher values: the tuned kernels with a choice they
+ * normally make from the shape fixed, so that tests reach every variant on any
+ * shape.  Products (with or without activation, weight gradients one at a time or grouped): 2 = full 256 x 256 tiles only, 3 =
+ * half-height tiles only, 4 = 128 x 128, 5 = 64 x 64, 6 = 128 x 64 tiles only (SwiGLU forward: 128 x 64 for 5; weight gradients:
+ * 64 x 64 for 6, the normal choice for 3); in fp32 2 / 3 / 4 = tiles of 64 x 64 / 32 x 32 / 16 x 16 (weight gradients: 32 x 32 for 4);
  * attention: 2 / 3 = forward and dQ workgroups of 8 / 4 wavefronts (dK/dV workgroups of 128 keys), 4 = forward and dQ
  * workgroups of 64 queries whose two wavefronts per query block each take half of the keys, dK/dV workgroups of 64 keys.
  * Return: 0, or STAGE_E_INVAL for
@@ -42,7 +42,7 @@ int stage_kernel_gemm(int dtype, int mode, int M, int N, int K, const void* A, i
  * (GELU) or [K, 2f] (SwiGLU, columns gate | up), and Aout [M, f] = gelu(Z) or silu(Z[:, :f]) * Z[:, f:].  The tuned kernel
  * forms the activation from the fp32 accumulators in the product's epilogue (one rounding less than reading Z back, and Z
  * is not re-read; in fp32 rows must be dense, ldz = f or 2f and lda_out = f); the plain kernels (kernel_set 1) run the
- * product and then the activation kernel on the stored Z, dense rows only.  kernel_set 2 / 3 as for stage_kernel_gemm. */
+ * product and then the activation kernel on the stored Z, dense rows only. */
 int stage_kernel_gemm_act(int dtype, int act, int M, int f, int K, const void* A, int64_t lda, const void* B, int64_t ldb,
                           void* Z, int64_t ldz, void* Aout, int64_t lda_out, int kernel_set, void* hip_stream);
 

@@ -129,14 +129,16 @@ hipError_t rope_apply(DType dt, void* x, int64_t ld, int64_t rows, int s, int nh
 
 // tuned gfx950 kernels (bf16 MFMA)
 bool gemm_mfma_supported(const GemmArgs& g);
-// tile_shape: 0 = full 256 x 256 tiles, half-height ones for a thin last round or a small product; 1 = full tiles only;
-// 2 = half-height tiles only (1 and 2 exist so that tests reach both on any shape)
+// tile_shape: 0 = full 256 x 256 tiles for complete rounds of one per compute unit, smaller ones for a short last round or a small
+// product; otherwise (so that tests reach each on any shape) all tiles 1 = full, 2 = half-height, 3 = 128 x 128, 4 = 64 x 64 (SwiGLU
+// forward: 128 x 64), 5 = 128 x 64 (weight gradients: 2 is the rule, 5 is 64 x 64)
 hipError_t gemm_mfma(const GemmArgs& g, hipStream_t s, int tile_shape = 0);
-// several weight-gradient (TN, fp32-accumulating) products in one launch of persistent workgroups; each may reduce
-// over nseg operand pairs in turn, pair s at (A + seg_delta[s] bytes, B + seg_delta[s] bytes), seg_delta[0] = 0
+// several weight-gradient (TN, fp32-accumulating) products together: persistent workgroups over the full tiles of complete
+// rounds, a second launch for a short last round (or list) in small tiles; each product may reduce over nseg operand pairs in
+// turn, pair s at (A + seg_delta[s] bytes, B + seg_delta[s] bytes), seg_delta[0] = 0
 constexpr int GEMM_MAX_SEG = 8;
 bool gemm_mfma_wgrad_group_supported(const GemmArgs* list, int n, int nseg, const int64_t* seg_delta);
-hipError_t gemm_mfma_wgrad_group(const GemmArgs* list, int n, int nseg, const int64_t* seg_delta, hipStream_t s);
+hipError_t gemm_mfma_wgrad_group(const GemmArgs* list, int n, int nseg, const int64_t* seg_delta, hipStream_t s, int tile_shape = 0);
 bool attn_mfma_supported(const AttnArgs& a);
 hipError_t attn_fwd_mfma(const AttnArgs& a, hipStream_t s);
 hipError_t attn_bwd_mfma(const AttnArgs& a, hipStream_t s);

@@ -900,7 +900,7 @@ hipError_t launch_tiny(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles_
 // against full ones, 2048 x 6144 x 2048: 49 / 48 (60 / 53).  The half-height tile is left to the SwiGLU backward, whose z it
 // rewrites in whole rows through LDS (2048 x 2816 x 2048: 36 / 39).  All give the same bits.
 // `shape`: 0 = this rule, else one tile shape for all: 1 = full, 2 = half-height, 3 = 128 x 128, 4 = 64 x 64 (SwiGLU: 128 x 64),
-// 5 = 128 x 64 (weight gradients: always full).
+// 5 = 128 x 64.
 template <bool AKC, bool BKC, int EPI>
 hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   const int tiles_m = (g.M + BM - 1) / BM;
@@ -980,7 +980,7 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t s, int tile_shape) {
       if (g.act_bwd == 1) return launch<true, true, EPI_DGELU>(g, s, tile_shape);
       if (g.act_bwd == 2) return launch<true, true, EPI_DSWIGLU>(g, s, tile_shape);
       return launch<true, true, EPI_STORE>(g, s, tile_shape);
-    case GEMM_TN: return tile_shape == 0 ? gemm_mfma_wgrad_group(&g, 1, 1, nullptr, s) : launch<false, false, EPI_ACC32>(g, s, tile_shape);
+    case GEMM_TN: return gemm_mfma_wgrad_group(&g, 1, 1, nullptr, s, tile_shape);
   }
   return hipErrorInvalidValue;
 }
@@ -994,7 +994,7 @@ bool gemm_mfma_wgrad_group_supported(const GemmArgs* list, int n, int nseg, cons
   return true;
 }
 
-hipError_t gemm_mfma_wgrad_group(const GemmArgs* list, int n, int nseg, const int64_t* seg_delta, hipStream_t s) {
+hipError_t gemm_mfma_wgrad_group(const GemmArgs* list, int n, int nseg, const int64_t* seg_delta, hipStream_t s, int shape) {
   auto kern = gemm_wgrad_group_kernel<WAVE_COLS_WGRAD>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
   if (attr != hipSuccess) return attr;
@@ -1018,7 +1018,8 @@ hipError_t gemm_mfma_wgrad_group(const GemmArgs* list, int n, int nseg, const in
     // the time, take 64 x 64 tiles (75 tiles, K 400: 18.1 / 15.2 us; 9 tiles, K 400: 10.2 / 5.6; but 72 tiles, K 1500: 29 / 33).  Measured (us, full tiles against this rule's): 48 tiles, K 128: 22.5 / 9.7;
     // 75 tiles, K 400: 28.9 / 17.7; 64 tiles, K 4096: 91.7 / 42.4; 128 tiles, K 8192: 172 / 159; on fuller rounds the doubled
     // operand traffic loses (196 tiles, K 3000: 86 / 113).
-    const int tail = total % n_cu, n_quarter = 2 * tail <= n_cu ? tail : 0, n_full = total - n_quarter;
+    // (`shape`: 0 = this rule; 1 = full tiles, 3 = 128 x 128, 4 and 5 = 64 x 64 for the whole list.)
+    const int tail = total % n_cu, n_small = shape >= 3 ? total : shape == 1 || 2 * tail > n_cu ? 0 : tail, n_full = total - n_small;
     if (n_full) {
       const int grid = n_full < n_cu ? n_full : n_cu;       // one workgroup per CU (160 KiB of LDS each)
       gg.total_tiles = n_full;
@@ -1026,12 +1027,13 @@ hipError_t gemm_mfma_wgrad_group(const GemmArgs* list, int n, int nseg, const in
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
-    if (n_quarter) {
+    if (n_small) {
       int kmax = 0;
       for (int i = 0; i < gg.n; ++i) kmax = gg.p[i].K > kmax ? gg.p[i].K : kmax;
-      const hipError_t e = (kmax * nseg <= 512 || 16 * n_quarter <= 2 * n_cu) ? launch_wgrad_small<0, 0, 2>(gg, n_full, n_quarter, s)
-                           : 4 * n_quarter <= n_cu                            ? launch_wgrad_small<1, 1, 4>(gg, n_full, n_quarter, s)
-                                                                              : launch_wgrad_small<1, 1, 2>(gg, n_full, n_quarter, s);
+      const bool tiny = shape >= 3 ? shape > 3 : kmax * nseg <= 512 || 16 * n_small <= 2 * n_cu;
+      const hipError_t e = tiny                    ? launch_wgrad_small<0, 0, 2>(gg, n_full, n_small, s)
+                           : 4 * n_small <= n_cu ? launch_wgrad_small<1, 1, 4>(gg, n_full, n_small, s)
+                                                 : launch_wgrad_small<1, 1, 2>(gg, n_full, n_small, s);
       if (e != hipSuccess) return e;
     }
   }

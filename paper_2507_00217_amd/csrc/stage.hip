@@ -510,22 +510,27 @@ int exec_backward_input(stage* st, int mb, const void* dy, void* dx, int l0, int
   return STAGE_OK;
 }
 
+// a kernel-level entry's kernel_set as the tile shape it forces: bf16 (2 .. 6) and fp32 products (2 .. 4); 0 = the rule on sizes
+int shape16(int kernel_set) { return kernel_set >= 2 && kernel_set <= 6 ? kernel_set - 1 : 0; }
+int shape32(int kernel_set) { return kernel_set >= 2 && kernel_set <= 4 ? kernel_set - 1 : 0; }
+
 // A list of weight-gradient products, each reducing over nseg operand pairs in turn (pair s = the list's A and B
 // moved by seg_delta[s] bytes): one launch of persistent workgroups when the tuned kernel takes all of them, else
 // product by product and pair by pair -- the same accumulation order, hence the same bits.
 hipError_t wgrad_list(DType dt, int kernel_set, const GemmArgs* list, int n, int nseg, const int64_t* seg_delta, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  if (kernel_set == 0 && dt == DT_BF16 && gemm_mfma_wgrad_group_supported(list, n, nseg, seg_delta))
-    return gemm_mfma_wgrad_group(list, n, nseg, seg_delta, s);
-  if (kernel_set == 0 && dt == DT_F32 && wgrad32_group_supported(list, n, nseg, seg_delta))
-    return wgrad32_group(list, n, nseg, seg_delta, s);
+  const bool tuned = kernel_set != 1;
+  if (tuned && dt == DT_BF16 && gemm_mfma_wgrad_group_supported(list, n, nseg, seg_delta))
+    return gemm_mfma_wgrad_group(list, n, nseg, seg_delta, s, shape16(kernel_set));
+  if (tuned && dt == DT_F32 && wgrad32_group_supported(list, n, nseg, seg_delta))
+    return wgrad32_group(list, n, nseg, seg_delta, s, shape32(kernel_set));
   for (int sg = 0; sg < nseg; ++sg)
     for (int i = 0; i < n; ++i) {
       GemmArgs g = list[i];
       if (sg > 0) { g.A = (const char*)g.A + seg_delta[sg]; g.B = (const char*)g.B + seg_delta[sg]; }
-      const hipError_t e = (kernel_set == 0 && dt == DT_BF16 && gemm_mfma_supported(g)) ? gemm_mfma(g, s)
-                           : (kernel_set == 0 && dt == DT_F32 && gemm32_supported(g))   ? gemm32(g, s)
-                                                                                        : gemm_ref(dt, g, s);
+      const hipError_t e = (tuned && dt == DT_BF16 && gemm_mfma_supported(g)) ? gemm_mfma(g, s, shape16(kernel_set))
+                           : (tuned && dt == DT_F32 && gemm32_supported(g))   ? gemm32(g, s, shape32(kernel_set))
+                                                                              : gemm_ref(dt, g, s);
       if (e != hipSuccess) return e;
     }
   return hipSuccess;
@@ -980,7 +985,6 @@ const char* stage_strerror(int code) {
 extern "C" {
 
 static int hip_rc(hipError_t e) { return e == hipSuccess ? STAGE_OK : (e == hipErrorInvalidValue ? STAGE_E_INVAL : STAGE_E_HIP); }
-static int shape32(int kernel_set) { return kernel_set >= 2 && kernel_set <= 4 ? kernel_set - 1 : 0; }
 static bool dtype_ok(int dt) { return dt == STAGE_DTYPE_FP32 || dt == STAGE_DTYPE_BF16; }
 
 int stage_kernel_gemm(int dtype, int mode, int M, int N, int K, const void* A, int64_t lda, const void* B, int64_t ldb,
@@ -989,7 +993,7 @@ int stage_kernel_gemm(int dtype, int mode, int M, int N, int K, const void* A, i
   if ((mode == GEMM_TN) != (acc_f32 != 0) || (acc_f32 && R)) return STAGE_E_INVAL;
   GemmArgs g{mode, M, N, K, A, lda, B, ldb, C, ldc, R, ldr, acc_f32};
   if (kernel_set != 1 && dtype == STAGE_DTYPE_BF16 && gemm_mfma_supported(g))
-    return hip_rc(gemm_mfma(g, (hipStream_t)hip_stream, kernel_set == 2 ? 1 : kernel_set == 3 ? 2 : kernel_set == 4 ? 3 : kernel_set == 5 ? 4 : kernel_set == 6 ? 5 : 0));
+    return hip_rc(gemm_mfma(g, (hipStream_t)hip_stream, shape16(kernel_set)));
   if (kernel_set != 1 && dtype == STAGE_DTYPE_FP32 && gemm32_supported(g)) return hip_rc(gemm32(g, (hipStream_t)hip_stream, shape32(kernel_set)));
   return hip_rc(gemm_ref((DType)dtype, g, (hipStream_t)hip_stream));
 }
@@ -1003,7 +1007,7 @@ int stage_kernel_gemm_act(int dtype, int act, int M, int f, int K, const void* A
   GemmArgs g{GEMM_NN, M, fin, K, A, lda, B, ldb, Z, ldz, nullptr, 0, 0, 0, 0};
   g.act = act == STAGE_ACT_SWIGLU ? 2 : 1; g.C2 = Aout; g.ldc2 = lda_out;
   if (kernel_set != 1 && dtype == STAGE_DTYPE_BF16 && gemm_mfma_supported(g))
-    return hip_rc(gemm_mfma(g, (hipStream_t)hip_stream, kernel_set == 2 ? 1 : kernel_set == 3 ? 2 : 0));
+    return hip_rc(gemm_mfma(g, (hipStream_t)hip_stream, shape16(kernel_set)));
   // fp32, and the plain kernels (the product, then the activation from the stored z): dense rows
   if (ldz != fin || lda_out != f) return STAGE_E_INVAL;
   if (kernel_set != 1 && dtype == STAGE_DTYPE_FP32 && gemm32_supported(g)) return hip_rc(gemm32(g, (hipStream_t)hip_stream, shape32(kernel_set)));
@@ -1023,7 +1027,7 @@ int stage_kernel_gemm_act_bwd(int dtype, int act, int M, int f, int K, const voi
   GemmArgs g{GEMM_NT, M, f, K, dY, ldy, W, ldw, nullptr, (int64_t)f, nullptr, 0, 0, 0, 0};
   g.act_bwd = nop; g.Z = Z; g.ldz = ldz;
   if (kernel_set != 1 && dtype == STAGE_DTYPE_BF16 && gemm_mfma_supported(g))
-    return hip_rc(gemm_mfma(g, (hipStream_t)hip_stream, kernel_set == 2 ? 1 : kernel_set == 3 ? 2 : 0));
+    return hip_rc(gemm_mfma(g, (hipStream_t)hip_stream, shape16(kernel_set)));
   // fp32, and the plain kernels (the product into the scratch, then the activation backward kernel): dense z rows
   if (!da_scratch || ldz != (int64_t)nop * f) return STAGE_E_INVAL;
   g.C = da_scratch;

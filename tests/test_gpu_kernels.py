@@ -57,7 +57,7 @@ GEMM_SHAPES = [(128, 256, 768), (200, 192, 136), (328, 1088, 512), (512, 512, 20
 @pytest.mark.parametrize("M,N,K", GEMM_SHAPES)
 def test_gemm(dtype, mode, kernel_set, M, N, K):
     """kernel_set 2 / 3 / 4: the tuned kernel with full 256 x 256 tiles only / half-height tiles only / 128 x 128 tiles only
-    (0 picks by shape; weight gradients have full tiles only)."""
+    (0 picks by shape; weight gradients have no half-height tiles)."""
     import torch
     a_shape = (K, M) if mode == 2 else (M, K)
     b_shape = (N, K) if mode == 1 else (K, N)

@@ -33,10 +33,13 @@ def test_small_tiles_agree_bitwise(mode, M, N, K):
 
 @pytest.mark.parametrize("act", [0, 1])
 @pytest.mark.parametrize("M,f,K", [(1, 8, 64), (127, 64, 64), (129, 72, 128), (128, 136, 320), (257, 200, 384),
-                                   (1100, 72, 128), (300, 2000, 192)])      # beyond one round of 64 x 64 (GELU) / 128 x 64 (SwiGLU)
+                                   (1100, 72, 128), (300, 2000, 192),
+                                   (1100, 1736, 64), (1100, 3000, 64), (1100, 4200, 64)])
 def test_fused_activations_on_small_products(act, M, f, K):
-    """Products this small take 64 x 64 or 128 x 64 tiles (SwiGLU: 32 features), the last ones larger ones: one row, one past a tile in
-    each dimension, reductions from one K tile to past the ring.  Tolerance: one bf16 rounding of the output and of z, as for the larger tiles."""
+    """The tiles that the rule picks on 256 compute units, one round of which is enough: 64 x 64 (SwiGLU forward: 128 x 64, of 32 features)
+    up to (300, 2000); then 128 x 64, 128 x 128 and two 128 x 128 workgroups to a compute unit (SwiGLU forward: the last of these twice, then
+    full ones; SwiGLU backward: half-height ones at the end).  One row, one past a tile in each dimension, reductions from one K tile to past the ring.  Tolerance: one
+    bf16 rounding of the output and of z, as for the larger tiles."""
     import torch
     fin = (1 + act) * f
     sh = so.Shape(1, 64, 1, 1, f, 1, 1, act="swiglu" if act else "gelu")
@@ -52,6 +55,29 @@ def test_fused_activations_on_small_products(act, M, f, K):
     da = dY.astype(np.float64) @ V.astype(np.float64).T
     assert L().stage_kernel_gemm_act_bwd(1, act, M, f, K, P(dYd), K, P(Vd), K, P(Zd), fin, None, 0, None) == 0
     assert so.max_rel_err(to_np(Zd), so.act_backward(sh, zr, da)) <= KTOL["bf16"]
+
+
+@pytest.mark.parametrize("act", [0, 1])
+@pytest.mark.parametrize("M,f,K", [(1, 8, 64), (65, 72, 448), (129, 136, 512), (200, 264, 576), (400, 1736, 192), (1100, 3400, 64)])
+def test_fused_tiles_agree_bitwise(act, M, f, K):
+    """64 x 64 (5), 128 x 64 (6) and 128 x 128 tiles (4) of the fused products, and half-height ones (3), against full ones (2) and the rule (0):
+    z, the activation and its backward, with rows and features past every tile's edge and reductions around the rings' depths;
+    the last shape has more than 64 full tiles, so its 128 x 128 ones go out two to a compute unit."""
+    import torch
+    fin = (1 + act) * f
+    X, W = rnd(synth.normal(44, 1, (M, K)), "bf16"), rnd(synth.normal(44, 2, (K, fin), std=1.5 * K ** -0.5), "bf16")
+    dY, V = rnd(synth.normal(44, 3, (M, K)), "bf16"), rnd(synth.normal(44, 4, (f, K), std=1.5 * K ** -0.5), "bf16")
+    Xd, Wd, dYd, Vd = (to_dev(t, "bf16") for t in (X, W, dY, V))
+    outs = []
+    for ks in (2, 3, 4, 5, 6, 0):
+        Zd, Aout = (torch.full((M, n), float("nan"), dtype=torch.bfloat16, device="cuda:0") for n in (fin, f))
+        assert L().stage_kernel_gemm_act(1, act, M, f, K, P(Xd), K, P(Wd), fin, P(Zd), fin, P(Aout), f, ks, None) == 0
+        z = Zd.clone()
+        assert L().stage_kernel_gemm_act_bwd(1, act, M, f, K, P(dYd), K, P(Vd), K, P(Zd), fin, None, ks, None) == 0
+        outs.append((z, Aout, Zd))
+    assert not any(bool(torch.isnan(o).any()) for o in outs[0])
+    for o in outs[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(outs[0], o))
 
 
 @pytest.mark.parametrize("kernel_set", [0, 2])
@@ -75,11 +101,15 @@ def test_fused_gelu_is_the_plain_gelu(kernel_set):
         assert torch.equal(x, y), "%d of 65536 differ" % int((x != y).sum())
 
 
+# full tiles of the lists: 1, 1, 7, 256 + 35, 48, 90, 256 + 54, 151
 @pytest.mark.parametrize("shapes", [[(8, 8, 1)], [(128, 136, 65)], [(264, 520, 200), (136, 8, 64)],
-                                    [(4096, 4096, 72), (2560, 264, 320), (520, 1032, 129)],                 # 256 full tiles and a tail
-                                    [(2048, 4104, 40), (1032, 520, 136)]])                                  # a tail of more than 64
+                                    [(4096, 4096, 72), (2560, 264, 320), (520, 1032, 129)],
+                                    [(1800, 1288, 520)], [(2056, 2312, 584)], [(4096, 4096, 64), (1288, 2056, 600)],
+                                    [(2048, 4104, 40), (1032, 520, 136)]])      # 151 tiles: more than half a round, full tiles
 def test_weight_gradients_of_a_short_last_round(shapes):
-    """Lists whose last round keeps at most half of the CUs busy go out (partly) as 128 x 128 tiles: the same bits as full tiles."""
+    """Lists whose last round keeps at most half of the CUs busy go out (partly) in smaller tiles: 64 x 64 (reductions of at most 512, or at most 32
+    tiles), 128 x 128 with a deep ring (at most 64 tiles) or two to a compute unit.  The same bits as full tiles, whether the
+    rule picks the tiles (0) or they are forced on the whole list (4, 5)."""
     import torch
     n = len(shapes)
     g = torch.Generator().manual_seed(42)
@@ -87,12 +117,41 @@ def test_weight_gradients_of_a_short_last_round(shapes):
     for M, N, K in shapes:
         A.append(torch.randn((K, M), generator=g).bfloat16().to("cuda:0")); B.append(torch.randn((K, N), generator=g).bfloat16().to("cuda:0"))
         Cs.append(torch.randn((M, N), generator=g).to("cuda:0"))
-    full = [c.clone() for c in Cs]
     Ms, Ns, Ks = zip(*shapes)
     ia, la, pa = (lambda v: (C.c_int * n)(*v)), (lambda v: (C.c_int64 * n)(*v)), (lambda t: (C.c_void_p * n)(*[u.data_ptr() for u in t]))
-    assert L().stage_kernel_wgrad_group(1, n, ia(Ms), ia(Ns), ia(Ks), pa(A), la(Ms), pa(B), la(Ns), pa(Cs), la(Ns), 0, None) == 0
-    for (M, N, K), a, b, c in zip(shapes, A, B, full):
+
+    def run(ks):
+        out = [c.clone() for c in Cs]
+        assert L().stage_kernel_wgrad_group(1, n, ia(Ms), ia(Ns), ia(Ks), pa(A), la(Ms), pa(B), la(Ns), pa(out), la(Ns), ks, None) == 0
+        return out
+    full = run(2)
+    for (M, N, K), a, b, c, got in zip(shapes, A, B, Cs, full):
         ref = c.double() + a.double().t() @ b.double()
-        assert L().stage_kernel_gemm(1, 2, M, N, K, P(a), M, P(b), N, P(c), N, None, 0, 1, 2, None) == 0
-        assert ((c.double() - ref).abs().max() / ref.abs().max()).item() <= 1e-5 * max(1.0, K ** 0.5)
-    assert all(torch.equal(x, y) for x, y in zip(Cs, full))
+        assert ((got.double() - ref).abs().max() / ref.abs().max()).item() <= 1e-5 * max(1.0, K ** 0.5)
+        one = c.clone()
+        assert L().stage_kernel_gemm(1, 2, M, N, K, P(a), M, P(b), N, P(one), N, None, 0, 1, 2, None) == 0
+        assert torch.equal(one, got)
+    for ks in (0, 4, 5):
+        assert all(torch.equal(x, y) for x, y in zip(run(ks), full)), ks
+
+
+@pytest.mark.parametrize("hidden,ffn", [(512, 1408), (768, 2048)])
+def test_merged_weight_gradients_in_small_tiles(hidden, ffn):
+    """W ops at the end of the list reduce over all microbatches in one pass: 3 x 300 tokens in 40 (128 x 128 tiles, deep ring) and 84
+    full tiles (two to a compute unit), the same bits as W right behind each B, whose reductions of 300 take 64 x 64 tiles."""
+    import torch
+    from paper_2507_00217_amd import stage as S
+    cfg = dict(n_layers=1, hidden=hidden, n_heads=hidden // 128, n_kv_heads=hidden // 128, head_dim=128, ffn=ffn, seq=300, mb_size=1, n_microbatches=3,
+               norm="layernorm", act="gelu", dtype="bf16", stash_cap=3, enforce_mb_order=1)
+    params, X, G = synth.make_weights(cfg, 71), synth.make_boundary(cfg, 72), synth.make_boundary(cfg, 73)
+    grads = []
+    for ops in ([(o, m) for m in range(3) for o in (0, 1, 2)], [(o, m) for m in range(3) for o in (0, 1)] + [(2, m) for m in range(3)]):
+        st = S.Stage(cfg)
+        st.load_weights(params)
+        Xd, Gd = to_dev(X, "bf16"), to_dev(G, "bf16")
+        st.run_schedule(ops, Xd, Gd, torch.zeros_like(Xd), torch.zeros_like(Xd))
+        torch.cuda.synchronize()
+        grads.append(st.grads())
+        st.close()
+    for a, b in zip(*grads):
+        assert all(np.array_equal(a[k], b[k]) for k in a)
