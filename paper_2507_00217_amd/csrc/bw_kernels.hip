@@ -373,7 +373,7 @@ static hipError_t norm_bwd_pick(const NormArgs& n, hipStream_t s, int* parts) {
   if constexpr (sizeof(T) == 2) {
     if (n.x_f32 && n.resid_f32 && n.resid) return norm_bwd_width<T, KIND, true, true>(n, s, parts);
     if (n.x_f32) return norm_bwd_width<T, KIND, true, false>(n, s, parts);
-    if (n.resid_f32 && n.resid) return norm_bwd_width<T, KIND, false, true>(n, s, parts);
+    if (n.resid_f32 && n.resid) return hipErrorInvalidValue;       // no caller: the residual stream is fp32 where x is
   }
   return norm_bwd_width<T, KIND, false, false>(n, s, parts);
 }

@@ -221,19 +221,20 @@ __device__ __forceinline__ void dswiglu4(f32x4 da, bf16x4 gt, bf16x4 up, bf16x4&
 // pass over K then does the work of nseg launches with a single read-modify-write of C, and -- fp32 accumulators
 // written to and read back from fp32 memory unchanged -- gives the same bits as those launches one after another.
 // WR, WC = rows and columns of 128 in the tile: (2, 2) -> 256 x 256 (wave grid 2 x WGN); (1, 2) -> 128 x 256 (wave grid
-// 1 x WGN, half the wavefronts; A must be a [row][k] operand); (1, 1) -> 128 x 128 (four wavefronts of 64 x 64); (1, 0) -> 128 x
-// 64 (four of 64 x 32, or 32 x 64 for SwiGLU, whose gate and up columns are a wavefront's two halves); (0, 0) -> 64 x 64 (four of 32 x 32).  The smaller tiles exist for the work a grid of full tiles would leave to a fraction of the
-// CUs: the last, partly filled round of a product, and products with few tiles.
+// 1 x WGN, half the wavefronts; EPI_DSWIGLU only); (1, 1) -> 128 x 128 (four wavefronts of 64 x 64); (1, 0) -> 128 x 64 (four of 64
+// x 32, or 32 x 64 for SwiGLU, whose gate and up columns are a wavefront's two halves); (0, 0) -> 64 x 64 (four of 32 x 32).
+// The smaller tiles exist for the work a grid of full tiles would leave to a fraction of the CUs: the last, partly filled
+// round of a product, and products with few tiles.
 template <bool AKC, bool BKC, int EPI, int TN, int WR = 2, int WC = 2, int SMALL_DEPTH = 4>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds_char* smem, int nseg = 1,
                                           const int64_t* seg_delta = nullptr) {
-  static_assert(WR == 2 || AKC || WC <= 1, "the half-height tile takes a [row][k] A operand");
+  static_assert(!(WR == 1 && WC == 2) || EPI == EPI_DSWIGLU, "the half-height tile is the SwiGLU backward's");
   static_assert(WC == 2 || (WR == 1 && WC == 1 && TN == 2) || (WR <= 1 && WC == 0 && TN == 1) || (WR == 1 && WC == 0 && TN == 2),
                 "four wavefronts of 64 x 64, 64 x 32, 32 x 64 or 32 x 32");
   constexpr bool GLU = EPI == EPI_SWIGLU;
   static_assert(!GLU || (TN == 2 && !BKC), "gate and up blocks are the two halves of a wavefront's columns");
   constexpr int BMV = WR ? WR * 128 : 64, BNV = WC ? WC * 128 : 64;                // tile: BMV rows, BNV columns
-  constexpr int RW = WR == 0 || (WC == 0 && TN == 2) ? 32 : WC <= 1 ? 64 : 128;                                           // rows of a wavefront's sub-tile
+  constexpr int RW = WR == 0 || (WC == 0 && TN == 2) ? 32 : WC <= 1 ? 64 : 128;   // rows of a wavefront's sub-tile
   constexpr int WGN = BNV / (TN * 32), WAVES = (BMV / RW) * WGN;
   constexpr int A_BYTES = BMV * BK * 2, B_BYTES = BNV * BK * 2;
   constexpr int PCS = BNV / 8;                                                     // 16-byte pieces per row of C / per reduction row of a [k][row] B tile
@@ -721,8 +722,9 @@ __device__ __forceinline__ int compact(int i, int n) {
 }
 
 // one workgroup per tile: workgroup `bid` takes the full tile number first + bid of the walk order (WR == 2), or the
-// upper (even bid) / lower (odd bid) 128 rows of full tile number first + bid / 2 (WR == 1)
-template <bool AKC, bool BKC, int EPI, int TN, int WR>
+// upper (even bid) / lower (odd bid) 128 rows of full tile number first + bid / 2 (WR == 1).  A is a [row][k] operand in all
+// products but weight gradients, which have kernels of their own below.
+template <bool BKC, int EPI, int TN, int WR>
 // The second launch bound (wavefronts per SIMD the register budget must allow) is 2 for the half-height tile: its four
 // wavefronts of 128 x 64 then get the 256 registers the full tile's eight have, all of them ordinary VGPRs.  Left at
 // one per SIMD (512 registers), the compiler kept the accumulators in AGPRs, gave the MFMAs a destination other than
@@ -739,13 +741,13 @@ __global__ __launch_bounds__(WR * 512 / TN, WR == 1 ? 2 : 1) void gemm_mfma_kern
   }
   int tile_m, tile_n;
   tile_of(first + (WR == 2 ? bid : compact<2>(bid >> 1, nb >> 1)), tiles_m, tiles_n, tile_m, tile_n);
-  gemm_tile<AKC, BKC, EPI, TN, WR>(g, tile_m * BM + (WR == 2 ? 0 : (bid & 1) * 128), tile_n * (EPI == EPI_SWIGLU ? GLU_BN : BN),
+  gemm_tile<true, BKC, EPI, TN, WR>(g, tile_m * BM + (WR == 2 ? 0 : (bid & 1) * 128), tile_n * (EPI == EPI_SWIGLU ? GLU_BN : BN),
                                    (lds_char*)smem_raw);
 }
 
 // one workgroup per 128 x 128 tile (four wavefronts of 64 x 64): workgroup `bid` takes quadrant bid % 4 of the full
 // tile number first + bid / 4 of the walk order; a quadrant that lies outside the matrix has nothing to do
-template <bool AKC, bool BKC, int EPI, int DEPTH>
+template <bool BKC, int EPI, int DEPTH>
 __global__ __launch_bounds__(256, 2) void gemm_quarter_kernel(   // (register budget: as for the half-height tile)
     GemmArgs g, int tiles_m, int tiles_n, int first) {
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
@@ -759,12 +761,12 @@ __global__ __launch_bounds__(256, 2) void gemm_quarter_kernel(   // (register bu
   constexpr int TB = EPI == EPI_SWIGLU ? GLU_BN : BN;
   const int m0 = tile_m * BM + (bid & 1) * 128, n0 = tile_n * TB + ((bid >> 1) & 1) * (TB / 2);
   if (m0 >= g.M || n0 >= (EPI == EPI_SWIGLU ? g.N / 2 : g.N)) return;                  // the same for the whole workgroup
-  gemm_tile<AKC, BKC, EPI, 2, 1, 1, DEPTH>(g, m0, n0, (lds_char*)smem_raw);
+  gemm_tile<true, BKC, EPI, 2, 1, 1, DEPTH>(g, m0, n0, (lds_char*)smem_raw);
 }
 
 // one workgroup per 64 x 64 (WR == 0) or 128 x 64 tile (WR == 1): workgroup `bid` takes the sixteenth bid % 16 (eighth bid % 8) of full
 // tile number first + bid / 16 (/ 8)
-template <bool AKC, bool BKC, int EPI, int WR>
+template <bool BKC, int EPI, int WR>
 __global__ __launch_bounds__(256, 2) void gemm_tiny_kernel(GemmArgs g, int tiles_m, int tiles_n, int first) {
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   int bid = blockIdx.x;
@@ -778,7 +780,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tiny_kernel(GemmArgs g, int tiles
   constexpr int TB = EPI == EPI_SWIGLU ? GLU_BN : BN;
   const int m0 = tile_m * BM + (bid & ((1 << RB) - 1)) * (BM >> RB), n0 = tile_n * TB + ((bid >> RB) & 3) * (TB / 4);
   if (m0 >= g.M || n0 >= (EPI == EPI_SWIGLU ? g.N / 2 : g.N)) return;
-  gemm_tile<AKC, BKC, EPI, EPI == EPI_SWIGLU ? 2 : 1, WR, 0, WR ? 4 : TINY_DEPTH>(g, m0, n0, (lds_char*)smem_raw);
+  gemm_tile<true, BKC, EPI, EPI == EPI_SWIGLU ? 2 : 1, WR, 0, WR ? 4 : TINY_DEPTH>(g, m0, n0, (lds_char*)smem_raw);
 }
 
 // Several weight-gradient products C_p += A_p^T . B_p in one launch of persistent workgroups.  Each workgroup
@@ -813,9 +815,9 @@ __global__ __launch_bounds__(1024 / TN) void gemm_wgrad_group_kernel(GemmGroup g
   }
 }
 
-// The same products in tiles of 128 x 128 (WR, WC = 1, 1), 128 x 64 (1, 0) or 64 x 64 (0, 0), one workgroup each: workgroup `bid` takes part
-// bid % (4, 8, 16) of the full tile number first + bid / (4, 8, 16).
-template <int WR, int WC, int DEPTH>
+// The same products in tiles of 128 x 128 (WT = 1) or 64 x 64 (WT = 0), one workgroup each: workgroup `bid` takes part bid % 4 (% 16) of
+// the full tile number first + bid / 4 (/ 16).
+template <int WT, int DEPTH>
 __global__ __launch_bounds__(256, 2) void gemm_wgrad_small_kernel(GemmGroup gg, int first) {
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   int bid = blockIdx.x;
@@ -823,16 +825,16 @@ __global__ __launch_bounds__(256, 2) void gemm_wgrad_small_kernel(GemmGroup gg, 
     const int per = (int)gridDim.x >> 3, main = per << 3;
     if (bid < main) bid = (bid & 7) * per + (bid >> 3);
   }
-  constexpr int RB = WR ? 1 : 2, CB = WC ? 1 : 2;      // log2 of the tile's rows and columns inside a full tile
-  const int t = first + compact<1>(bid >> (RB + CB), (int)gridDim.x >> (RB + CB));
+  constexpr int B = WT ? 1 : 2;                        // log2 of the tile rows (and columns) inside a full tile
+  const int t = first + compact<1>(bid >> (2 * B), (int)gridDim.x >> (2 * B));
   int pi = 0;
   while (pi + 1 < gg.n && t >= gg.first_tile[pi + 1]) ++pi;
   const GemmArgs& g = gg.p[pi];
   int tile_m, tile_n;
   tile_of(t - gg.first_tile[pi], (g.M + BM - 1) / BM, (g.N + BN - 1) / BN, tile_m, tile_n);
-  const int m0 = tile_m * BM + (bid & ((1 << RB) - 1)) * (BM >> RB), n0 = tile_n * BN + ((bid >> RB) & ((1 << CB) - 1)) * (BN >> CB);
+  const int m0 = tile_m * BM + (bid & ((1 << B) - 1)) * (BM >> B), n0 = tile_n * BN + ((bid >> B) & ((1 << B) - 1)) * (BN >> B);
   if (m0 >= g.M || n0 >= g.N) return;
-  gemm_tile<false, false, EPI_ACC32, WC ? 2 : 1, WR, WC, DEPTH>(g, m0, n0, (lds_char*)smem_raw, gg.nseg, gg.seg_delta);
+  gemm_tile<false, false, EPI_ACC32, WT ? 2 : 1, WT, WT, DEPTH>(g, m0, n0, (lds_char*)smem_raw, gg.nseg, gg.seg_delta);
 }
 
 // Eight wavefronts of 128x64 or four of 128x128 per tile: the wider ones read a third less from LDS and are ahead on
@@ -845,24 +847,24 @@ constexpr int WIDE_MIN_K = 8192;       // input gradients: four wavefronts from 
 
 // One-time set-up (a kernel's LDS limit, like the CU count) sits in function-local statics, whose initialisation the language
 // makes thread-safe: concurrent first calls from several threads run it once.
-template <bool AKC, bool BKC, int EPI, int WR, int TN = WAVE_COLS>
+template <bool BKC, int EPI, int WR, int TN = WAVE_COLS>
 hipError_t launch_tiles(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles_n, int first, int n_wg) {
   // the ring of operand tiles; every epilogue's staging (at most 128 KiB) fits inside it
   constexpr size_t LDS = LDS_BYTES;
-  auto kern = gemm_mfma_kernel<AKC, BKC, EPI, TN, WR>;
+  auto kern = gemm_mfma_kernel<BKC, EPI, TN, WR>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL(kern, dim3(n_wg), dim3(WR * 512 / TN), LDS, s, g, tiles_m, tiles_n, first);
   return hipGetLastError();
 }
 
-template <int WR, int WC, int DEPTH>
+template <int WT, int DEPTH>
 hipError_t launch_wgrad_small(const GemmGroup& gg, int first, int n, hipStream_t s) {
-  constexpr size_t LDS = (size_t)(2 * DEPTH + 1) * (WR ? TILE_BYTES / 2 : TILE_BYTES / 4);
-  auto kern = gemm_wgrad_small_kernel<WR, WC, DEPTH>;
+  constexpr size_t LDS = (size_t)(2 * DEPTH + 1) * (WT ? TILE_BYTES / 2 : TILE_BYTES / 4);
+  auto kern = gemm_wgrad_small_kernel<WT, DEPTH>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3((WC ? 4 : WR ? 8 : 16) * n), dim3(256), LDS, s, gg, first);
+  hipLaunchKernelGGL(kern, dim3((WT ? 4 : 16) * n), dim3(256), LDS, s, gg, first);
   return hipGetLastError();
 }
 
@@ -870,19 +872,19 @@ hipError_t launch_wgrad_small(const GemmGroup& gg, int first, int n, hipStream_t
 inline bool tiny_fits(const GemmArgs& g, int tail, int total, int n_cu, int rows) {      // (SwiGLU: 32 features, gate and up; N = 2f)
   return tail > 0 && (tail == total ? (int64_t)((g.M + rows - 1) / rows) * ((g.N + 63) / 64) : tail * (1024 / rows)) <= n_cu;
 }
-template <bool AKC, bool BKC, int EPI, int DEPTH>
+template <bool BKC, int EPI, int DEPTH>
 hipError_t launch_quarter(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles_n, int total, int n) {
   constexpr size_t LDS = (size_t)(2 * DEPTH + 1) * (TILE_BYTES / 2);
-  auto kern = gemm_quarter_kernel<AKC, BKC, EPI, DEPTH>;
+  auto kern = gemm_quarter_kernel<BKC, EPI, DEPTH>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL(kern, dim3(4 * n), dim3(256), LDS, s, g, tiles_m, tiles_n, total - n);
   return hipGetLastError();
 }
-template <bool AKC, bool BKC, int EPI, int WR>
+template <bool BKC, int EPI, int WR>
 hipError_t launch_tiny(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles_n, int total, int n) {
   constexpr size_t LDS = WR ? (size_t)9 * (TILE_BYTES / 2) : (size_t)(2 * TINY_DEPTH + 1) * (TILE_BYTES / 4);
-  auto kern = gemm_tiny_kernel<AKC, BKC, EPI, WR>;
+  auto kern = gemm_tiny_kernel<BKC, EPI, WR>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL(kern, dim3((WR ? 8 : 16) * n), dim3(256), LDS, s, g, tiles_m, tiles_n, total - n);
@@ -899,41 +901,40 @@ hipError_t launch_tiny(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles_
 // 1280: 18.3 / 20.1 (operands from HBM: 22 / 28), 4096 x 1536 x 4096: 51 / 51 (59 / 72), and with more than half a tile per CU
 // against full ones, 2048 x 6144 x 2048: 49 / 48 (60 / 53).  The half-height tile is left to the SwiGLU backward, whose z it
 // rewrites in whole rows through LDS (2048 x 2816 x 2048: 36 / 39).  All give the same bits.
-// `shape`: 0 = this rule, else one tile shape for all: 1 = full, 2 = half-height, 3 = 128 x 128, 4 = 64 x 64 (SwiGLU: 128 x 64),
-// 5 = 128 x 64.
-template <bool AKC, bool BKC, int EPI>
+// `shape`: 0 = this rule, else one tile shape for all: 1 = full, 2 = half-height (SwiGLU backward; elsewhere the rule), 3 = 128 x
+// 128, 4 = 64 x 64 (SwiGLU forward: 128 x 64), 5 = 128 x 64.
+template <bool BKC, int EPI>
 hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
+  constexpr bool HALF = EPI == EPI_DSWIGLU;            // where there are half-height tiles
+  if (shape == 2 && !HALF) shape = 0;
   const int tiles_m = (g.M + BM - 1) / BM;
   const int tiles_n = EPI == EPI_SWIGLU ? (g.N / 2 + GLU_BN - 1) / GLU_BN : (g.N + BN - 1) / BN, total = tiles_m * tiles_n;
-  int n_half = 0, n_quarter = 0, n_tiny = 0;          // full tiles at the end of the walk order that are split in 2 / 4 / 16
+  int n_half = 0, n_quarter = 0, n_tiny = 0;          // full tiles at the end of the walk order that are split in 2 / 4 / 8 or 16
   const int n_cu = cu_count(), tail = total % n_cu;
-  if constexpr (AKC) {
-    if (shape >= 4 || (shape == 0 && tiny_fits(g, tail, total, n_cu, 128))) n_tiny = shape ? total : tail;
-    else if (shape == 3 || (shape == 0 && (EPI == EPI_DSWIGLU ? 4 : 2) * tail <= n_cu)) n_quarter = shape ? total : tail;
-    else n_half = shape == 2 ? total : shape == 1 ? 0 : (2 * tail <= n_cu ? tail : 0);
-  }
-  const int n_small = n_half + n_quarter + n_tiny;
-  if (total > n_small) {
+  if (shape >= 4 || (shape == 0 && tiny_fits(g, tail, total, n_cu, 128))) n_tiny = shape ? total : tail;
+  else if (shape == 3 || (shape == 0 && (HALF ? 4 : 2) * tail <= n_cu)) n_quarter = shape ? total : tail;
+  else if (HALF) n_half = shape == 2 ? total : shape == 0 && 2 * tail <= n_cu ? tail : 0;
+  const int n_full = total - n_half - n_quarter - n_tiny;
+  if (n_full) {
     hipError_t e;
-    if constexpr (AKC && BKC && EPI == EPI_STORE)
-      e = g.K >= WIDE_MIN_K ? launch_tiles<AKC, BKC, EPI, 2, 4>(g, s, tiles_m, tiles_n, 0, total - n_small)
-                            : launch_tiles<AKC, BKC, EPI, 2>(g, s, tiles_m, tiles_n, 0, total - n_small);
+    if constexpr (BKC && EPI == EPI_STORE)
+      e = g.K >= WIDE_MIN_K ? launch_tiles<BKC, EPI, 2, 4>(g, s, tiles_m, tiles_n, 0, n_full) : launch_tiles<BKC, EPI, 2>(g, s, tiles_m, tiles_n, 0, n_full);
     else
-      e = launch_tiles<AKC, BKC, EPI, 2>(g, s, tiles_m, tiles_n, 0, total - n_small);
+      e = launch_tiles<BKC, EPI, 2>(g, s, tiles_m, tiles_n, 0, n_full);
     if (e != hipSuccess) return e;
   }
-  if constexpr (AKC) {
-    if (n_half) return launch_tiles<AKC, BKC, EPI, 1>(g, s, tiles_m, tiles_n, total - n_half, 2 * n_half);
+  if constexpr (HALF) {
+    if (n_half) return launch_tiles<BKC, EPI, 1>(g, s, tiles_m, tiles_n, n_full, 2 * n_half);
   }
-  if constexpr (AKC) {
-    if (n_tiny) {
-      if constexpr (EPI != EPI_SWIGLU)
-        if (shape == 4 || (shape == 0 && tiny_fits(g, tail, total, n_cu, 64))) return launch_tiny<AKC, BKC, EPI, 0>(g, s, tiles_m, tiles_n, total, n_tiny);
-      return launch_tiny<AKC, BKC, EPI, 1>(g, s, tiles_m, tiles_n, total, n_tiny);
-    }
+  if (n_tiny) {
+    if constexpr (EPI != EPI_SWIGLU)
+      if (shape == 4 || (shape == 0 && tiny_fits(g, tail, total, n_cu, 64))) return launch_tiny<BKC, EPI, 0>(g, s, tiles_m, tiles_n, total, n_tiny);
+    return launch_tiny<BKC, EPI, 1>(g, s, tiles_m, tiles_n, total, n_tiny);
   }
-  if constexpr (AKC) {
-    if (n_quarter) return 4 * n_quarter > n_cu ? launch_quarter<AKC, BKC, EPI, 2>(g, s, tiles_m, tiles_n, total, n_quarter) : launch_quarter<AKC, BKC, EPI, 4>(g, s, tiles_m, tiles_n, total, n_quarter);
+  if (n_quarter) {
+    if constexpr (!HALF)
+      if (4 * n_quarter > n_cu) return launch_quarter<BKC, EPI, 2>(g, s, tiles_m, tiles_n, total, n_quarter);
+    return launch_quarter<BKC, EPI, 4>(g, s, tiles_m, tiles_n, total, n_quarter);
   }
   return hipSuccess;
 }
@@ -973,13 +974,13 @@ bool gemm_mfma_supported(const GemmArgs& g) {
 hipError_t gemm_mfma(const GemmArgs& g, hipStream_t s, int tile_shape) {
   switch (g.mode) {
     case GEMM_NN:
-      if (g.act == 1) return launch<true, false, EPI_GELU>(g, s, tile_shape);
-      if (g.act == 2) return launch<true, false, EPI_SWIGLU>(g, s, tile_shape);
-      return (g.R || g.c_f32) ? launch<true, false, EPI_RESID>(g, s, tile_shape) : launch<true, false, EPI_STORE>(g, s, tile_shape);
+      if (g.act == 1) return launch<false, EPI_GELU>(g, s, tile_shape);
+      if (g.act == 2) return launch<false, EPI_SWIGLU>(g, s, tile_shape);
+      return (g.R || g.c_f32) ? launch<false, EPI_RESID>(g, s, tile_shape) : launch<false, EPI_STORE>(g, s, tile_shape);
     case GEMM_NT:
-      if (g.act_bwd == 1) return launch<true, true, EPI_DGELU>(g, s, tile_shape);
-      if (g.act_bwd == 2) return launch<true, true, EPI_DSWIGLU>(g, s, tile_shape);
-      return launch<true, true, EPI_STORE>(g, s, tile_shape);
+      if (g.act_bwd == 1) return launch<true, EPI_DGELU>(g, s, tile_shape);
+      if (g.act_bwd == 2) return launch<true, EPI_DSWIGLU>(g, s, tile_shape);
+      return launch<true, EPI_STORE>(g, s, tile_shape);
     case GEMM_TN: return gemm_mfma_wgrad_group(&g, 1, 1, nullptr, s, tile_shape);
   }
   return hipErrorInvalidValue;
@@ -1031,9 +1032,9 @@ hipError_t gemm_mfma_wgrad_group(const GemmArgs* list, int n, int nseg, const in
       int kmax = 0;
       for (int i = 0; i < gg.n; ++i) kmax = gg.p[i].K > kmax ? gg.p[i].K : kmax;
       const bool tiny = shape >= 3 ? shape > 3 : kmax * nseg <= 512 || 16 * n_small <= 2 * n_cu;
-      const hipError_t e = tiny                    ? launch_wgrad_small<0, 0, 2>(gg, n_full, n_small, s)
-                           : 4 * n_small <= n_cu ? launch_wgrad_small<1, 1, 4>(gg, n_full, n_small, s)
-                                                 : launch_wgrad_small<1, 1, 2>(gg, n_full, n_small, s);
+      const hipError_t e = tiny                    ? launch_wgrad_small<0, 2>(gg, n_full, n_small, s)
+                           : 4 * n_small <= n_cu ? launch_wgrad_small<1, 4>(gg, n_full, n_small, s)
+                                                 : launch_wgrad_small<1, 2>(gg, n_full, n_small, s);
       if (e != hipSuccess) return e;
     }
   }

@@ -56,8 +56,7 @@ GEMM_SHAPES = [(128, 256, 768), (200, 192, 136), (328, 1088, 512), (512, 512, 20
 @pytest.mark.parametrize("mode", [0, 1, 2])
 @pytest.mark.parametrize("M,N,K", GEMM_SHAPES)
 def test_gemm(dtype, mode, kernel_set, M, N, K):
-    """kernel_set 2 / 3 / 4: the tuned kernel with full 256 x 256 tiles only / half-height tiles only / 128 x 128 tiles only
-    (0 picks by shape; weight gradients have no half-height tiles)."""
+    """kernel_set 2 / 4: the tuned kernel with full 256 x 256 / 128 x 128 tiles only (0 picks by shape, and so does 3 here)."""
     import torch
     a_shape = (K, M) if mode == 2 else (M, K)
     b_shape = (N, K) if mode == 1 else (K, N)
@@ -85,7 +84,7 @@ def test_gemm(dtype, mode, kernel_set, M, N, K):
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("M,N,K", [(1160, 2304, 320), (520, 1088, 512), (1280, 5376, 192), (4352, 4104, 128)])
 def test_gemm_tile_shapes_agree_bitwise(mode, M, N, K):
-    """Full tiles, half-height tiles, 128 x 128 tiles and the mix chosen from the shape give the same bits: every output
+    """Full tiles, 128 x 128 tiles and the mix chosen from the shape (0, and 3 here) give the same bits: every output
     element is the same sequence of MFMAs over K whichever tile it falls in.  (The third shape has 105 full tiles and the first 45:
     with forced shapes both kernels see ragged edges in M and N; the last one has 17 x 17 = 289 full tiles on 256 CUs, so the
     rule gives its last 33 tiles to the 128 x 128 kernel.)"""
@@ -110,7 +109,7 @@ def test_gemm_tile_shapes_agree_bitwise(mode, M, N, K):
 def test_gemm_with_fused_activation(dtype, kernel_set, act, M, f, K):
     """The forward FFN-in product and its activation in one call: Z against the product's definition, Aout against the
     oracle's activation of the exact product (the tuned kernel forms it from fp32 accumulators; the plain kernels from
-    the stored Z).  Ragged tiles in every dimension; kernel_set 2 / 3 force full / half-height tiles."""
+    the stored Z).  Ragged tiles in every dimension; kernel_set 2 forces full tiles (3 is the normal choice here)."""
     import torch
     kind = {"gelu": 0, "swiglu": 1}[act]
     fin = 2 * f if act == "swiglu" else f

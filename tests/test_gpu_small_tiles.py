@@ -60,9 +60,9 @@ def test_fused_activations_on_small_products(act, M, f, K):
 @pytest.mark.parametrize("act", [0, 1])
 @pytest.mark.parametrize("M,f,K", [(1, 8, 64), (65, 72, 448), (129, 136, 512), (200, 264, 576), (400, 1736, 192), (1100, 3400, 64)])
 def test_fused_tiles_agree_bitwise(act, M, f, K):
-    """64 x 64 (5), 128 x 64 (6) and 128 x 128 tiles (4) of the fused products, and half-height ones (3), against full ones (2) and the rule (0):
+    """64 x 64 (5), 128 x 64 (6) and 128 x 128 tiles (4) of the fused products, and half-height ones (3, SwiGLU backward), against full ones (2) and the rule (0):
     z, the activation and its backward, with rows and features past every tile's edge and reductions around the rings' depths;
-    the last shape has more than 64 full tiles, so its 128 x 128 ones go out two to a compute unit."""
+    the last shape has more than 64 full tiles, so its 128 x 128 ones (except the SwiGLU backward's) go out two to a compute unit."""
     import torch
     fin = (1 + act) * f
     X, W = rnd(synth.normal(44, 1, (M, K)), "bf16"), rnd(synth.normal(44, 2, (K, fin), std=1.5 * K ** -0.5), "bf16")
