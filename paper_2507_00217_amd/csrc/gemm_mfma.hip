@@ -245,7 +245,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   // 128 x 128 tile's operand tiles are half the size and its K tile takes a quarter of the MFMA time, so the same LDS
   // holds -- and the same lead in time needs -- twice the depth: with a lead of two K tiles (about 1 us here) operands
   // that come from HBM rather than from a cache arrive late, and products of this tile ran a quarter to a third slower
-  // on cold operands than on warm ones.
+  // on cold operands than on warm ones.  (Two 128 x 128 workgroups that share a CU keep two K tiles ahead each.)
   constexpr bool SMALL = WC <= 1;
   constexpr int SLOT = WR == 0 ? TILE_BYTES / 4 : SMALL ? TILE_BYTES / 2 : TILE_BYTES, DEPTH = SMALL ? SMALL_DEPTH : 2, NSLOT = 2 * DEPTH + 1;
   static_assert(A_BYTES <= SLOT && B_BYTES <= SLOT && (size_t)NSLOT * SLOT <= LDS_BYTES, "ring fits");
@@ -448,7 +448,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   }
   const int sub_b = (col_l & 4) * 2;      // byte inside a 16-byte piece at which this lane's 4 columns start
   if constexpr ((EPI == EPI_DGELU || EPI == EPI_DSWIGLU) && SMALL) {
-    // Activation backward on a 128 x 128 tile: z is read and rewritten where the accumulators lie, 4 columns of a row at a
+    // Activation backward on the smaller tiles: z is read and rewritten where the accumulators lie, 4 columns of a row at a
     // time.  The rows go through L2 in 32-byte pieces, which a tile this size does not notice; all reads of a block row are
     // in flight at once.
     const int f = g.N;
@@ -698,7 +698,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   }
 }
 
-// Walk order of the 256x256 tiles of one product: groups of 8 tile rows, column by column inside a group.
+// Walk order of the tiles of one product: groups of 8 tile rows, column by column inside a group.
 __device__ __forceinline__ void tile_of(int idx, int tiles_m, int tiles_n, int& tile_m, int& tile_n) {
   constexpr int GROUP = 8;
   const int in_group = GROUP * tiles_n;
@@ -745,41 +745,48 @@ __global__ __launch_bounds__(WR * 512 / TN, WR == 1 ? 2 : 1) void gemm_mfma_kern
                                    (lds_char*)smem_raw);
 }
 
-// one workgroup per 128 x 128 tile (four wavefronts of 64 x 64): workgroup `bid` takes quadrant bid % 4 of the full
-// tile number first + bid / 4 of the walk order; a quadrant that lies outside the matrix has nothing to do
+// Origin of small tile `bid` of 1 << RB by 1 << CB ones per full tile (of 256 rows and TB columns, or SwiGLU features).  first < 0:
+// the whole product goes out in this shape, and tiles_m x tiles_n counts it in small tiles; otherwise workgroup `bid` takes
+// part bid % (1 << (RB + CB)) of full tile number first + bid / (1 << (RB + CB)) of the walk order, and a part that lies outside the
+// matrix has nothing to do (false).  A whole product is counted in its own tiles because empty workgroups are not free: they
+// recur with the period of the parts, and so does the placement of workgroups on the shader engines of an XCD -- 24 rows x
+// 5720 x 1280 in 64 x 64 tiles kept a quarter of the engines busy, 15.1 us instead of 8.
+template <int RB, int CB, int TB, bool COMPACT>
+__device__ __forceinline__ bool small_tile(int tiles_m, int tiles_n, int first, int rows, int cols, int& m0, int& n0) {
+  int bid = blockIdx.x;
+  {
+    const int per = (int)gridDim.x >> 3, main = per << 3;
+    if (bid < main) bid = (bid & 7) * per + (bid >> 3);
+  }
+  int tile_m, tile_n;
+  if (first < 0) {
+    tile_of(bid, tiles_m, tiles_n, tile_m, tile_n);
+    m0 = tile_m * (BM >> RB); n0 = tile_n * (TB >> CB);
+    return true;
+  }
+  const int full = bid >> (RB + CB), n = (int)gridDim.x >> (RB + CB);
+  tile_of(first + (COMPACT ? compact<1>(full, n) : full), tiles_m, tiles_n, tile_m, tile_n);
+  m0 = tile_m * BM + (bid & ((1 << RB) - 1)) * (BM >> RB);
+  n0 = tile_n * TB + ((bid >> RB) & ((1 << CB) - 1)) * (TB >> CB);
+  return m0 < rows && n0 < cols;
+}
+
+// one workgroup per 128 x 128 tile (four wavefronts of 64 x 64)
 template <bool BKC, int EPI, int DEPTH>
 __global__ __launch_bounds__(256, 2) void gemm_quarter_kernel(   // (register budget: as for the half-height tile)
     GemmArgs g, int tiles_m, int tiles_n, int first) {
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
-  int bid = blockIdx.x;
-  {
-    const int per = (int)gridDim.x >> 3, main = per << 3;
-    if (bid < main) bid = (bid & 7) * per + (bid >> 3);
-  }
-  int tile_m, tile_n;
-  tile_of(first + compact<1>(bid >> 2, (int)gridDim.x >> 2), tiles_m, tiles_n, tile_m, tile_n);
-  constexpr int TB = EPI == EPI_SWIGLU ? GLU_BN : BN;
-  const int m0 = tile_m * BM + (bid & 1) * 128, n0 = tile_n * TB + ((bid >> 1) & 1) * (TB / 2);
-  if (m0 >= g.M || n0 >= (EPI == EPI_SWIGLU ? g.N / 2 : g.N)) return;                  // the same for the whole workgroup
+  int m0, n0;
+  if (!small_tile<1, 1, EPI == EPI_SWIGLU ? GLU_BN : BN, true>(tiles_m, tiles_n, first, g.M, EPI == EPI_SWIGLU ? g.N / 2 : g.N, m0, n0)) return;
   gemm_tile<true, BKC, EPI, 2, 1, 1, DEPTH>(g, m0, n0, (lds_char*)smem_raw);
 }
 
-// one workgroup per 64 x 64 (WR == 0) or 128 x 64 tile (WR == 1): workgroup `bid` takes the sixteenth bid % 16 (eighth bid % 8) of full
-// tile number first + bid / 16 (/ 8)
+// one workgroup per 64 x 64 (WR == 0) or 128 x 64 tile (WR == 1)
 template <bool BKC, int EPI, int WR>
 __global__ __launch_bounds__(256, 2) void gemm_tiny_kernel(GemmArgs g, int tiles_m, int tiles_n, int first) {
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
-  int bid = blockIdx.x;
-  {
-    const int per = (int)gridDim.x >> 3, main = per << 3;
-    if (bid < main) bid = (bid & 7) * per + (bid >> 3);
-  }
-  int tile_m, tile_n;
-  constexpr int RB = WR ? 1 : 2;                       // log2 of the tile rows inside a full tile
-  tile_of(first + (bid >> (RB + 2)), tiles_m, tiles_n, tile_m, tile_n);
-  constexpr int TB = EPI == EPI_SWIGLU ? GLU_BN : BN;
-  const int m0 = tile_m * BM + (bid & ((1 << RB) - 1)) * (BM >> RB), n0 = tile_n * TB + ((bid >> RB) & 3) * (TB / 4);
-  if (m0 >= g.M || n0 >= (EPI == EPI_SWIGLU ? g.N / 2 : g.N)) return;
+  int m0, n0;
+  if (!small_tile<WR ? 1 : 2, 2, EPI == EPI_SWIGLU ? GLU_BN : BN, false>(tiles_m, tiles_n, first, g.M, EPI == EPI_SWIGLU ? g.N / 2 : g.N, m0, n0)) return;
   gemm_tile<true, BKC, EPI, EPI == EPI_SWIGLU ? 2 : 1, WR, 0, WR ? 4 : TINY_DEPTH>(g, m0, n0, (lds_char*)smem_raw);
 }
 
@@ -868,26 +875,32 @@ hipError_t launch_wgrad_small(const GemmGroup& gg, int first, int n, hipStream_t
   return hipGetLastError();
 }
 
-// Whether what is left over fits one round of `rows` x 64 tiles (counting only those inside the matrix when it is all of it)
-inline bool tiny_fits(const GemmArgs& g, int tail, int total, int n_cu, int rows) {      // (SwiGLU: 32 features, gate and up; N = 2f)
-  return tail > 0 && (tail == total ? (int64_t)((g.M + rows - 1) / rows) * ((g.N + 63) / 64) : tail * (1024 / rows)) <= n_cu;
+// The last n of a product's `total` full tiles in tiles of 256 / (1 << RB) rows and 1 / (1 << CB) of a full tile's columns; if they are all
+// of it, counted in small tiles (see small_tile).
+struct SmallGrid { int tiles_m, tiles_n, first, n; };
+template <int EPI>
+SmallGrid small_grid(const GemmArgs& g, int RB, int CB, int total, int n) {
+  constexpr int TB = EPI == EPI_SWIGLU ? GLU_BN : BN;
+  const int cols = EPI == EPI_SWIGLU ? g.N / 2 : g.N, h = n == total ? BM >> RB : BM, w = n == total ? TB >> CB : TB;
+  const int tiles_m = (g.M + h - 1) / h, tiles_n = (cols + w - 1) / w;
+  return n == total ? SmallGrid{tiles_m, tiles_n, -1, tiles_m * tiles_n} : SmallGrid{tiles_m, tiles_n, total - n, n << (RB + CB)};
 }
 template <bool BKC, int EPI, int DEPTH>
-hipError_t launch_quarter(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles_n, int total, int n) {
+hipError_t launch_quarter(const GemmArgs& g, hipStream_t s, const SmallGrid& t) {
   constexpr size_t LDS = (size_t)(2 * DEPTH + 1) * (TILE_BYTES / 2);
   auto kern = gemm_quarter_kernel<BKC, EPI, DEPTH>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(4 * n), dim3(256), LDS, s, g, tiles_m, tiles_n, total - n);
+  hipLaunchKernelGGL(kern, dim3(t.n), dim3(256), LDS, s, g, t.tiles_m, t.tiles_n, t.first);
   return hipGetLastError();
 }
 template <bool BKC, int EPI, int WR>
-hipError_t launch_tiny(const GemmArgs& g, hipStream_t s, int tiles_m, int tiles_n, int total, int n) {
+hipError_t launch_tiny(const GemmArgs& g, hipStream_t s, const SmallGrid& t) {
   constexpr size_t LDS = WR ? (size_t)9 * (TILE_BYTES / 2) : (size_t)(2 * TINY_DEPTH + 1) * (TILE_BYTES / 4);
   auto kern = gemm_tiny_kernel<BKC, EPI, WR>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3((WR ? 8 : 16) * n), dim3(256), LDS, s, g, tiles_m, tiles_n, total - n);
+  hipLaunchKernelGGL(kern, dim3(t.n), dim3(256), LDS, s, g, t.tiles_m, t.tiles_n, t.first);
   return hipGetLastError();
 }
 
@@ -911,7 +924,8 @@ hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   const int tiles_n = EPI == EPI_SWIGLU ? (g.N / 2 + GLU_BN - 1) / GLU_BN : (g.N + BN - 1) / BN, total = tiles_m * tiles_n;
   int n_half = 0, n_quarter = 0, n_tiny = 0;          // full tiles at the end of the walk order that are split in 2 / 4 / 8 or 16
   const int n_cu = cu_count(), tail = total % n_cu;
-  if (shape >= 4 || (shape == 0 && tiny_fits(g, tail, total, n_cu, 128))) n_tiny = shape ? total : tail;
+  const SmallGrid t64 = small_grid<EPI>(g, 2, 2, total, shape ? total : tail), t128 = small_grid<EPI>(g, 1, 2, total, shape ? total : tail);
+  if (shape >= 4 || (shape == 0 && tail > 0 && t128.n <= n_cu)) n_tiny = shape ? total : tail;
   else if (shape == 3 || (shape == 0 && (HALF ? 4 : 2) * tail <= n_cu)) n_quarter = shape ? total : tail;
   else if (HALF) n_half = shape == 2 ? total : shape == 0 && 2 * tail <= n_cu ? tail : 0;
   const int n_full = total - n_half - n_quarter - n_tiny;
@@ -928,13 +942,14 @@ hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   }
   if (n_tiny) {
     if constexpr (EPI != EPI_SWIGLU)
-      if (shape == 4 || (shape == 0 && tiny_fits(g, tail, total, n_cu, 64))) return launch_tiny<BKC, EPI, 0>(g, s, tiles_m, tiles_n, total, n_tiny);
-    return launch_tiny<BKC, EPI, 1>(g, s, tiles_m, tiles_n, total, n_tiny);
+      if (shape == 4 || (shape == 0 && t64.n <= n_cu)) return launch_tiny<BKC, EPI, 0>(g, s, t64);
+    return launch_tiny<BKC, EPI, 1>(g, s, t128);
   }
   if (n_quarter) {
+    const SmallGrid t = small_grid<EPI>(g, 1, 1, total, n_quarter);
     if constexpr (!HALF)
-      if (4 * n_quarter > n_cu) return launch_quarter<BKC, EPI, 2>(g, s, tiles_m, tiles_n, total, n_quarter);
-    return launch_quarter<BKC, EPI, 4>(g, s, tiles_m, tiles_n, total, n_quarter);
+      if (t.n > n_cu) return launch_quarter<BKC, EPI, 2>(g, s, t);
+    return launch_quarter<BKC, EPI, 4>(g, s, t);
   }
   return hipSuccess;
 }

@@ -13,10 +13,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("mode", [0, 1])
-@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (64, 64, 128), (65, 72, 448), (129, 136, 512), (200, 264, 576), (400, 1736, 1088)])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (64, 64, 128), (65, 72, 448), (129, 136, 512), (200, 264, 576), (400, 1736, 1088),
+                                   (24, 5720, 64), (6000, 136, 64), (4352, 4096, 64), (4600, 4096, 64)])
 def test_small_tiles_agree_bitwise(mode, M, N, K):
     """64 x 64 (5), 128 x 64 (6) and 128 x 128 tiles (4) against full ones (2) and the rule (0): one row, one past a tile, reductions
-    from one K tile over the ring's depth of eight to two rounds of it."""
+    from one K tile over the ring's depth of eight to two rounds of it; products a fraction of a full tile high or wide, and last
+    rounds of 16 and 32 full tiles behind a complete one, which the rule gives to 64 x 64 and 128 x 64 tiles."""
     import torch
     A, Bm = rnd(synth.normal(43, 1, (M, K)), "bf16"), rnd(synth.normal(43, 2, (N, K) if mode else (K, N)), "bf16")
     R = rnd(synth.normal(43, 3, (M, N)), "bf16")
@@ -58,11 +60,12 @@ def test_fused_activations_on_small_products(act, M, f, K):
 
 
 @pytest.mark.parametrize("act", [0, 1])
-@pytest.mark.parametrize("M,f,K", [(1, 8, 64), (65, 72, 448), (129, 136, 512), (200, 264, 576), (400, 1736, 192), (1100, 3400, 64)])
+@pytest.mark.parametrize("M,f,K", [(1, 8, 64), (65, 72, 448), (129, 136, 512), (200, 264, 576), (400, 1736, 192), (1100, 3400, 64), (24, 5720, 64), (4352, 4096, 64)])
 def test_fused_tiles_agree_bitwise(act, M, f, K):
     """64 x 64 (5), 128 x 64 (6) and 128 x 128 tiles (4) of the fused products, and half-height ones (3, SwiGLU backward), against full ones (2) and the rule (0):
     z, the activation and its backward, with rows and features past every tile's edge and reductions around the rings' depths;
-    the last shape has more than 64 full tiles, so its 128 x 128 ones (except the SwiGLU backward's) go out two to a compute unit."""
+    1100 x 3400 has more than 256 tiles of 128 x 128, which (except the SwiGLU backward's) then go out two to a compute unit; the last shape
+    has a last round of 16 (SwiGLU forward: 32) full tiles."""
     import torch
     fin = (1 + act) * f
     X, W = rnd(synth.normal(44, 1, (M, K)), "bf16"), rnd(synth.normal(44, 2, (K, fin), std=1.5 * K ** -0.5), "bf16")
