@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 TOL = 2e-5
 
 # one tile and less, one past a tile edge in M, reductions below / at / past a 16-deep slice, W slices and their double buffer
-SHAPES = [(1, 4, 4), (16, 16, 16), (17, 20, 20), (33, 36, 132), (65, 68, 260), (63, 64, 1028), (130, 196, 524)]
+SHAPES = [(1, 4, 4), (16, 16, 16), (17, 20, 20), (33, 36, 132), (65, 68, 260), (63, 64, 1028), (130, 196, 524),
+          (2052, 2048, 63), (2052, 2048, 64)]      # weight gradients on either side of the rule for short reductions of large outputs (K + 1 below)
 
 
 @pytest.mark.parametrize("shape", [0, 2, 3, 4])
@@ -27,6 +28,8 @@ def test_products(mode, shape, M, N, K):
     if mode == 2:
         M = (M + 3) // 4 * 4
         K = K + 1                                   # a slow reduction index has no alignment
+    else:
+        K = (K + 3) // 4 * 4
     A = synth.normal(31, 1, (K, M) if mode == 2 else (M, K)); B = synth.normal(31, 2, (N, K) if mode == 1 else (K, N))
     C0 = synth.normal(31, 3, (M, N))
     ref = (A.astype(np.float64).T if mode == 2 else A.astype(np.float64)) @ (B.astype(np.float64).T if mode == 1 else B.astype(np.float64))
