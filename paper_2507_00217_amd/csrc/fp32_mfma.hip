@@ -339,9 +339,10 @@ bool gemm32_supported(const GemmArgs& g) {
   if ((g.mode == GEMM_TN) != (g.acc_f32 != 0) || (g.acc_f32 && (g.R || g.bias))) return false;
   // an operand with a slow reduction index relies on its rows past K lying past the end of its buffer: no row may overlap the next
   if (g.lda < (g.mode == GEMM_TN ? g.M : 0) || g.ldb < (g.mode == GEMM_NT ? 0 : g.N)) return false;
-  // Weight gradients of short reductions over large outputs move C and little else, which the plain kernel's many small workgroups
-  // do better (us, plain / these: 2048 x 2048 x 52 17.9 / 19.2, x 64 18.3 / 19.1, x 80 20.5 / 19.3; 4096 x 4096 x 43 47 / 63; 1024 x 1024 x 32 8.7 / 7.0).
-  if (g.mode == GEMM_TN && g.K <= 64 && (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64) >= 4 * cu_count()) return false;
+  // Short reductions over large outputs move C and little else, which the plain kernel's many small workgroups do better than workgroups
+  // with 64 KiB of LDS (us, plain / these: weight gradients 2048 x 2048 x 52 17.9 / 19.2, x 64 18.3 / 19.1, x 80 20.5 / 19.3; 4096 x 4096 x 43
+  // 47 / 63; 1024 x 1024 x 32 8.7 / 7.0; forward 4096 x 4096 x 48 41 / 56, input gradients 42 / 52).
+  if (g.K <= 64 && !g.act && !g.act_bwd && (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64) >= 4 * cu_count()) return false;
   const int64_t lim = (int64_t)1 << 29;        // byte offsets stay below 2 GiB, slices fetched past the end (less than 2048 rows) included
   const int64_t a_rows = g.mode == GEMM_TN ? g.K + 2048 : g.M, b_rows = g.mode == GEMM_NT ? g.N : (int64_t)g.K + 2048;
   if (a_rows * g.lda >= lim || b_rows * g.ldb >= lim || (g.mode != GEMM_TN && (int64_t)g.K + 2048 >= lim)) return false;
