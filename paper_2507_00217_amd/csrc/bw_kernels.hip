@@ -343,12 +343,12 @@ static hipError_t norm_fwd_t(const NormArgs& n, hipStream_t s) {
 // wavefronts hold, one such workgroup per CU -- half the partial rows of two workgroups of half the size (us, two against
 // one; 2048 x 2048 with an fp32 residual stream: 18.6 / 17.8; 4096 x 2048 in bf16: 20.2 / 19.1; 448 x 4096 in fp32: 14.1 / 12.7).
 // Other rows go one to a workgroup, two workgroups per CU (4096 x 4096 in bf16: 35.2, two rows in one workgroup per CU 38.8).
-// Prefetch (PF): in fp32, with one piece, and with two where nothing is stored in fp32 (4096 x 3072: 30.5 / 34.4); beyond that its
-// registers cost more rows in flight than it hides (4096 x 5120 with an fp32 residual stream: 74.8 / 72.4; 2048 x 6144: 52.2 /
-// 50.4; 4096 x 8192 would spill).
+// Prefetch (PF): in fp32 and with one or two pieces (4096 x 3072 in bf16 30.5, without 34.4; 4096 x 4096 with an fp32 residual stream
+// between its neighbours in a layer 34.2 / 38.3); beyond that its registers cost more rows in flight than it hides (4096 x 5120 with
+// an fp32 residual stream: 74.8 / 72.4; 2048 x 6144: 52.2 / 50.4; 4096 x 8192 would spill).
 template <typename T, int KIND, bool XW, bool RW, int CH>
 static hipError_t norm_bwd_launch(const NormArgs& n, hipStream_t s, int* parts) {
-  constexpr bool SIDE = CH == 1 || sizeof(T) == 4, PF = SIDE || (CH == 2 && !XW && !RW);
+  constexpr bool SIDE = CH == 1 || sizeof(T) == 4, PF = SIDE || CH == 2;
   const int units = (n.d / Vec<T>::N + 63) / 64, tpr = 64 * (units < 4 ? units : 4);
   int ngrp = SIDE ? NB_THREADS / tpr : 1;
   const int n_cu = cu_count();
