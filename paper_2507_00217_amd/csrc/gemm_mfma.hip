@@ -698,9 +698,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   }
 }
 
-// Walk order of the tiles of one product: groups of 8 tile rows, column by column inside a group.
-__device__ __forceinline__ void tile_of(int idx, int tiles_m, int tiles_n, int& tile_m, int& tile_n) {
-  constexpr int GROUP = 8;
+// Walk order of the tiles of one product: groups of GROUP tile rows, column by column inside a group.
+template <int GROUP = 8> __device__ __forceinline__ void tile_of(int idx, int tiles_m, int tiles_n, int& tile_m, int& tile_n) {
   const int in_group = GROUP * tiles_n;
   const int gid = idx / in_group;
   const int first_m = gid * GROUP;
@@ -750,7 +749,9 @@ __global__ __launch_bounds__(WR * 512 / TN, WR == 1 ? 2 : 1) void gemm_mfma_kern
 // part bid % (1 << (RB + CB)) of full tile number first + bid / (1 << (RB + CB)) of the walk order, and a part that lies outside the
 // matrix has nothing to do (false).  A whole product is counted in its own tiles because empty workgroups are not free: they
 // recur with the period of the parts, and so does the placement of workgroups on the shader engines of an XCD -- 24 rows x
-// 5720 x 1280 in 64 x 64 tiles kept a quarter of the engines busy, 15.1 us instead of 8.
+// 5720 x 1280 in 64 x 64 tiles kept a quarter of the engines busy, 15.1 us instead of 8.  (More than one round of 128 x 128 tiles
+// without empty parts keeps the other order: 4096 x 1536 x 4096 between its neighbours in a layer 60 us, 74 in the order of its own
+// tiles; one round is better off in that, 2048 x 2048 outputs 50 to 53 us, 53 to 55 in the other.)
 template <int RB, int CB, int TB, bool COMPACT>
 __device__ __forceinline__ bool small_tile(int tiles_m, int tiles_n, int first, int rows, int cols, int& m0, int& n0) {
   int bid = blockIdx.x;
@@ -760,7 +761,7 @@ __device__ __forceinline__ bool small_tile(int tiles_m, int tiles_n, int first, 
   }
   int tile_m, tile_n;
   if (first < 0) {
-    tile_of(bid, tiles_m, tiles_n, tile_m, tile_n);
+    tile_of<RB < CB ? 4 : 8>(bid, tiles_m, tiles_n, tile_m, tile_n);           // patches of 512 (128 x 128 tiles: 1024) rows
     m0 = tile_m * (BM >> RB); n0 = tile_n * (TB >> CB);
     return true;
   }
@@ -876,14 +877,16 @@ hipError_t launch_wgrad_small(const GemmGroup& gg, int first, int n, hipStream_t
 }
 
 // The last n of a product's `total` full tiles in tiles of 256 / (1 << RB) rows and 1 / (1 << CB) of a full tile's columns; if they are all
-// of it, counted in small tiles (see small_tile).
+// of it, counted in small tiles (see small_tile), 128 x 128 ones only if that makes one round or leaves empty parts out.
 struct SmallGrid { int tiles_m, tiles_n, first, n; };
 template <int EPI>
 SmallGrid small_grid(const GemmArgs& g, int RB, int CB, int total, int n) {
   constexpr int TB = EPI == EPI_SWIGLU ? GLU_BN : BN;
-  const int cols = EPI == EPI_SWIGLU ? g.N / 2 : g.N, h = n == total ? BM >> RB : BM, w = n == total ? TB >> CB : TB;
-  const int tiles_m = (g.M + h - 1) / h, tiles_n = (cols + w - 1) / w;
-  return n == total ? SmallGrid{tiles_m, tiles_n, -1, tiles_m * tiles_n} : SmallGrid{tiles_m, tiles_n, total - n, n << (RB + CB)};
+  const int cols = EPI == EPI_SWIGLU ? g.N / 2 : g.N;
+  auto tiles = [](int x, int w) { return (x + w - 1) / w; };
+  const int tm = tiles(g.M, BM >> RB), tn = tiles(cols, TB >> CB), parts = n << (RB + CB);
+  if (n == total && (CB == 2 || tm * tn <= cu_count() || tm * tn < parts)) return SmallGrid{tm, tn, -1, tm * tn};
+  return SmallGrid{tiles(g.M, BM), tiles(cols, TB), total - n, parts};
 }
 template <bool BKC, int EPI, int DEPTH>
 hipError_t launch_quarter(const GemmArgs& g, hipStream_t s, const SmallGrid& t) {
