@@ -225,28 +225,36 @@ __device__ __forceinline__ void dswiglu4(f32x4 da, bf16x4 gt, bf16x4 up, bf16x4&
 // x 32, or 32 x 64 for SwiGLU, whose gate and up columns are a wavefront's two halves); (0, 0) -> 64 x 64 (four of 32 x 32).
 // The smaller tiles exist for the work a grid of full tiles would leave to a fraction of the CUs: the last, partly filled
 // round of a product, and products with few tiles.
-template <bool AKC, bool BKC, int EPI, int TN, int WR = 2, int WC = 2, int SMALL_DEPTH = 4>
+// LW > 0: LW further wavefronts do the loading and the four that multiply none of it (the smaller tiles, but not where two
+// workgroups share a CU).  A K tile of a small tile is 128 to 512 cycles of MFMA and 256 to 512 of the CU's load path (64 bytes a clock); a
+// wavefront that does both stands still whenever its load does not fit the queue, and the queue runs empty while it waits
+// at the barrier.  Apart they overlap: a 64 x 64 tile by itself 0.168 -> 0.117 us per K tile, 128 x 128 0.35 -> 0.29; 400 x 640 x 1728
+// (64 x 64 tiles) 8.1 -> 6.6 us, 400 x 1920 x 640 5.6 -> 5.0, 2048 x 2048 x 6144 (128 x 128) 47 -> 43.  What is left on operands that come from the
+// last-level cache is that cache's latency: a CU then gets 85 to 93 bytes/ns whatever the depth of the ring, from HBM 50 to 60.
+// (Two 128 x 128 workgroups to a CU with two loading wavefronts each: 1000 x 5120 x 1280 18.9 -> 24.4.)
+template <bool AKC, bool BKC, int EPI, int TN, int WR = 2, int WC = 2, int SMALL_DEPTH = 4, int LW = 0>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds_char* smem, int nseg = 1,
                                           const int64_t* seg_delta = nullptr) {
   static_assert(!(WR == 1 && WC == 2) || EPI == EPI_DSWIGLU, "the half-height tile is the SwiGLU backward's");
-  static_assert(WC == 2 || (WR == 1 && WC == 1 && TN == 2) || (WR <= 1 && WC == 0 && TN == 1) || (WR == 1 && WC == 0 && TN == 2),
-                "four wavefronts of 64 x 64, 64 x 32, 32 x 64 or 32 x 32");
   constexpr bool GLU = EPI == EPI_SWIGLU;
+  static_assert(WC == 2 || (WC == 1 && TN == 2) || (WC == 0 && TN <= 2), "four wavefronts of 64 x 64, 64 x 32, 32 x 64 or 32 x 32");
   static_assert(!GLU || (TN == 2 && !BKC), "gate and up blocks are the two halves of a wavefront's columns");
   constexpr int BMV = WR ? WR * 128 : 64, BNV = WC ? WC * 128 : 64;                // tile: BMV rows, BNV columns
-  constexpr int RW = WR == 0 || (WC == 0 && TN == 2) ? 32 : WC <= 1 ? 64 : 128;   // rows of a wavefront's sub-tile
-  constexpr int WGN = BNV / (TN * 32), WAVES = (BMV / RW) * WGN;
+  constexpr int WGN = BNV / (TN * 32);                                             // wavefronts side by side
+  constexpr int RW = WC == 2 ? 128 : BMV * WGN / 4;                                // rows of a wavefront's sub-tile
+  constexpr int WAVES = (BMV / RW) * WGN;                                          // wavefronts that multiply ...
+  constexpr bool SMALL = WC <= 1, SPLIT = LW > 0;
+  constexpr int LOADERS = SPLIT ? LW : WAVES;                                      // ... and those that load: the same, or others
   constexpr int A_BYTES = BMV * BK * 2, B_BYTES = BNV * BK * 2;
   constexpr int PCS = BNV / 8;                                                     // 16-byte pieces per row of C / per reduction row of a [k][row] B tile
   constexpr int PCA = BMV / 8;                                                     // ... of a [k][row] A tile
-  constexpr int CHA = (A_BYTES / 16) / (WAVES * 64), CHB = (B_BYTES / 16) / (WAVES * 64); // loads per thread and K tile
+  constexpr int CHA = (A_BYTES / 16) / (LOADERS * 64), CHB = (B_BYTES / 16) / (LOADERS * 64); // loads per thread and K tile
   constexpr int NI = RW / 16, NJ = 2 * TN;                                         // 16 x 16 accumulator blocks per wavefront
   // The ring of operand tiles (see below): DEPTH K tiles ahead of the one being multiplied, 2 * DEPTH + 1 slots.  The
   // 128 x 128 tile's operand tiles are half the size and its K tile takes a quarter of the MFMA time, so the same LDS
   // holds -- and the same lead in time needs -- twice the depth: with a lead of two K tiles (about 1 us here) operands
   // that come from HBM rather than from a cache arrive late, and products of this tile ran a quarter to a third slower
   // on cold operands than on warm ones.  (Two 128 x 128 workgroups that share a CU keep two K tiles ahead each.)
-  constexpr bool SMALL = WC <= 1;
   constexpr int SLOT = WR == 0 ? TILE_BYTES / 4 : SMALL ? TILE_BYTES / 2 : TILE_BYTES, DEPTH = SMALL ? SMALL_DEPTH : 2, NSLOT = 2 * DEPTH + 1;
   static_assert(A_BYTES <= SLOT && B_BYTES <= SLOT && (size_t)NSLOT * SLOT <= LDS_BYTES, "ring fits");
   const int tid = threadIdx.x, lane = tid & 63;
@@ -258,8 +266,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   const unsigned bytesB = (unsigned)(((int64_t)((BKC ? g.N : g.K) - 1) * g.ldb + (BKC ? g.K : g.N)) * 2);
   rsrc_words rsA = raw_rsrc(g.A, bytesA), rsB = raw_rsrc(g.B, bytesB);
   unsigned offa[CHA], offb[CHB];
-  tile_offsets<AKC, WAVES, CHA, AKC ? 32 : PCA>(offa, g.lda, m0, g.M, wave, lane);
-  tile_offsets<BKC, WAVES, CHB, PCS>(offb, g.ldb, n0, g.N, wave, lane, GLU ? g.N / 2 : 0);
+  const int lw = SPLIT ? wave - WAVES : wave;                                      // number among those that load
+  tile_offsets<AKC, LOADERS, CHA, AKC ? 32 : PCA>(offa, g.lda, m0, g.M, lw, lane);
+  tile_offsets<BKC, LOADERS, CHB, PCS>(offb, g.ldb, n0, g.N, lw, lane, GLU ? g.N / 2 : 0);
 
   // LDS map: a ring of NSLOT slots of one operand tile each; the operand tiles of the reduction take the slots in the
   // order A0 B0 A1 B1 A2 ..., tile number i (A_t = 2t, B_t = 2t + 1) sitting in slot i % NSLOT.
@@ -285,15 +294,59 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
       if (segB + 1 >= nseg) endB = NEVER;
     }
   };
+  std::integral_constant<int, 0> c0; std::integral_constant<int, 1> c1;
+  auto wait_vm = [](auto n_c) { constexpr int n = decltype(n_c)::value; static_assert(n < 64, "vmcnt is a 6-bit count"); __builtin_amdgcn_s_waitcnt(0x0070 | (n & 15) | ((n >> 4) << 14)); };
   // start-up: A0 B0 A1 B1 ... of the first DEPTH K tiles, as far as they exist
+  if (!SPLIT || wave >= WAVES) {
 #pragma unroll
-  for (int t = 0; t < DEPTH; ++t)
-    if (t == 0 || nk > t) {
-      g2s<AKC, WAVES, CHA>(smem + 2 * t * SLOT, rsA, offa, g.lda, kA, wave);
-      advanceA();
-      g2s<BKC, WAVES, CHB>(smem + (2 * t + 1) * SLOT, rsB, offb, g.ldb, kB, wave);
-      advanceB();
+    for (int t = 0; t < DEPTH; ++t)
+      if (t == 0 || nk > t) {
+        g2s<AKC, LOADERS, CHA>(smem + 2 * t * SLOT, rsA, offa, g.lda, kA, lw);
+        advanceA();
+        g2s<BKC, LOADERS, CHB>(smem + (2 * t + 1) * SLOT, rsB, offb, g.ldb, kB, lw);
+        advanceB();
+      }
+  }
+  if constexpr (SPLIT) {
+    if (wave >= WAVES) {
+      // The wavefronts that load.  Barrier number t + 1 (the one inside trip t of the others) says that tile t + 1 has landed and
+      // that the fragments of tile t are in registers, which frees both its slots.
+      if (nk > DEPTH) { g2s<AKC, LOADERS, CHA>(smem + 2 * DEPTH * SLOT, rsA, offa, g.lda, kA, lw); advanceA(); }
+      if (nk > DEPTH) wait_vm(std::integral_constant<int, (DEPTH - 1) * (CHA + CHB) + CHA>{});
+      else __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      int slot = 0, kt = 0;
+      for (; kt + DEPTH + 1 < nk; ++kt) {
+        wait_vm(std::integral_constant<int, (DEPTH - 2) * (CHA + CHB) + CHA>{});
+        __syncthreads();
+        g2s<BKC, LOADERS, CHB>(smem + slot * SLOT, rsB, offb, g.ldb, kB, lw);
+        advanceB();
+        g2s<AKC, LOADERS, CHA>(smem + (slot + 1 == NSLOT ? 0 : slot + 1) * SLOT, rsA, offa, g.lda, kA, lw);
+        advanceA();
+        slot = slot + 2 >= NSLOT ? slot + 2 - NSLOT : slot + 2;
+      }
+      if (kt + DEPTH < nk) {
+        wait_vm(std::integral_constant<int, (DEPTH - 2) * (CHA + CHB) + CHA>{});
+        __syncthreads();
+        g2s<BKC, LOADERS, CHB>(smem + slot * SLOT, rsB, offb, g.ldb, kB, lw);
+        ++kt;
+      }
+      for (; kt < nk; ++kt) {
+        // the last trips: of the tiles beyond kt + 1 all that are left may be outstanding
+        auto left = [&](auto n_c) {
+          constexpr int n = decltype(n_c)::value;
+          if constexpr (n > 0 && n <= DEPTH - 2) { if (nk - kt >= n + 2) { wait_vm(std::integral_constant<int, n * (CHA + CHB)>{}); return true; } }
+          return false;
+        };
+        if (!(left(std::integral_constant<int, 6>{}) || left(std::integral_constant<int, 5>{}) || left(std::integral_constant<int, 4>{}) ||
+              left(std::integral_constant<int, 3>{}) || left(std::integral_constant<int, 2>{}) || left(std::integral_constant<int, 1>{})))
+          __builtin_amdgcn_s_waitcnt(0);
+        static_assert(DEPTH <= 8, "cases above");
+        __syncthreads();
+      }
+      return;                 // (a wavefront that has ended is not waited for at the barriers of the epilogue)
     }
+  }
 
   // acc[i][j][e] = C[m0 + wm + i*16 + lane%16][n0 + wn + j*16 + (lane/16)*4 + e]: the MFMA is issued with the operands
   // swapped, which leaves every lane with 4 consecutive columns of one row.
@@ -334,87 +387,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   }
   int slotA = 0;               // slot of the A tile being read; its B tile sits in the next slot of the ring
 
-  // Software pipeline, one K tile (2 k-steps of 32) per trip t, fragments double-buffered in registers:
-  //   S0  MFMA k0 | read frags k1 | A(t+2)'s loads
-  //   -- wait for A(t+1), B(t+1); barrier --
-  //   S1  MFMA k1 | frags k0 of tile t+1 | B(t+2)'s loads
-  // The barrier frees the two slots just read: B(t+2) goes into A(t)'s, A(t+3) -- half a trip later -- into B(t)'s.
-  // With five slots the loads are issued at an even rate, one operand tile per k-step and a few MFMAs apart, instead of
-  // all at once after the barrier (the CU's vector-memory path takes about half a trip to move a trip's 64 KiB, and a
-  // wavefront whose load does not fit the queue stands still, MFMAs included), and every load has half a trip or more
-  // to land.  Away from the end of the reduction the loop body has no branches.
-  constexpr int NMFMA = NI * NJ;                                // MFMAs per k-step
-  constexpr int NFRAG = NI + NJ;                                // fragments per k-step
-  constexpr int EVERY = NMFMA >= 2 * NFRAG ? 2 : 1;             // MFMAs per fragment read
-  static_assert(NMFMA % CHA == 0 && NMFMA % CHB == 0 && NMFMA >= EVERY * NFRAG, "placement of loads and fragment reads");
-  bf16x8 fa[2][NI], fb[2][NJ];
-  // one k-step: the MFMAs on fragment set `cur`; after every second MFMA (every one on the smallest tile) one fragment of `ks_next` into the other set
-  // (B's first: the first MFMAs of the next k-step need all of them); and the loads of operand tile `op` (0 = A, 1 = B)
-  // spread between the MFMAs
-  auto kstep = [&](auto cur_c, auto ks_c, auto op_c, auto tail_c, lds_char* dst) __attribute__((always_inline)) {
-    constexpr int cur = decltype(cur_c)::value, ks_next = decltype(ks_c)::value, op = decltype(op_c)::value;
-    constexpr int NL = op ? CHB : CHA, GAP = NMFMA / NL;
-    constexpr bool do_load = !decltype(tail_c)::value;            // the last DEPTH trips have nothing left to fetch
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int js = (TN == 2 && (i & 1)) ? NJ - 1 - j : j;     // boustrophedon: consecutive MFMAs always share one operand
-                                                                  // (with four column groups the register allocator spills on it)
-        acc[i][js] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[cur][js], fa[cur][i], acc[i][js], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        const int n = i * NJ + j;
-        if (n % EVERY == 0 && n / EVERY < NFRAG) {
-          const int f = n / EVERY;
-          if (f < NJ) fb[cur ^ 1][f] = frag<BKC, NPB, PCS>(pb, f, ks_next);
-          else fa[cur ^ 1][f - NJ] = frag<AKC, NPA, PCA>(pa, f - NJ, ks_next);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (do_load) if (n % GAP == GAP - 1) {
-          const int l = n / GAP;
-          if (op == 0) g2s_one<AKC, WAVES, CHA>(dst, rsA, offa, g.lda, kA, wave, l);
-          else g2s_one<BKC, WAVES, CHB>(dst, rsB, offb, g.ldb, kB, wave, l);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-  };
-  std::integral_constant<int, 0> c0; std::integral_constant<int, 1> c1;
-
-  auto wait_vm = [](auto n_c) { constexpr int n = decltype(n_c)::value; static_assert(n < 64, "vmcnt is a 6-bit count"); __builtin_amdgcn_s_waitcnt(0x0070 | (n & 15) | ((n >> 4) << 14)); };
-  // the first K tile has landed (with weight gradients, whose C is fetched after the start-up tiles: all of them, and C)
-  if (EPI != EPI_ACC32 && nk >= DEPTH) wait_vm(std::integral_constant<int, (DEPTH - 1) * (CHA + CHB)>{});
-  else __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) fb[0][j] = frag<BKC, NPB, PCS>(pb, j, 0);
-#pragma unroll
-  for (int i = 0; i < NI; ++i) fa[0][i] = frag<AKC, NPA, PCA>(pa, i, 0);
-  int kt = 0;
-  auto trip = [&](auto tail_c) __attribute__((always_inline)) {
-    constexpr bool tail = decltype(tail_c)::value;
-    // ring position (wave-uniform) of tile 2(kt + DEPTH) = A(kt+DEPTH): the slot before A(kt)'s, which B(kt-1) has left;
-    // tile 2(kt + DEPTH) + 1 = B(kt+DEPTH) takes A(kt)'s slot
-    const int s4 = slotA == 0 ? NSLOT - 1 : slotA - 1;
-    kstep(c0, c1, c0, tail_c, smem + s4 * SLOT);
-    if (!tail) advanceA();
-    // A(kt+1), B(kt+1) have landed once nothing older than the loads of A(kt+2) ... A(kt+DEPTH) is outstanding (in the
-    // last trips: of the tiles that are left beyond kt+1); own LDS reads are done
-    constexpr int VM = (DEPTH - 1) * CHA + (DEPTH - 2) * CHB;
-    if constexpr (!tail) wait_vm(std::integral_constant<int, VM>{});
-    else {
-      auto left = [&](auto n_c) {                     // n K tiles beyond kt + 1 may be outstanding
-        constexpr int n = decltype(n_c)::value;
-        if constexpr (n > 0 && n <= DEPTH - 2) { if (nk - kt == n + 2) { wait_vm(std::integral_constant<int, n * (CHA + CHB)>{}); return true; } }
-        return false;
-      };
-      if (!(left(std::integral_constant<int, 6>{}) || left(std::integral_constant<int, 5>{}) || left(std::integral_constant<int, 4>{}) ||
-            left(std::integral_constant<int, 3>{}) || left(std::integral_constant<int, 2>{}) || left(std::integral_constant<int, 1>{})))
-        __builtin_amdgcn_s_waitcnt(0);
-      static_assert(DEPTH <= 8, "cases above");
-    }
-    __syncthreads();
-    __builtin_amdgcn_sched_barrier(0);
-    {
+  if constexpr (SPLIT) {
+    // Tile t is multiplied out of one register set while all fragments of tile t + 1 go from LDS into the other, the reads first,
+    // so that they have landed by the barrier.  The order of the products is that of the loop below: the same bits.
+    constexpr int NM = NI * NJ, NF = NI + NJ;
+    auto hop = [&]() __attribute__((always_inline)) {                            // fragment addresses to the next tile of the ring
       const int dA = (slotA >= NSLOT - 2 ? 2 - NSLOT : 2) * SLOT;
       const int sB = slotA + 1 >= NSLOT ? slotA + 1 - NSLOT : slotA + 1;
       const int dB = (sB >= NSLOT - 2 ? 2 - NSLOT : 2) * SLOT;
@@ -422,13 +399,138 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
       for (int x = 0; x < NPA; ++x) pa[x] += dA;
 #pragma unroll
       for (int x = 0; x < NPB; ++x) pb[x] += dB;
+      slotA = slotA + 2 >= NSLOT ? slotA + 2 - NSLOT : slotA + 2;
+    };
+    __syncthreads();                                                             // tile 0 has landed
+    constexpr int RP = (NF + NM - 1) / NM;                                       // fragments read behind an MFMA
+    bf16x8 fa[2][2][NI], fb[2][2][NJ];
+    auto read = [&](auto set_c, int f) __attribute__((always_inline)) {          // fragment f of the next K tile
+      constexpr int set = decltype(set_c)::value;
+      const int ks = f / NF, x = f % NF;
+      if (x < NJ) fb[set][ks][x] = frag<BKC, NPB, PCS>(pb, x, ks);
+      else fa[set][ks][x - NJ] = frag<AKC, NPA, PCA>(pa, x - NJ, ks);
+    };
+#pragma unroll
+    for (int f = 0; f < 2 * NF; ++f) read(c0, f);
+    auto trip = [&](auto cur_c) __attribute__((always_inline)) {
+      constexpr int cur = decltype(cur_c)::value;
+      hop();
+      __builtin_amdgcn_s_waitcnt(0xc07f);                                        // lgkmcnt(0): the fragments of tile t are here
+      __syncthreads();                                                           // tile t + 1 has landed
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            const int js = (i & 1) ? NJ - 1 - j : j, n = (ks * NI + i) * NJ + j;
+            acc[i][js] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[cur][ks][js], fa[cur][ks][i], acc[i][js], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int f = n * RP; f < (n + 1) * RP && f < 2 * NF; ++f) read(std::integral_constant<int, cur ^ 1>{}, f);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+    };
+    for (int kt = 0; kt < nk; kt += 2) {
+      trip(c0);
+      if (kt + 1 < nk) trip(c1);
     }
-    kstep(c1, c0, c1, tail_c, smem + slotA * SLOT);           // (fragments past the last tile are read and not used)
-    if (!tail) advanceB();
-    slotA = slotA + 2 >= NSLOT ? slotA + 2 - NSLOT : slotA + 2;
-  };
-  for (; kt + DEPTH < nk; ++kt) trip(std::false_type{});
-  for (; kt < nk; ++kt) trip(std::true_type{});
+  } else {
+    // Software pipeline, one K tile (2 k-steps of 32) per trip t, fragments double-buffered in registers:
+    //   S0  MFMA k0 | read frags k1 | A(t+2)'s loads
+    //   -- wait for A(t+1), B(t+1); barrier --
+    //   S1  MFMA k1 | frags k0 of tile t+1 | B(t+2)'s loads
+    // The barrier frees the two slots just read: B(t+2) goes into A(t)'s, A(t+3) -- half a trip later -- into B(t)'s.
+    // With five slots the loads are issued at an even rate, one operand tile per k-step and a few MFMAs apart, instead of
+    // all at once after the barrier (the CU's vector-memory path takes about half a trip to move a trip's 64 KiB, and a
+    // wavefront whose load does not fit the queue stands still, MFMAs included), and every load has half a trip or more
+    // to land.  Away from the end of the reduction the loop body has no branches.
+    constexpr int NMFMA = NI * NJ;                                // MFMAs per k-step
+    constexpr int NFRAG = NI + NJ;                                // fragments per k-step
+    constexpr int EVERY = NMFMA >= 2 * NFRAG ? 2 : 1;             // MFMAs per fragment read
+    static_assert(NMFMA % CHA == 0 && NMFMA % CHB == 0 && NMFMA >= EVERY * NFRAG, "placement of loads and fragment reads");
+    bf16x8 fa[2][NI], fb[2][NJ];
+    // one k-step: the MFMAs on fragment set `cur`; after every second MFMA (every one on the smallest tile) one fragment of `ks_next` into the other set
+    // (B's first: the first MFMAs of the next k-step need all of them); and the loads of operand tile `op` (0 = A, 1 = B)
+    // spread between the MFMAs
+    auto kstep = [&](auto cur_c, auto ks_c, auto op_c, auto tail_c, lds_char* dst) __attribute__((always_inline)) {
+      constexpr int cur = decltype(cur_c)::value, ks_next = decltype(ks_c)::value, op = decltype(op_c)::value;
+      constexpr int NL = op ? CHB : CHA, GAP = NMFMA / NL;
+      constexpr bool do_load = !decltype(tail_c)::value;            // the last DEPTH trips have nothing left to fetch
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int js = (TN == 2 && (i & 1)) ? NJ - 1 - j : j;     // boustrophedon: consecutive MFMAs always share one operand
+                                                                    // (with four column groups the register allocator spills on it)
+          acc[i][js] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[cur][js], fa[cur][i], acc[i][js], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          const int n = i * NJ + j;
+          if (n % EVERY == 0 && n / EVERY < NFRAG) {
+            const int f = n / EVERY;
+            if (f < NJ) fb[cur ^ 1][f] = frag<BKC, NPB, PCS>(pb, f, ks_next);
+            else fa[cur ^ 1][f - NJ] = frag<AKC, NPA, PCA>(pa, f - NJ, ks_next);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (do_load) if (n % GAP == GAP - 1) {
+            const int l = n / GAP;
+            if (op == 0) g2s_one<AKC, WAVES, CHA>(dst, rsA, offa, g.lda, kA, wave, l);
+            else g2s_one<BKC, WAVES, CHB>(dst, rsB, offb, g.ldb, kB, wave, l);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    // the first K tile has landed (with weight gradients, whose C is fetched after the start-up tiles: all of them, and C)
+    if (EPI != EPI_ACC32 && nk >= DEPTH) wait_vm(std::integral_constant<int, (DEPTH - 1) * (CHA + CHB)>{});
+    else __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) fb[0][j] = frag<BKC, NPB, PCS>(pb, j, 0);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) fa[0][i] = frag<AKC, NPA, PCA>(pa, i, 0);
+    int kt = 0;
+    auto trip = [&](auto tail_c) __attribute__((always_inline)) {
+      constexpr bool tail = decltype(tail_c)::value;
+      // ring position (wave-uniform) of tile 2(kt + DEPTH) = A(kt+DEPTH): the slot before A(kt)'s, which B(kt-1) has left;
+      // tile 2(kt + DEPTH) + 1 = B(kt+DEPTH) takes A(kt)'s slot
+      const int s4 = slotA == 0 ? NSLOT - 1 : slotA - 1;
+      kstep(c0, c1, c0, tail_c, smem + s4 * SLOT);
+      if (!tail) advanceA();
+      // A(kt+1), B(kt+1) have landed once nothing older than the loads of A(kt+2) ... A(kt+DEPTH) is outstanding (in the
+      // last trips: of the tiles that are left beyond kt+1); own LDS reads are done
+      constexpr int VM = (DEPTH - 1) * CHA + (DEPTH - 2) * CHB;
+      if constexpr (!tail) wait_vm(std::integral_constant<int, VM>{});
+      else {
+        auto left = [&](auto n_c) {                     // n K tiles beyond kt + 1 may be outstanding
+          constexpr int n = decltype(n_c)::value;
+          if constexpr (n > 0 && n <= DEPTH - 2) { if (nk - kt == n + 2) { wait_vm(std::integral_constant<int, n * (CHA + CHB)>{}); return true; } }
+          return false;
+        };
+        if (!(left(std::integral_constant<int, 6>{}) || left(std::integral_constant<int, 5>{}) || left(std::integral_constant<int, 4>{}) ||
+              left(std::integral_constant<int, 3>{}) || left(std::integral_constant<int, 2>{}) || left(std::integral_constant<int, 1>{})))
+          __builtin_amdgcn_s_waitcnt(0);
+        static_assert(DEPTH <= 8, "cases above");
+      }
+      __syncthreads();
+      __builtin_amdgcn_sched_barrier(0);
+      {
+        const int dA = (slotA >= NSLOT - 2 ? 2 - NSLOT : 2) * SLOT;
+        const int sB = slotA + 1 >= NSLOT ? slotA + 1 - NSLOT : slotA + 1;
+        const int dB = (sB >= NSLOT - 2 ? 2 - NSLOT : 2) * SLOT;
+#pragma unroll
+        for (int x = 0; x < NPA; ++x) pa[x] += dA;
+#pragma unroll
+        for (int x = 0; x < NPB; ++x) pb[x] += dB;
+      }
+      kstep(c1, c0, c1, tail_c, smem + slotA * SLOT);           // (fragments past the last tile are read and not used)
+      if (!tail) advanceB();
+      slotA = slotA + 2 >= NSLOT ? slotA + 2 - NSLOT : slotA + 2;
+    };
+    for (; kt + DEPTH < nk; ++kt) trip(std::false_type{});
+    for (; kt < nk; ++kt) trip(std::true_type{});
+  }
 
   // epilogue
   if (EPI != EPI_ACC32 && g.bias) {       // wave-uniform; the bias of a column goes to every row of it
@@ -772,23 +874,23 @@ __device__ __forceinline__ bool small_tile(int tiles_m, int tiles_n, int first, 
   return m0 < rows && n0 < cols;
 }
 
-// one workgroup per 128 x 128 tile (four wavefronts of 64 x 64)
+// one workgroup per 128 x 128 tile (four wavefronts of 64 x 64, and four that load unless two workgroups share the CU)
 template <bool BKC, int EPI, int DEPTH>
-__global__ __launch_bounds__(256, 2) void gemm_quarter_kernel(   // (register budget: as for the half-height tile)
+__global__ __launch_bounds__(DEPTH == 2 ? 256 : 512, 2) void gemm_quarter_kernel(   // (register budget: as for the half-height tile)
     GemmArgs g, int tiles_m, int tiles_n, int first) {
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   int m0, n0;
   if (!small_tile<1, 1, EPI == EPI_SWIGLU ? GLU_BN : BN, true>(tiles_m, tiles_n, first, g.M, EPI == EPI_SWIGLU ? g.N / 2 : g.N, m0, n0)) return;
-  gemm_tile<true, BKC, EPI, 2, 1, 1, DEPTH>(g, m0, n0, (lds_char*)smem_raw);
+  gemm_tile<true, BKC, EPI, 2, 1, 1, DEPTH, DEPTH == 2 ? 0 : 4>(g, m0, n0, (lds_char*)smem_raw);
 }
 
-// one workgroup per 64 x 64 (WR == 0) or 128 x 64 tile (WR == 1)
+// one workgroup per 64 x 64 (WR == 0) or 128 x 64 tile (WR == 1); four more wavefronts load
 template <bool BKC, int EPI, int WR>
-__global__ __launch_bounds__(256, 2) void gemm_tiny_kernel(GemmArgs g, int tiles_m, int tiles_n, int first) {
+__global__ __launch_bounds__(512, 2) void gemm_tiny_kernel(GemmArgs g, int tiles_m, int tiles_n, int first) {
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   int m0, n0;
   if (!small_tile<WR ? 1 : 2, 2, EPI == EPI_SWIGLU ? GLU_BN : BN, false>(tiles_m, tiles_n, first, g.M, EPI == EPI_SWIGLU ? g.N / 2 : g.N, m0, n0)) return;
-  gemm_tile<true, BKC, EPI, EPI == EPI_SWIGLU ? 2 : 1, WR, 0, WR ? 4 : TINY_DEPTH>(g, m0, n0, (lds_char*)smem_raw);
+  gemm_tile<true, BKC, EPI, EPI == EPI_SWIGLU ? 2 : 1, WR, 0, WR ? 4 : TINY_DEPTH, 4>(g, m0, n0, (lds_char*)smem_raw);
 }
 
 // Several weight-gradient products C_p += A_p^T . B_p in one launch of persistent workgroups.  Each workgroup
@@ -826,7 +928,7 @@ __global__ __launch_bounds__(1024 / TN) void gemm_wgrad_group_kernel(GemmGroup g
 // The same products in tiles of 128 x 128 (WT = 1) or 64 x 64 (WT = 0), one workgroup each: workgroup `bid` takes part bid % 4 (% 16) of
 // the full tile number first + bid / 4 (/ 16).
 template <int WT, int DEPTH>
-__global__ __launch_bounds__(256, 2) void gemm_wgrad_small_kernel(GemmGroup gg, int first) {
+__global__ __launch_bounds__(DEPTH == 2 ? 256 : 512, 2) void gemm_wgrad_small_kernel(GemmGroup gg, int first) {
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   int bid = blockIdx.x;
   {
@@ -842,7 +944,7 @@ __global__ __launch_bounds__(256, 2) void gemm_wgrad_small_kernel(GemmGroup gg, 
   tile_of(t - gg.first_tile[pi], (g.M + BM - 1) / BM, (g.N + BN - 1) / BN, tile_m, tile_n);
   const int m0 = tile_m * BM + (bid & ((1 << B) - 1)) * (BM >> B), n0 = tile_n * BN + ((bid >> B) & ((1 << B) - 1)) * (BN >> B);
   if (m0 >= g.M || n0 >= g.N) return;
-  gemm_tile<false, false, EPI_ACC32, WT ? 2 : 1, WT, WT, DEPTH>(g, m0, n0, (lds_char*)smem_raw, gg.nseg, gg.seg_delta);
+  gemm_tile<false, false, EPI_ACC32, WT ? 2 : 1, WT, WT, DEPTH, DEPTH == 2 ? 0 : 4>(g, m0, n0, (lds_char*)smem_raw, gg.nseg, gg.seg_delta);
 }
 
 // Eight wavefronts of 128x64 or four of 128x128 per tile: the wider ones read a third less from LDS and are ahead on
@@ -872,7 +974,7 @@ hipError_t launch_wgrad_small(const GemmGroup& gg, int first, int n, hipStream_t
   auto kern = gemm_wgrad_small_kernel<WT, DEPTH>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3((WT ? 4 : 16) * n), dim3(256), LDS, s, gg, first);
+  hipLaunchKernelGGL(kern, dim3((WT ? 4 : 16) * n), dim3(DEPTH == 2 ? 256 : 512), LDS, s, gg, first);
   return hipGetLastError();
 }
 
@@ -894,7 +996,7 @@ hipError_t launch_quarter(const GemmArgs& g, hipStream_t s, const SmallGrid& t) 
   auto kern = gemm_quarter_kernel<BKC, EPI, DEPTH>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(t.n), dim3(256), LDS, s, g, t.tiles_m, t.tiles_n, t.first);
+  hipLaunchKernelGGL(kern, dim3(t.n), dim3(DEPTH == 2 ? 256 : 512), LDS, s, g, t.tiles_m, t.tiles_n, t.first);
   return hipGetLastError();
 }
 template <bool BKC, int EPI, int WR>
@@ -903,7 +1005,7 @@ hipError_t launch_tiny(const GemmArgs& g, hipStream_t s, const SmallGrid& t) {
   auto kern = gemm_tiny_kernel<BKC, EPI, WR>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(t.n), dim3(256), LDS, s, g, t.tiles_m, t.tiles_n, t.first);
+  hipLaunchKernelGGL(kern, dim3(t.n), dim3(512), LDS, s, g, t.tiles_m, t.tiles_n, t.first);
   return hipGetLastError();
 }
 

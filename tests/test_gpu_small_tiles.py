@@ -33,6 +33,27 @@ def test_small_tiles_agree_bitwise(mode, M, N, K):
     assert all(torch.equal(outs[0], o) for o in outs[1:])
 
 
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_reductions_around_the_ring(mode):
+    """One to 20 K tiles on small tiles whose operands other wavefronts load, four (128 x 128, 128 x 64) or eight (64 x 64) K tiles ahead: the start-up,
+    the steady state and the end of the ring with every remainder, against full tiles; a ragged last K tile for weight gradients."""
+    import torch
+    M, N = 136, 72
+    A, B = torch.randn((M, 1280), device="cuda:0").bfloat16(), torch.randn((N, 1280), device="cuda:0").bfloat16()
+    for K in [64 * i for i in range(1, 21)] + ([57, 185, 313] if mode == 2 else []):
+        a = A[:, :K].t().contiguous() if mode == 2 else A[:, :K].contiguous()
+        b = B[:, :K].contiguous() if mode == 1 else B[:, :K].t().contiguous()
+        outs = []
+        for ks in (2, 4, 5, 6):
+            c = torch.ones((M, N), dtype=torch.float32 if mode == 2 else torch.bfloat16, device="cuda:0")
+            assert L().stage_kernel_gemm(1, mode, M, N, K, P(a), a.shape[1], P(b), b.shape[1], P(c), N, None, 0, int(mode == 2), ks, None) == 0
+            outs.append(c)
+        ref = A[:, :K].double() @ B[:, :K].double().t() + (1 if mode == 2 else 0)
+        # one bf16 rounding of the output, or fp32 sums of K products
+        assert ((outs[0].double() - ref).abs().max() / ref.abs().max()).item() <= (1e-5 * K ** 0.5 if mode == 2 else KTOL["bf16"])
+        assert all(torch.equal(outs[0], o) for o in outs[1:]), K
+
+
 @pytest.mark.parametrize("act", [0, 1])
 @pytest.mark.parametrize("M,f,K", [(1, 8, 64), (127, 64, 64), (129, 72, 128), (128, 136, 320), (257, 200, 384),
                                    (1100, 72, 128), (300, 2000, 192),
