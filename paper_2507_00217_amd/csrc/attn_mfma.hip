@@ -75,9 +75,6 @@ __device__ __forceinline__ rsrc_words raw_rsrc(const void* base, unsigned bytes)
 __device__ __forceinline__ void load_to_lds_b128(rsrc_words rsrc, unsigned lds_addr, unsigned voffset) {
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds_addr), "v"(voffset), "s"(rsrc) : "memory");
 }
-__device__ __forceinline__ void load_to_lds_b32(rsrc_words rsrc, unsigned lds_addr, unsigned voffset) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds" :: "s"(lds_addr), "v"(voffset), "s"(rsrc) : "memory");
-}
 
 // Per-thread byte offsets (relative to row 0 of the tile's first row, column 0 of the head) of the pieces it
 // fetches: load j of wavefront w fills slots (j*NW + w)*64 .. +63.
@@ -285,34 +282,34 @@ __device__ __forceinline__ void fwd_tile(lds_char* lds, const FragOff<HD>& fo, c
   for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[c][e]);
-  float p[NC][16];
-  mx = half_max(mx, hf);
-  const float mn = fmaxf(m, mx * sl2);
-  float sum = 0.f;
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) p[c][e] = fast_exp2(fmaf(sacc[c][e], sl2, -mn));
-  if (__any(mn != m)) {                          // the running max moved for some query of the wavefront
+  // A row's keys are held by two lanes, l and l + 32.  They exchange their maxima only when one of them found a larger one, and
+  // never their sums: each keeps its own until the end.
+  if (__any(mx * sl2 > m)) {                      // the running max moves for some query of the wavefront
+    const float mn = fmaxf(m, half_max(mx, hf) * sl2);
     const float alpha = fast_exp2(m - mn);
     l *= alpha;
 #pragma unroll
     for (int hb = 0; hb < G::NHB; ++hb)
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[hb][e] *= alpha;
+    m = mn;
   }
+  float p[NC][16];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) p[c][e] = fast_exp2(fmaf(sacc[c][e], sl2, -m));
   bf16x8 pf[NC][2];
 #pragma unroll
   for (int c = 0; c < NC; ++c) { pf[c][0] = pack8(&p[c][0]); pf[c][1] = pack8(&p[c][8]); }
   // row sum of the probabilities as rounded for the P.V product (so the weights applied to V sum to one exactly),
   // two per instruction
+  float sum = 0.f;
 #pragma unroll
   for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int t2 = 0; t2 < 2; ++t2) sum = dot_ones(pf[c][t2], sum);
-  sum = half_sum(sum, hf);
   l += sum;
-  m = mn;
   SCHED_FENCE;
   // O^T[hd][query] += V^T . P^T
 #pragma unroll
@@ -370,7 +367,7 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_fwd_kernel(AttnArgs a, in
   f32x16 o[G::NHB];
 #pragma unroll
   for (int hb = 0; hb < G::NHB; ++hb) zero(o[hb]);
-  float m = -1e30f, l = 0.f;                       // running max (in log2 units, scaled) and sum of the lane's query
+  float m = -1e30f, l = 0.f;                       // running max (in log2 units, scaled) of the lane's query and sum over the lane's keys
 
   FragOff<HD> fo;
   fo.init(lane, lds);
@@ -401,6 +398,7 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_fwd_kernel(AttnArgs a, in
     if (t + 1 < ntiles) step(t + 1, std::integral_constant<int, BUFB>{});
   }
 
+  l = half_sum(l, hf);             // the lane 32 further on holds the row's other keys
   if constexpr (KS == 2) {
     // The loop's last barrier has passed: nobody reads the tiles any more and no load is in flight.  The second half's
     // wavefront leaves its (O, m, l) in LDS ([piece][lane] of 16 bytes), the first half's folds them into its own.
@@ -454,7 +452,7 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_fwd_kernel(AttnArgs a, in
 template <int HD, int BUF>
 __device__ __forceinline__ void dq_block(lds_char* lds, const FragOff<HD>& fo, const bf16x8 (&qf)[HD / 16], const bf16x8 (&dof)[HD / 16],
                                          f32x16 (&dq)[HD / 32], int c, int kv0, int q, int hf, int s, int causal, float sl2,
-                                         float lse2, float dl, bool need_mask) {
+                                         float lse2, const f32x16& ndl, bool need_mask) {
   using G = Geo<HD>;
   constexpr int KT = BUF, VT = BUF + G::TILEB, AHEAD = 3, NDQ = G::NHB * 2, VA = 4;
   bf16x8 kf[AHEAD + 1][2];                                          // [ring slot][K rows, V rows]
@@ -467,7 +465,7 @@ __device__ __forceinline__ void dq_block(lds_char* lds, const FragOff<HD>& fo, c
       kf[(kk + AHEAD) % (AHEAD + 1)][0] = frag_rows<HD>(lds, fo, KT, c * 32, kk + AHEAD);
       kf[(kk + AHEAD) % (AHEAD + 1)][1] = frag_rows<HD>(lds, fo, VT, c * 32, kk + AHEAD);
     }
-    if (kk == 0) { sacc = mfma0(kf[0][0], qf[0]); pacc = mfma0(kf[0][1], dof[0]); }          // S^T = K . Q^T, dP^T = V . dO^T
+    if (kk == 0) { sacc = mfma0(kf[0][0], qf[0]); pacc = MFMA(kf[0][1], dof[0], ndl); }      // S^T = K . Q^T, dP^T - delta = V . dO^T - delta
     else {
       sacc = MFMA(kf[kk % (AHEAD + 1)][0], qf[kk], sacc);
       pacc = MFMA(kf[kk % (AHEAD + 1)][1], dof[kk], pacc);
@@ -489,7 +487,7 @@ __device__ __forceinline__ void dq_block(lds_char* lds, const FragOff<HD>& fo, c
       if (acc_row(e, 0) > bound) ds[e] = 0.f;
   }
 #pragma unroll
-  for (int e = 0; e < 16; ++e) ds[e] *= pacc[e] - dl;
+  for (int e = 0; e < 16; ++e) ds[e] *= pacc[e];
   const bf16x8 dsf[2] = {pack8(&ds[0]), pack8(&ds[8])};
   SCHED_FENCE;
 #pragma unroll
@@ -569,6 +567,12 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_dq_kernel(AttnArgs a, int
   f32x16 dq[G::NHB];
 #pragma unroll
   for (int hb = 0; hb < G::NHB; ++hb) zero(dq[hb]);
+  // What the dP products start from: -delta of the lane's query.  The subtraction then costs no vector instruction (16 per
+  // 32 x 32 block here and in dK/dV); with the statistics prepared once per tile there, the backward of 4096 positions x 32 heads of
+  // 128 takes 461 us instead of 470, of 8192 x 8 of 64 294 instead of 309.
+  f32x16 ndl;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) ndl[e] = -dl;
 
   FragOff<HD> fo;
   fo.init(lane, lds);
@@ -585,13 +589,13 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_dq_kernel(AttnArgs a, int
     if (active && q0w < a.s) {
       if constexpr (KS == 2) {
         const bool need_mask = (a.causal && kvw + 31 > q0w) || kvw + 32 > a.s;
-        dq_block<HD, BUF>(lds, fo, qf, dof, dq, 0, kvw, q, hf, a.s, a.causal, sl2, lse2, dl, need_mask);
+        dq_block<HD, BUF>(lds, fo, qf, dof, dq, 0, kvw, q, hf, a.s, a.causal, sl2, lse2, ndl, need_mask);
       } else {
         const bool need_mask = (a.causal && kv0 + TK - 1 > q0w) || kv0 + TK > a.s;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
           if (a.causal && kv0 + c * 32 > q0w + 31) continue;          // the whole 32-key block is in the future
-          dq_block<HD, BUF>(lds, fo, qf, dof, dq, c, kv0, q, hf, a.s, a.causal, sl2, lse2, dl, need_mask);
+          dq_block<HD, BUF>(lds, fo, qf, dof, dq, c, kv0, q, hf, a.s, a.causal, sl2, lse2, ndl, need_mask);
         }
       }
     }
@@ -665,9 +669,9 @@ constexpr int DKV_TQ = 128, DKV_TQ_SMALL = 64;
 // the light half, lightest first
 __device__ __forceinline__ int key_tile_of_rank(int rank, int n, int fold) { return n - 1 - tile_of_rank(rank, n, fold); }
 
-// acc = sum over head_dim of rows(tile `TILE`, rows rb..rb+31) x bfr (the wavefront's K or V fragments); fragment
+// acc = (ADD: acc +) sum over head_dim of rows(tile `TILE`, rows rb..rb+31) x bfr (the wavefront's K or V fragments); fragment
 // reads run three k-steps ahead
-template <int HD, int TILE>
+template <int HD, int TILE, bool ADD = false>
 __device__ __forceinline__ void dkv_rows_product(lds_char* lds, const FragOff<HD>& fo, int rb, const bf16x8 (&bfr)[HD / 16], f32x16& acc) {
   using G = Geo<HD>;
   constexpr int AHEAD = 3;
@@ -677,28 +681,8 @@ __device__ __forceinline__ void dkv_rows_product(lds_char* lds, const FragOff<HD
 #pragma unroll
   for (int kk = 0; kk < G::NKK; ++kk) {
     if (kk + AHEAD < G::NKK) f[(kk + AHEAD) % (AHEAD + 1)] = frag_rows<HD>(lds, fo, TILE, rb, kk + AHEAD);
-    if (kk == 0) acc = mfma0(f[0], bfr[0]);
+    if (kk == 0 && !ADD) acc = mfma0(f[0], bfr[0]);
     else acc = MFMA(f[kk % (AHEAD + 1)], bfr[kk], acc);
-    SCHED_FENCE;
-  }
-}
-// the same for two products at once (S from the Q tile, dP from the dO tile), their MFMAs alternating
-template <int HD, int TILE_A, int TILE_B>
-__device__ __forceinline__ void dkv_rows_product2(lds_char* lds, const FragOff<HD>& fo, int rb, const bf16x8 (&bfa)[HD / 16],
-                                                  const bf16x8 (&bfb)[HD / 16], f32x16& acca, f32x16& accb) {
-  using G = Geo<HD>;
-  constexpr int AHEAD = 3;
-  bf16x8 f[AHEAD + 1][2];
-#pragma unroll
-  for (int kk = 0; kk < AHEAD; ++kk) { f[kk][0] = frag_rows<HD>(lds, fo, TILE_A, rb, kk); f[kk][1] = frag_rows<HD>(lds, fo, TILE_B, rb, kk); }
-#pragma unroll
-  for (int kk = 0; kk < G::NKK; ++kk) {
-    if (kk + AHEAD < G::NKK) {
-      f[(kk + AHEAD) % (AHEAD + 1)][0] = frag_rows<HD>(lds, fo, TILE_A, rb, kk + AHEAD);
-      f[(kk + AHEAD) % (AHEAD + 1)][1] = frag_rows<HD>(lds, fo, TILE_B, rb, kk + AHEAD);
-    }
-    if (kk == 0) { acca = mfma0(f[0][0], bfa[0]); accb = mfma0(f[0][1], bfb[0]); }
-    else { acca = MFMA(f[kk % (AHEAD + 1)][0], bfa[kk], acca); accb = MFMA(f[kk % (AHEAD + 1)][1], bfb[kk], accb); }
     SCHED_FENCE;
   }
 }
@@ -770,20 +754,29 @@ __global__ __launch_bounds__(TQ * 4, 2) void attn_dkv_kernel(AttnArgs a, int nsp
       load_to_lds_b128(rsrc, (unsigned)(size_t)(tile + (j * (NTHR / 64) + wave) * 1024),
                        off0 + (unsigned)((int64_t)(row0 + j * SWEEP) * ld * 2));
   };
-  // iteration `it` = (query head jj of the group, query tile t): its Q and dO tiles, lse and delta -> buffer at `buf`
+  // iteration `it` = (query head jj of the group, query tile t): its Q and dO tiles -> buffer at `buf`, lse and delta -> registers
+  float stat_l = 0.f, stat_d = 0.f;
   auto fetch = [&](int it, lds_char* buf) {
     const int jj = it / per_head, t = t_first + it % per_head;
     const int j = j0 + jj;
     tile_fetch(buf + QT, head_rsrc(base + j * HD, a.ld, a.s, HD), offq0, a.ld, t * TQ);
     tile_fetch(buf + OT, head_rsrc(dobase + j * HD, d, a.s, HD), offo0, d, t * TQ);
-    if (wave < TQ / 64) {   // 64 floats per load; queries past the end read as zero, and so do their Q and dO rows
+    if (wave < TQ / 64) {   // one query per lane; queries past the end count as zero, as do their Q and dO rows
+      const int qi = t * TQ + wave * 64 + lane;
       const int64_t row = ((int64_t)ib * a.h + j) * a.s;
-      const unsigned vo = (unsigned)((t * TQ + wave * 64 + lane) * 4);
-      load_to_lds_b32(raw_rsrc(a.lse + row, (unsigned)a.s * 4u), (unsigned)(size_t)(buf + LT + wave * 256), vo);
-      load_to_lds_b32(raw_rsrc(a.delta + row, (unsigned)a.s * 4u), (unsigned)(size_t)(buf + DT + wave * 256), vo);
+      stat_l = qi < a.s ? a.lse[row + qi] : 0.f;
+      stat_d = qi < a.s ? a.delta[row + qi] : 0.f;
     }
   };
-  if (niter > 0) fetch(0, lds);
+  // the statistics of the tile fetched last, as the two roles use them: -log2 e * lse and -delta, formed once per tile
+  // (in the dV wavefronts 16 multiplications per 32 x 32 block otherwise)
+  auto put_stats = [&](lds_char* buf) {
+    if (wave < TQ / 64) {
+      *(__attribute__((address_space(3))) float*)(buf + LT + (wave * 64 + lane) * 4) = -LOG2E * stat_l;
+      *(__attribute__((address_space(3))) float*)(buf + DT + (wave * 64 + lane) * 4) = -stat_d;
+    }
+  };
+  if (niter > 0) { fetch(0, lds); put_stats(lds); }
   if (niter > 1) fetch(1, lds + BUFB);
 
   FragOff<HD> fo;
@@ -805,6 +798,7 @@ __global__ __launch_bounds__(TQ * 4, 2) void attn_dkv_kernel(AttnArgs a, int nsp
 
   // end of an iteration: the next tiles have landed and every wavefront is done with this buffer; refill it
   auto turn = [&](int it) {
+    if (it + 1 < niter) put_stats(cur + hopb);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (it + 2 < niter) fetch(it + 2, cur);
@@ -815,11 +809,11 @@ __global__ __launch_bounds__(TQ * 4, 2) void attn_dkv_kernel(AttnArgs a, int nsp
   };
   // P of elements e4*4 .. +3 of query block qc (element e is query q0 + qc*32 + e4*8 + hf*4 + e).  Only the diagonal
   // tile needs the causal mask: an element is masked when its query is before the lane's key, i.e. e < lim.
-  // (l4: the lse values of those queries, read from LDS ahead of the product that makes sacc -- read where they are
+  // (l4: -log2 e * lse of those queries, read from LDS ahead of the product that makes sacc -- read where they are
   // used, each of the four loads would cost the wavefront a full LDS round trip)
   auto probs4 = [&](const f32x16& sacc, const f32x4& l4, int qc, int e4, bool diag, int lim0, float (&pv)[4]) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) pv[e] = fast_exp2(fmaf(sacc[e4 * 4 + e], sl2, -LOG2E * l4[e]));
+    for (int e = 0; e < 4; ++e) pv[e] = fast_exp2(fmaf(sacc[e4 * 4 + e], sl2, l4[e]));
     if (diag) {
       asm volatile("" ::: "memory");                  // keep this a (wave-uniform) branch: it is rarely taken
       const int lim = lim0 - qc * 32 - e4 * 8;
@@ -882,11 +876,14 @@ __global__ __launch_bounds__(TQ * 4, 2) void attn_dkv_kernel(AttnArgs a, int nsp
     for (int it = 0; it < niter; ++it) {
 #pragma unroll
       for (int qc = 0; qc < NB; ++qc) {
-        f32x4 d4[4];                                    // delta of the block's queries, ahead of the product (see probs4)
+        f32x16 pacc;                                    // starts at -delta of the block's queries
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) d4[e4] = *reinterpret_cast<lds_f4>(ldp + (DT - LT) + (qc * 32 + e4 * 8) * 4);
-        f32x16 pacc;
-        dkv_rows_product<HD, OT>(lds, fo, qc * 32, vf, pacc);                     // dP = dO.V^T
+        for (int e4 = 0; e4 < 4; ++e4) {
+          const f32x4 d4 = *reinterpret_cast<lds_f4>(ldp + (DT - LT) + (qc * 32 + e4 * 8) * 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) pacc[e4 * 4 + e] = d4[e];
+        }
+        dkv_rows_product<HD, OT, true>(lds, fo, qc * 32, vf, pacc);               // dP - delta = dO.V^T - delta
         bf16x8 tf[4];
         dkv_tr_read<HD, QT>(lds, fo, qc * 32, tf);
         SCHED_FENCE;
@@ -901,7 +898,7 @@ __global__ __launch_bounds__(TQ * 4, 2) void attn_dkv_kernel(AttnArgs a, int nsp
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) ds[e4 * 4 + e] = pv[e4][e] * (pacc[e4 * 4 + e] - d4[e4][e]);
+          for (int e = 0; e < 4; ++e) ds[e4 * 4 + e] = pv[e4][e] * pacc[e4 * 4 + e];
         }
         const bf16x8 df[2] = {pack8(&ds[0]), pack8(&ds[8])};
         SCHED_FENCE;
