@@ -326,17 +326,19 @@ __device__ __forceinline__ void fwd_tile(lds_char* lds, const FragOff<HD>& fo, c
 
 // KS = 2 (small grids): two wavefronts per 32 queries, each taking one 32-key half of every key tile, so that a
 // workgroup of 4 wavefronts covers only 64 queries and there are twice as many workgroups (and still two wavefronts on
-// every SIMD); the halves' (O, m, l) are merged through LDS at the end.
+// every SIMD); the halves' (O, m, l) are merged through LDS at the end.  KS = 4 (smaller still): four wavefronts per 32 queries,
+// each taking 32 of the 128 keys of two tiles, which make one step.
 template <int HD, int FWD_THREADS, int KS>
-__global__ __launch_bounds__(FWD_THREADS, 2) void attn_fwd_kernel(AttnArgs a, int fold) {
+__global__ __launch_bounds__(FWD_THREADS, KS == 4 && HD == 64 ? 4 : 2) void attn_fwd_kernel(AttnArgs a, int fold) {
   using G = Geo<HD>;
-  constexpr int KT = 0, VT = G::TILEB, BUFB = 2 * G::TILEB;   // two buffers of (K tile, V tile)
+  constexpr int SUB = KS == 4 ? 2 : 1, TS = TK * SUB;         // 64-key tiles, keys of one step
+  constexpr int KT = 0, VT = G::TILEB, BUFB = SUB * 2 * G::TILEB;   // two buffers of SUB (K tile, V tile) each
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   lds_char* lds = (lds_char*)smem_raw;
   const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  constexpr int BQ = fwd_bq(FWD_THREADS, KS), KW = TK / KS;
-  const int qb = KS == 2 ? wave >> 1 : wave, kh = KS == 2 ? wave & 1 : 0;   // query block, key half
+  constexpr int BQ = fwd_bq(FWD_THREADS, KS), KW = KS == 1 ? 64 : 32;   // keys of a wavefront per step
+  const int qb = wave / KS, kh = wave % KS;   // query block, key half
   const int nqt = (a.s + BQ - 1) / BQ;
   const int qt = tile_of_rank(blockIdx.y / a.b, nqt, fold);   // slow grid index: heavy (late) query tiles are dispatched first
   const int j = blockIdx.x, ib = blockIdx.y % a.b;
@@ -350,15 +352,18 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_fwd_kernel(AttnArgs a, in
   const float sl2 = rsqrtf((float)HD) * LOG2E;
 
   const int last_q = min(q0b + BQ, a.s) - 1;
-  const int ntiles = a.causal ? last_q / TK + 1 : (a.s + TK - 1) / TK;
+  const int nstep = a.causal ? last_q / TS + 1 : (a.s + TS - 1) / TS;
   unsigned off[TK * G::PPR / FWD_THREADS];
   tile_offsets<HD, FWD_THREADS>(off, a.ld, wave, lane);
-  tile_g2s<HD, FWD_THREADS>(lds + KT, rsK, off, a.ld, 0, wave);
-  tile_g2s<HD, FWD_THREADS>(lds + VT, rsV, off, a.ld, 0, wave);
-  if (ntiles > 1) {
-    tile_g2s<HD, FWD_THREADS>(lds + BUFB + KT, rsK, off, a.ld, TK, wave);
-    tile_g2s<HD, FWD_THREADS>(lds + BUFB + VT, rsV, off, a.ld, TK, wave);
-  }
+  auto fetch = [&](int buf, int row0) {
+#pragma unroll
+    for (int u = 0; u < SUB; ++u) {
+      tile_g2s<HD, FWD_THREADS>(lds + buf + u * 2 * G::TILEB + KT, rsK, off, a.ld, row0 + u * TK, wave);
+      tile_g2s<HD, FWD_THREADS>(lds + buf + u * 2 * G::TILEB + VT, rsV, off, a.ld, row0 + u * TK, wave);
+    }
+  };
+  fetch(0, 0);
+  if (nstep > 1) fetch(BUFB, TS);
 
   bf16x8 qf[G::NKK];
 #pragma unroll
@@ -371,7 +376,7 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_fwd_kernel(AttnArgs a, in
 
   FragOff<HD> fo;
   fo.init(lane, lds);
-  if (KS == 2) fo.hop(kh * 32 * G::ROWB);           // this wavefront's half of every tile
+  if (KS > 1) fo.hop((kh >> 1) * 2 * G::TILEB + (kh & 1) * 32 * G::ROWB);   // this wavefront's 32 keys of every step
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
@@ -380,56 +385,57 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_fwd_kernel(AttnArgs a, in
   // covers two tiles so that the buffer is a compile-time part of every LDS address.
   auto step = [&](int t, auto buf) {
     constexpr int BUF = decltype(buf)::value;
-    const int kv0 = t * TK, kvw = kv0 + kh * 32;     // first key of the tile, of the wavefront's part of it
+    const int kv0 = t * TS, kvw = kv0 + kh * 32;     // first key of the tile, of the wavefront's part of it
     const bool active = kvw < a.s && (!a.causal || kvw <= min(q0w + 32, a.s) - 1);
     if (active && q0w < a.s) {
       const bool need_mask = (a.causal && kvw + KW - 1 > q0w) || kvw + KW > a.s;
-      fwd_tile<HD, BUF, 2 / KS>(lds, fo, qf, o, m, l, kvw, q, hf, a.s, a.causal, sl2, need_mask);
+      fwd_tile<HD, BUF, KW / 32>(lds, fo, qf, o, m, l, kvw, q, hf, a.s, a.causal, sl2, need_mask);
     }
     __builtin_amdgcn_s_waitcnt(0);                  // tile t+1 has landed (issued a whole tile ago), own LDS reads done
     __syncthreads();
-    if (t + 2 < ntiles) {
-      tile_g2s<HD, FWD_THREADS>(lds + BUF + KT, rsK, off, a.ld, kv0 + 2 * TK, wave);
-      tile_g2s<HD, FWD_THREADS>(lds + BUF + VT, rsV, off, a.ld, kv0 + 2 * TK, wave);
-    }
+    if (t + 2 < nstep) fetch(BUF, kv0 + 2 * TS);
   };
-  for (int t = 0; t < ntiles; t += 2) {
+  for (int t = 0; t < nstep; t += 2) {
     step(t, std::integral_constant<int, 0>{});
-    if (t + 1 < ntiles) step(t + 1, std::integral_constant<int, BUFB>{});
+    if (t + 1 < nstep) step(t + 1, std::integral_constant<int, BUFB>{});
   }
 
   l = half_sum(l, hf);             // the lane 32 further on holds the row's other keys
-  if constexpr (KS == 2) {
-    // The loop's last barrier has passed: nobody reads the tiles any more and no load is in flight.  The second half's
-    // wavefront leaves its (O, m, l) in LDS ([piece][lane] of 16 bytes), the first half's folds them into its own.
-    constexpr int OB = G::NHB * 4 * 1024;            // bytes of one wavefront's O: NHB * 4 pieces of 16 bytes per lane
-    static_assert(2 * (OB + 512) <= 4 * G::TILEB, "the merge area fits the tile buffers");
-    lds_char* mo = lds + qb * (OB + 512) + lane * 16;
-    lds_char* ml = lds + qb * (OB + 512) + OB + lane * 8;
-    if (kh == 1) {
+  if constexpr (KS > 1) {
+    // The loop's last barrier has passed: nobody reads the tiles any more and no load is in flight.  The other key parts'
+    // wavefronts leave their (O, m, l) in LDS ([piece][lane] of 16 bytes), the first part's folds them into its own in order.
+    constexpr int OB = G::NHB * 4 * 1024, NQB = BQ / 32;   // bytes of one wavefront's O: NHB * 4 pieces of 16 bytes per lane
+    static_assert((KS - 1) * NQB * (OB + 512) <= 2 * BUFB, "the merge area fits the tile buffers");
+    auto area = [&](int part) { return lds + ((part - 1) * NQB + qb) * (OB + 512); };
+    if (kh > 0) {
+      lds_char* mo = area(kh) + lane * 16;
 #pragma unroll
       for (int hb = 0; hb < G::NHB; ++hb)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
           *(__attribute__((address_space(3))) f32x4*)(mo + (hb * 4 + q4) * 1024) =
               f32x4{o[hb][q4 * 4], o[hb][q4 * 4 + 1], o[hb][q4 * 4 + 2], o[hb][q4 * 4 + 3]};
-      *(__attribute__((address_space(3))) f32x2*)ml = f32x2{m, l};
+      *(__attribute__((address_space(3))) f32x2*)(area(kh) + OB + lane * 8) = f32x2{m, l};
     }
     __syncthreads();
-    if (kh == 1) return;
-    const f32x2 other = *(__attribute__((address_space(3))) const f32x2*)ml;
-    const float mn = fmaxf(m, other.x);
-    const float a0 = fast_exp2(m - mn), a1 = fast_exp2(other.x - mn);   // a half that saw no key has m = -1e30, l = 0, O = 0
-    l = l * a0 + other.y * a1;
+    if (kh > 0) return;
 #pragma unroll
-    for (int hb = 0; hb < G::NHB; ++hb)
+    for (int part = 1; part < KS; ++part) {
+      lds_char* mo = area(part) + lane * 16;
+      const f32x2 other = *(__attribute__((address_space(3))) const f32x2*)(area(part) + OB + lane * 8);
+      const float mn = fmaxf(m, other.x);
+      const float a0 = fast_exp2(m - mn), a1 = fast_exp2(other.x - mn);   // a part that saw no key has m = -1e30, l = 0, O = 0
+      l = l * a0 + other.y * a1;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const f32x4 v = *(__attribute__((address_space(3))) const f32x4*)(mo + (hb * 4 + q4) * 1024);
+      for (int hb = 0; hb < G::NHB; ++hb)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[hb][q4 * 4 + e] = o[hb][q4 * 4 + e] * a0 + v[e] * a1;
-      }
-    m = mn;
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const f32x4 v = *(__attribute__((address_space(3))) const f32x4*)(mo + (hb * 4 + q4) * 1024);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[hb][q4 * 4 + e] = o[hb][q4 * 4 + e] * a0 + v[e] * a1;
+        }
+      m = mn;
+    }
   }
   if (q < a.s) {
     const float inv = 1.f / l;
@@ -509,13 +515,14 @@ __device__ __forceinline__ void dq_block(lds_char* lds, const FragOff<HD>& fo, c
 template <int HD, int FWD_THREADS, int KS>
 __global__ __launch_bounds__(FWD_THREADS, 2) void attn_dq_kernel(AttnArgs a, int fold) {
   using G = Geo<HD>;
-  constexpr int KT = 0, VT = G::TILEB, BUFB = 2 * G::TILEB;   // two buffers of (K tile, V tile)
+  constexpr int SUB = KS == 4 ? 2 : 1, TS = TK * SUB;         // 64-key tiles, keys of one step
+  constexpr int KT = 0, VT = G::TILEB, BUFB = SUB * 2 * G::TILEB;   // two buffers of SUB (K tile, V tile) each
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   lds_char* lds = (lds_char*)smem_raw;
   const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int BQ = fwd_bq(FWD_THREADS, KS);
-  const int qb = KS == 2 ? wave >> 1 : wave, kh = KS == 2 ? wave & 1 : 0;   // query block, key half (as in the forward)
+  const int qb = wave / KS, kh = wave % KS;   // query block, key half (as in the forward)
   const int nqt = (a.s + BQ - 1) / BQ;
   const int qt = tile_of_rank(blockIdx.y / a.b, nqt, fold);   // slow grid index: heavy query tiles first
   const int j = blockIdx.x, ib = blockIdx.y % a.b;
@@ -530,15 +537,18 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_dq_kernel(AttnArgs a, int
   const int q = q0w + (lane & 31);
 
   const int last_q = min(q0b + BQ, a.s) - 1;
-  const int ntiles = a.causal ? last_q / TK + 1 : (a.s + TK - 1) / TK;
+  const int nstep = a.causal ? last_q / TS + 1 : (a.s + TS - 1) / TS;
   unsigned off[TK * G::PPR / FWD_THREADS];
   tile_offsets<HD, FWD_THREADS>(off, a.ld, wave, lane);
-  tile_g2s<HD, FWD_THREADS>(lds + KT, rsK, off, a.ld, 0, wave);
-  tile_g2s<HD, FWD_THREADS>(lds + VT, rsV, off, a.ld, 0, wave);
-  if (ntiles > 1) {
-    tile_g2s<HD, FWD_THREADS>(lds + BUFB + KT, rsK, off, a.ld, TK, wave);
-    tile_g2s<HD, FWD_THREADS>(lds + BUFB + VT, rsV, off, a.ld, TK, wave);
-  }
+  auto fetch = [&](int buf, int row0) {
+#pragma unroll
+    for (int u = 0; u < SUB; ++u) {
+      tile_g2s<HD, FWD_THREADS>(lds + buf + u * 2 * G::TILEB + KT, rsK, off, a.ld, row0 + u * TK, wave);
+      tile_g2s<HD, FWD_THREADS>(lds + buf + u * 2 * G::TILEB + VT, rsV, off, a.ld, row0 + u * TK, wave);
+    }
+  };
+  fetch(0, 0);
+  if (nstep > 1) fetch(BUFB, TS);
 
   bf16x8 qf[G::NKK], dof[G::NKK];
 #pragma unroll
@@ -576,18 +586,18 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_dq_kernel(AttnArgs a, int
 
   FragOff<HD> fo;
   fo.init(lane, lds);
-  if (KS == 2) fo.hop(kh * 32 * G::ROWB);           // this wavefront's half of every tile
+  if (KS > 1) fo.hop((kh >> 1) * 2 * G::TILEB + (kh & 1) * 32 * G::ROWB);   // this wavefront's 32 keys of every step
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
   // two tiles per loop body, so that the buffer is a compile-time part of every LDS address
   auto step = [&](int t, auto buf) {
     constexpr int BUF = decltype(buf)::value;
-    const int kv0 = t * TK;
+    const int kv0 = t * TS;
     const int kvw = kv0 + kh * 32;                    // first key of the wavefront's part of the tile
     const bool active = kvw < a.s && (!a.causal || kvw <= min(q0w + 32, a.s) - 1);
     if (active && q0w < a.s) {
-      if constexpr (KS == 2) {
+      if constexpr (KS > 1) {
         const bool need_mask = (a.causal && kvw + 31 > q0w) || kvw + 32 > a.s;
         dq_block<HD, BUF>(lds, fo, qf, dof, dq, 0, kvw, q, hf, a.s, a.causal, sl2, lse2, ndl, need_mask);
       } else {
@@ -601,20 +611,18 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_dq_kernel(AttnArgs a, int
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (t + 2 < ntiles) {
-      tile_g2s<HD, FWD_THREADS>(lds + BUF + KT, rsK, off, a.ld, kv0 + 2 * TK, wave);
-      tile_g2s<HD, FWD_THREADS>(lds + BUF + VT, rsV, off, a.ld, kv0 + 2 * TK, wave);
-    }
+    if (t + 2 < nstep) fetch(BUF, kv0 + 2 * TS);
   };
-  for (int t = 0; t < ntiles; t += 2) {
+  for (int t = 0; t < nstep; t += 2) {
     step(t, std::integral_constant<int, 0>{});
-    if (t + 1 < ntiles) step(t + 1, std::integral_constant<int, BUFB>{});
+    if (t + 1 < nstep) step(t + 1, std::integral_constant<int, BUFB>{});
   }
 
-  if constexpr (KS == 2) {      // add the second key half's dQ to the first's, through LDS (the tiles are no longer read)
-    static_assert(2 * G::NHB * 4 * 1024 <= 4 * G::TILEB, "the merge area fits the tile buffers");
-    lds_char* mo = lds + qb * (G::NHB * 4 * 1024) + lane * 16;
-    if (kh == 1) {
+  if constexpr (KS > 1) {      // add the other key parts' dQ to the first's, in order, through LDS (the tiles are no longer read)
+    constexpr int OB = G::NHB * 4 * 1024, NQB = BQ / 32;
+    static_assert((KS - 1) * NQB * OB <= 2 * BUFB, "the merge area fits the tile buffers");
+    if (kh > 0) {
+      lds_char* mo = lds + ((kh - 1) * NQB + qb) * OB + lane * 16;
 #pragma unroll
       for (int hb = 0; hb < G::NHB; ++hb)
 #pragma unroll
@@ -623,15 +631,19 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_dq_kernel(AttnArgs a, int
               f32x4{dq[hb][q4 * 4], dq[hb][q4 * 4 + 1], dq[hb][q4 * 4 + 2], dq[hb][q4 * 4 + 3]};
     }
     __syncthreads();
-    if (kh == 1) return;
+    if (kh > 0) return;
 #pragma unroll
-    for (int hb = 0; hb < G::NHB; ++hb)
+    for (int part = 1; part < KS; ++part) {
+      lds_char* mo = lds + ((part - 1) * NQB + qb) * OB + lane * 16;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const f32x4 v = *(__attribute__((address_space(3))) const f32x4*)(mo + (hb * 4 + q4) * 1024);
+      for (int hb = 0; hb < G::NHB; ++hb)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) dq[hb][q4 * 4 + e] += v[e];
-      }
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const f32x4 v = *(__attribute__((address_space(3))) const f32x4*)(mo + (hb * 4 + q4) * 1024);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dq[hb][q4 * 4 + e] += v[e];
+        }
+    }
   }
   if (q < a.s) {
     bf16* row = (bf16*)a.dqkv + ((int64_t)ib * a.s + q) * a.ld + j * HD;
@@ -663,7 +675,8 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_dq_kernel(AttnArgs a, int
 // LDS directly, two buffers, one barrier per tile).
 // ---------------------------------------------------------------------------
 // TQ = keys per workgroup = queries per tile: 128 (8 wavefronts, one workgroup per CU) or, for small grids, 64
-// (4 wavefronts, two workgroups per CU: twice as many workgroups for the same number of resident wavefronts)
+// (4 wavefronts, two workgroups per CU: twice as many workgroups for the same number of resident wavefronts).  QS = 2: two pairs
+// of wavefronts per key block, one on the even and one on the odd 32-query blocks, their sums added through LDS at the end.
 constexpr int DKV_TQ = 128, DKV_TQ_SMALL = 64;
 // early key tiles see the most queries: plain order is kt = rank; folded (see tile_of_rank) the heavy half first, then
 // the light half, lightest first
@@ -710,17 +723,17 @@ __device__ __forceinline__ void dkv_tr_product(lds_char* lds, const FragOff<HD>&
   }
 }
 
-template <int HD, int TQ>
-__global__ __launch_bounds__(TQ * 4, 2) void attn_dkv_kernel(AttnArgs a, int nsplit, int fold) {
+template <int HD, int TQ, int QS>
+__global__ __launch_bounds__(TQ * 4 * QS, QS == 2 && HD == 64 ? 4 : 2) void attn_dkv_kernel(AttnArgs a, int nsplit, int fold) {
   using G = Geo<HD>;
-  constexpr int NTHR = TQ * 4, NB = TQ / 32, NKW = TQ / 32, TILEB = TQ * G::ROWB;   // NKW key blocks, two wavefronts each
+  constexpr int NTHR = TQ * 4 * QS, NB = TQ / 32 / QS, NKW = TQ / 32, TILEB = TQ * G::ROWB;   // NKW key blocks, QS pairs of wavefronts each; NB query blocks per pair and tile
   // two buffers of (Q tile, dO tile, lse of the tile's queries, delta of the tile's queries)
   constexpr int QT = 0, OT = TILEB, LT = 2 * TILEB, DT = LT + TQ * 4, BUFB = DT + TQ * 4;
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   lds_char* lds = (lds_char*)smem_raw;
   const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int role = wave / NKW, kw = wave % NKW;          // role 0: dV and the producer of P (on the older wavefront), role 1: dK; with 8 wavefronts kw and kw+4 share a SIMD
+  const int role = wave / (NKW * QS), kw = wave % NKW, qs = QS == 2 ? (wave / NKW) % 2 : 0;   // role 0: dV and the producer of P (on the older wavefront), role 1: dK; with 8 wavefronts kw and kw+4 share a SIMD
   const int nkt = (a.s + TQ - 1) / TQ;
   const int kt = key_tile_of_rank(blockIdx.y / a.b, nkt, fold);   // slow grid index: heavy (early) key tiles first
   // grid.x = KV heads x splits: this workgroup takes `grp` of the query heads of KV head g, starting at head j0
@@ -781,15 +794,16 @@ __global__ __launch_bounds__(TQ * 4, 2) void attn_dkv_kernel(AttnArgs a, int nsp
 
   FragOff<HD> fo;
   fo.init(lane, lds);
+  if (QS == 2) fo.hop(qs * 32 * G::ROWB);             // the pair's query blocks: every second one
   lds_char* cur = lds;                                // buffer being read, refilled after the barrier (wave-uniform)
-  lds_char* ldp = lds + LT + hf * 16;                 // this lane's lse values of the current buffer; delta follows TQ*4 later
+  lds_char* ldp = lds + LT + hf * 16 + qs * 128;                 // this lane's lse values of the current buffer; delta follows TQ*4 later
   int hopb = BUFB;
   typedef __attribute__((address_space(3))) const f32x4* lds_f4;
   // the pair's P slot ([e4][lane] f32x4) and its counts: produced = blocks written, consumed = blocks read
-  lds_char* pslot = lds + 2 * BUFB + kw * 4096 + lane * 16;
-  volatile __attribute__((address_space(3))) int* produced = (volatile __attribute__((address_space(3))) int*)(lds + 2 * BUFB + NKW * 4096) + kw;
-  volatile __attribute__((address_space(3))) int* consumed = produced + NKW;
-  if (tid < 2 * NKW) ((volatile __attribute__((address_space(3))) int*)(lds + 2 * BUFB + NKW * 4096))[tid] = 0;   // published by the barrier below
+  lds_char* pslot = lds + 2 * BUFB + (qs * NKW + kw) * 4096 + lane * 16;
+  volatile __attribute__((address_space(3))) int* produced = (volatile __attribute__((address_space(3))) int*)(lds + 2 * BUFB + QS * NKW * 4096) + qs * NKW + kw;
+  volatile __attribute__((address_space(3))) int* consumed = produced + QS * NKW;
+  if (tid < 2 * QS * NKW) ((volatile __attribute__((address_space(3))) int*)(lds + 2 * BUFB + QS * NKW * 4096))[tid] = 0;   // published by the barrier below
   auto wait_for = [&](volatile __attribute__((address_space(3))) int* count, int value) {
     for (int guard = 0; *count != value && guard < (1 << 20); ++guard) __builtin_amdgcn_s_sleep(1);
     asm volatile("" ::: "memory");                       // nothing of what follows is read or written ahead of the wait
@@ -835,22 +849,22 @@ __global__ __launch_bounds__(TQ * 4, 2) void attn_dkv_kernel(AttnArgs a, int nsp
     for (int it = 0; it < niter; ++it) {
       const int q0 = (t_first + it % per_head) * TQ;
       const bool diag = a.causal && it % per_head == 0;          // wave-uniform
-      const int lim0 = key - q0 - hf * 4;
+      const int lim0 = key - q0 - hf * 4 - qs * 32;
 #pragma unroll
       for (int qc = 0; qc < NB; ++qc) {
         f32x4 l4[4];
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) l4[e4] = *reinterpret_cast<lds_f4>(ldp + (qc * 32 + e4 * 8) * 4);
+        for (int e4 = 0; e4 < 4; ++e4) l4[e4] = *reinterpret_cast<lds_f4>(ldp + (qc * QS * 32 + e4 * 8) * 4);
         f32x16 sacc;
-        dkv_rows_product<HD, QT>(lds, fo, qc * 32, kf, sacc);
+        dkv_rows_product<HD, QT>(lds, fo, qc * QS * 32, kf, sacc);
         bf16x8 tf[4];
-        dkv_tr_read<HD, OT>(lds, fo, qc * 32, tf);
+        dkv_tr_read<HD, OT>(lds, fo, qc * QS * 32, tf);
         SCHED_FENCE;
         float p[16];
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
           float pv[4];
-          probs4(sacc, l4[e4], qc, e4, diag, lim0, pv);
+          probs4(sacc, l4[e4], qc * QS, e4, diag, lim0, pv);
 #pragma unroll
           for (int e = 0; e < 4; ++e) p[e4 * 4 + e] = pv[e];
         }
@@ -863,7 +877,7 @@ __global__ __launch_bounds__(TQ * 4, 2) void attn_dkv_kernel(AttnArgs a, int nsp
         asm volatile("" ::: "memory");
         const bf16x8 pf[2] = {pack8(&p[0]), pack8(&p[8])};
         SCHED_FENCE;
-        dkv_tr_product<HD, OT>(lds, fo, qc * 32, tf, pf, acc);          // dV^T += dO^T . P
+        dkv_tr_product<HD, OT>(lds, fo, qc * QS * 32, tf, pf, acc);          // dV^T += dO^T . P
       }
       turn(it);
     }
@@ -879,13 +893,13 @@ __global__ __launch_bounds__(TQ * 4, 2) void attn_dkv_kernel(AttnArgs a, int nsp
         f32x16 pacc;                                    // starts at -delta of the block's queries
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
-          const f32x4 d4 = *reinterpret_cast<lds_f4>(ldp + (DT - LT) + (qc * 32 + e4 * 8) * 4);
+          const f32x4 d4 = *reinterpret_cast<lds_f4>(ldp + (DT - LT) + (qc * QS * 32 + e4 * 8) * 4);
 #pragma unroll
           for (int e = 0; e < 4; ++e) pacc[e4 * 4 + e] = d4[e];
         }
-        dkv_rows_product<HD, OT, true>(lds, fo, qc * 32, vf, pacc);               // dP - delta = dO.V^T - delta
+        dkv_rows_product<HD, OT, true>(lds, fo, qc * QS * 32, vf, pacc);               // dP - delta = dO.V^T - delta
         bf16x8 tf[4];
-        dkv_tr_read<HD, QT>(lds, fo, qc * 32, tf);
+        dkv_tr_read<HD, QT>(lds, fo, qc * QS * 32, tf);
         SCHED_FENCE;
         wait_for(produced, nblk + 1);                  // the partner has left this block's P (masked where causal) in the slot
         f32x4 pv[4];
@@ -902,10 +916,33 @@ __global__ __launch_bounds__(TQ * 4, 2) void attn_dkv_kernel(AttnArgs a, int nsp
         }
         const bf16x8 df[2] = {pack8(&ds[0]), pack8(&ds[8])};
         SCHED_FENCE;
-        dkv_tr_product<HD, QT>(lds, fo, qc * 32, tf, df, acc);          // dK^T += Q^T . dS
+        dkv_tr_product<HD, QT>(lds, fo, qc * QS * 32, tf, df, acc);          // dK^T += Q^T . dS
       }
       turn(it);
     }
+  }
+
+  if constexpr (QS == 2) {       // add the second pair's sums to the first's, through LDS (the last barrier has passed: the tiles are no longer read)
+    static_assert(2 * NKW * G::NHB * 4 * 1024 <= 2 * BUFB, "the merge area fits the tile buffers");
+    lds_char* mo = lds + (role * NKW + kw) * (G::NHB * 4 * 1024) + lane * 16;
+    if (qs == 1) {
+#pragma unroll
+      for (int hb = 0; hb < G::NHB; ++hb)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          *(__attribute__((address_space(3))) f32x4*)(mo + (hb * 4 + q4) * 1024) =
+              f32x4{acc[hb][q4 * 4], acc[hb][q4 * 4 + 1], acc[hb][q4 * 4 + 2], acc[hb][q4 * 4 + 3]};
+    }
+    __syncthreads();
+    if (qs == 1) return;
+#pragma unroll
+    for (int hb = 0; hb < G::NHB; ++hb)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const f32x4 v = *(__attribute__((address_space(3))) const f32x4*)(mo + (hb * 4 + q4) * 1024);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[hb][q4 * 4 + e] += v[e];
+      }
   }
 
   // role 0 holds dV, role 1 holds dK (still to be scaled)
@@ -954,8 +991,8 @@ __global__ __launch_bounds__(256) void attn_dkv_reduce_kernel(AttnArgs a, int ns
 }
 
 // dynamic LDS of the kernels above
-template <int HD> constexpr size_t fwd_lds() { return (size_t)4 * Geo<HD>::TILEB; }
-template <int HD, int TQ> constexpr size_t dkv_lds() { return (size_t)2 * (2 * TQ * Geo<HD>::ROWB + 2 * TQ * 4) + (TQ / 32) * 4096 + 64; }   // + P slots and counts
+template <int HD, int KS> constexpr size_t fwd_lds() { return (size_t)(KS == 4 ? 8 : 4) * Geo<HD>::TILEB; }
+template <int HD, int TQ, int QS> constexpr size_t dkv_lds() { return (size_t)2 * (2 * TQ * Geo<HD>::ROWB + 2 * TQ * 4) + QS * (TQ / 32) * 4096 + 64; }   // + P slots and counts
 
 template <typename K>
 hipError_t allow_lds(K kern, size_t bytes) {
@@ -970,24 +1007,31 @@ constexpr int64_t RESIDENT = 2 * 256;
 // Forward / dQ workgroup shape: 8 wavefronts x 32 queries when that gives two workgroups per CU (they read every K/V
 // tile once for twice the queries); else 4 x 32 queries; else (still under two per CU) 64 queries with the key range of
 // each query block split over two wavefronts.
-enum FwdShape { SHAPE_WIDE = 1, SHAPE_NARROW = 2, SHAPE_SPLIT = 3 };
+enum FwdShape { SHAPE_WIDE = 1, SHAPE_NARROW = 2, SHAPE_SPLIT = 3, SHAPE_SPLIT4 = 4 };
 static int64_t fwd_count(const AttnArgs& a, int bq) { return (int64_t)a.b * a.h * ((a.s + bq - 1) / bq); }
-static FwdShape fwd_shape(const AttnArgs& a) {
-  if (a.width >= 1 && a.width <= 3) return (FwdShape)a.width;
+// Four key parts instead of two (8 wavefronts on 64 queries, two to a SIMD where there was one) once there are steps enough to
+// halve: the merge and the longer start cost more below.  Measured (us, two parts / four; heads x positions): forward, head_dim
+// 128 8 x 1024 17.9 / 16.5, 8 x 2048 30.8 / 26.0, but 16 x 700 14.2 / 14.3, 8 x 512 11.5 / 11.8; head_dim 64 16 x 1024 12.7 / 11.1, 16 x 2048 22.6 /
+// 19.3, but 36 x 777 11.4 / 11.9.  dQ, whose registers allow one such workgroup per CU: 8 x 2048 32.0 / 30.5, 4 x 4096 55.8 / 50.8, but
+// 8 x 1024 19.3 / 20.4, and head_dim 64 in 512 workgroups 23.1 / 29.0.
+static FwdShape fwd_shape(const AttnArgs& a, bool dq = false) {
+  if (a.width >= 1 && a.width <= 4) return (FwdShape)a.width;
   if (fwd_count(a, fwd_bq(FWD_WIDE)) >= RESIDENT) return SHAPE_WIDE;
   if (fwd_count(a, fwd_bq(FWD_NARROW)) >= RESIDENT) return SHAPE_NARROW;
-  return SHAPE_SPLIT;
+  const bool resident = fwd_count(a, fwd_bq(FWD_WIDE, 4)) <= (a.hd == 64 && !dq ? RESIDENT : RESIDENT / 2);
+  return resident && a.s >= (dq ? 2048 : 1000) ? SHAPE_SPLIT4 : SHAPE_SPLIT;
 }
 
 template <int HD, int NT, int KS>
 hipError_t fwd_launch(const AttnArgs& a, hipStream_t s) {
-  static const hipError_t ready = allow_lds(attn_fwd_kernel<HD, NT, KS>, fwd_lds<HD>());
+  constexpr size_t lds_bytes = fwd_lds<HD, KS>();
+  static const hipError_t ready = allow_lds(attn_fwd_kernel<HD, NT, KS>, lds_bytes);
   if (ready != hipSuccess) return ready;
   const int nqt = (a.s + fwd_bq(NT, KS) - 1) / fwd_bq(NT, KS);
   // 4-wavefront workgroups sit two to a CU: when the whole grid is resident at once, pair heavy with light.  (8-wavefront
   // ones sit one to a CU and come in two rounds or more: heaviest first, and the light ones fill in behind.)
-  const int fold = NT == FWD_NARROW && a.causal && (int64_t)a.b * a.h * nqt <= RESIDENT;
-  hipLaunchKernelGGL((attn_fwd_kernel<HD, NT, KS>), dim3(a.h, nqt * a.b), dim3(NT), fwd_lds<HD>(), s, a, fold);
+  const int fold = (NT == FWD_NARROW || KS == 4) && a.causal && (int64_t)a.b * a.h * nqt <= RESIDENT;
+  hipLaunchKernelGGL((attn_fwd_kernel<HD, NT, KS>), dim3(a.h, nqt * a.b), dim3(NT), lds_bytes, s, a, fold);
   return hipGetLastError();
 }
 template <int HD>
@@ -995,17 +1039,19 @@ hipError_t fwd_t(const AttnArgs& a, hipStream_t s) {
   switch (fwd_shape(a)) {
     case SHAPE_WIDE: return fwd_launch<HD, FWD_WIDE, 1>(a, s);
     case SHAPE_NARROW: return fwd_launch<HD, FWD_NARROW, 1>(a, s);
-    default: return fwd_launch<HD, FWD_NARROW, 2>(a, s);
+    case SHAPE_SPLIT: return fwd_launch<HD, FWD_NARROW, 2>(a, s);
+    default: return fwd_launch<HD, FWD_WIDE, 4>(a, s);
   }
 }
 
 template <int HD, int NT, int KS>
 hipError_t dq_launch(const AttnArgs& a, hipStream_t s) {
-  static const hipError_t ready = allow_lds(attn_dq_kernel<HD, NT, KS>, fwd_lds<HD>());
+  constexpr size_t lds_bytes = fwd_lds<HD, KS>();
+  static const hipError_t ready = allow_lds(attn_dq_kernel<HD, NT, KS>, lds_bytes);
   if (ready != hipSuccess) return ready;
   const int nqt = (a.s + fwd_bq(NT, KS) - 1) / fwd_bq(NT, KS);
-  const int fold = NT == FWD_NARROW && a.causal && (int64_t)a.b * a.h * nqt <= RESIDENT;      // as in the forward
-  hipLaunchKernelGGL((attn_dq_kernel<HD, NT, KS>), dim3(a.h, nqt * a.b), dim3(NT), fwd_lds<HD>(), s, a, fold);
+  const int fold = (NT == FWD_NARROW || KS == 4) && a.causal && (int64_t)a.b * a.h * nqt <= RESIDENT;      // as in the forward
+  hipLaunchKernelGGL((attn_dq_kernel<HD, NT, KS>), dim3(a.h, nqt * a.b), dim3(NT), lds_bytes, s, a, fold);
   return hipGetLastError();
 }
 
@@ -1024,20 +1070,20 @@ static int dkv_splits(int b, int s, int h, int hkv, int tq) {
 }
 // 64-key workgroups when 128-key ones, split as far as they go, still number fewer than two per CU
 static bool dkv_small(int b, int s, int h, int hkv, int width) {
-  if (width) return width == 3;
+  if (width) return width >= 3;
   return (int64_t)b * hkv * ((s + DKV_TQ - 1) / DKV_TQ) * dkv_splits(b, s, h, hkv, DKV_TQ) < RESIDENT;
 }
 
-template <int HD, int TQ>
+template <int HD, int TQ, int QS>
 hipError_t dkv_launch(const AttnArgs& a, hipStream_t s) {
-  constexpr size_t lds_bytes = dkv_lds<HD, TQ>();
-  static const hipError_t ready = allow_lds(attn_dkv_kernel<HD, TQ>, lds_bytes);
+  constexpr size_t lds_bytes = dkv_lds<HD, TQ, QS>();
+  static const hipError_t ready = allow_lds(attn_dkv_kernel<HD, TQ, QS>, lds_bytes);
   if (ready != hipSuccess) return ready;
   const int nsplit = a.dkv_part ? dkv_splits(a.b, a.s, a.h, a.hkv, TQ) : 1;
   const int nkt = (a.s + TQ - 1) / TQ;
   // two 64-key workgroups share a CU: when all are resident at once, pair heavy key tiles with light ones
   const int fold = TQ == DKV_TQ_SMALL && a.causal && (int64_t)a.b * a.hkv * nsplit * nkt <= RESIDENT;
-  hipLaunchKernelGGL((attn_dkv_kernel<HD, TQ>), dim3(a.hkv * nsplit, nkt * a.b), dim3(TQ * 4), lds_bytes, s, a, nsplit, fold);
+  hipLaunchKernelGGL((attn_dkv_kernel<HD, TQ, QS>), dim3(a.hkv * nsplit, nkt * a.b), dim3(TQ * 4 * QS), lds_bytes, s, a, nsplit, fold);
   if (nsplit > 1) {
     const int64_t pieces = (int64_t)a.b * a.s * (2 * a.hkv * HD / 4);
     hipLaunchKernelGGL(attn_dkv_reduce_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, a, nsplit, a.h * HD, a.hkv * HD);
@@ -1048,13 +1094,20 @@ hipError_t dkv_launch(const AttnArgs& a, hipStream_t s) {
 template <int HD>
 hipError_t bwd_t(const AttnArgs& a, hipStream_t s) {
   hipError_t e;      // dQ first: it also leaves delta = rowsum(dO * O) in a.delta for the dK/dV pass
-  switch (fwd_shape(a)) {
+  switch (fwd_shape(a, true)) {
     case SHAPE_WIDE: e = dq_launch<HD, FWD_WIDE, 1>(a, s); break;
     case SHAPE_NARROW: e = dq_launch<HD, FWD_NARROW, 1>(a, s); break;
-    default: e = dq_launch<HD, FWD_NARROW, 2>(a, s); break;
+    case SHAPE_SPLIT: e = dq_launch<HD, FWD_NARROW, 2>(a, s); break;
+    default: e = dq_launch<HD, FWD_WIDE, 4>(a, s); break;
   }
   if (e != hipSuccess) return e;
-  return dkv_small(a.b, a.s, a.h, a.hkv, a.width) ? dkv_launch<HD, DKV_TQ_SMALL>(a, s) : dkv_launch<HD, DKV_TQ>(a, s);
+  if (!dkv_small(a.b, a.s, a.h, a.hkv, a.width)) return dkv_launch<HD, DKV_TQ, 1>(a, s);
+  // Two pairs of wavefronts per 32 keys, each on every second 32 queries, where that many 8-wavefront workgroups are resident at once
+  // and there is more than a handful of query tiles.  Measured (us, one pair / two; heads x positions): head_dim 128 8 x 512 17.8 / 16.3,
+  // 16 x 1024 31.0 / 26.0, 8 x 2048 54.5 / 42.1; head_dim 64 36 x 777 22.1 / 19.5, 16 x 2048 44.3 / 36.5; but 10 x 200 11.7 / 11.9.
+  const int64_t wgs = (int64_t)a.b * a.hkv * ((a.s + DKV_TQ_SMALL - 1) / DKV_TQ_SMALL) * (a.dkv_part ? dkv_splits(a.b, a.s, a.h, a.hkv, DKV_TQ_SMALL) : 1);
+  const bool two = a.width ? a.width == 4 : a.s > 320 && wgs <= (HD == 64 ? RESIDENT : RESIDENT / 2);
+  return two ? dkv_launch<HD, DKV_TQ_SMALL, 2>(a, s) : dkv_launch<HD, DKV_TQ_SMALL, 1>(a, s);
 }
 
 }  // namespace
