@@ -18,7 +18,8 @@
  * forward: 128 x 64 for 5; weight gradients: 64 x 64 for 6); in fp32 2 / 3 / 4 = tiles of 64 x 64 / 32 x 32 / 16 x 16 (weight gradients: 32 x 32 for 4);
  * attention: 2 / 3 = forward and dQ workgroups of 8 / 4 wavefronts (dK/dV workgroups of 128 keys), 4 = forward and dQ
  * workgroups of 64 queries whose two wavefronts per query block each take half of the keys, dK/dV workgroups of 64 keys, 5 = the
- * same with four wavefronts per query block and, in dK/dV, two pairs of wavefronts per key block.
+ * same with four wavefronts per query block and, in dK/dV, two pairs of wavefronts per key block, 6 / 7 = the backward of 4 / 5 as
+ * one launch.
  * Return: 0, or STAGE_E_INVAL for
  * a shape the kernel does not take, STAGE_E_HIP for a failed launch.
  */

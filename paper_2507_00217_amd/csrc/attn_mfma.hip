@@ -513,19 +513,17 @@ __device__ __forceinline__ void dq_block(lds_char* lds, const FragOff<HD>& fo, c
 // wavefront's exp / dS arithmetic overlaps the other's MFMAs
 // ---------------------------------------------------------------------------
 template <int HD, int FWD_THREADS, int KS>
-__global__ __launch_bounds__(FWD_THREADS, 2) void attn_dq_kernel(AttnArgs a, int fold) {
+__device__ __forceinline__ void dq_workgroup(const AttnArgs& a, int fold, lds_char* lds, int bx, int by) {
   using G = Geo<HD>;
   constexpr int SUB = KS == 4 ? 2 : 1, TS = TK * SUB;         // 64-key tiles, keys of one step
   constexpr int KT = 0, VT = G::TILEB, BUFB = SUB * 2 * G::TILEB;   // two buffers of SUB (K tile, V tile) each
-  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
-  lds_char* lds = (lds_char*)smem_raw;
   const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int BQ = fwd_bq(FWD_THREADS, KS);
   const int qb = wave / KS, kh = wave % KS;   // query block, key half (as in the forward)
   const int nqt = (a.s + BQ - 1) / BQ;
-  const int qt = tile_of_rank(blockIdx.y / a.b, nqt, fold);   // slow grid index: heavy query tiles first
-  const int j = blockIdx.x, ib = blockIdx.y % a.b;
+  const int qt = tile_of_rank(by / a.b, nqt, fold);   // slow grid index: heavy query tiles first
+  const int j = bx, ib = by % a.b;
   const int d = a.h * HD, dkv = a.hkv * HD, g = j / (a.h / a.hkv);
   const bf16* base = (const bf16*)a.qkv + (int64_t)ib * a.s * a.ld;
   const bf16* qp = base + j * HD;
@@ -658,6 +656,11 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void attn_dq_kernel(AttnArgs a, int
       }
   }
 }
+template <int HD, int FWD_THREADS, int KS>
+__global__ __launch_bounds__(FWD_THREADS, 2) void attn_dq_kernel(AttnArgs a, int fold) {
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  dq_workgroup<HD, FWD_THREADS, KS>(a, fold, (lds_char*)smem_raw, blockIdx.x, blockIdx.y);
+}
 
 // ---------------------------------------------------------------------------
 // dK/dV: one workgroup = 128 keys of one (sequence, kv head) = 4 key blocks of 32, each worked on by TWO wavefronts
@@ -723,21 +726,20 @@ __device__ __forceinline__ void dkv_tr_product(lds_char* lds, const FragOff<HD>&
   }
 }
 
-template <int HD, int TQ, int QS>
-__global__ __launch_bounds__(TQ * 4 * QS, QS == 2 && HD == 64 ? 4 : 2) void attn_dkv_kernel(AttnArgs a, int nsplit, int fold) {
+// OWN_DELTA: delta is formed here, from dO and O (which the dQ pass, running at the same time, cannot provide)
+template <int HD, int TQ, int QS, bool OWN_DELTA>
+__device__ __forceinline__ void dkv_workgroup(const AttnArgs& a, int nsplit, int fold, lds_char* lds, int bx, int by) {
   using G = Geo<HD>;
   constexpr int NTHR = TQ * 4 * QS, NB = TQ / 32 / QS, NKW = TQ / 32, TILEB = TQ * G::ROWB;   // NKW key blocks, QS pairs of wavefronts each; NB query blocks per pair and tile
   // two buffers of (Q tile, dO tile, lse of the tile's queries, delta of the tile's queries)
   constexpr int QT = 0, OT = TILEB, LT = 2 * TILEB, DT = LT + TQ * 4, BUFB = DT + TQ * 4;
-  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
-  lds_char* lds = (lds_char*)smem_raw;
   const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int role = wave / (NKW * QS), kw = wave % NKW, qs = QS == 2 ? (wave / NKW) % 2 : 0;   // role 0: dV and the producer of P (on the older wavefront), role 1: dK; with 8 wavefronts kw and kw+4 share a SIMD
   const int nkt = (a.s + TQ - 1) / TQ;
-  const int kt = key_tile_of_rank(blockIdx.y / a.b, nkt, fold);   // slow grid index: heavy (early) key tiles first
+  const int kt = key_tile_of_rank(by / a.b, nkt, fold);   // slow grid index: heavy (early) key tiles first
   // grid.x = KV heads x splits: this workgroup takes `grp` of the query heads of KV head g, starting at head j0
-  const int g = blockIdx.x / nsplit, sp = blockIdx.x % nsplit, ib = blockIdx.y % a.b;
+  const int g = bx / nsplit, sp = bx % nsplit, ib = by % a.b;
   const int d = a.h * HD, dkv = a.hkv * HD, grp = a.h / a.hkv / nsplit, j0 = g * (a.h / a.hkv) + sp * grp;
   const bf16* base = (const bf16*)a.qkv + (int64_t)ib * a.s * a.ld;
   const bf16* dobase = (const bf16*)a.dout + (int64_t)ib * a.s * d;
@@ -769,6 +771,7 @@ __global__ __launch_bounds__(TQ * 4 * QS, QS == 2 && HD == 64 ? 4 : 2) void attn
   };
   // iteration `it` = (query head jj of the group, query tile t): its Q and dO tiles -> buffer at `buf`, lse and delta -> registers
   float stat_l = 0.f, stat_d = 0.f;
+  bf16x8 of[OWN_DELTA ? NLD : 1];
   auto fetch = [&](int it, lds_char* buf) {
     const int jj = it / per_head, t = t_first + it % per_head;
     const int j = j0 + jj;
@@ -778,18 +781,50 @@ __global__ __launch_bounds__(TQ * 4 * QS, QS == 2 && HD == 64 ? 4 : 2) void attn
       const int qi = t * TQ + wave * 64 + lane;
       const int64_t row = ((int64_t)ib * a.h + j) * a.s;
       stat_l = qi < a.s ? a.lse[row + qi] : 0.f;
-      stat_d = qi < a.s ? a.delta[row + qi] : 0.f;
+      if (!OWN_DELTA) stat_d = qi < a.s ? a.delta[row + qi] : 0.f;
+    }
+    if constexpr (OWN_DELTA) {      // the pieces of O that go with the pieces of dO this thread has just asked for
+      const bf16* oh = (const bf16*)a.o + (int64_t)ib * a.s * d + j * HD;
+      const int sl = wave * 64 + lane, c = (sl % G::PPR) ^ G::swz(sl / G::PPR);
+#pragma unroll
+      for (int n = 0; n < NLD; ++n) {
+        const int r = t * TQ + n * SWEEP + sl / G::PPR;
+        of[n] = *reinterpret_cast<const bf16x8*>(oh + (int64_t)min(r, a.s - 1) * d + c * 8);     // (dO is zero past the end)
+      }
     }
   };
   // the statistics of the tile fetched last, as the two roles use them: -log2 e * lse and -delta, formed once per tile
   // (in the dV wavefronts 16 multiplications per 32 x 32 block otherwise)
-  auto put_stats = [&](lds_char* buf) {
+  auto put_stats = [&](lds_char* buf, int q_of) {
     if (wave < TQ / 64) {
       *(__attribute__((address_space(3))) float*)(buf + LT + (wave * 64 + lane) * 4) = -LOG2E * stat_l;
-      *(__attribute__((address_space(3))) float*)(buf + DT + (wave * 64 + lane) * 4) = -stat_d;
+      if (!OWN_DELTA) *(__attribute__((address_space(3))) float*)(buf + DT + (wave * 64 + lane) * 4) = -stat_d;
+    }
+    if constexpr (OWN_DELTA) {
+      // own loads only, so no barrier: thread and piece correspond as in tile_fetch, PPR lanes hold a row
+      __builtin_amdgcn_s_waitcnt(0);
+      float part[NLD];
+#pragma unroll
+      for (int n = 0; n < NLD; ++n) {
+        const bf16x8 dv = *(__attribute__((address_space(3))) const bf16x8*)(buf + OT + (n * (NTHR / 64) + wave) * 1024 + lane * 16);
+        part[n] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) part[n] = fmaf((float)dv[e], (float)of[n][e], part[n]);
+      }
+#pragma unroll
+      for (int x = 1; x < G::PPR; x <<= 1)
+#pragma unroll
+        for (int n = 0; n < NLD; ++n) part[n] += __shfl_xor(part[n], x);
+      if (lane % G::PPR == 0) {
+#pragma unroll
+        for (int n = 0; n < NLD; ++n) {
+          const int r = n * SWEEP + (wave * 64 + lane) / G::PPR;
+          *(__attribute__((address_space(3))) float*)(buf + DT + r * 4) = q_of + r < a.s ? -part[n] : 0.f;
+        }
+      }
     }
   };
-  if (niter > 0) { fetch(0, lds); put_stats(lds); }
+  if (niter > 0) { fetch(0, lds); put_stats(lds, t_first * TQ); }
   if (niter > 1) fetch(1, lds + BUFB);
 
   FragOff<HD> fo;
@@ -812,7 +847,7 @@ __global__ __launch_bounds__(TQ * 4 * QS, QS == 2 && HD == 64 ? 4 : 2) void attn
 
   // end of an iteration: the next tiles have landed and every wavefront is done with this buffer; refill it
   auto turn = [&](int it) {
-    if (it + 1 < niter) put_stats(cur + hopb);
+    if (it + 1 < niter) put_stats(cur + hopb, (t_first + (it + 1) % per_head) * TQ);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (it + 2 < niter) fetch(it + 2, cur);
@@ -973,6 +1008,22 @@ __global__ __launch_bounds__(TQ * 4 * QS, QS == 2 && HD == 64 ? 4 : 2) void attn
     }
   }
 }
+template <int HD, int TQ, int QS>
+__global__ __launch_bounds__(TQ * 4 * QS, QS == 2 && HD == 64 ? 4 : 2) void attn_dkv_kernel(AttnArgs a, int nsplit, int fold) {
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  dkv_workgroup<HD, TQ, QS, false>(a, nsplit, fold, (lds_char*)smem_raw, blockIdx.x, blockIdx.y);
+}
+
+// dQ and dK/dV of a small problem in one launch, which neither of them fills by itself: the first n_dkv workgroups are dK/dV's
+// (the longer ones), the others dQ's.
+template <int HD, int KS, int QS>
+__global__ __launch_bounds__(256 * QS, 2) void attn_bwd_kernel(AttnArgs a, int nsplit, int n_dkv, int fold) {
+  static_assert(KS == 2 * QS, "one workgroup size");
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  const int id = blockIdx.x;
+  if (id < n_dkv) dkv_workgroup<HD, DKV_TQ_SMALL, QS, true>(a, nsplit, fold, (lds_char*)smem_raw, id % (a.hkv * nsplit), id / (a.hkv * nsplit));
+  else dq_workgroup<HD, 256 * QS, KS>(a, fold, (lds_char*)smem_raw, (id - n_dkv) % a.h, (id - n_dkv) / a.h);
+}
 
 // dK | dV of dqkv = sum over splits, in split order (bit-reproducible), rounded once to bf16
 __global__ __launch_bounds__(256) void attn_dkv_reduce_kernel(AttnArgs a, int nsplit, int d, int dkv) {
@@ -1070,7 +1121,7 @@ static int dkv_splits(int b, int s, int h, int hkv, int tq) {
 }
 // 64-key workgroups when 128-key ones, split as far as they go, still number fewer than two per CU
 static bool dkv_small(int b, int s, int h, int hkv, int width) {
-  if (width) return width >= 3;
+  if (width >= 1 && width <= 4) return width >= 3;
   return (int64_t)b * hkv * ((s + DKV_TQ - 1) / DKV_TQ) * dkv_splits(b, s, h, hkv, DKV_TQ) < RESIDENT;
 }
 
@@ -1091,8 +1142,36 @@ hipError_t dkv_launch(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int HD, int KS, int QS>
+hipError_t bwd_fused_launch(const AttnArgs& a, hipStream_t s) {
+  constexpr size_t dq_bytes = fwd_lds<HD, KS>(), dkv_bytes = dkv_lds<HD, DKV_TQ_SMALL, QS>(), lds_bytes = dq_bytes > dkv_bytes ? dq_bytes : dkv_bytes;
+  static const hipError_t ready = allow_lds(attn_bwd_kernel<HD, KS, QS>, lds_bytes);
+  if (ready != hipSuccess) return ready;
+  const int nsplit = a.dkv_part ? dkv_splits(a.b, a.s, a.h, a.hkv, DKV_TQ_SMALL) : 1, nt = (a.s + 63) / 64;
+  const int n_dkv = a.hkv * nsplit * nt * a.b, n_dq = a.h * nt * a.b;
+  hipLaunchKernelGGL((attn_bwd_kernel<HD, KS, QS>), dim3(n_dkv + n_dq), dim3(256 * QS), lds_bytes, s, a, nsplit, n_dkv, 0);
+  if (nsplit > 1) {
+    const int64_t pieces = (int64_t)a.b * a.s * (2 * a.hkv * HD / 4);
+    hipLaunchKernelGGL(attn_dkv_reduce_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, a, nsplit, a.h * HD, a.hkv * HD);
+  }
+  return hipGetLastError();
+}
+
 template <int HD>
 hipError_t bwd_t(const AttnArgs& a, hipStream_t s) {
+  // Both passes in one launch while the workgroups of the two (64 queries, 64 keys) number little more than what is resident: with two
+  // wavefronts per SIMD and workgroup up to one per CU (causal: two, whose light halves make room), with one up to 960 of them where
+  // registers allow three to a CU.  Measured (us, two launches / one; heads x positions): head_dim 128 10 x 200 21.4 / 14.1, 8 x 1024 43.1 /
+  // 32.4, 8 x 2048 70.8 / 60.0, but 16 x 2048 96.1 / 103, without mask 16 x 1000 49.8 / 53.6; head_dim 64 16 x 1024 32.1 / 26.1, 36 x 777 31.9 /
+  // 29.5, 40 x 512 25.7 / 19.0, but 16 x 2048 59.7 / 62.6.
+  if (a.width == 5) return bwd_fused_launch<HD, 2, 1>(a, s);
+  if (a.width == 6) return bwd_fused_launch<HD, 4, 2>(a, s);
+  if (a.width == 0) {
+    const int64_t per_head = (int64_t)a.b * ((a.s + 63) / 64);
+    const int64_t total = per_head * (a.h + a.hkv * (a.dkv_part ? dkv_splits(a.b, a.s, a.h, a.hkv, DKV_TQ_SMALL) : 1));
+    if (2 * total <= RESIDENT || (a.causal && total <= RESIDENT && (HD == 128 || a.s > 320))) return bwd_fused_launch<HD, 4, 2>(a, s);
+    if (HD == 64 && total <= 960) return bwd_fused_launch<HD, 2, 1>(a, s);
+  }
   hipError_t e;      // dQ first: it also leaves delta = rowsum(dO * O) in a.delta for the dK/dV pass
   switch (fwd_shape(a, true)) {
     case SHAPE_WIDE: e = dq_launch<HD, FWD_WIDE, 1>(a, s); break;
