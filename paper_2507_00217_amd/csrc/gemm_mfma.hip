@@ -27,7 +27,7 @@
 // 16x16 block), which leaves every lane with 4 consecutive columns of one row:
 // 8-byte bf16 / 16-byte fp32 epilogue accesses.  Workgroup ids are remapped so
 // that each XCD (own L2) works on a compact band of tiles.  Smaller tiles (128x128,
-// 128x64, 64x64, four wavefronts each; 128x256 for one epilogue) take over where full
+// 192x128, 128x192, 128x64, 96x64, 64x64; 128x256 for one epilogue) take over where full
 // tiles would keep at most half of the CUs busy: the last round of a product, or a
 // product with few tiles.
 #include "common.h"
@@ -99,8 +99,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, un
 // swz of a [k][row] tile with PCS pieces per reduction row; with 8 (128-byte rows) two consecutive rows share a turn of the
 // banks, so bit 1 of k and not bit 0 moves a row by 64 bytes
 template <int PCS> __device__ __forceinline__ int swz(int k) {
-  static_assert(PCS == 8 || PCS == 16 || PCS == 32, "row widths of the tiles");
-  return PCS == 8 ? (((k >> 1) & 1) << 2) | (((k >> 3) & 1) << 1) : ((k & 3) << 2) | (((k >> 3) & 1) << 1);
+  static_assert(PCS == 8 || PCS == 16 || PCS == 24 || PCS == 32, "row widths of the tiles");
+  return PCS % 16 == 8 ? (((k >> 1) & 1) << 2) | (((k >> 3) & 1) << 1) : ((k & 3) << 2) | (((k >> 3) & 1) << 1);
 }
 template <bool KC, int WAVES, int CH, int PCS = 32>
 __device__ __forceinline__ void tile_offsets(unsigned (&off)[CH], int64_t ld, int row0, int rows, int wave, int lane,
@@ -232,22 +232,23 @@ __device__ __forceinline__ void dswiglu4(f32x4 da, bf16x4 gt, bf16x4 up, bf16x4&
 // (64 x 64 tiles) 8.1 -> 6.6 us, 400 x 1920 x 640 5.6 -> 5.0, 2048 x 2048 x 6144 (128 x 128) 47 -> 43.  What is left on operands that come from the
 // last-level cache is that cache's latency: a CU then gets 85 to 93 bytes/ns whatever the depth of the ring, from HBM 50 to 60.
 // (Two 128 x 128 workgroups to a CU with two loading wavefronts each: 1000 x 5120 x 1280 18.9 -> 24.4.)
-template <bool AKC, bool BKC, int EPI, int TN, int WR = 2, int WC = 2, int SMALL_DEPTH = 4, int LW = 0>
+constexpr int tile_rows(int WR) { return WR == 0 ? 64 : WR == 3 ? 96 : WR == 4 ? 192 : WR * 128; }
+template <bool AKC, bool BKC, int EPI, int TN, int WR = 2, int WC = 2, int SMALL_DEPTH = 4, int LW = 0, int CW = 4>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds_char* smem, int nseg = 1,
                                           const int64_t* seg_delta = nullptr) {
   static_assert(!(WR == 1 && WC == 2) || EPI == EPI_DSWIGLU, "the half-height tile is the SwiGLU backward's");
   constexpr bool GLU = EPI == EPI_SWIGLU;
-  static_assert(WC == 2 || (WC == 1 && TN == 2) || (WC == 0 && TN <= 2), "four wavefronts of 64 x 64, 64 x 32, 32 x 64 or 32 x 32");
   static_assert(!GLU || (TN == 2 && !BKC), "gate and up blocks are the two halves of a wavefront's columns");
-  constexpr int BMV = WR ? WR * 128 : 64, BNV = WC ? WC * 128 : 64;                // tile: BMV rows, BNV columns
+  constexpr int BMV = tile_rows(WR), BNV = WC == 0 ? 64 : WC == 3 ? 192 : WC * 128;                     // tile: BMV rows, BNV columns
   constexpr int WGN = BNV / (TN * 32);                                             // wavefronts side by side
-  constexpr int RW = WC == 2 ? 128 : BMV * WGN / 4;                                // rows of a wavefront's sub-tile
+  constexpr int RW = WC == 2 ? 128 : BMV * WGN / CW;                               // rows of a wavefront's sub-tile
   constexpr int WAVES = (BMV / RW) * WGN;                                          // wavefronts that multiply ...
-  constexpr bool SMALL = WC <= 1, SPLIT = LW > 0;
+  constexpr bool SMALL = WC != 2, SPLIT = LW > 0;
   constexpr int LOADERS = SPLIT ? LW : WAVES;                                      // ... and those that load: the same, or others
+  static_assert(WC == 2 || (RW % 16 == 0 && BMV % RW == 0), "CW wavefronts of RW x 32 TN");
   constexpr int A_BYTES = BMV * BK * 2, B_BYTES = BNV * BK * 2;
   constexpr int PCS = BNV / 8;                                                     // 16-byte pieces per row of C / per reduction row of a [k][row] B tile
-  constexpr int PCA = BMV / 8;                                                     // ... of a [k][row] A tile
+  constexpr int PCA = AKC ? 32 : BMV / 8;                                                     // ... of a [k][row] A tile
   constexpr int CHA = (A_BYTES / 16) / (LOADERS * 64), CHB = (B_BYTES / 16) / (LOADERS * 64); // loads per thread and K tile
   constexpr int NI = RW / 16, NJ = 2 * TN;                                         // 16 x 16 accumulator blocks per wavefront
   // The ring of operand tiles (see below): DEPTH K tiles ahead of the one being multiplied, 2 * DEPTH + 1 slots.  The
@@ -255,7 +256,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   // holds -- and the same lead in time needs -- twice the depth: with a lead of two K tiles (about 1 us here) operands
   // that come from HBM rather than from a cache arrive late, and products of this tile ran a quarter to a third slower
   // on cold operands than on warm ones.  (Two 128 x 128 workgroups that share a CU keep two K tiles ahead each.)
-  constexpr int SLOT = WR == 0 ? TILE_BYTES / 4 : SMALL ? TILE_BYTES / 2 : TILE_BYTES, DEPTH = SMALL ? SMALL_DEPTH : 2, NSLOT = 2 * DEPTH + 1;
+  constexpr int SLOT = WR == 0 ? TILE_BYTES / 4 : WR == 4 || WC == 3 ? 3 * (TILE_BYTES / 4) : SMALL ? TILE_BYTES / 2 : TILE_BYTES, DEPTH = SMALL ? SMALL_DEPTH : 2, NSLOT = 2 * DEPTH + 1;
   static_assert(A_BYTES <= SLOT && B_BYTES <= SLOT && (size_t)NSLOT * SLOT <= LDS_BYTES, "ring fits");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -402,39 +403,74 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
       slotA = slotA + 2 >= NSLOT ? slotA + 2 - NSLOT : slotA + 2;
     };
     __syncthreads();                                                             // tile 0 has landed
-    constexpr int RP = (NF + NM - 1) / NM;                                       // fragments read behind an MFMA
-    bf16x8 fa[2][2][NI], fb[2][2][NJ];
-    auto read = [&](auto set_c, int f) __attribute__((always_inline)) {          // fragment f of the next K tile
-      constexpr int set = decltype(set_c)::value;
-      const int ks = f / NF, x = f % NF;
-      if (x < NJ) fb[set][ks][x] = frag<BKC, NPB, PCS>(pb, x, ks);
-      else fa[set][ks][x - NJ] = frag<AKC, NPA, PCA>(pa, x - NJ, ks);
-    };
+    if constexpr (WR != 4 && WC != 3) {
+      constexpr int RP = (NF + NM - 1) / NM;                                       // fragments read behind an MFMA
+      bf16x8 fa[2][2][NI], fb[2][2][NJ];
+      auto read = [&](auto set_c, int f) __attribute__((always_inline)) {          // fragment f of the next K tile
+        constexpr int set = decltype(set_c)::value;
+        const int ks = f / NF, x = f % NF;
+        if (x < NJ) fb[set][ks][x] = frag<BKC, NPB, PCS>(pb, x, ks);
+        else fa[set][ks][x - NJ] = frag<AKC, NPA, PCA>(pa, x - NJ, ks);
+      };
 #pragma unroll
-    for (int f = 0; f < 2 * NF; ++f) read(c0, f);
-    auto trip = [&](auto cur_c) __attribute__((always_inline)) {
-      constexpr int cur = decltype(cur_c)::value;
-      hop();
-      __builtin_amdgcn_s_waitcnt(0xc07f);                                        // lgkmcnt(0): the fragments of tile t are here
-      __syncthreads();                                                           // tile t + 1 has landed
-      __builtin_amdgcn_sched_barrier(0);
+      for (int f = 0; f < 2 * NF; ++f) read(c0, f);
+      auto trip = [&](auto cur_c) __attribute__((always_inline)) {
+        constexpr int cur = decltype(cur_c)::value;
+        hop();
+        __builtin_amdgcn_s_waitcnt(0xc07f);                                        // lgkmcnt(0): the fragments of tile t are here
+        __syncthreads();                                                           // tile t + 1 has landed
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+              const int js = (i & 1) ? NJ - 1 - j : j, n = (ks * NI + i) * NJ + j;
+              acc[i][js] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[cur][ks][js], fa[cur][ks][i], acc[i][js], 0, 0, 0);
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int f = n * RP; f < (n + 1) * RP && f < 2 * NF; ++f) read(std::integral_constant<int, cur ^ 1>{}, f);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+      };
+      for (int kt = 0; kt < nk; kt += 2) {
+        trip(c0);
+        if (kt + 1 < nk) trip(c1);
+      }
+    } else {
+      // 192 rows or columns: registers for half a K tile ahead only, as in the loop below
+      constexpr int EVERY = NM >= 2 * NF ? 2 : 1;
+      bf16x8 fa[2][NI], fb[2][NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) fb[0][j] = frag<BKC, NPB, PCS>(pb, j, 0);
+#pragma unroll
+      for (int i = 0; i < NI; ++i) fa[0][i] = frag<AKC, NPA, PCA>(pa, i, 0);
+      auto kstep = [&](auto cur_c, auto ks_c) __attribute__((always_inline)) {
+        constexpr int cur = decltype(cur_c)::value, ks_next = decltype(ks_c)::value;
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll
           for (int j = 0; j < NJ; ++j) {
-            const int js = (i & 1) ? NJ - 1 - j : j, n = (ks * NI + i) * NJ + j;
-            acc[i][js] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[cur][ks][js], fa[cur][ks][i], acc[i][js], 0, 0, 0);
+            const int js = (i & 1) ? NJ - 1 - j : j, n = i * NJ + j;
+            acc[i][js] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[cur][js], fa[cur][i], acc[i][js], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int f = n * RP; f < (n + 1) * RP && f < 2 * NF; ++f) read(std::integral_constant<int, cur ^ 1>{}, f);
+            if (n % EVERY == 0 && n / EVERY < NF) {
+              const int f = n / EVERY;
+              if (f < NJ) fb[cur ^ 1][f] = frag<BKC, NPB, PCS>(pb, f, ks_next);
+              else fa[cur ^ 1][f - NJ] = frag<AKC, NPA, PCA>(pa, f - NJ, ks_next);
+            }
             __builtin_amdgcn_sched_barrier(0);
           }
-    };
-    for (int kt = 0; kt < nk; kt += 2) {
-      trip(c0);
-      if (kt + 1 < nk) trip(c1);
+      };
+      for (int kt = 0; kt < nk; ++kt) {
+        kstep(c0, c1);
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        hop();
+        kstep(c1, c0);
+      }
     }
   } else {
     // Software pipeline, one K tile (2 k-steps of 32) per trip t, fragments double-buffered in registers:
@@ -548,6 +584,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
       }
     }
   }
+  constexpr int PX = PCS == 24 ? 7 : PCS - 1;         // staged rows of C: bits of the row that move its pieces
   const int sub_b = (col_l & 4) * 2;      // byte inside a 16-byte piece at which this lane's 4 columns start
   if constexpr ((EPI == EPI_DGELU || EPI == EPI_DSWIGLU) && SMALL) {
     // Activation backward on the smaller tiles: z is read and rewritten where the accumulators lie, 4 columns of a row at a
@@ -672,12 +709,21 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
           bf16x4 o;
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[e] = (bf16)fn(acc[i][j][e]);
-          *reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(smem + r * (PCS * 16) + ((p ^ (r & (PCS - 1))) << 4) + sub_b) = o;
+          *reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(smem + r * (PCS * 16) + ((p ^ (r & PX)) << 4) + sub_b) = o;
           if (EPI == EPI_GELU) __builtin_amdgcn_sched_barrier(0);      // keeps the erf expansions from piling up in registers
         }
       }
     };
     auto store_tile = [&](bf16* out, int64_t ld) {      // LDS -> global, whole rows
+      if constexpr (PCS == 24) {                         // rows of 24 pieces: the wavefront's rows as one run of pieces
+#pragma unroll
+        for (int t = 0; t < BMV / WAVES * PCS / 64; ++t) {
+          const int x = t * 64 + lane, r = wave * (BMV / WAVES) + x / PCS, p = x % PCS, m = m0 + r, n = n0 + p * 8;
+          const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) const u32x4*>(smem + r * (PCS * 16) + ((p ^ (r & PX)) << 4));
+          if (m < g.M && n < g.N) *reinterpret_cast<u32x4*>(out + (int64_t)m * ld + n) = v;   // N % 8 == 0
+        }
+        return;
+      }
       constexpr int RPI = 64 / PCS;                      // rows per instruction
       const int p = lane & (PCS - 1);
       int n = n0 + p * 8;
@@ -686,7 +732,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
 #pragma unroll
       for (int t = 0; t < BMV / WAVES / RPI; ++t) {
         const int r = wave * (BMV / WAVES) + RPI * t + lane / PCS, m = m0 + r;
-        const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) const u32x4*>(smem + r * (PCS * 16) + ((p ^ (r & (PCS - 1))) << 4));
+        const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) const u32x4*>(smem + r * (PCS * 16) + ((p ^ (r & PX)) << 4));
         if (m < g.M && n_ok) *reinterpret_cast<u32x4*>(out + (int64_t)m * ld + n) = v;   // N % 8 == 0
       }
     };
@@ -893,6 +939,30 @@ __global__ __launch_bounds__(512, 2) void gemm_tiny_kernel(GemmArgs g, int tiles
   gemm_tile<true, BKC, EPI, EPI == EPI_SWIGLU ? 2 : 1, WR, 0, WR ? 4 : TINY_DEPTH, 4>(g, m0, n0, (lds_char*)smem_raw);
 }
 
+// One workgroup per tile of a whole product, by the shape S: 96 x 64 (four wavefronts of 48 x 32), 192 x 128 (eight of 96 x 32) or 128 x
+// 192 (eight of 32 x 96), and four that load.  They take products whose tiles of the next smaller shape are a little more than one
+// round and of the next larger one far less.  Two wavefronts per SIMD on the larger ones: GELU's arithmetic in the epilogue then
+// covers its own latency (1000 x 5120 x 1280: 24.0 us, 28.4 with four of 96 x 64).
+enum MidShape { MID_96x64, MID_192x128, MID_128x192 };
+template <int S> struct Mid {
+  static constexpr int rows = S == MID_96x64 ? 96 : S == MID_192x128 ? 192 : 128, cols = S == MID_96x64 ? 64 : S == MID_192x128 ? 128 : 192;
+  static constexpr int CW = S == MID_96x64 ? 4 : 8, threads = (CW + 4) * 64, depth = S == MID_96x64 ? 4 : 2;
+  static constexpr size_t lds = (size_t)(2 * depth + 1) * (S == MID_96x64 ? TILE_BYTES / 2 : 3 * (TILE_BYTES / 4));
+};
+template <bool BKC, int EPI, int S>
+__global__ __launch_bounds__(Mid<S>::threads, Mid<S>::threads / 256) void gemm_mid_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  int bid = blockIdx.x;
+  {
+    const int per = (int)gridDim.x >> 3, main = per << 3;
+    if (bid < main) bid = (bid & 7) * per + (bid >> 3);
+  }
+  int tile_m, tile_n;
+  tile_of<4>(bid, tiles_m, tiles_n, tile_m, tile_n);
+  gemm_tile<true, BKC, EPI, S == MID_128x192 ? 3 : 1, S == MID_96x64 ? 3 : S == MID_192x128 ? 4 : 1, S == MID_96x64 ? 0 : S == MID_192x128 ? 1 : 3,
+            Mid<S>::depth, 4, Mid<S>::CW>(g, tile_m * Mid<S>::rows, tile_n * Mid<S>::cols, (lds_char*)smem_raw);
+}
+
 // Several weight-gradient products C_p += A_p^T . B_p in one launch of persistent workgroups.  Each workgroup
 // takes the tiles  r * gridDim.x + (its slot)  of the concatenated tile list, r = 0, 1, ...: after it has issued a
 // tile's stores it goes straight on to the next tile's C and operand loads, so the read-modify-write of the fp32
@@ -1009,6 +1079,16 @@ hipError_t launch_tiny(const GemmArgs& g, hipStream_t s, const SmallGrid& t) {
   return hipGetLastError();
 }
 
+template <int S> int mid_tiles(const GemmArgs& g) { return ((g.M + Mid<S>::rows - 1) / Mid<S>::rows) * ((g.N + Mid<S>::cols - 1) / Mid<S>::cols); }
+template <bool BKC, int EPI, int S>
+hipError_t launch_mid(const GemmArgs& g, hipStream_t s) {
+  auto kern = gemm_mid_kernel<BKC, EPI, S>;
+  static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Mid<S>::lds);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(kern, dim3(mid_tiles<S>(g)), dim3(Mid<S>::threads), Mid<S>::lds, s, g, (g.M + Mid<S>::rows - 1) / Mid<S>::rows, (g.N + Mid<S>::cols - 1) / Mid<S>::cols);
+  return hipGetLastError();
+}
+
 // Full tiles for every complete round of one tile per CU; what is left over -- a last round that would keep at most half of
 // the CUs busy, or a whole product with that few tiles -- goes out in smaller tiles, the smallest of which one round is
 // enough: 64 x 64, 128 x 64, 128 x 128, and beyond that 128 x 128 with a shallow ring, two workgroups to a CU.  A tile's time per K
@@ -1020,7 +1100,7 @@ hipError_t launch_tiny(const GemmArgs& g, hipStream_t s, const SmallGrid& t) {
 // against full ones, 2048 x 6144 x 2048: 49 / 48 (60 / 53).  The half-height tile is left to the SwiGLU backward, whose z it
 // rewrites in whole rows through LDS (2048 x 2816 x 2048: 36 / 39).  All give the same bits.
 // `shape`: 0 = this rule, else one tile shape for all: 1 = full, 2 = half-height (SwiGLU backward; elsewhere the rule), 3 = 128 x
-// 128, 4 = 64 x 64 (SwiGLU forward: 128 x 64), 5 = 128 x 64.
+// 128, 4 = 64 x 64 (SwiGLU forward: 128 x 64), 5 = 128 x 64, 6 = 96 x 64, 7 = 192 x 128, 8 = 128 x 192 (SwiGLU: 128 x 64 for these).
 template <bool BKC, int EPI>
 hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   constexpr bool HALF = EPI == EPI_DSWIGLU;            // where there are half-height tiles
@@ -1029,7 +1109,18 @@ hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   const int tiles_n = EPI == EPI_SWIGLU ? (g.N / 2 + GLU_BN - 1) / GLU_BN : (g.N + BN - 1) / BN, total = tiles_m * tiles_n;
   int n_half = 0, n_quarter = 0, n_tiny = 0;          // full tiles at the end of the walk order that are split in 2 / 4 / 8 or 16
   const int n_cu = cu_count(), tail = total % n_cu;
+  const int t128x128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
   const SmallGrid t64 = small_grid<EPI>(g, 2, 2, total, shape ? total : tail), t128 = small_grid<EPI>(g, 1, 2, total, shape ? total : tail);
+  if constexpr (EPI != EPI_SWIGLU && !HALF) {
+    // Between two of the shapes above, for products that they would give to part of the CUs or twice to some: 96 x 64 before 128 x 64
+    // (us; operands from HBM in brackets: 1000 x 1280 x 5120 24.8 / 23.8 (34.7 / 29.3), 1536 x 1024 x 1536 9.4 / 8.0), 192 x 128 or 128 x 192
+    // before two 128 x 128 to a CU (1000 x 5120 x 1280 18.9 / 16.3 (21.9 / 19.5), with GELU 27.0 / 23.7, its backward 31.2 / 27.1; 4096 x
+    // 1536 x 4096 52.7 / 44.4 (58.0 / 55.9), 2048 x 3072 x 4096 50.6 / 44.2).
+    const bool whole = shape == 0 && total < n_cu;
+    if (shape == 6 || (whole && t64.n > n_cu && mid_tiles<MID_96x64>(g) <= n_cu)) return launch_mid<BKC, EPI, MID_96x64>(g, s);
+    if (shape == 7 || (whole && t128x128 > n_cu && mid_tiles<MID_192x128>(g) <= n_cu)) return launch_mid<BKC, EPI, MID_192x128>(g, s);
+    if (shape == 8 || (whole && t128x128 > n_cu && mid_tiles<MID_128x192>(g) <= n_cu)) return launch_mid<BKC, EPI, MID_128x192>(g, s);
+  }
   if (shape >= 4 || (shape == 0 && tail > 0 && t128.n <= n_cu)) n_tiny = shape ? total : tail;
   else if (shape == 3 || (shape == 0 && (HALF ? 4 : 2) * tail <= n_cu)) n_quarter = shape ? total : tail;
   else if (HALF) n_half = shape == 2 ? total : shape == 0 && 2 * tail <= n_cu ? tail : 0;

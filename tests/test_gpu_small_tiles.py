@@ -54,6 +54,29 @@ def test_reductions_around_the_ring(mode):
         assert all(torch.equal(outs[0], o) for o in outs[1:]), K
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (96, 64, 128), (97, 72, 192), (193, 136, 256), (129, 200, 320), (200, 392, 448), (400, 1736, 1088),
+                                   (1000, 1280, 64), (1000, 5120, 64), (4096, 1536, 64)])
+def test_tiles_between_the_powers_of_two(M, N, K):
+    """96 x 64 (7), 192 x 128 (8) and 128 x 192 tiles (9) against full ones (2) and the rule (0), every epilogue they have: one row, one past a
+    tile, reductions around the ring's depths of two and four; the last three shapes are what the rule gives to each of them."""
+    import torch
+    P0, R = P, lambda i, *sh: to_dev(rnd(synth.normal(45, i, sh, std=1.0 if i != 2 else 1.5 * K ** -0.5), "bf16"), "bf16")
+    A, B, Bt, Rd, Z = R(1, M, K), R(2, K, N), R(2, N, K), R(3, M, N), R(4, M, N)
+    outs = []
+    for ks in (2, 7, 8, 9, 0):
+        Cs = [torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(5)]
+        dz = Z.clone()
+        for c, mode, w, r in ((Cs[0], 0, B, None), (Cs[1], 0, B, Rd), (Cs[2], 1, Bt, None)):
+            assert L().stage_kernel_gemm(1, mode, M, N, K, P0(A), K, P0(w), w.shape[1], P0(c), N, None if r is None else P0(r), N, 0, ks, None) == 0
+        assert L().stage_kernel_gemm_act(1, 0, M, N, K, P0(A), K, P0(B), N, P0(Cs[3]), N, P0(Cs[4]), N, ks, None) == 0
+        assert L().stage_kernel_gemm_act_bwd(1, 0, M, N, K, P0(A), K, P0(Bt), K, P0(dz), N, None, ks, None) == 0
+        outs.append(Cs + [dz])
+    ref = A.double() @ B.double()
+    assert ((outs[0][0].double() - ref).abs().max() / ref.abs().max()).item() <= KTOL["bf16"]          # one bf16 rounding of the output
+    for i, o in enumerate(outs[1:]):
+        assert all(torch.equal(x, y) for x, y in zip(outs[0], o)), i
+
+
 @pytest.mark.parametrize("act", [0, 1])
 @pytest.mark.parametrize("M,f,K", [(1, 8, 64), (127, 64, 64), (129, 72, 128), (128, 136, 320), (257, 200, 384),
                                    (1100, 72, 128), (300, 2000, 192),
