@@ -5,7 +5,7 @@
 // 64 x 64 output tiles than the chip has CUs and what counts is the length of the serial chain in one workgroup, not the
 // matrix rate.  So the wavefronts of a workgroup share one output tile and split the REDUCTION between them (each takes
 // every W-th slice of it), and the partial tiles are added up through LDS in wavefront order at the end: no barrier inside
-// the loop, no workspace, the same bits on every run.  Operand fragments go global -> registers directly: an fp32 MFMA
+// the loop, no workspace, the same bits on every run.  Operand fragments go global -> registers directly (but for one round of 32 x 32 tiles): an fp32 MFMA
 // takes 32 cycles, so a 64 x 64 wavefront tile asks for 16 bytes per clock and CU, a quarter of what the caches deliver,
 // and staging tiles in LDS would buy nothing but barriers.  The order of the reduction inside a 16-deep slice is free as
 // long as both operands agree: lane group g takes k = 4g .. 4g + 3 in the four MFMAs of a slice, so an operand whose
@@ -105,11 +105,123 @@ __device__ __forceinline__ float dgelu32(float u) {
 }
 __device__ __forceinline__ float sigm32(float v) { return 1.f / (1.f + __expf(-v)); }
 
+// ---- operands through LDS ----------------------------------------------------------------------------------------------
+// Fragments loaded straight into registers are 16 rows x 64 bytes at a time where the reduction is contiguous, half of every
+// line, which a CU takes at 30 bytes a clock: the matrix cores wait.  Here a wavefront's slice is 32 deep, whole lines, and goes
+// through a ring of two slices of its own in LDS: nobody else reads it, so there is no barrier, and the second wavefront of the
+// SIMD multiplies while the first one waits.  128 KiB, one workgroup per CU.
+//   reduction contiguous: [32 rows][8 pieces of 16 bytes], piece p of row r in place p ^ ((r >> 1) & 7): 16 lanes read the same
+//     piece of 16 rows, from all banks
+//   reduction slow: [32 reduction rows][8 pieces = 32 columns], row k in place k ^ ((k >> 2) & 1), piece p in p ^ (((k >> 3) & 1) << 2):
+//     the four lane groups read rows 4 apart, from different banks
+typedef __attribute__((address_space(3))) char lds_char;
+typedef int rsrc32 __attribute__((ext_vector_type(4)));
+constexpr int SLICE32 = 32, SLICE_BYTES = 32 * SLICE32 * 4, SLICE_LOADS = SLICE_BYTES / 1024;      // per operand
+
+template <bool KC, bool GLU>
+struct SliceLoad {
+  rsrc32 rs;
+  unsigned off[SLICE_LOADS], ld4;
+  int kp, K;
+  __device__ __forceinline__ void init(const void* p, int64_t ld, int row0, int rows, int Kred, int second, int lane) {
+    const uint64_t a = (uint64_t)p;
+    const int64_t span = KC ? (int64_t)(rows - 1) * ld + Kred : (int64_t)(Kred - 1) * ld + (second ? second + rows : rows);
+    rs = rsrc32{(int)(unsigned)a, (int)(unsigned)((a >> 32) & 0xffffu), (int)(unsigned)(span * 4), 0x00020000};
+    ld4 = (unsigned)(ld * 4); K = Kred;
+#pragma unroll
+    for (int j = 0; j < SLICE_LOADS; ++j) {
+      const int x = j * 8 + (lane >> 3);                                          // place of the row
+      if (KC) {
+        const int pc = (lane & 7) ^ ((x >> 1) & 7);
+        if (j == 0) kp = pc * 4;                                                  // (rows 8 apart: piece ^ 4)
+        off[j] = row0 + x < rows ? (unsigned)(row0 + x) * ld4 + (unsigned)pc * 16u : OOB32;
+      } else {
+        const int k = x ^ ((x >> 2) & 1), pc = (lane & 7) ^ (((k >> 3) & 1) << 2), col = row0 + (GLU ? pc & 3 : pc) * 4;
+        off[j] = col < rows ? (unsigned)(col + (GLU && pc > 3 ? second : 0)) * 4u + (unsigned)k * ld4 : OOB32;
+      }
+    }
+  }
+  __device__ __forceinline__ void load(lds_char* dst, int k0) const {
+#pragma unroll
+    for (int j = 0; j < SLICE_LOADS; ++j) {
+      // past the end of the reduction: contiguous pieces are redirected, rows of a slow one lie past the end of the buffer
+      const unsigned o = KC ? (k0 + (kp ^ ((j & 1) << 4)) < K ? off[j] + (unsigned)k0 * 4u : OOB32) : off[j] + (unsigned)k0 * ld4;
+      asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                   :: "s"((unsigned)(size_t)(dst + j * 1024)), "v"(o), "s"(rs) : "memory");
+    }
+  }
+};
+
+template <bool AKC, bool BKC, int W, bool GLU>
+__device__ __forceinline__ void reduce_via_lds(f32x4 (&acc)[2][2], const GemmArgs& g, int m0, int n0, int nfeat, lds_char* ring, int w, int lane) {
+  typedef __attribute__((address_space(3))) const f32x4* p4;
+  typedef __attribute__((address_space(3))) const f32x2* p2;
+  typedef __attribute__((address_space(3))) const float* p1;
+  const int c = lane & 15, gr = lane >> 4;
+  SliceLoad<AKC, false> la; SliceLoad<BKC, GLU> lb;
+  la.init(g.A, g.lda, m0, g.M, g.K, 0, lane);
+  lb.init(g.B, g.ldb, n0, nfeat, g.K, GLU ? nfeat : 0, lane);
+  lds_char* mine = ring + w * (4 * SLICE_BYTES);                                    // two slots of A, B
+  const int ns = (g.K + SLICE32 - 1) / SLICE32;
+  auto fetch = [&](int t, int slot) { la.load(mine + slot * 2 * SLICE_BYTES, t * SLICE32); lb.load(mine + slot * 2 * SLICE_BYTES + SLICE_BYTES, t * SLICE32); };
+  if (w < ns) fetch(w, 0);
+  if (w + W < ns) fetch(w + W, 1);
+  // fragments: h = 16-deep half, f[h][block][j] as in Operand
+  auto read_kc = [&](f32x4 (&f)[2][2], lds_char* st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) f[h][i] = *(p4)(st + (16 * i + c) * 128 + (((4 * h + gr) ^ ((c >> 1) & 7)) << 4));
+  };
+  auto read_slow = [&](f32x4 (&f)[2][2], lds_char* st, auto glu) __attribute__((always_inline)) {
+    const int x = (gr >> 1) << 2;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        lds_char* row = st + (16 * h + 4 * gr + (j ^ (gr & 1))) * 128;
+        if constexpr (decltype(glu)::value) {
+          f[h][0][j] = *(p1)(row + (((c >> 2) ^ x) << 4) + (c & 3) * 4);
+          f[h][1][j] = *(p1)(row + ((((c >> 2) + 4) ^ x) << 4) + (c & 3) * 4);
+        } else {
+          const f32x2 v = *(p2)(row + (((c >> 1) ^ x) << 4) + (c & 1) * 8);
+          f[h][0][j] = v[0]; f[h][1][j] = v[1];
+        }
+      }
+  };
+  auto step = [&](int t, lds_char* st, int slot) __attribute__((always_inline)) {
+    // slice t has landed: nothing but the next one's loads outstanding
+    if (t + W < ns) __builtin_amdgcn_s_waitcnt(0x0f70 | (2 * SLICE_LOADS)); else __builtin_amdgcn_s_waitcnt(0x0f70);
+    asm volatile("" ::: "memory");
+    f32x4 fa[2][2], fb[2][2];
+    if constexpr (AKC) read_kc(fa, st); else read_slow(fa, st, std::false_type{});
+    if constexpr (BKC) read_kc(fb, st + SLICE_BYTES); else read_slow(fb, st + SLICE_BYTES, std::integral_constant<bool, GLU>{});
+    __builtin_amdgcn_s_waitcnt(0xc07f);                  // lgkmcnt(0): the fragments are in registers, the slot is free
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + 2 * W < ns) fetch(t + 2 * W, slot);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int n = 0; n < 2; ++n) acc[i][n] = mfma4(fb[h][n][j], fa[h][i][j], acc[i][n]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int t = w; t < ns; t += 2 * W) {
+    step(t, mine, 0);
+    if (t + W < ns) step(t + W, mine + 2 * SLICE_BYTES, 1);
+  }
+}
+
 // The tile at (m0, n0), 16 * MB x 16 * NB outputs (SwiGLU forward: 8 * NB features, gate and up), by W wavefronts that split
 // the reduction.  The MFMA is issued with the operands swapped, which leaves every lane with columns of one row of C.
 // `red`: W * MB * NB * 64 float4 of LDS.  nseg > 1 (weight gradients): the product of the operand pair moved by seg_delta[s]
 // bytes is added to C for s = 0, 1, ... in turn -- the same bits as one launch per pair.
-template <int MODE, int MB, int NB, int W, int EPI>
+// VIA_LDS: operands through LDS (products of 32 x 32 tiles by eight wavefronts; `red` is the ring).
+template <int MODE, int MB, int NB, int W, int EPI, bool VIA_LDS = false>
 __device__ __forceinline__ void tile32(const GemmArgs& g, int m0, int n0, f32x4* red, int nseg, const int64_t* seg_delta) {
   constexpr bool AKC = MODE != GEMM_TN, BKC = MODE == GEMM_NT, GLU = EPI == E32_SWIGLU;
   static_assert(!GLU || (!BKC && NB >= 2), "gate and up blocks");
@@ -122,15 +234,19 @@ __device__ __forceinline__ void tile32(const GemmArgs& g, int m0, int n0, f32x4*
   f32x4 run[(NQ + W - 1) / W];                         // weight gradients over several segments: C so far
 
   for (int sg = 0; sg < nseg; ++sg) {
-    const int64_t delta = MODE == GEMM_TN && sg > 0 ? seg_delta[sg] : 0;
-    Operand<AKC, MB, MB> oa; Operand<BKC, NB, SPB> ob;
-    oa.init((const char*)g.A + delta, g.lda, m0, g.M, g.K, 0, c, gr);
-    ob.init((const char*)g.B + delta, g.ldb, n0, nfeat, g.K, GLU ? nfeat : 0, c, gr);
     f32x4 acc[MB][NB];
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (VIA_LDS) {
+      reduce_via_lds<AKC, BKC, W, GLU>(acc, g, m0, n0, nfeat, (lds_char*)red, w, lane);
+      __syncthreads();                                 // the ring becomes `red`
+    } else {
+    const int64_t delta = MODE == GEMM_TN && sg > 0 ? seg_delta[sg] : 0;
+    Operand<AKC, MB, MB> oa; Operand<BKC, NB, SPB> ob;
+    oa.init((const char*)g.A + delta, g.lda, m0, g.M, g.K, 0, c, gr);
+    ob.init((const char*)g.B + delta, g.ldb, n0, nfeat, g.K, GLU ? nfeat : 0, c, gr);
     f32x4 fa[2][U][MB], fb[2][U][NB];
     auto load = [&](int set, int ch) __attribute__((always_inline)) {
 #pragma unroll
@@ -160,6 +276,7 @@ __device__ __forceinline__ void tile32(const GemmArgs& g, int m0, int n0, f32x4*
       mul(0);
       load(0, ch + 2 * W);
       mul(1);
+    }
     }
     if (sg > 0) __syncthreads();                       // the previous segment's partial tiles have been read
     // quad q = i * NB + p of a lane: row i of its row blocks, 4 consecutive columns (see quad_n below)
@@ -274,6 +391,17 @@ __global__ __launch_bounds__(W * 64) void gemm32_kernel(GemmArgs g, int tiles_m,
   tile32<MODE, MB, NB, W, EPI>(g, tm * 16 * MB, tn * (EPI == E32_SWIGLU ? 8 : 16) * NB, red, 1, nullptr);
 }
 
+// 32 x 32 tiles with the operands through LDS
+constexpr size_t LDS32_BYTES = (size_t)8 * 4 * SLICE_BYTES;
+template <int MODE, int EPI>
+__global__ __launch_bounds__(512, 2) void gemm32_lds_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  static_assert(8 * 4 * 64 * 16 <= LDS32_BYTES, "the partial tiles fit");
+  int tm, tn;
+  tile32_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
+  tile32<MODE, 2, 2, 8, EPI, true>(g, tm * 32, tn * (EPI == E32_SWIGLU ? 16 : 32), (f32x4*)smem_raw, 1, nullptr);
+}
+
 // several weight-gradient products in one launch, one workgroup per tile of the concatenated tile list
 constexpr int GROUP32_MAX = 8;
 struct Wgrad32 { const void *A, *B; void* C; int64_t lda, ldb, ldc; int M, N, K, first; };
@@ -292,20 +420,20 @@ __global__ __launch_bounds__(W * 64) void wgrad32_group_kernel(Wgrad32Group gg) 
   tile32<GEMM_TN, MB, NB, W, E32_GENERAL>(g, tm * 16 * MB, tn * 16 * NB, red, gg.nseg, gg.seg_delta);
 }
 
-// Tile shapes: 0 = 64 x 64 by 4 wavefronts, 1 = 32 x 32 by 8, 2 = 16 x 16 (SwiGLU forward: 16 x 32) by 16.  The rule takes
+// Tile shapes: 0 = 64 x 64 by 4 wavefronts, 1 = 32 x 32 by 8 (3 = the same through LDS), 2 = 16 x 16 (SwiGLU forward: 16 x 32) by 16.  The rule takes
 // the one whose matrix-core time on the fullest CU is least: rounds of one tile per CU, times the tile's area, times what
 // the shape loses to operand traffic.  The losses are measured where every shape fills the chip (M 1400, N 8192, K 1024: 208 /
 // 259 / 507 us with a slow-index B; 197 / 321 / 692 us with both operands reduction-contiguous, whose loads touch 16 rows
 // each); the rounds decide where they do not (448 x 512 x 1408: 26.5 / 11.3 / 18.3 us, 128 x 256 x 1024: 20.1 / 8.0 / 4.8 us).
 int pick32(int mode, int M, int N, int n_shapes) {
   static const int tile[3] = {64, 32, 16};
-  static const double loss[2][3] = {{1., 1.2, 2.4}, {1., 1.45, 2.8}};
+  static const double loss[2][3] = {{1., 1.2, 2.4}, {1., 1.45, 2.8}}, one_round[2] = {1.1, 1.2};      // (32 x 32 through LDS, see below)
   const int n_cu = cu_count();
   int best = 0;
   double bt = 0.;
   for (int i = 0; i < n_shapes; ++i) {
     const int64_t tiles = (int64_t)((M + tile[i] - 1) / tile[i]) * ((N + tile[i] - 1) / tile[i]);
-    const double t = (double)((tiles + n_cu - 1) / n_cu) * tile[i] * tile[i] * loss[mode == GEMM_NT][i];
+    const double t = (double)((tiles + n_cu - 1) / n_cu) * tile[i] * tile[i] * (i == 1 && tiles <= n_cu ? one_round[mode == GEMM_NT] : loss[mode == GEMM_NT][i]);
     if (i == 0 || t < bt) { best = i; bt = t; }
   }
   return best;
@@ -319,10 +447,26 @@ hipError_t launch32(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 template <int MODE, int EPI>
+hipError_t launch32_lds(const GemmArgs& g, hipStream_t s) {
+  constexpr int TN = EPI == E32_SWIGLU ? 16 : 32;
+  auto kern = gemm32_lds_kernel<MODE, EPI>;
+  static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS32_BYTES);
+  if (attr != hipSuccess) return attr;
+  const int tiles_m = (g.M + 31) / 32, tiles_n = ((EPI == E32_SWIGLU ? g.N / 2 : g.N) + TN - 1) / TN;
+  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(512), LDS32_BYTES, s, g, tiles_m, tiles_n);
+  return hipGetLastError();
+}
+template <int MODE, int EPI>
 hipError_t pick_launch32(const GemmArgs& g, hipStream_t s, int shape) {
   constexpr int NB3 = EPI == E32_SWIGLU ? 2 : 1;
   const int which = shape > 0 ? shape - 1 : pick32(MODE, g.M, g.N, 3);
   if (which == 0) return launch32<MODE, 4, 4, 4, EPI>(g, s);
+  // One round of 32 x 32 tiles takes its operands through LDS (us, direct / through LDS: input gradients 448 x 512 x 512 6.1 / 5.5, x 1536
+  // 13.2 / 10.6, x 2816 22.2 / 16.8, 200 x 640 x 640 7.2 / 6.0, forward 448 x 512 x 1408 10.6 / 9.5, x 512 5.4 / 5.4, GELU backward 128 x 1024 x
+  // 256 4.8 / 4.5); more tiles than that share a CU and hide each other's loads, which 128 KiB of LDS would not let them (forward
+  // 448 x 1536 x 512 12.0 / 13.6, SwiGLU 448 x 1408 x 512 22.7 / 26.8).
+  const int tiles32 = ((g.M + 31) / 32) * (EPI == E32_SWIGLU ? (g.N / 2 + 15) / 16 : (g.N + 31) / 32);
+  if (which == 3 || (shape == 0 && which == 1 && tiles32 <= cu_count())) return launch32_lds<MODE, EPI>(g, s);
   if (which == 1) return launch32<MODE, 2, 2, 8, EPI>(g, s);
   return launch32<MODE, 1, NB3, 16, EPI>(g, s);
 }
