@@ -5,7 +5,7 @@
 // 64 x 64 output tiles than the chip has CUs and what counts is the length of the serial chain in one workgroup, not the
 // matrix rate.  So the wavefronts of a workgroup share one output tile and split the REDUCTION between them (each takes
 // every W-th slice of it), and the partial tiles are added up through LDS in wavefront order at the end: no barrier inside
-// the loop, no workspace, the same bits on every run.  Operand fragments go global -> registers directly (but for one round of 32 x 32 tiles): an fp32 MFMA
+// the loop, no workspace, the same bits on every run.  Operand fragments go global -> registers directly (but for 32 x 32 tiles): an fp32 MFMA
 // takes 32 cycles, so a 64 x 64 wavefront tile asks for 16 bytes per clock and CU, a quarter of what the caches deliver,
 // and staging tiles in LDS would buy nothing but barriers.  The order of the reduction inside a 16-deep slice is free as
 // long as both operands agree: lane group g takes k = 4g .. 4g + 3 in the four MFMAs of a slice, so an operand whose
@@ -108,8 +108,10 @@ __device__ __forceinline__ float sigm32(float v) { return 1.f / (1.f + __expf(-v
 // ---- operands through LDS ----------------------------------------------------------------------------------------------
 // Fragments loaded straight into registers are 16 rows x 64 bytes at a time where the reduction is contiguous, half of every
 // line, which a CU takes at 30 bytes a clock: the matrix cores wait.  Here a wavefront's slice is 32 deep, whole lines, and goes
-// through a ring of two slices of its own in LDS: nobody else reads it, so there is no barrier, and the second wavefront of the
-// SIMD multiplies while the first one waits.  128 KiB, one workgroup per CU.
+// through a place of its own in LDS: nobody else reads it, so there is no barrier.  Once its fragments are in registers the next
+// slice is on its way there; it has this slice's 32 MFMAs, and those of the other wavefronts of the SIMD, to land.  64 KiB for eight
+// wavefronts, two workgroups per CU.  (Two places per wavefront, one workgroup per CU: 448 x 512 x 2816 16.6 us instead of 15.5, 700 x 1024 x
+// 3072 52 instead of 43.)
 //   reduction contiguous: [32 rows][8 pieces of 16 bytes], piece p of row r in place p ^ ((r >> 1) & 7): 16 lanes read the same
 //     piece of 16 rows, from all banks
 //   reduction slow: [32 reduction rows][8 pieces = 32 columns], row k in place k ^ ((k >> 2) & 1), piece p in p ^ (((k >> 3) & 1) << 2):
@@ -152,20 +154,17 @@ struct SliceLoad {
   }
 };
 
-template <bool AKC, bool BKC, int W, bool GLU>
+template <bool BKC, int W, bool GLU>
 __device__ __forceinline__ void reduce_via_lds(f32x4 (&acc)[2][2], const GemmArgs& g, int m0, int n0, int nfeat, lds_char* ring, int w, int lane) {
   typedef __attribute__((address_space(3))) const f32x4* p4;
   typedef __attribute__((address_space(3))) const f32x2* p2;
   typedef __attribute__((address_space(3))) const float* p1;
   const int c = lane & 15, gr = lane >> 4;
-  SliceLoad<AKC, false> la; SliceLoad<BKC, GLU> lb;
+  SliceLoad<true, false> la; SliceLoad<BKC, GLU> lb;
   la.init(g.A, g.lda, m0, g.M, g.K, 0, lane);
   lb.init(g.B, g.ldb, n0, nfeat, g.K, GLU ? nfeat : 0, lane);
-  lds_char* mine = ring + w * (4 * SLICE_BYTES);                                    // two slots of A, B
-  const int ns = (g.K + SLICE32 - 1) / SLICE32;
-  auto fetch = [&](int t, int slot) { la.load(mine + slot * 2 * SLICE_BYTES, t * SLICE32); lb.load(mine + slot * 2 * SLICE_BYTES + SLICE_BYTES, t * SLICE32); };
-  if (w < ns) fetch(w, 0);
-  if (w + W < ns) fetch(w + W, 1);
+  lds_char* mine = ring + w * (2 * SLICE_BYTES);
+  auto fetch = [&](int k) { la.load(mine, k); lb.load(mine + SLICE_BYTES, k); };
   // fragments: h = 16-deep half, f[h][block][j] as in Operand
   auto read_kc = [&](f32x4 (&f)[2][2], lds_char* st) __attribute__((always_inline)) {
 #pragma unroll
@@ -189,17 +188,18 @@ __device__ __forceinline__ void reduce_via_lds(f32x4 (&acc)[2][2], const GemmArg
         }
       }
   };
-  auto step = [&](int t, lds_char* st, int slot) __attribute__((always_inline)) {
-    // slice t has landed: nothing but the next one's loads outstanding
-    if (t + W < ns) __builtin_amdgcn_s_waitcnt(0x0f70 | (2 * SLICE_LOADS)); else __builtin_amdgcn_s_waitcnt(0x0f70);
+  const int step = W * SLICE32;
+  if (w * SLICE32 < g.K) fetch(w * SLICE32);
+  for (int k = w * SLICE32; k < g.K; k += step) {
+    __builtin_amdgcn_s_waitcnt(0x0f70);                  // vmcnt(0): the slice has landed
     asm volatile("" ::: "memory");
     f32x4 fa[2][2], fb[2][2];
-    if constexpr (AKC) read_kc(fa, st); else read_slow(fa, st, std::false_type{});
-    if constexpr (BKC) read_kc(fb, st + SLICE_BYTES); else read_slow(fb, st + SLICE_BYTES, std::integral_constant<bool, GLU>{});
-    __builtin_amdgcn_s_waitcnt(0xc07f);                  // lgkmcnt(0): the fragments are in registers, the slot is free
+    read_kc(fa, mine);
+    if constexpr (BKC) read_kc(fb, mine + SLICE_BYTES); else read_slow(fb, mine + SLICE_BYTES, std::integral_constant<bool, GLU>{});
+    __builtin_amdgcn_s_waitcnt(0xc07f);                  // lgkmcnt(0): the fragments are in registers, the place is free
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    if (t + 2 * W < ns) fetch(t + 2 * W, slot);
+    if (k + step < g.K) fetch(k + step);
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -209,10 +209,6 @@ __device__ __forceinline__ void reduce_via_lds(f32x4 (&acc)[2][2], const GemmArg
 #pragma unroll
           for (int n = 0; n < 2; ++n) acc[i][n] = mfma4(fb[h][n][j], fa[h][i][j], acc[i][n]);
     __builtin_amdgcn_sched_barrier(0);
-  };
-  for (int t = w; t < ns; t += 2 * W) {
-    step(t, mine, 0);
-    if (t + W < ns) step(t + W, mine + 2 * SLICE_BYTES, 1);
   }
 }
 
@@ -220,7 +216,7 @@ __device__ __forceinline__ void reduce_via_lds(f32x4 (&acc)[2][2], const GemmArg
 // the reduction.  The MFMA is issued with the operands swapped, which leaves every lane with columns of one row of C.
 // `red`: W * MB * NB * 64 float4 of LDS.  nseg > 1 (weight gradients): the product of the operand pair moved by seg_delta[s]
 // bytes is added to C for s = 0, 1, ... in turn -- the same bits as one launch per pair.
-// VIA_LDS: operands through LDS (products of 32 x 32 tiles by eight wavefronts; `red` is the ring).
+// VIA_LDS: the operands of a 32 x 32 tile go through LDS first (`red` serves as the ring).
 template <int MODE, int MB, int NB, int W, int EPI, bool VIA_LDS = false>
 __device__ __forceinline__ void tile32(const GemmArgs& g, int m0, int n0, f32x4* red, int nseg, const int64_t* seg_delta) {
   constexpr bool AKC = MODE != GEMM_TN, BKC = MODE == GEMM_NT, GLU = EPI == E32_SWIGLU;
@@ -239,11 +235,11 @@ __device__ __forceinline__ void tile32(const GemmArgs& g, int m0, int n0, f32x4*
     for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int64_t delta = MODE == GEMM_TN && sg > 0 ? seg_delta[sg] : 0;
     if constexpr (VIA_LDS) {
-      reduce_via_lds<AKC, BKC, W, GLU>(acc, g, m0, n0, nfeat, (lds_char*)red, w, lane);
+      reduce_via_lds<BKC, W, GLU>(acc, g, m0, n0, nfeat, (lds_char*)red, w, lane);
       __syncthreads();                                 // the ring becomes `red`
     } else {
-    const int64_t delta = MODE == GEMM_TN && sg > 0 ? seg_delta[sg] : 0;
     Operand<AKC, MB, MB> oa; Operand<BKC, NB, SPB> ob;
     oa.init((const char*)g.A + delta, g.lda, m0, g.M, g.K, 0, c, gr);
     ob.init((const char*)g.B + delta, g.ldb, n0, nfeat, g.K, GLU ? nfeat : 0, c, gr);
@@ -383,23 +379,13 @@ __device__ __forceinline__ void tile32_of(int idx, int tiles_m, int tiles_n, int
   tn = (idx % in_group) / gsz;
 }
 
-template <int MODE, int MB, int NB, int W, int EPI>
+template <int MODE, int MB, int NB, int W, int EPI, bool VIA_LDS>
 __global__ __launch_bounds__(W * 64) void gemm32_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-  __shared__ f32x4 red[W * MB * NB * 64];
+  static_assert(!VIA_LDS || (MB == 2 && NB == 2), "32 x 32 tiles; their partial tiles take half of the ring");
+  __shared__ __attribute__((aligned(1024))) f32x4 red[VIA_LDS ? W * 2 * SLICE_BYTES / 16 : W * MB * NB * 64];
   int tm, tn;
   tile32_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
-  tile32<MODE, MB, NB, W, EPI>(g, tm * 16 * MB, tn * (EPI == E32_SWIGLU ? 8 : 16) * NB, red, 1, nullptr);
-}
-
-// 32 x 32 tiles with the operands through LDS
-constexpr size_t LDS32_BYTES = (size_t)8 * 4 * SLICE_BYTES;
-template <int MODE, int EPI>
-__global__ __launch_bounds__(512, 2) void gemm32_lds_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
-  static_assert(8 * 4 * 64 * 16 <= LDS32_BYTES, "the partial tiles fit");
-  int tm, tn;
-  tile32_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
-  tile32<MODE, 2, 2, 8, EPI, true>(g, tm * 32, tn * (EPI == E32_SWIGLU ? 16 : 32), (f32x4*)smem_raw, 1, nullptr);
+  tile32<MODE, MB, NB, W, EPI, VIA_LDS>(g, tm * 16 * MB, tn * (EPI == E32_SWIGLU ? 8 : 16) * NB, red, 1, nullptr);
 }
 
 // several weight-gradient products in one launch, one workgroup per tile of the concatenated tile list
@@ -420,40 +406,30 @@ __global__ __launch_bounds__(W * 64) void wgrad32_group_kernel(Wgrad32Group gg) 
   tile32<GEMM_TN, MB, NB, W, E32_GENERAL>(g, tm * 16 * MB, tn * 16 * NB, red, gg.nseg, gg.seg_delta);
 }
 
-// Tile shapes: 0 = 64 x 64 by 4 wavefronts, 1 = 32 x 32 by 8 (3 = the same through LDS), 2 = 16 x 16 (SwiGLU forward: 16 x 32) by 16.  The rule takes
+// Tile shapes: 0 = 64 x 64 by 4 wavefronts, 1 = 32 x 32 by 8, 2 = 16 x 16 (SwiGLU forward: 16 x 32) by 16.  The rule takes
 // the one whose matrix-core time on the fullest CU is least: rounds of one tile per CU, times the tile's area, times what
 // the shape loses to operand traffic.  The losses are measured where every shape fills the chip (M 1400, N 8192, K 1024: 208 /
-// 259 / 507 us with a slow-index B; 197 / 321 / 692 us with both operands reduction-contiguous, whose loads touch 16 rows
-// each); the rounds decide where they do not (448 x 512 x 1408: 26.5 / 11.3 / 18.3 us, 128 x 256 x 1024: 20.1 / 8.0 / 4.8 us).
+// 234 / 507 us with a slow-index B; 16 x 16 tiles lose more with both operands reduction-contiguous, whose loads touch 16 rows
+// each); the rounds decide where they do not (448 x 512 x 1408: 26.1 / 9.2 / 18.2 us, 128 x 256 x 1024: 19.9 / 7.2 / 4.8 us).
 int pick32(int mode, int M, int N, int n_shapes) {
   static const int tile[3] = {64, 32, 16};
-  static const double loss[2][3] = {{1., 1.2, 2.4}, {1., 1.45, 2.8}}, one_round[2] = {1.1, 1.2};      // (32 x 32 through LDS, see below)
+  static const double loss[2][3] = {{1., 1.15, 2.4}, {1., 1.15, 2.8}};
   const int n_cu = cu_count();
   int best = 0;
   double bt = 0.;
   for (int i = 0; i < n_shapes; ++i) {
     const int64_t tiles = (int64_t)((M + tile[i] - 1) / tile[i]) * ((N + tile[i] - 1) / tile[i]);
-    const double t = (double)((tiles + n_cu - 1) / n_cu) * tile[i] * tile[i] * (i == 1 && tiles <= n_cu ? one_round[mode == GEMM_NT] : loss[mode == GEMM_NT][i]);
+    const double t = (double)((tiles + n_cu - 1) / n_cu) * tile[i] * tile[i] * loss[mode == GEMM_NT][i];
     if (i == 0 || t < bt) { best = i; bt = t; }
   }
   return best;
 }
 
-template <int MODE, int MB, int NB, int W, int EPI>
+template <int MODE, int MB, int NB, int W, int EPI, bool VIA_LDS = false>
 hipError_t launch32(const GemmArgs& g, hipStream_t s) {
   constexpr int TM = 16 * MB, TN = (EPI == E32_SWIGLU ? 8 : 16) * NB;
   const int tiles_m = (g.M + TM - 1) / TM, tiles_n = ((EPI == E32_SWIGLU ? g.N / 2 : g.N) + TN - 1) / TN;
-  hipLaunchKernelGGL((gemm32_kernel<MODE, MB, NB, W, EPI>), dim3(tiles_m * tiles_n), dim3(W * 64), 0, s, g, tiles_m, tiles_n);
-  return hipGetLastError();
-}
-template <int MODE, int EPI>
-hipError_t launch32_lds(const GemmArgs& g, hipStream_t s) {
-  constexpr int TN = EPI == E32_SWIGLU ? 16 : 32;
-  auto kern = gemm32_lds_kernel<MODE, EPI>;
-  static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS32_BYTES);
-  if (attr != hipSuccess) return attr;
-  const int tiles_m = (g.M + 31) / 32, tiles_n = ((EPI == E32_SWIGLU ? g.N / 2 : g.N) + TN - 1) / TN;
-  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(512), LDS32_BYTES, s, g, tiles_m, tiles_n);
+  hipLaunchKernelGGL((gemm32_kernel<MODE, MB, NB, W, EPI, VIA_LDS>), dim3(tiles_m * tiles_n), dim3(W * 64), 0, s, g, tiles_m, tiles_n);
   return hipGetLastError();
 }
 template <int MODE, int EPI>
@@ -461,13 +437,16 @@ hipError_t pick_launch32(const GemmArgs& g, hipStream_t s, int shape) {
   constexpr int NB3 = EPI == E32_SWIGLU ? 2 : 1;
   const int which = shape > 0 ? shape - 1 : pick32(MODE, g.M, g.N, 3);
   if (which == 0) return launch32<MODE, 4, 4, 4, EPI>(g, s);
-  // One round of 32 x 32 tiles takes its operands through LDS (us, direct / through LDS: input gradients 448 x 512 x 512 6.1 / 5.5, x 1536
-  // 13.2 / 10.6, x 2816 22.2 / 16.8, 200 x 640 x 640 7.2 / 6.0, forward 448 x 512 x 1408 10.6 / 9.5, x 512 5.4 / 5.4, GELU backward 128 x 1024 x
-  // 256 4.8 / 4.5); more tiles than that share a CU and hide each other's loads, which 128 KiB of LDS would not let them (forward
-  // 448 x 1536 x 512 12.0 / 13.6, SwiGLU 448 x 1408 x 512 22.7 / 26.8).
-  const int tiles32 = ((g.M + 31) / 32) * (EPI == E32_SWIGLU ? (g.N / 2 + 15) / 16 : (g.N + 31) / 32);
-  if (which == 3 || (shape == 0 && which == 1 && tiles32 <= cu_count())) return launch32_lds<MODE, EPI>(g, s);
-  if (which == 1) return launch32<MODE, 2, 2, 8, EPI>(g, s);
+  if (which == 1) {
+    // 32 x 32 tiles through LDS against straight to registers (us): input gradients 448 x 512 x 512 6.2 / 5.1, x 1536 13.8 / 10.0, x 2816 22.8 /
+    // 15.8, 700 x 1024 x 3072 66 / 44, forward 448 x 512 x 1408 11.3 / 9.2, 700 x 3072 x 1024 54.5 / 50.4, SwiGLU 300 x 1024 x 768 20.6 / 16.7, its
+    // backward 448 x 1408 x 512 15.7 / 13.2.  An activation with its second output over many rounds keeps the form that lets four workgroups
+    // share a CU: GELU 700 x 3072 x 768 44.8 / 46.1, SwiGLU 448 x 1408 x 512 22.7 / 23.2.
+    if constexpr (EPI == E32_GELU || EPI == E32_SWIGLU) {
+      if ((int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32) > 4 * cu_count()) return launch32<MODE, 2, 2, 8, EPI>(g, s);
+    }
+    return launch32<MODE, 2, 2, 8, EPI, true>(g, s);
+  }
   return launch32<MODE, 1, NB3, 16, EPI>(g, s);
 }
 
