@@ -283,33 +283,68 @@ __global__ __launch_bounds__(SIDE ? NB_THREADS : NORM_THREADS) void norm_bwd_ker
   }
 }
 
-// dst[col] += sum over a job's partial rows, in a fixed order, for all jobs of the list (norm-parameter and bias gradients of a
-// layer) in one launch: 64 columns per workgroup, SUM_WAVES wavefronts that take every SUM_WAVES-th partial row (coalesced
-// 256-byte reads, 16 of a wavefront's loads in flight at once: a few microseconds of memory latency, not bandwidth), then
-// wavefront 0 adds the shares in order.
+// dst[col] += sum over a job's rows, in a fixed order, for all jobs of the list (norm-parameter and bias gradients of a layer) in
+// one launch: 64 columns per workgroup, the rows dealt out to SUM_WAVES wavefronts, whose shares wavefront 0 adds in order.
+// What bounds it is a few microseconds of memory latency, not bandwidth, so every job has its loads in flight together: partial
+// sums take one row per wavefront and load (coalesced 256 bytes), 16 of them at once; gradient rows (below) 16 bytes per lane,
+// 8 (bf16) or 4 rows per wavefront and load, 8 at once, that is up to 1024 or 512 rows without a second wait.
 constexpr int SUM_WAVES = 16;
+template <typename T>
+__device__ __forceinline__ void gradient_row_sums(const ColSum& j, int col0, int w, int lane, float* share) {
+  constexpr int V = Vec<T>::N, C = 64 / V, R = 64 / C, U = 8;   // C lanes across the 64 columns, R rows at once
+  const int col = col0 + (lane % C) * V;
+  float acc[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) acc[e] = 0.f;
+  if (col < j.cols)                                            // cols is a multiple of V
+    for (int r0 = w * R + lane / C; r0 < j.parts; r0 += SUM_WAVES * R * U) {
+      Vec<T> v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int r = r0 + u * SUM_WAVES * R;
+        if (r < j.parts) v[u] = ldv((const T*)j.part + (int64_t)r * j.stride + col);
+        else v[u] = Vec<T>{};
+      }
+#pragma unroll
+      for (int e = 0; e < V; ++e)
+        acc[e] += ((to_f32(v[0].v[e]) + to_f32(v[1].v[e])) + (to_f32(v[2].v[e]) + to_f32(v[3].v[e]))) +
+                  ((to_f32(v[4].v[e]) + to_f32(v[5].v[e])) + (to_f32(v[6].v[e]) + to_f32(v[7].v[e])));
+    }
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+#pragma unroll
+    for (int o = C; o < 64; o <<= 1) acc[e] += __shfl_xor(acc[e], o);
+    if (lane < C) share[lane * V + e] = acc[e];
+  }
+}
+
 __global__ __launch_bounds__(SUM_WAVES * 64) void col_sum_kernel(ColSumList l) {
   __shared__ float sums[SUM_WAVES][64];
   int ji = 0;
   while (ji + 1 < l.n && (int)blockIdx.x >= l.first[ji + 1]) ++ji;
   const ColSum j = l.j[ji];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int col = ((int)blockIdx.x - l.first[ji]) * 64 + lane;
-  float s = 0.f;
-  if (col < j.cols) {
-    constexpr int U = 16;
-    for (int p0 = w; p0 < j.parts; p0 += SUM_WAVES * U) {
-      float v[U];
+  const int col0 = ((int)blockIdx.x - l.first[ji]) * 64, col = col0 + lane;
+  if (j.rows_of == COL_SUM_BF16_ROWS) gradient_row_sums<bf16>(j, col0, w, lane, sums[w]);
+  else if (j.rows_of == COL_SUM_F32_ROWS) gradient_row_sums<float>(j, col0, w, lane, sums[w]);
+  else {
+    float s = 0.f;
+    if (col < j.cols) {
+      constexpr int U = 16;
+      const float* part = (const float*)j.part;
+      for (int p0 = w; p0 < j.parts; p0 += SUM_WAVES * U) {
+        float v[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int p = p0 + u * SUM_WAVES;
-        v[u] = p < j.parts ? j.part[(int64_t)p * j.stride + col] : 0.f;
+        for (int u = 0; u < U; ++u) {
+          const int p = p0 + u * SUM_WAVES;
+          v[u] = p < j.parts ? part[(int64_t)p * j.stride + col] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += v[u];
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u) s += v[u];
     }
+    sums[w][lane] = s;
   }
-  sums[w][lane] = s;
   __syncthreads();
   if (w == 0 && col < j.cols) {
     float r = sums[0][lane];
@@ -392,8 +427,8 @@ hipError_t norm_bwd_rows(DType dt, const NormArgs& n, hipStream_t s, int* parts)
   return dt == DT_F32 ? norm_bwd_t<float>(n, s, parts) : norm_bwd_t<bf16>(n, s, parts);
 }
 void norm_col_sums(const NormArgs& n, int parts, ColSumList* l) {
-  l->j[l->n++] = ColSum{n.partial, (int64_t)2 * n.d, n.d, parts, n.dgamma};
-  if (n.kind == 0) l->j[l->n++] = ColSum{n.partial + n.d, (int64_t)2 * n.d, n.d, parts, n.dbeta};
+  l->j[l->n++] = ColSum{n.partial, (int64_t)2 * n.d, n.d, parts, n.dgamma, COL_SUM_PARTS};
+  if (n.kind == 0) l->j[l->n++] = ColSum{n.partial + n.d, (int64_t)2 * n.d, n.d, parts, n.dbeta, COL_SUM_PARTS};
 }
 hipError_t norm_bwd(DType dt, const NormArgs& n, hipStream_t s) {
   int parts = 0;
@@ -442,12 +477,18 @@ hipError_t norm_bwd_noalloc(DType dt, const NormArgs& n, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Gradient of a linear map's bias: the column sums of its dZ, added to the fp32 accumulator.  Two steps with a fixed
-// summation order (no atomics): BIAS_PARTS row ranges are summed by one workgroup each per 32 x (16 / sizeof(T))
-// columns -- 8 row lanes per column group, combined through LDS in lane order -- then col_sum_kernel adds the parts.  The
-// four maps of a layer go out together: at 400 tokens each of the two steps is launch latency, 3-5 us, eight times over.
+// Gradient of a linear map's bias: the column sums of its dZ, added to the fp32 accumulator, with a fixed summation order (no
+// atomics).  Up to BIAS_DIRECT_ROWS rows col_sum_kernel sums dZ itself, in the launch that also adds the norms' partial sums.
+// Beyond that two steps: BIAS_PARTS row ranges are summed by one workgroup each per 32 x (16 / sizeof(T)) columns -- 8 row
+// lanes per column group, combined through LDS in lane order -- then col_sum_kernel adds the parts.  The four maps of a
+// layer go out together.
+// The line: a workgroup of the one step owns its 64 columns alone, so its time grows with the rows, where the two steps spread
+// them over 64 workgroups but pay a second launch.  us, one step / two, 4928 columns: bf16 400 rows 4.2 / 6.8, 1024 4.4 / 7.0,
+// 2048 6.1 / 8.0, 4096 9.9 / 11.0; 18432 columns: 400 rows 6.9 / 11.5, 2048 18.1 / 18.8, 3072 25.4 / 23.8; fp32, 1920 columns:
+// 400 rows 3.4 / 6.5, 2048 6.1 / 6.5, 3072 9.4 / 7.4.
 // ---------------------------------------------------------------------------
 constexpr int BIAS_PARTS = 64;
+constexpr int BIAS_DIRECT_ROWS = 2048;
 size_t bias_grad_partial_bytes(int n) { return n > 0 ? (size_t)BIAS_PARTS * n * sizeof(float) : 0; }
 
 template <typename T>
@@ -485,17 +526,21 @@ __global__ __launch_bounds__(256) void bias_grad_partial_kernel(BiasGradList l) 
   }
 }
 
+bool bias_grad_direct(int rows) { return rows <= BIAS_DIRECT_ROWS; }
 hipError_t bias_grad_rows(DType dt, BiasGradList& l, ColSumList* sums, hipStream_t s) {
   const int V = dt == DT_F32 ? 4 : 8;
   if (l.n == 0) return hipSuccess;
+  const bool direct = bias_grad_direct(l.rows);
   int total = 0;
   for (int i = 0; i < l.n; ++i) {
     const BiasGrad& j = l.j[i];
     if (l.rows < 1 || j.cols < 1 || j.cols % V || j.ld % V || !j.dz || !j.part || !j.dbias || ((uintptr_t)j.dz & 15)) return hipErrorInvalidValue;
     l.first[i] = total;
     total += (j.cols / V + 31) / 32;
-    sums->j[sums->n++] = ColSum{j.part, j.cols, j.cols, BIAS_PARTS, j.dbias};
+    if (direct) sums->j[sums->n++] = ColSum{j.dz, j.ld, j.cols, l.rows, j.dbias, dt == DT_BF16 ? COL_SUM_BF16_ROWS : COL_SUM_F32_ROWS};
+    else sums->j[sums->n++] = ColSum{j.part, j.cols, j.cols, BIAS_PARTS, j.dbias, COL_SUM_PARTS};
   }
+  if (direct) return hipSuccess;
   const dim3 grid(total, BIAS_PARTS);
   if (dt == DT_F32) hipLaunchKernelGGL((bias_grad_partial_kernel<float>), grid, dim3(256), 0, s, l);
   else hipLaunchKernelGGL((bias_grad_partial_kernel<bf16>), grid, dim3(256), 0, s, l);

@@ -92,8 +92,10 @@ struct ActArgs {
 int norm_partial_rows();
 int cu_count();                      // compute units of the device that is current at the first call
 
-// Column sums of fp32 partial rows, added to dst: the last step of every parameter gradient that is a sum over rows
-struct ColSum { const float* part; int64_t stride; int cols, parts; float* dst; };
+// Column sums, added to dst: the last step of every parameter gradient that is a sum over rows.  What is summed are fp32 partial
+// sums, or the gradient rows themselves in fp32 or bf16 (16-byte rows).
+enum ColSumRows { COL_SUM_PARTS = 0, COL_SUM_F32_ROWS = 1, COL_SUM_BF16_ROWS = 2 };
+struct ColSum { const void* part; int64_t stride; int cols, parts; float* dst; int rows_of; };
 constexpr int COL_SUM_MAX = 8;       // two norms' gamma and beta, four biases
 struct ColSumList { int n; int first[COL_SUM_MAX]; ColSum j[COL_SUM_MAX]; };
 // Bias gradients of several maps over the same rows; part: bias_grad_partial_bytes(cols) bytes each
@@ -112,6 +114,7 @@ hipError_t norm_bwd(DType dt, const NormArgs& n, hipStream_t s);
 // then col_sums_add of what norm_col_sums (and bias_grad_rows) put on a list
 hipError_t norm_bwd_rows(DType dt, const NormArgs& n, hipStream_t s, int* parts);
 void norm_col_sums(const NormArgs& n, int parts, ColSumList* l);
+bool bias_grad_direct(int rows);     // bias_grad_rows puts the gradient rows themselves on the list and launches nothing
 hipError_t bias_grad_rows(DType dt, BiasGradList& l, ColSumList* sums, hipStream_t s);
 hipError_t col_sums_add(ColSumList& l, hipStream_t s);
 // the same with the partial sums in a fixed device array of the library (n.partial ignored); d <= norm_bwd_noalloc_max_d()

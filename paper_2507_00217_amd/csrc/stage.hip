@@ -493,6 +493,7 @@ int exec_backward_input(stage* st, int mb, const void* dy, void* dx, int l0, int
     norm_col_sums(n, parts, &sums);
     // bias gradients: the column sums of the layer's four dZ tensors, all of which the slot holds until W; then one launch adds
     // every partial sum of the layer to its parameter's gradient
+    double sum_bytes = 0.0;
     if (D.bias) {
       BiasGradList bl{};
       float* bp = (float*)(st->ws + w.bpart);
@@ -502,10 +503,16 @@ int exec_backward_input(stage* st, int mb, const void* dy, void* dx, int l0, int
         bp += bias_grad_partial_bytes(cols) / sizeof(float);
       };
       add(o.dyb, D.d, STAGE_P_BOUT); add(o.z, D.fin, STAGE_P_BIN); add(o.dx1b, D.d, STAGE_P_BO); add(o.dqkv, D.dq, STAGE_P_BQKV);
-      ProfScope ps(st, STAGE_K_COPY, (double)D.T * (2 * D.d + D.fin + D.dq) * D.es);
-      HIPCHK(bias_grad_rows(st->dt, bl, &sums, st->stream));
+      const double bytes = (double)D.T * (2 * D.d + D.fin + D.dq) * D.es;
+      if (bias_grad_direct(D.T)) {                             // no launch of its own
+        HIPCHK(bias_grad_rows(st->dt, bl, &sums, st->stream));
+        sum_bytes = bytes;
+      } else {
+        ProfScope ps(st, STAGE_K_COPY, bytes);
+        HIPCHK(bias_grad_rows(st->dt, bl, &sums, st->stream));
+      }
     }
-    { ProfScope ps(st, STAGE_K_NORM_BWD, 0.0); HIPCHK(col_sums_add(sums, st->stream)); }
+    { ProfScope ps(st, STAGE_K_NORM_BWD, sum_bytes); HIPCHK(col_sums_add(sums, st->stream)); }
   }
   return STAGE_OK;
 }

@@ -1,0 +1,29 @@
+"""Bias gradients on both sides of the row count up to which one launch sums the gradient rows directly.  Needs a GPU."""
+import numpy as np
+import pytest
+
+from tests import test_gpu_kernels as T
+from tests.gpu_util import rnd, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("rows,n,ld", [(1, 8, 8), (127, 64, 64), (129, 72, 80), (511, 200, 200), (513, 136, 136), (1023, 64, 72),
+                                       (1025, 1000, 1000), (2047, 192, 192), (2048, 328, 336), (2049, 328, 336)])
+def test_direct_and_two_step_sums(dtype, rows, n, ld):
+    """Edges of the rows in flight (512 / 1024 per step), of the 64 columns of a workgroup, and of the rule; dbias is added to.
+
+    Tolerance: the longest chain of fp32 additions is at most rows / 128 * 2 + 40 in either form, so the error is at most that
+    many half-ulps (2^-24) of the sum of magnitudes."""
+    import torch
+    lib = T.L()
+    x = rnd(np.random.default_rng(rows + n).standard_normal((rows, ld)), dtype)
+    start = np.linspace(-1, 1, n, dtype=np.float32)
+    xd, db = to_dev(x, dtype), torch.from_numpy(start).to("cuda:0")
+    scr = torch.zeros(lib.stage_kernel_bias_grad_scratch_bytes(n) // 4, dtype=torch.float32, device="cuda:0")
+    assert lib.stage_kernel_bias_grad(T.DT[dtype], rows, n, T.P(xd), ld, T.P(db), T.P(scr), None) == 0
+    torch.cuda.synchronize()
+    ref = start.astype(np.float64) + x[:, :n].astype(np.float64).sum(0)
+    bound = (rows / 128 * 2 + 40) * 2.0 ** -24 * (np.abs(x[:, :n]).astype(np.float64).sum(0) + np.abs(start))
+    assert np.all(np.abs(to_np(db) - ref) <= bound)
