@@ -232,7 +232,7 @@ __device__ __forceinline__ void dswiglu4(f32x4 da, bf16x4 gt, bf16x4 up, bf16x4&
 // (64 x 64 tiles) 8.1 -> 6.6 us, 400 x 1920 x 640 5.6 -> 5.0, 2048 x 2048 x 6144 (128 x 128) 47 -> 43.  What is left on operands that come from the
 // last-level cache is that cache's latency: a CU then gets 85 to 93 bytes/ns whatever the depth of the ring, from HBM 50 to 60.
 // (Two 128 x 128 workgroups to a CU with two loading wavefronts each: 1000 x 5120 x 1280 18.9 -> 24.4.)
-constexpr int tile_rows(int WR) { return WR == 0 ? 64 : WR == 3 ? 96 : WR == 4 ? 192 : WR * 128; }
+constexpr int tile_rows(int WR) { return WR == 0 ? 64 : WR == 3 ? 96 : WR == 4 ? 192 : WR == 5 ? 32 : WR * 128; }
 template <bool AKC, bool BKC, int EPI, int TN, int WR = 2, int WC = 2, int SMALL_DEPTH = 4, int LW = 0, int CW = 4>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds_char* smem, int nseg = 1,
                                           const int64_t* seg_delta = nullptr) {
@@ -256,7 +256,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
   // holds -- and the same lead in time needs -- twice the depth: with a lead of two K tiles (about 1 us here) operands
   // that come from HBM rather than from a cache arrive late, and products of this tile ran a quarter to a third slower
   // on cold operands than on warm ones.  (Two 128 x 128 workgroups that share a CU keep two K tiles ahead each.)
-  constexpr int SLOT = WR == 0 ? TILE_BYTES / 4 : WR == 4 || WC == 3 ? 3 * (TILE_BYTES / 4) : SMALL ? TILE_BYTES / 2 : TILE_BYTES, DEPTH = SMALL ? SMALL_DEPTH : 2, NSLOT = 2 * DEPTH + 1;
+  constexpr int SLOT = WR == 0 || WR == 5 ? TILE_BYTES / 4 : WR == 4 || WC == 3 ? 3 * (TILE_BYTES / 4) : SMALL ? TILE_BYTES / 2 : TILE_BYTES, DEPTH = SMALL ? SMALL_DEPTH : 2, NSLOT = 2 * DEPTH + 1;
   static_assert(A_BYTES <= SLOT && B_BYTES <= SLOT && (size_t)NSLOT * SLOT <= LDS_BYTES, "ring fits");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -939,15 +939,16 @@ __global__ __launch_bounds__(512, 2) void gemm_tiny_kernel(GemmArgs g, int tiles
   gemm_tile<true, BKC, EPI, EPI == EPI_SWIGLU ? 2 : 1, WR, 0, WR ? 4 : TINY_DEPTH, 4>(g, m0, n0, (lds_char*)smem_raw);
 }
 
-// One workgroup per tile of a whole product, by the shape S: 96 x 64 (four wavefronts of 48 x 32), 192 x 128 (eight of 96 x 32) or 128 x
-// 192 (eight of 32 x 96), and four that load.  They take products whose tiles of the next smaller shape are a little more than one
-// round and of the next larger one far less.  Two wavefronts per SIMD on the larger ones: GELU's arithmetic in the epilogue then
+// One workgroup per tile of a whole product, by the shape S: 32 x 64 (four wavefronts of 16 x 32), 96 x 64 (four of 48 x 32), 192 x 128
+// (eight of 96 x 32) or 128 x 192 (eight of 32 x 96), and four that load.  The first takes products of which it makes one round; the
+// others those whose tiles of the next smaller shape are a little more than one round and of the next larger one far less.  Two wavefronts per SIMD on the larger ones: GELU's arithmetic in the epilogue then
 // covers its own latency (1000 x 5120 x 1280: 24.0 us, 28.4 with four of 96 x 64).
-enum MidShape { MID_96x64, MID_192x128, MID_128x192 };
+enum MidShape { MID_96x64, MID_192x128, MID_128x192, MID_32x64 };
 template <int S> struct Mid {
-  static constexpr int rows = S == MID_96x64 ? 96 : S == MID_192x128 ? 192 : 128, cols = S == MID_96x64 ? 64 : S == MID_192x128 ? 128 : 192;
-  static constexpr int CW = S == MID_96x64 ? 4 : 8, threads = (CW + 4) * 64, depth = S == MID_96x64 ? 4 : 2;
-  static constexpr size_t lds = (size_t)(2 * depth + 1) * (S == MID_96x64 ? TILE_BYTES / 2 : 3 * (TILE_BYTES / 4));
+  static constexpr int WR = S == MID_96x64 ? 3 : S == MID_192x128 ? 4 : S == MID_128x192 ? 1 : 5, WC = S == MID_192x128 ? 1 : S == MID_128x192 ? 3 : 0;
+  static constexpr int rows = tile_rows(WR), cols = WC == 0 ? 64 : WC == 1 ? 128 : 192, TN = WC == 3 ? 3 : 1;
+  static constexpr int CW = WC == 0 ? 4 : 8, threads = (CW + 4) * 64, depth = S == MID_32x64 ? TINY_DEPTH : S == MID_96x64 ? 4 : 2;
+  static constexpr size_t lds = (size_t)(2 * depth + 1) * (S == MID_32x64 ? TILE_BYTES / 4 : S == MID_96x64 ? TILE_BYTES / 2 : 3 * (TILE_BYTES / 4));
 };
 template <bool BKC, int EPI, int S>
 __global__ __launch_bounds__(Mid<S>::threads, Mid<S>::threads / 256) void gemm_mid_kernel(GemmArgs g, int tiles_m, int tiles_n) {
@@ -959,8 +960,7 @@ __global__ __launch_bounds__(Mid<S>::threads, Mid<S>::threads / 256) void gemm_m
   }
   int tile_m, tile_n;
   tile_of<4>(bid, tiles_m, tiles_n, tile_m, tile_n);
-  gemm_tile<true, BKC, EPI, S == MID_128x192 ? 3 : 1, S == MID_96x64 ? 3 : S == MID_192x128 ? 4 : 1, S == MID_96x64 ? 0 : S == MID_192x128 ? 1 : 3,
-            Mid<S>::depth, 4, Mid<S>::CW>(g, tile_m * Mid<S>::rows, tile_n * Mid<S>::cols, (lds_char*)smem_raw);
+  gemm_tile<true, BKC, EPI, Mid<S>::TN, Mid<S>::WR, Mid<S>::WC, Mid<S>::depth, 4, Mid<S>::CW>(g, tile_m * Mid<S>::rows, tile_n * Mid<S>::cols, (lds_char*)smem_raw);
 }
 
 // Several weight-gradient products C_p += A_p^T . B_p in one launch of persistent workgroups.  Each workgroup
@@ -1091,7 +1091,7 @@ hipError_t launch_mid(const GemmArgs& g, hipStream_t s) {
 
 // Full tiles for every complete round of one tile per CU; what is left over -- a last round that would keep at most half of
 // the CUs busy, or a whole product with that few tiles -- goes out in smaller tiles, the smallest of which one round is
-// enough: 64 x 64, 128 x 64, 128 x 128, and beyond that 128 x 128 with a shallow ring, two workgroups to a CU.  A tile's time per K
+// enough: 32 x 64 (whole products), 64 x 64, 128 x 64, 128 x 128, and beyond that 128 x 128 with a shallow ring, two workgroups to a CU.  A tile's time per K
 // tile is what its CU's LDS and load path take (0.19, 0.28, 0.36 us for the first three while few CUs are busy, 0.5 for the third
 // when all are; full 1.05 to 1.4), so a smaller tile always finishes sooner than a larger one, but no two rounds of it do.
 // Measured (us; 64 x 64 / 128 x 64 / 128 x 128): 400 x 640 x 1728: 8.6 / 9.8 / 13.7; 1000 x 1280 x 5120: 36 / 26 / 34; 2048 x 2048 x
@@ -1100,7 +1100,7 @@ hipError_t launch_mid(const GemmArgs& g, hipStream_t s) {
 // against full ones, 2048 x 6144 x 2048: 49 / 48 (60 / 53).  The half-height tile is left to the SwiGLU backward, whose z it
 // rewrites in whole rows through LDS (2048 x 2816 x 2048: 36 / 39).  All give the same bits.
 // `shape`: 0 = this rule, else one tile shape for all: 1 = full, 2 = half-height (SwiGLU backward; elsewhere the rule), 3 = 128 x
-// 128, 4 = 64 x 64 (SwiGLU forward: 128 x 64), 5 = 128 x 64, 6 = 96 x 64, 7 = 192 x 128, 8 = 128 x 192 (SwiGLU: 128 x 64 for these).
+// 128, 4 = 64 x 64 (SwiGLU forward: 128 x 64), 5 = 128 x 64, 6 = 96 x 64, 7 = 192 x 128, 8 = 128 x 192, 9 = 32 x 64 (SwiGLU forward: 128 x 64 for these, backward for 6 to 8).
 template <bool BKC, int EPI>
 hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   constexpr bool HALF = EPI == EPI_DSWIGLU;            // where there are half-height tiles
@@ -1111,6 +1111,12 @@ hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   const int n_cu = cu_count(), tail = total % n_cu;
   const int t128x128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
   const SmallGrid t64 = small_grid<EPI>(g, 2, 2, total, shape ? total : tail), t128 = small_grid<EPI>(g, 1, 2, total, shape ? total : tail);
+  // 32 x 64 wherever these are one round: a CU loads a quarter less per K tile than for 64 x 64, and twice the CUs share the epilogue
+  // (us, operands from HBM in brackets: 400 x 640 x 1728 with residual 7.8 / 6.7 (9.3 / 7.6), 400 x 640 x 640 4.7 / 4.2 (5.2 / 4.6), 512 x
+  // 1024 x 1024 5.5 / 5.0, with GELU 7.9 / 6.2, its backward 8.1 / 6.1, 8 x 4096 x 4096 10.4 / 8.9 (15.0 / 13.4); from 64 x 64 x 64 on never
+  // slower).  In two rounds they lose: 100 x 5120 x 1280 7.0 / 10.3.
+  if constexpr (EPI != EPI_SWIGLU)
+    if (shape == 9 || (shape == 0 && mid_tiles<MID_32x64>(g) <= n_cu)) return launch_mid<BKC, EPI, MID_32x64>(g, s);
   if constexpr (EPI != EPI_SWIGLU && !HALF) {
     // Between two of the shapes above, for products that they would give to part of the CUs or twice to some: 96 x 64 before 128 x 64
     // (us; operands from HBM in brackets: 1000 x 1280 x 5120 24.8 / 23.8 (34.7 / 29.3), 1536 x 1024 x 1536 9.4 / 8.0), 192 x 128 or 128 x 192

@@ -517,8 +517,8 @@ int exec_backward_input(stage* st, int mb, const void* dy, void* dx, int l0, int
   return STAGE_OK;
 }
 
-// a kernel-level entry's kernel_set as the tile shape it forces: bf16 (2 .. 6) and fp32 products (2 .. 4); 0 = the rule on sizes
-int shape16(int kernel_set) { return kernel_set >= 2 && kernel_set <= 9 ? kernel_set - 1 : 0; }
+// a kernel-level entry's kernel_set as the tile shape it forces: bf16 (2 .. 10) and fp32 products (2 .. 4); 0 = the rule on sizes
+int shape16(int kernel_set) { return kernel_set >= 2 && kernel_set <= 10 ? kernel_set - 1 : 0; }
 int shape32(int kernel_set) { return kernel_set >= 2 && kernel_set <= 4 ? kernel_set - 1 : 0; }
 
 // A list of weight-gradient products, each reducing over nseg operand pairs in turn (pair s = the list's A and B

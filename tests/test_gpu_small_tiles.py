@@ -77,12 +77,35 @@ def test_tiles_between_the_powers_of_two(M, N, K):
         assert all(torch.equal(x, y) for x, y in zip(outs[0], o)), i
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (31, 64, 128), (33, 72, 448), (64, 136, 512), (65, 56, 576), (130, 200, 1088), (512, 1024, 64), (513, 1024, 64)])
+def test_tiles_of_32_rows(M, N, K):
+    """32 x 64 tiles (10) against full ones (2) and the rule (0), every epilogue they have: one row, on either side of a tile, reductions from one
+    K tile over the ring's depth of eight to two rounds of it; the last two are the largest that the rule gives to them and one past it."""
+    import torch
+    P0, R = P, lambda i, *sh: to_dev(rnd(synth.normal(46, i, sh, std=1.0 if i != 2 else 1.5 * K ** -0.5), "bf16"), "bf16")
+    A, B, Bt, Rd, Z = R(1, M, K), R(2, K, N), R(2, N, K), R(3, M, N), R(4, M, 2 * N)
+    outs = []
+    for ks in (2, 10, 0):
+        Cs = [torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(5)]
+        for c, mode, w, r in ((Cs[0], 0, B, None), (Cs[1], 0, B, Rd), (Cs[2], 1, Bt, None)):
+            assert L().stage_kernel_gemm(1, mode, M, N, K, P0(A), K, P0(w), w.shape[1], P0(c), N, None if r is None else P0(r), N, 0, ks, None) == 0
+        assert L().stage_kernel_gemm_act(1, 0, M, N, K, P0(A), K, P0(B), N, P0(Cs[3]), N, P0(Cs[4]), N, ks, None) == 0
+        dz = [Z[:, :N].contiguous().clone(), Z.clone()]      # (a single row is contiguous already)
+        for act in (0, 1):
+            assert L().stage_kernel_gemm_act_bwd(1, act, M, N, K, P0(A), K, P0(Bt), K, P0(dz[act]), (1 + act) * N, None, ks, None) == 0
+        outs.append(Cs + dz)
+    ref = A.double() @ B.double()
+    assert ((outs[0][0].double() - ref).abs().max() / ref.abs().max()).item() <= KTOL["bf16"]          # one bf16 rounding of the output
+    for i, o in enumerate(outs[1:]):
+        assert all(torch.equal(x, y) for x, y in zip(outs[0], o)), i
+
+
 @pytest.mark.parametrize("act", [0, 1])
 @pytest.mark.parametrize("M,f,K", [(1, 8, 64), (127, 64, 64), (129, 72, 128), (128, 136, 320), (257, 200, 384),
                                    (1100, 72, 128), (300, 2000, 192),
                                    (1100, 1736, 64), (1100, 3000, 64), (1100, 4200, 64)])
 def test_fused_activations_on_small_products(act, M, f, K):
-    """The tiles that the rule picks on 256 compute units, one round of which is enough: 64 x 64 (SwiGLU forward: 128 x 64, of 32 features)
+    """The tiles that the rule picks on 256 compute units, one round of which is enough: 32 x 64 or 64 x 64 (SwiGLU forward: 128 x 64, of 32 features)
     up to (300, 2000); then 128 x 64, 128 x 128 and two 128 x 128 workgroups to a compute unit (SwiGLU forward: the last of these twice, then
     full ones; SwiGLU backward: half-height ones at the end).  One row, one past a tile in each dimension, reductions from one K tile to past the ring.  Tolerance: one
     bf16 rounding of the output and of z, as for the larger tiles."""
