@@ -282,23 +282,27 @@ __device__ __forceinline__ void fwd_tile(lds_char* lds, const FragOff<HD>& fo, c
   for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[c][e]);
-  // A row's keys are held by two lanes, l and l + 32.  They exchange their maxima only when one of them found a larger one, and
-  // never their sums: each keeps its own until the end.
-  if (__any(mx * sl2 > m)) {                      // the running max moves for some query of the wavefront
-    const float mn = fmaxf(m, half_max(mx, hf) * sl2);
+  // A row's keys are held by two lanes, l and l + 32: they exchange their maxima, but never their sums, of which each keeps its own
+  // until the end.  The exponentials come before the branch that rescales O, not behind it: with the branch first, entered only
+  // where a maximum moves, the head_dim 64 kernel needs 134 registers instead of 126, so one of its 8-wavefront workgroups fits a CU
+  // instead of two (us, 134 / 126: 8 x 40 heads x 300 25.7 / 20.1, x 700 59.7 / 48.4, 4 x 16 x 2048 without mask 86.7 / 80.9), and
+  // head_dim 128 gains nothing by it (32 x 4096 141.3 / 140.8).
+  float p[NC][16];
+  mx = half_max(mx, hf);
+  const float mn = fmaxf(m, mx * sl2);
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) p[c][e] = fast_exp2(fmaf(sacc[c][e], sl2, -mn));
+  if (__any(mn != m)) {                          // the running max moved for some query of the wavefront
     const float alpha = fast_exp2(m - mn);
     l *= alpha;
 #pragma unroll
     for (int hb = 0; hb < G::NHB; ++hb)
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[hb][e] *= alpha;
-    m = mn;
   }
-  float p[NC][16];
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) p[c][e] = fast_exp2(fmaf(sacc[c][e], sl2, -m));
+  m = mn;
   bf16x8 pf[NC][2];
 #pragma unroll
   for (int c = 0; c < NC; ++c) { pf[c][0] = pack8(&p[c][0]); pf[c][1] = pack8(&p[c][8]); }
@@ -1079,9 +1083,10 @@ hipError_t fwd_launch(const AttnArgs& a, hipStream_t s) {
   static const hipError_t ready = allow_lds(attn_fwd_kernel<HD, NT, KS>, lds_bytes);
   if (ready != hipSuccess) return ready;
   const int nqt = (a.s + fwd_bq(NT, KS) - 1) / fwd_bq(NT, KS);
-  // 4-wavefront workgroups sit two to a CU: when the whole grid is resident at once, pair heavy with light.  (8-wavefront
-  // ones sit one to a CU and come in two rounds or more: heaviest first, and the light ones fill in behind.)
-  const int fold = (NT == FWD_NARROW || KS == 4) && a.causal && (int64_t)a.b * a.h * nqt <= RESIDENT;
+  // 4-wavefront workgroups, and those of head_dim 64, sit two to a CU: when the whole grid is resident at once, pair heavy with light
+  // (head_dim 64, 32 heads x 4096 107 us plain, 93 paired; 16 x 8192 195, 167).  (8-wavefront ones of head_dim 128 sit one to a CU
+  // and come in two rounds or more: heaviest first, and the light ones fill in behind.)
+  const int fold = (NT == FWD_NARROW || KS == 4 || HD == 64) && a.causal && (int64_t)a.b * a.h * nqt <= RESIDENT;
   hipLaunchKernelGGL((attn_fwd_kernel<HD, NT, KS>), dim3(a.h, nqt * a.b), dim3(NT), lds_bytes, s, a, fold);
   return hipGetLastError();
 }

@@ -1,0 +1,50 @@
+"""What the compiler made of kernels whose speed hangs on it: read from the code objects of the built library.  Runs without a GPU."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2507_00217_amd import build
+
+LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
+
+
+@pytest.fixture(scope="module")
+def code_objects(tmp_path_factory):
+    """The library's gfx950 code objects, one per translation unit with kernels, as files."""
+    if not os.path.exists(build.LIB):
+        build.build(verbose=False)
+    blob, d, paths, at = open(build.LIB, "rb").read(), tmp_path_factory.mktemp("co"), [], 0
+    while (at := blob.find(b"__CLANG_OFFLOAD_BUNDLE__", at)) >= 0:
+        n, p = struct.unpack_from("<Q", blob, at + 24)[0], at + 32
+        for _ in range(n):
+            off, size, tlen = struct.unpack_from("<QQQ", blob, p)
+            if blob[p + 24:p + 24 + tlen].endswith(b"gfx950") and size:
+                paths.append(d / f"{len(paths)}.co")
+                paths[-1].write_bytes(blob[at + off:at + off + size])
+            p += 24 + tlen
+        at += 24
+    assert paths
+    return paths
+
+
+@pytest.fixture(scope="module")
+def resources(code_objects):
+    """kernel -> {vgpr_count, vgpr_spill_count, private_segment_fixed_size}"""
+    out = {}
+    for path in code_objects:
+        text = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+        for kernel in text.split("- .agpr_count:")[1:]:
+            name = re.search(r"\.name:\s+(\S+)", kernel)[1]
+            out[name] = {k: int(re.search(rf"\.{k}:\s+(\d+)", kernel)[1]) for k in ("vgpr_count", "vgpr_spill_count", "private_segment_fixed_size")}
+    return out
+
+
+def test_two_forward_workgroups_of_head_dim_64_fit_a_compute_unit(resources):
+    """8 wavefronts each, so four to a SIMD: 512 / 4 registers, none spilled."""
+    found = {n: r for n, r in resources.items() if re.search(r"attn_fwd_kernelILi64ELi512E", n)}
+    assert len(found) == 2, sorted(resources)
+    for n, r in found.items():
+        assert r["vgpr_count"] <= 128 and r["vgpr_spill_count"] == 0 and r["private_segment_fixed_size"] == 0, (n, r)
