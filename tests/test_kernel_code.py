@@ -48,3 +48,33 @@ def test_two_forward_workgroups_of_head_dim_64_fit_a_compute_unit(resources):
     assert len(found) == 2, sorted(resources)
     for n, r in found.items():
         assert r["vgpr_count"] <= 128 and r["vgpr_spill_count"] == 0 and r["private_segment_fixed_size"] == 0, (n, r)
+
+
+def test_loading_wavefronts_wait_by_count(code_objects):
+    """The loops of the wavefronts that only load (loads to LDS and a barrier, no MFMA): the one wait in them is the counted one that leaves
+    later tiles outstanding."""
+    seen = 0
+    for path in code_objects:
+        text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", str(path)], capture_output=True, text=True, check=True).stdout
+        for func in re.split(r"\n(?=[0-9a-f]{16} <)", text):
+            name = re.search(r"<(\S+)>:", func)
+            if not name or not re.search(r"gemm_(quarter|tiny|mid)_kernel", name[1]):
+                continue
+            code = [(int(a, 16), i.strip()) for i, a in re.findall(r"^\s+(.+?)\s*// ([0-9A-F]+):", func, re.M)]
+            at, loops = {a: n for n, (a, _) in enumerate(code)}, []
+            for n, (a, ins) in enumerate(code):
+                jump = re.match(r"s_(?:cbranch_\w+|branch) (\d+)", ins)
+                if jump and int(jump[1]) >= 1 << 15:                              # a 16-bit count of words, negative: back
+                    first = at[a + 4 + 4 * (int(jump[1]) - (1 << 16))]
+                    body = [x for _, x in code[first:n]]
+                    if any(x.startswith("buffer_load") and x.endswith("lds") for x in body) and any(x == "s_barrier" for x in body):
+                        loops.append(body)
+            if not loops:
+                continue
+            body = min(loops, key=len)
+            if any(x.startswith("v_mfma") for x in body):                         # its own wavefronts load: no such loop
+                continue
+            waits = [x for x in body if x.startswith("s_waitcnt")]
+            assert len(waits) == 1 and re.search(r"vmcnt\([1-9]", waits[0]), (name[1], waits)
+            seen += 1
+    assert seen >= 30
