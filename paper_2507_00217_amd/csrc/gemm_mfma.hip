@@ -934,13 +934,13 @@ __global__ __launch_bounds__(DEPTH == 2 ? 256 : 512, 2) void gemm_quarter_kernel
   gemm_tile<true, BKC, EPI, 2, 1, 1, DEPTH, DEPTH == 2 ? 0 : 4>(g, m0, n0, (lds_char*)smem_raw);
 }
 
-// one workgroup per 64 x 64 (WR == 0) or 128 x 64 tile (WR == 1); four more wavefronts load
-template <bool BKC, int EPI, int WR>
-__global__ __launch_bounds__(512, 2) void gemm_tiny_kernel(GemmArgs g, int tiles_m, int tiles_n, int first) {
+// one workgroup per 64 x 64 (WR == 0) or 128 x 64 tile (WR == 1); four more wavefronts load (LW == 0: the four that multiply, see keeps_pace)
+template <bool BKC, int EPI, int WR, int LW = 4>
+__global__ __launch_bounds__(256 + 64 * LW, 2) void gemm_tiny_kernel(GemmArgs g, int tiles_m, int tiles_n, int first) {
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   int m0, n0;
   if (!small_tile<WR ? 1 : 2, 2, EPI == EPI_SWIGLU ? GLU_BN : BN, false>(tiles_m, tiles_n, first, g.M, EPI == EPI_SWIGLU ? g.N / 2 : g.N, m0, n0)) return;
-  gemm_tile<true, BKC, EPI, EPI == EPI_SWIGLU ? 2 : 1, WR, 0, WR ? 4 : TINY_DEPTH, 4>(g, m0, n0, (lds_char*)smem_raw);
+  gemm_tile<true, BKC, EPI, EPI == EPI_SWIGLU ? 2 : 1, WR, 0, WR ? 4 : TINY_DEPTH, LW>(g, m0, n0, (lds_char*)smem_raw);
 }
 
 // One workgroup per tile of a whole product, by the shape S: 32 x 64 (four wavefronts of 16 x 32), 96 x 64 (four of 48 x 32), 192 x 128
@@ -1073,13 +1073,13 @@ hipError_t launch_quarter(const GemmArgs& g, hipStream_t s, const SmallGrid& t) 
   hipLaunchKernelGGL(kern, dim3(t.n), dim3(DEPTH == 2 ? 256 : 512), LDS, s, g, t.tiles_m, t.tiles_n, t.first);
   return hipGetLastError();
 }
-template <bool BKC, int EPI, int WR>
+template <bool BKC, int EPI, int WR, int LW = 4>
 hipError_t launch_tiny(const GemmArgs& g, hipStream_t s, const SmallGrid& t) {
   constexpr size_t LDS = WR ? (size_t)9 * (TILE_BYTES / 2) : (size_t)(2 * TINY_DEPTH + 1) * (TILE_BYTES / 4);
-  auto kern = gemm_tiny_kernel<BKC, EPI, WR>;
+  auto kern = gemm_tiny_kernel<BKC, EPI, WR, LW>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(t.n), dim3(512), LDS, s, g, t.tiles_m, t.tiles_n, t.first);
+  hipLaunchKernelGGL(kern, dim3(t.n), dim3(256 + 64 * LW), LDS, s, g, t.tiles_m, t.tiles_n, t.first);
   return hipGetLastError();
 }
 
@@ -1091,6 +1091,16 @@ hipError_t launch_mid(const GemmArgs& g, hipStream_t s) {
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL(kern, dim3(mid_tiles<S>(g)), dim3(Mid<S>::threads), Mid<S>::lds, s, g, (g.M + Mid<S>::rows - 1) / Mid<S>::rows, (g.N + Mid<S>::cols - 1) / Mid<S>::cols);
   return hipGetLastError();
+}
+
+// 64 x 64 tiles whose last row of tiles is little filled, below others, over a B of more than 80 MiB: the wavefronts that multiply load
+// too.  With wavefronts of its own a tile goes at the speed of its loads, so the last row, which has few A rows to load, runs ahead of
+// the row that reads the same B until the L2 has dropped what they shared; where the multiplying wavefronts set the pace all tiles go
+// alike (us, with loading wavefronts / without: 65 x 8000 x 12352 54.2 / 40.1, its input-gradient form 54.3 / 39.7, 73 x 7168 x 8192 30.1 /
+// 26.9 and 31.0 / 24.9, 130 x 5120 x 13824 49.7 / 44.2; but 110 x 8000 x 12352 40.6 / 40.2, 65 x 7168 x 4096 14.1 / 15.4, 130 x 4096 x 8192
+// 23.5 / 25.4.  128 x 128 tiles gain by them on either side of this line).
+inline bool keeps_pace(const GemmArgs& g, const SmallGrid& t) {
+  return t.first < 0 && t.tiles_m > 1 && g.M % 64 > 0 && g.M % 64 <= 40 && (int64_t)g.N * g.K >= (int64_t)40 << 20;
 }
 
 // Full tiles for every complete round of one tile per CU; what is left over -- a last round that would keep at most half of
@@ -1148,7 +1158,11 @@ hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   }
   if (n_tiny) {
     if constexpr (EPI != EPI_SWIGLU)
-      if (shape == 4 || (shape == 0 && t64.n <= n_cu)) return launch_tiny<BKC, EPI, 0>(g, s, t64);
+      if (shape == 4 || (shape == 0 && t64.n <= n_cu)) {
+        if constexpr (EPI == EPI_STORE || EPI == EPI_RESID)
+          if (shape == 0 && keeps_pace(g, t64)) return launch_tiny<BKC, EPI, 0, 0>(g, s, t64);
+        return launch_tiny<BKC, EPI, 0>(g, s, t64);
+      }
     return launch_tiny<BKC, EPI, 1>(g, s, t128);
   }
   if (n_quarter) {

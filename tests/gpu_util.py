@@ -39,3 +39,34 @@ SMALL = {
 }
 for _c in SMALL.values():          # cap = the schedule's own peak of live microbatches
     _c["stash_cap"] = synth.peak_live(synth.make_schedule(_c))
+
+
+def launches(call):
+    """The kernels that call(stream) enqueues, as (mangled name, workgroups, threads of one), read off a stream capture; nothing runs."""
+    import ctypes as C
+
+    import torch
+
+    from paper_2507_00217_amd import stage as S
+
+    class KernelNodeParams(C.Structure):
+        _fields_ = [("block", C.c_uint * 3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", C.c_uint * 3), ("args", C.c_void_p), ("shared", C.c_uint)]
+
+    hip = S.lib()
+    hip.hipKernelNameRefByPtr.restype = C.c_char_p
+    stream = torch.cuda.Stream()
+    handle, graph, n = C.c_void_p(stream.cuda_stream), C.c_void_p(), C.c_size_t()
+    torch.cuda.synchronize()
+    assert hip.hipStreamBeginCapture(handle, 2) == 0            # relaxed
+    rc = call(handle)
+    assert hip.hipStreamEndCapture(handle, C.byref(graph)) == 0 and rc == 0
+    assert hip.hipGraphGetNodes(graph, None, C.byref(n)) == 0
+    nodes = (C.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, C.byref(n)) == 0
+    out = []
+    for node in nodes:
+        p = KernelNodeParams()
+        assert hip.hipGraphKernelNodeGetParams(C.c_void_p(node), C.byref(p)) == 0
+        out.append((hip.hipKernelNameRefByPtr(C.c_void_p(p.func), handle).decode(), p.grid[0] * p.grid[1] * p.grid[2], p.block[0]))
+    assert hip.hipGraphDestroy(graph) == 0
+    return out

@@ -6,7 +6,7 @@ import pytest
 
 from oracle import stage_oracle as so
 from paper_2507_00217_amd import synth
-from tests.gpu_util import rnd, to_dev, to_np
+from tests.gpu_util import launches, rnd, to_dev, to_np
 from tests.test_gpu_kernels import KTOL, L, P
 
 pytestmark = pytest.mark.gpu
@@ -225,3 +225,23 @@ def test_merged_weight_gradients_in_small_tiles(hidden, ffn):
         st.close()
     for a, b in zip(*grads):
         assert all(np.array_equal(a[k], b[k]) for k in a)
+
+
+@pytest.mark.parametrize("M,N,K,paced", [(65, 8000, 5248, True), (104, 8000, 5248, True), (105, 8000, 5248, False), (65, 8000, 5184, False), (129, 5120, 8256, True)])
+@pytest.mark.parametrize("form", ["forward", "residual", "input gradient"])
+def test_last_tile_row_keeps_pace(form, M, N, K, paced):
+    """64 x 64 tiles over a B of more than 80 MiB with 1 to 40 rows in the last row of tiles: the wavefronts that multiply load as well (four per
+    workgroup, not eight), with the bits of the other form; on either side of the lines."""
+    import torch
+    torch.manual_seed(47)
+    A, B = torch.randn((M, K), device="cuda:0").bfloat16(), torch.randn((N, K) if form == "input gradient" else (K, N), device="cuda:0").bfloat16()
+    R = torch.randn((M, N), device="cuda:0").bfloat16() if form == "residual" else None
+    outs = [torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(2)]
+
+    def run(out, ks, stream=None):
+        return L().stage_kernel_gemm(1, int(form == "input gradient"), M, N, K, P(A), K, P(B), B.shape[1], P(out), N, None if R is None else P(R), N, 0, ks, stream)
+    for o, ks in zip(outs, (0, 5)):
+        assert run(o, ks) == 0
+    assert torch.equal(outs[0], outs[1])
+    (name, _, threads), = launches(lambda stream: run(outs[0], 0, stream))
+    assert "gemm_tiny_kernel" in name and threads == (256 if paced else 512)
