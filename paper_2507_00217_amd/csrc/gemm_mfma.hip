@@ -1135,11 +1135,13 @@ hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
     // Between two of the shapes above, for products that they would give to part of the CUs or twice to some: 96 x 64 before 128 x 64
     // (us; operands from HBM in brackets: 1000 x 1280 x 5120 24.8 / 23.8 (34.7 / 29.3), 1536 x 1024 x 1536 9.4 / 8.0), 192 x 128 or 128 x 192
     // before two 128 x 128 to a CU (1000 x 5120 x 1280 18.9 / 16.3 (21.9 / 19.5), with GELU 27.0 / 23.7, its backward 31.2 / 27.1; 4096 x
-    // 1536 x 4096 52.7 / 44.4 (58.0 / 55.9), 2048 x 3072 x 4096 50.6 / 44.2).
-    const bool whole = shape == 0 && total < n_cu;
+    // 1536 x 4096 52.7 / 44.4 (58.0 / 55.9), 2048 x 3072 x 4096 50.6 / 44.2).  Short reductions with nothing but a store behind them are
+    // left to the two 128 x 128, of which one loads while the other stores (K 64 / 128 / 192, two 128 x 128 against 192 x 128: 1000 x 5120
+    // 5.4 / 6.1 / 7.0, 5.9 / 6.6 / 6.9, 565 x 10408 5.8 / 6.5 / 7.3, 6.4 / 7.1 / 7.3; with residual, K 64, 11.2 / 9.7).
+    const bool whole = shape == 0 && total < n_cu, large = whole && t128x128 > n_cu && (EPI != EPI_STORE || g.K >= 192);
     if (shape == 6 || (whole && t64.n > n_cu && mid_tiles<MID_96x64>(g) <= n_cu)) return launch_mid<BKC, EPI, MID_96x64>(g, s);
-    if (shape == 7 || (whole && t128x128 > n_cu && mid_tiles<MID_192x128>(g) <= n_cu)) return launch_mid<BKC, EPI, MID_192x128>(g, s);
-    if (shape == 8 || (whole && t128x128 > n_cu && mid_tiles<MID_128x192>(g) <= n_cu)) return launch_mid<BKC, EPI, MID_128x192>(g, s);
+    if (shape == 7 || (large && mid_tiles<MID_192x128>(g) <= n_cu)) return launch_mid<BKC, EPI, MID_192x128>(g, s);
+    if (shape == 8 || (large && mid_tiles<MID_128x192>(g) <= n_cu)) return launch_mid<BKC, EPI, MID_128x192>(g, s);
   }
   if (shape >= 4 || (shape == 0 && tail > 0 && t128.n <= n_cu)) n_tiny = shape ? total : tail;
   else if (shape == 3 || (shape == 0 && (HALF ? 4 : 2) * tail <= n_cu)) n_quarter = shape ? total : tail;

@@ -55,7 +55,7 @@ def test_reductions_around_the_ring(mode):
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 8, 64), (96, 64, 128), (97, 72, 192), (193, 136, 256), (129, 200, 320), (200, 392, 448), (400, 1736, 1088),
-                                   (1000, 1280, 64), (1000, 5120, 64), (4096, 1536, 64)])
+                                   (1000, 1280, 64), (1000, 5120, 192), (4096, 1536, 192)])
 def test_tiles_between_the_powers_of_two(M, N, K):
     """96 x 64 (7), 192 x 128 (8) and 128 x 192 tiles (9) against full ones (2) and the rule (0), every epilogue they have: one row, one past a
     tile, reductions around the ring's depths of two and four; the last three shapes are what the rule gives to each of them."""
@@ -245,3 +245,24 @@ def test_last_tile_row_keeps_pace(form, M, N, K, paced):
     assert torch.equal(outs[0], outs[1])
     (name, _, threads), = launches(lambda stream: run(outs[0], 0, stream))
     assert "gemm_tiny_kernel" in name and threads == (256 if paced else 512)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M,N", [(1000, 5120), (4096, 1536)])
+def test_short_reductions_with_a_plain_store(mode, M, N):
+    """192 x 128 and 128 x 192 tiles from 192 terms on; below, two 128 x 128 workgroups to a compute unit.  With a residual at any length."""
+    import torch
+    for K in (64, 128, 192):
+        A, B, R = (torch.randn(sh, device="cuda:0").bfloat16() for sh in ((M, K), (N, K) if mode else (K, N), (M, N)))
+        outs = [torch.empty((M, N), dtype=torch.bfloat16, device="cuda:0") for _ in range(2)]
+
+        def run(out, ks, stream=None, res=None):
+            return L().stage_kernel_gemm(1, mode, M, N, K, P(A), K, P(B), B.shape[1], P(out), N, res, N, 0, ks, stream)
+        for o, ks in zip(outs, (0, 2)):
+            assert run(o, ks) == 0
+        assert torch.equal(outs[0], outs[1])
+        (name, _, _), = launches(lambda stream: run(outs[0], 0, stream))
+        assert ("gemm_mid_kernel" if K >= 192 else "gemm_quarter_kernel") in name
+        if mode == 0:
+            (name, _, _), = launches(lambda stream: run(outs[0], 0, stream, P(R)))
+            assert "gemm_mid_kernel" in name
