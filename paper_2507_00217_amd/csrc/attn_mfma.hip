@@ -1164,19 +1164,24 @@ hipError_t bwd_fused_launch(const AttnArgs& a, hipStream_t s) {
 
 template <int HD>
 hipError_t bwd_t(const AttnArgs& a, hipStream_t s) {
-  // Both passes in one launch while the workgroups of the two (64 queries, 64 keys) number little more than what is resident: with two
-  // wavefronts per SIMD and workgroup up to one per CU (causal: two, whose light halves make room), with one up to 960 of them where
-  // registers allow three to a CU.  Measured (us, two launches / one; heads x positions): head_dim 128 10 x 200 21.4 / 14.1, 8 x 1024 43.1 /
-  // 32.4, 8 x 2048 70.8 / 60.0, but 16 x 2048 96.1 / 103, without mask 16 x 1000 49.8 / 53.6; head_dim 64 16 x 1024 32.1 / 26.1, 36 x 777 31.9 /
-  // 29.5, 40 x 512 25.7 / 19.0, but 16 x 2048 59.7 / 62.6.
-  if (a.width == 5) return bwd_fused_launch<HD, 2, 1>(a, s);
-  if (a.width == 6) return bwd_fused_launch<HD, 4, 2>(a, s);
-  if (a.width == 0) {
-    const int64_t per_head = (int64_t)a.b * ((a.s + 63) / 64);
-    const int64_t total = per_head * (a.h + a.hkv * (a.dkv_part ? dkv_splits(a.b, a.s, a.h, a.hkv, DKV_TQ_SMALL) : 1));
-    if (2 * total <= RESIDENT || (a.causal && total <= RESIDENT && (HD == 128 || a.s > 320))) return bwd_fused_launch<HD, 4, 2>(a, s);
-    if (HD == 64 && total <= 960) return bwd_fused_launch<HD, 2, 1>(a, s);
-  }
+  // Both passes in one launch while the workgroups of the two (64 queries, 64 keys) number little more than what is resident.  With two
+  // wavefronts per SIMD and workgroup (us, two launches / one; heads x positions): up to one per CU, head_dim 128 10 x 200 21.4 / 14.1, 8 x
+  // 1024 43.1 / 32.4, and with a causal mask, whose light halves make room, up to two, 8 x 2048 70.8 / 60.0; but 16 x 2048 96.1 / 103,
+  // without mask 16 x 1000 49.8 / 53.6; and of up to 320 positions, where there is little to make room in time, 100 x 65 17.2 / 22.0, 128 x 111
+  // 18.1 / 22.0, 82 x 192 24.0 / 26.8.
+  const int ns = a.dkv_part ? dkv_splits(a.b, a.s, a.h, a.hkv, DKV_TQ_SMALL) : 1;
+  const int64_t tiles = (int64_t)a.b * ((a.s + 63) / 64), n_dkv = tiles * a.hkv * ns, total = tiles * a.h + n_dkv;
+  // (Few dK/dV workgroups that walk several query heads each set the time by their chain, which two pairs of wavefronts halve.)
+  const bool long_chains = a.h > a.hkv * ns && n_dkv < RESIDENT / 2;
+  const bool two_pairs = 2 * total <= RESIDENT || (a.causal && total <= RESIDENT && (a.s > 320 || (HD == 128 && long_chains)));
+  if (a.width == 6 || (a.width == 0 && two_pairs)) return bwd_fused_launch<HD, 4, 2>(a, s);
+  // With one wavefront per SIMD: head_dim 128 those up to 320 positions, two to a CU (100 x 65 17.2 / 13.2, 128 x 111 18.1 / 14.7, 82 x 192 24.0 /
+  // 23.0; 51 x 316 29.0 / 28.0); head_dim 64 up to three to a CU, 768, and from three tiles on, which do not all end at once, up to 960 (16 x 1024
+  // 32.1 / 26.1, 36 x 777 31.9 / 29.5, 40 x 512 25.7 / 19.0, 160 x 192 without mask 18.8 / 16.9; but 240 x 65 without mask 13.9 / 16.3, 225 x 111
+  // 15.6 / 16.6, 16 x 2048 59.7 / 62.6).  Not the long chains (32 x 979 on 4 KV heads without scratch 199.8, as two launches with two pairs,
+  // below, 132; 8 x 2048 on 2 without mask 201, 131; 2 x 20 x 900 on 5 98.8, 80.0).
+  const bool one_pair = !long_chains && (HD == 128 ? a.causal && a.s <= 320 && total <= RESIDENT : total <= (a.s > 128 ? 960 : 768));
+  if (a.width == 5 || (a.width == 0 && one_pair)) return bwd_fused_launch<HD, 2, 1>(a, s);
   hipError_t e;      // dQ first: it also leaves delta = rowsum(dO * O) in a.delta for the dK/dV pass
   switch (fwd_shape(a, true)) {
     case SHAPE_WIDE: e = dq_launch<HD, FWD_WIDE, 1>(a, s); break;
@@ -1189,8 +1194,7 @@ hipError_t bwd_t(const AttnArgs& a, hipStream_t s) {
   // Two pairs of wavefronts per 32 keys, each on every second 32 queries, where that many 8-wavefront workgroups are resident at once
   // and there is more than a handful of query tiles.  Measured (us, one pair / two; heads x positions): head_dim 128 8 x 512 17.8 / 16.3,
   // 16 x 1024 31.0 / 26.0, 8 x 2048 54.5 / 42.1; head_dim 64 36 x 777 22.1 / 19.5, 16 x 2048 44.3 / 36.5; but 10 x 200 11.7 / 11.9.
-  const int64_t wgs = (int64_t)a.b * a.hkv * ((a.s + DKV_TQ_SMALL - 1) / DKV_TQ_SMALL) * (a.dkv_part ? dkv_splits(a.b, a.s, a.h, a.hkv, DKV_TQ_SMALL) : 1);
-  const bool two = a.width ? a.width == 4 : a.s > 320 && wgs <= (HD == 64 ? RESIDENT : RESIDENT / 2);
+  const bool two = a.width ? a.width == 4 : a.s > 320 && n_dkv <= (HD == 64 ? RESIDENT : RESIDENT / 2);
   return two ? dkv_launch<HD, DKV_TQ_SMALL, 2>(a, s) : dkv_launch<HD, DKV_TQ_SMALL, 1>(a, s);
 }
 

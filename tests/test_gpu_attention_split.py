@@ -1,7 +1,10 @@
 """Attention workgroups that split keys (forward, dQ) and queries (dK/dV) over more wavefronts."""
+import re
+
 import pytest
 
 from tests import test_gpu_kernels as K
+from tests.gpu_util import launches
 
 pytestmark = pytest.mark.gpu
 
@@ -15,11 +18,58 @@ def test_four_key_parts_and_two_query_parts(kernel_set, causal, b, s, h, hkv, hd
     K.test_attention("bf16", kernel_set, causal, b, s, h, hkv, hd)
 
 
-@pytest.mark.parametrize("causal,b,s,h,hkv,hd", [(0, 1, 320, 26, 26, 128), (0, 1, 321, 22, 22, 128), (1, 1, 1000, 2, 2, 128), (1, 2, 1000, 2, 1, 64),
-                                                 (1, 2, 321, 26, 26, 64), (1, 2, 320, 52, 26, 64), (1, 1, 2049, 1, 1, 64), (0, 1, 2048, 5, 5, 64)])
+ONE4, ONE2 = "bwd 4 2", "bwd 2 1"                     # one launch, two wavefronts per SIMD and workgroup or one
+ONE_PAIR, TWO_PAIRS = "dq 256 2, dkv 64 1", "dq 256 2, dkv 64 2"
+# (causal, b, s, h, hkv, hd, scratch): what the backward launches.  64-row tiles x (h + hkv x splits) is the count that the lines are drawn by.
+BACKWARD = [
+    ((0, 1, 320, 25, 25, 128, 0), ONE4), ((0, 1, 320, 26, 26, 128, 0), ONE_PAIR), ((0, 1, 321, 21, 21, 128, 0), ONE4), ((0, 1, 321, 22, 22, 128, 0), TWO_PAIRS),
+    ((1, 1, 320, 25, 25, 128, 0), ONE4), ((1, 1, 320, 26, 26, 128, 0), ONE2), ((1, 1, 320, 51, 51, 128, 0), ONE2), ((1, 1, 320, 52, 52, 128, 0), ONE_PAIR),
+    ((1, 2, 65, 33, 33, 128, 0), ONE2), ((1, 1, 321, 22, 22, 128, 0), ONE4), ((1, 1, 321, 42, 42, 128, 0), ONE4), ((1, 1, 321, 43, 43, 128, 0), ONE_PAIR),
+    ((0, 1, 2048, 8, 8, 128, 0), "dq 512 4, dkv 64 2"), ((1, 1, 2048, 8, 8, 128, 0), ONE4),
+    ((1, 2, 300, 32, 8, 128, 0), ONE4), ((1, 3, 81, 40, 20, 128, 0), ONE4), ((1, 3, 81, 40, 20, 128, 1), ONE2 + ", reduce"),      # long chains of query heads, and split
+    ((0, 1, 321, 21, 21, 64, 0), ONE4), ((0, 1, 321, 22, 22, 64, 0), ONE2), ((1, 1, 321, 42, 42, 64, 0), ONE4), ((1, 1, 321, 43, 43, 64, 0), ONE2),
+    ((1, 1, 320, 25, 25, 64, 0), ONE4), ((1, 1, 320, 26, 26, 64, 0), ONE2),
+    ((0, 1, 128, 192, 192, 64, 0), ONE2), ((0, 1, 128, 193, 193, 64, 0), ONE_PAIR), ((0, 1, 129, 160, 160, 64, 0), ONE2), ((0, 1, 129, 161, 161, 64, 0), ONE_PAIR),
+    ((0, 1, 385, 68, 68, 64, 0), ONE2), ((0, 1, 385, 69, 69, 64, 0), TWO_PAIRS),
+    ((0, 1, 512, 32, 8, 64, 0), TWO_PAIRS), ((0, 1, 512, 32, 8, 64, 1), ONE2 + ", reduce"), ((1, 1, 300, 64, 16, 64, 0), ONE_PAIR),
+]
+FORWARD = [((1, 1, 999, 2, 2, 128), "256 2"), ((1, 1, 1000, 2, 2, 128), "512 4"), ((1, 2, 1000, 8, 1, 128), "512 4"), ((1, 2, 1000, 9, 1, 128), "256 2"),
+           ((1, 2, 1000, 16, 1, 64), "512 4"), ((1, 2, 1000, 17, 1, 64), "256 2")]
+
+
+def _names(kernels):
+    out = []
+    for name, _, _ in kernels:
+        m = re.search(r"attn_(fwd|dq|dkv|bwd|dkv_reduce)_kernel(?:ILi\d+E(?:Li(\d+)E)(?:Li(\d+)E))?", name)
+        out.append("reduce" if m[1] == "dkv_reduce" else f"{m[1]} {m[2]} {m[3]}")
+    return ", ".join(out)
+
+
+@pytest.mark.parametrize("shape,expect", BACKWARD)
+def test_backward_launches_at_the_lines(shape, expect):
+    """The kernels themselves, on both sides of every line of the rule (a capture: nothing runs, so the buffers are only names)."""
+    import torch
+    causal, b, s, h, hkv, hd, scratch = shape
+    t = torch.zeros(256, dtype=torch.uint8, device="cuda:0")
+    need = K.L().stage_kernel_attention_bwd_scratch_bytes(b, s, h, hkv, hd)
+    assert not scratch or need > 0
+    got = launches(lambda stream: K.L().stage_kernel_attention_bwd_ws(1, b, s, h, hkv, hd, causal, *([K.P(t)] * 7 if scratch else [K.P(t)] * 6 + [None]),
+                                                                      need if scratch else 0, 0, stream))
+    assert _names(got) == expect
+
+
+@pytest.mark.parametrize("shape,expect", FORWARD)
+def test_forward_launches_at_the_lines(shape, expect):
+    import torch
+    causal, b, s, h, hkv, hd = shape
+    t = torch.zeros(256, dtype=torch.uint8, device="cuda:0")
+    got = launches(lambda stream: K.L().stage_kernel_attention_fwd(1, b, s, h, hkv, hd, causal, K.P(t), K.P(t), K.P(t), 0, stream))
+    assert _names(got) == "fwd " + expect
+
+
+@pytest.mark.parametrize("causal,b,s,h,hkv,hd", [x[:6] for x, _ in BACKWARD if not x[6]] + [(1, 1, 1000, 2, 2, 128), (1, 2, 1000, 2, 1, 64), (0, 1, 2048, 5, 5, 64)])
 def test_the_rule_at_its_lines(causal, b, s, h, hkv, hd):
-    """Where the rule changes shape: the backward in one launch up to 256, 512 and 960 workgroups, dK/dV above 320 positions, the forward
-    from 1000, dQ from 2048."""
+    """Both directions against the oracle on either side of every line of the rule, and where the forward takes four key parts."""
     K.test_attention("bf16", 0, causal, b, s, h, hkv, hd)
 
 
