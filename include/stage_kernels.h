@@ -19,8 +19,8 @@
  * (not SwiGLU or weight gradients), 10 = 32 x 64 (not SwiGLU forward or weight gradients); in fp32 2 / 3 / 4 = tiles of 64 x 64 / 32 x 32 / 16 x 16 (weight gradients: 32 x 32 for 4);
  * attention: 2 / 3 = forward and dQ workgroups of 8 / 4 wavefronts (dK/dV workgroups of 128 keys), 4 = forward and dQ
  * workgroups of 64 queries whose two wavefronts per query block each take half of the keys, dK/dV workgroups of 64 keys, 5 = the
- * same with four wavefronts per query block and, in dK/dV, two pairs of wavefronts per key block, 6 / 7 = the backward of 4 / 5 as
- * one launch.
+ * same with four wavefronts per query block in the forward and two pairs of wavefronts per key block in dK/dV, 6 / 7 = the backward
+ * of 4 / 5 as one launch (7: with four wavefronts per query block in dQ too; forward 6 / 7: the normal choice).
  * Return: 0, or STAGE_E_INVAL for
  * a shape the kernel does not take, STAGE_E_HIP for a failed launch.
  */

@@ -1067,14 +1067,14 @@ static int64_t fwd_count(const AttnArgs& a, int bq) { return (int64_t)a.b * a.h 
 // Four key parts instead of two (8 wavefronts on 64 queries, two to a SIMD where there was one) once there are steps enough to
 // halve: the merge and the longer start cost more below.  Measured (us, two parts / four; heads x positions): forward, head_dim
 // 128 8 x 1024 17.9 / 16.5, 8 x 2048 30.8 / 26.0, but 16 x 700 14.2 / 14.3, 8 x 512 11.5 / 11.8; head_dim 64 16 x 1024 12.7 / 11.1, 16 x 2048 22.6 /
-// 19.3, but 36 x 777 11.4 / 11.9.  dQ, whose registers allow one such workgroup per CU: 8 x 2048 32.0 / 30.5, 4 x 4096 55.8 / 50.8, but
-// 8 x 1024 19.3 / 20.4, and head_dim 64 in 512 workgroups 23.1 / 29.0.
-static FwdShape fwd_shape(const AttnArgs& a, bool dq = false) {
+// 19.3, but 36 x 777 11.4 / 11.9.  dQ takes four parts only inside the one-launch backward: where it is a launch of its own they give
+// nothing (backward of head_dim 128 without mask 8 x 2048 75.4 with four, 74.8 with two, 4 x 4096 134.1, 134.5, 5 x 3000 100.5, 100.4).
+static FwdShape fwd_shape(const AttnArgs& a) {
   if (a.width >= 1 && a.width <= 4) return (FwdShape)a.width;
   if (fwd_count(a, fwd_bq(FWD_WIDE)) >= RESIDENT) return SHAPE_WIDE;
   if (fwd_count(a, fwd_bq(FWD_NARROW)) >= RESIDENT) return SHAPE_NARROW;
-  const bool resident = fwd_count(a, fwd_bq(FWD_WIDE, 4)) <= (a.hd == 64 && !dq ? RESIDENT : RESIDENT / 2);
-  return resident && a.s >= (dq ? 2048 : 1000) ? SHAPE_SPLIT4 : SHAPE_SPLIT;
+  const bool resident = fwd_count(a, fwd_bq(FWD_WIDE, 4)) <= (a.hd == 64 ? RESIDENT : RESIDENT / 2);
+  return resident && a.s >= 1000 ? SHAPE_SPLIT4 : SHAPE_SPLIT;
 }
 
 template <int HD, int NT, int KS>
@@ -1106,7 +1106,7 @@ hipError_t dq_launch(const AttnArgs& a, hipStream_t s) {
   static const hipError_t ready = allow_lds(attn_dq_kernel<HD, NT, KS>, lds_bytes);
   if (ready != hipSuccess) return ready;
   const int nqt = (a.s + fwd_bq(NT, KS) - 1) / fwd_bq(NT, KS);
-  const int fold = (NT == FWD_NARROW || KS == 4) && a.causal && (int64_t)a.b * a.h * nqt <= RESIDENT;      // as in the forward
+  const int fold = NT == FWD_NARROW && a.causal && (int64_t)a.b * a.h * nqt <= RESIDENT;      // as in the forward
   hipLaunchKernelGGL((attn_dq_kernel<HD, NT, KS>), dim3(a.h, nqt * a.b), dim3(NT), lds_bytes, s, a, fold);
   return hipGetLastError();
 }
@@ -1183,11 +1183,10 @@ hipError_t bwd_t(const AttnArgs& a, hipStream_t s) {
   const bool one_pair = !long_chains && (HD == 128 ? a.causal && a.s <= 320 && total <= RESIDENT : total <= (a.s > 128 ? 960 : 768));
   if (a.width == 5 || (a.width == 0 && one_pair)) return bwd_fused_launch<HD, 2, 1>(a, s);
   hipError_t e;      // dQ first: it also leaves delta = rowsum(dO * O) in a.delta for the dK/dV pass
-  switch (fwd_shape(a, true)) {
+  switch (fwd_shape(a)) {
     case SHAPE_WIDE: e = dq_launch<HD, FWD_WIDE, 1>(a, s); break;
     case SHAPE_NARROW: e = dq_launch<HD, FWD_NARROW, 1>(a, s); break;
-    case SHAPE_SPLIT: e = dq_launch<HD, FWD_NARROW, 2>(a, s); break;
-    default: e = dq_launch<HD, FWD_WIDE, 4>(a, s); break;
+    default: e = dq_launch<HD, FWD_NARROW, 2>(a, s); break;
   }
   if (e != hipSuccess) return e;
   if (!dkv_small(a.b, a.s, a.h, a.hkv, a.width)) return dkv_launch<HD, DKV_TQ, 1>(a, s);

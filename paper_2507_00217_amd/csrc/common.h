@@ -48,9 +48,9 @@ struct AttnArgs {
   void* dqkv;                    // [b*s, d + 2*dkv]
   float* delta;                  // [b, h, s] scratch: rowsum(dout * o)
   int width;                     // workgroup shapes: 0 = chosen from the shape; forward / dQ 1 = 8 wavefronts, 2 = 4 wavefronts,
-                                 // 3 = 4 wavefronts with the keys split in two, 4 = 8 with the keys split in four; dK/dV 128 keys per
+                                 // 3 = 4 wavefronts with the keys split in two, 4 = 8 with the keys split in four (dQ: as 3); dK/dV 128 keys per
                                  // workgroup for 1 and 2, 64 for 3 and 4, with two pairs of wavefronts per 32 keys for 4;
-                                 // 5, 6 = the backward of 3, 4 in one launch (forward: by the shape)
+                                 // 5, 6 = the backward of 3, 4 in one launch, 6 with the keys split in four in dQ too (forward: by the shape)
   float* dkv_part;               // scratch for grouped-query attention, attn_bwd_part_bytes() bytes, or null: fp32 partial
                                  // dK | dV of each split of a KV head's query heads, [nsplit][b*s][2*dkv]
 };

@@ -25,7 +25,7 @@ BACKWARD = [
     ((0, 1, 320, 25, 25, 128, 0), ONE4), ((0, 1, 320, 26, 26, 128, 0), ONE_PAIR), ((0, 1, 321, 21, 21, 128, 0), ONE4), ((0, 1, 321, 22, 22, 128, 0), TWO_PAIRS),
     ((1, 1, 320, 25, 25, 128, 0), ONE4), ((1, 1, 320, 26, 26, 128, 0), ONE2), ((1, 1, 320, 51, 51, 128, 0), ONE2), ((1, 1, 320, 52, 52, 128, 0), ONE_PAIR),
     ((1, 2, 65, 33, 33, 128, 0), ONE2), ((1, 1, 321, 22, 22, 128, 0), ONE4), ((1, 1, 321, 42, 42, 128, 0), ONE4), ((1, 1, 321, 43, 43, 128, 0), ONE_PAIR),
-    ((0, 1, 2048, 8, 8, 128, 0), "dq 512 4, dkv 64 2"), ((1, 1, 2048, 8, 8, 128, 0), ONE4),
+    ((0, 1, 2048, 8, 8, 128, 0), TWO_PAIRS), ((1, 1, 2048, 8, 8, 128, 0), ONE4),
     ((1, 2, 300, 32, 8, 128, 0), ONE4), ((1, 3, 81, 40, 20, 128, 0), ONE4), ((1, 3, 81, 40, 20, 128, 1), ONE2 + ", reduce"),      # long chains of query heads, and split
     ((0, 1, 321, 21, 21, 64, 0), ONE4), ((0, 1, 321, 22, 22, 64, 0), ONE2), ((1, 1, 321, 42, 42, 64, 0), ONE4), ((1, 1, 321, 43, 43, 64, 0), ONE2),
     ((1, 1, 320, 25, 25, 64, 0), ONE4), ((1, 1, 320, 26, 26, 64, 0), ONE2),
