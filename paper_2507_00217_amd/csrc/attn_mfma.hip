@@ -1019,14 +1019,15 @@ __global__ __launch_bounds__(TQ * 4 * QS, QS == 2 && HD == 64 ? 4 : 2) void attn
 }
 
 // dQ and dK/dV of a small problem in one launch, which neither of them fills by itself: the first n_dkv workgroups are dK/dV's
-// (the longer ones), the others dQ's.
+// (the longer ones), the others dQ's, heaviest tiles first in both (heavy tiles paired with light ones, as in the launches of their own: head_dim
+// 128 8 x 2048 59.5, paired 63.8 us, 2 x 8 x 700 26.7, 29.5; head_dim 64 16 x 1000 26.1, 28.1, 8 x 2048 41.6, 41.8).
 template <int HD, int KS, int QS>
-__global__ __launch_bounds__(256 * QS, 2) void attn_bwd_kernel(AttnArgs a, int nsplit, int n_dkv, int fold) {
+__global__ __launch_bounds__(256 * QS, 2) void attn_bwd_kernel(AttnArgs a, int nsplit, int n_dkv) {
   static_assert(KS == 2 * QS, "one workgroup size");
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   const int id = blockIdx.x;
-  if (id < n_dkv) dkv_workgroup<HD, DKV_TQ_SMALL, QS, true>(a, nsplit, fold, (lds_char*)smem_raw, id % (a.hkv * nsplit), id / (a.hkv * nsplit));
-  else dq_workgroup<HD, 256 * QS, KS>(a, fold, (lds_char*)smem_raw, (id - n_dkv) % a.h, (id - n_dkv) / a.h);
+  if (id < n_dkv) dkv_workgroup<HD, DKV_TQ_SMALL, QS, true>(a, nsplit, 0, (lds_char*)smem_raw, id % (a.hkv * nsplit), id / (a.hkv * nsplit));
+  else dq_workgroup<HD, 256 * QS, KS>(a, 0, (lds_char*)smem_raw, (id - n_dkv) % a.h, (id - n_dkv) / a.h);
 }
 
 // dK | dV of dqkv = sum over splits, in split order (bit-reproducible), rounded once to bf16
@@ -1154,7 +1155,7 @@ hipError_t bwd_fused_launch(const AttnArgs& a, hipStream_t s) {
   if (ready != hipSuccess) return ready;
   const int nsplit = a.dkv_part ? dkv_splits(a.b, a.s, a.h, a.hkv, DKV_TQ_SMALL) : 1, nt = (a.s + 63) / 64;
   const int n_dkv = a.hkv * nsplit * nt * a.b, n_dq = a.h * nt * a.b;
-  hipLaunchKernelGGL((attn_bwd_kernel<HD, KS, QS>), dim3(n_dkv + n_dq), dim3(256 * QS), lds_bytes, s, a, nsplit, n_dkv, 0);
+  hipLaunchKernelGGL((attn_bwd_kernel<HD, KS, QS>), dim3(n_dkv + n_dq), dim3(256 * QS), lds_bytes, s, a, nsplit, n_dkv);
   if (nsplit > 1) {
     const int64_t pieces = (int64_t)a.b * a.s * (2 * a.hkv * HD / 4);
     hipLaunchKernelGGL(attn_dkv_reduce_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, a, nsplit, a.h * HD, a.hkv * HD);
@@ -1191,8 +1192,11 @@ hipError_t bwd_t(const AttnArgs& a, hipStream_t s) {
   if (e != hipSuccess) return e;
   if (!dkv_small(a.b, a.s, a.h, a.hkv, a.width)) return dkv_launch<HD, DKV_TQ, 1>(a, s);
   // Two pairs of wavefronts per 32 keys, each on every second 32 queries, where that many 8-wavefront workgroups are resident at once
-  // and there is more than a handful of query tiles.  Measured (us, one pair / two; heads x positions): head_dim 128 8 x 512 17.8 / 16.3,
-  // 16 x 1024 31.0 / 26.0, 8 x 2048 54.5 / 42.1; head_dim 64 36 x 777 22.1 / 19.5, 16 x 2048 44.3 / 36.5; but 10 x 200 11.7 / 11.9.
+  // and there is more than a handful of query tiles.  Measured on what comes here (backward in us, one pair / two; heads x positions):
+  // head_dim 128 without mask 8 x 2048 89.7 / 77.0, 16 x 1024 52.1 / 47.4, 32 x 512 33.0 / 31.9, but 9 x 2048 116 / 124, 40 x 400 37.7 / 42.6, 40 x
+  // 200 22.4 / 22.7; 32 on 4 KV heads x 979 without scratch 221 / 156; head_dim 64 (whose two-pair kernel spills 16 registers to stay at
+  // 128) 16 x 2048 66.5 / 58.2, 32 x 1024 39.7 / 36.8, without mask 85.0 / 79.9, 64 x 512 31.8 / 32.2, but 17 x 2048 without mask 108 / 113, 128 x 250 18.9
+  // / 20.6.
   const bool two = a.width ? a.width == 4 : a.s > 320 && n_dkv <= (HD == 64 ? RESIDENT : RESIDENT / 2);
   return two ? dkv_launch<HD, DKV_TQ_SMALL, 2>(a, s) : dkv_launch<HD, DKV_TQ_SMALL, 1>(a, s);
 }
