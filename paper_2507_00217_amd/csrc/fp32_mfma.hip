@@ -408,21 +408,49 @@ __global__ __launch_bounds__(W * 64) void wgrad32_group_kernel(Wgrad32Group gg) 
 
 // Tile shapes: 0 = 64 x 64 by 4 wavefronts, 1 = 32 x 32 by 8, 2 = 16 x 16 (SwiGLU forward: 16 x 32) by 16.  The rule takes
 // the one whose matrix-core time on the fullest CU is least: rounds of one tile per CU, times the tile's area, times what
-// the shape loses to operand traffic.  The losses are measured where every shape fills the chip (M 1400, N 8192, K 1024: 208 /
-// 234 / 507 us with a slow-index B; 16 x 16 tiles lose more with both operands reduction-contiguous, whose loads touch 16 rows
-// each); the rounds decide where they do not (448 x 512 x 1408: 26.1 / 9.2 / 18.2 us, 128 x 256 x 1024: 19.9 / 7.2 / 4.8 us).
-int pick32(int mode, int M, int N, int n_shapes) {
+// the shape loses to operand traffic.  For 32 x 32 tiles that depends on their form (via_lds32): 1.2 with a slow-index B, straight to registers
+// or through LDS (against 64 x 64 1.2 to 1.28 and 1.2 to 1.28 over 1024 x 2432 .. 1400 x 4096, K 448 .. 1024; SwiGLU 1.2 to 1.55: 1084 x 2016 x 448 54.8 us in
+// 64 x 64, 62.3, 900 x 1300 x 640 44.3, 52.8), 1.45 with both operands reduction-contiguous straight to registers and 1.19 through LDS
+// (1024 x 2432 x 1024 56.8 / 55.1, GELU backward 900 x 2600 x 640 55.0 / 44.4, 700 x 1024 x 1024 20.9 / 18.6), counted in pairs of rounds on wide
+// outputs, whose two workgroups per CU share less (171 x 4000 x 1024 20.9 / 24.3, 222 x 3232 x 512 12.6 / 14.4, 1084 x 4032 x 448 51.8 / 53.5).  M 1400, N 8192, K 1024: 208 /
+// 234 / 507 us with a slow-index B.  The rounds decide where a shape does not fill the chip (448 x 512 x 1408: 26.1 / 9.2 / 18.2 us, 128 x 256 x 1024:
+// 19.9 / 7.2 / 4.8 us).
+int pick32(int mode, int M, int N, bool via_lds) {
+  const double loss[3] = {1., mode != GEMM_NT ? 1.2 : via_lds ? 1.19 : 1.45, mode != GEMM_NT ? 2.4 : 2.8};
   static const int tile[3] = {64, 32, 16};
-  static const double loss[2][3] = {{1., 1.15, 2.4}, {1., 1.15, 2.8}};
   const int n_cu = cu_count();
   int best = 0;
   double bt = 0.;
-  for (int i = 0; i < n_shapes; ++i) {
+  for (int i = 0; i < 3; ++i) {
     const int64_t tiles = (int64_t)((M + tile[i] - 1) / tile[i]) * ((N + tile[i] - 1) / tile[i]);
-    const double t = (double)((tiles + n_cu - 1) / n_cu) * tile[i] * tile[i] * loss[mode == GEMM_NT][i];
+    int64_t rounds = (tiles + n_cu - 1) / n_cu;
+    if (i == 1 && mode == GEMM_NT && via_lds && N > 2048 && rounds > 1) rounds += rounds & 1;
+    const double t = (double)rounds * tile[i] * tile[i] * loss[i];
     if (i == 0 || t < bt) { best = i; bt = t; }
   }
   return best;
+}
+
+// Whether the operands of 32 x 32 tiles go through LDS (us, straight to registers / through LDS: input gradients 448 x 512 x 512 6.2 / 5.1, x
+// 1536 13.8 / 10.0, x 2816 22.8 / 15.8, 700 x 1024 x 3072 66 / 44, forward 448 x 512 x 1408 11.3 / 9.2, 700 x 3072 x 1024 54.5 / 50.4, SwiGLU 300 x 1024 x 768
+// 20.6 / 16.7, its backward 448 x 1408 x 512 15.7 / 13.2).  Not where
+//  - rows do not start on 128-byte lines, so that a slice's rows are not whole lines, unless the reduction is long (forward 700 x 1024 x 264
+//    7.3 / 8.8, 1000 x 1000 x 520 13.2 / 14.9, x 1288 31.7 / 30.7; GELU backward 700 x 1024 x 504 11.3 / 14.2, x 1288 28.2 / 27.6;
+//    SwiGLU 114 x 1020 x 1024 12.0 / 12.9);
+//  - there are more tiles than the two per CU that its LDS lets in at once, where four of the other form are, and little to win: up to
+//    256 terms (forward 700 x 1024 x 256 7.6 / 8.1, GELU backward 9.7 / 11.0, but input gradients 8.5 / 7.9), forward of more than four
+//    tiles per CU up to 512 (448 x 2816 x 512 18.1 / 20.6), GELU (222 x 3232 x 416 12.5 / 13.8, 700 x 1024 x 1408 27.8 / 29.7), SwiGLU of more than four
+//    (448 x 1408 x 512 22.7 / 23.2); and SwiGLU up to 256 terms at any count (514 x 432 x 64 4.2 / 4.4, 374 x 464 x 256 5.6 / 5.9).
+template <int MODE, int EPI>
+bool via_lds32(const GemmArgs& g) {
+  constexpr bool BKC = MODE == GEMM_NT;
+  const int64_t tiles = (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32), n_cu = cu_count();
+  const bool lines = g.lda % 32 == 0 && g.ldb % 32 == 0 && (((uintptr_t)g.A | (uintptr_t)g.B) & 127) == 0;
+  if (EPI == E32_GELU && tiles > 2 * n_cu) return false;
+  if (EPI == E32_SWIGLU && (tiles > 4 * n_cu || g.K <= 256)) return false;
+  if (!lines) return g.K >= 1280;
+  if (EPI == E32_GENERAL && BKC) return tiles <= 2 * n_cu || g.K > 64;
+  return tiles <= 2 * n_cu || g.K > (EPI == E32_GENERAL && tiles > 4 * n_cu ? 512 : 256);
 }
 
 template <int MODE, int MB, int NB, int W, int EPI, bool VIA_LDS = false>
@@ -435,18 +463,11 @@ hipError_t launch32(const GemmArgs& g, hipStream_t s) {
 template <int MODE, int EPI>
 hipError_t pick_launch32(const GemmArgs& g, hipStream_t s, int shape) {
   constexpr int NB3 = EPI == E32_SWIGLU ? 2 : 1;
-  const int which = shape > 0 ? shape - 1 : pick32(MODE, g.M, g.N, 3);
+  // (a forced shape keeps to LDS on fewer conditions, so that tests reach it at the edges of its slices)
+  const bool via_lds = shape > 0 ? !((EPI == E32_GELU || EPI == E32_SWIGLU) && (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32) > 4 * cu_count()) : via_lds32<MODE, EPI>(g);
+  const int which = shape > 0 ? shape - 1 : pick32(MODE, g.M, g.N, via_lds);
   if (which == 0) return launch32<MODE, 4, 4, 4, EPI>(g, s);
-  if (which == 1) {
-    // 32 x 32 tiles through LDS against straight to registers (us): input gradients 448 x 512 x 512 6.2 / 5.1, x 1536 13.8 / 10.0, x 2816 22.8 /
-    // 15.8, 700 x 1024 x 3072 66 / 44, forward 448 x 512 x 1408 11.3 / 9.2, 700 x 3072 x 1024 54.5 / 50.4, SwiGLU 300 x 1024 x 768 20.6 / 16.7, its
-    // backward 448 x 1408 x 512 15.7 / 13.2.  An activation with its second output over many rounds keeps the form that lets four workgroups
-    // share a CU: GELU 700 x 3072 x 768 44.8 / 46.1, SwiGLU 448 x 1408 x 512 22.7 / 23.2.
-    if constexpr (EPI == E32_GELU || EPI == E32_SWIGLU) {
-      if ((int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32) > 4 * cu_count()) return launch32<MODE, 2, 2, 8, EPI>(g, s);
-    }
-    return launch32<MODE, 2, 2, 8, EPI, true>(g, s);
-  }
+  if (which == 1) return via_lds ? launch32<MODE, 2, 2, 8, EPI, true>(g, s) : launch32<MODE, 2, 2, 8, EPI>(g, s);
   return launch32<MODE, 1, NB3, 16, EPI>(g, s);
 }
 

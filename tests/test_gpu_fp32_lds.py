@@ -1,7 +1,11 @@
 """fp32 products whose 32 x 32 tiles take their operands through LDS."""
+import re
+
 import pytest
 
 from tests import test_gpu_fp32 as F
+from tests.gpu_util import launches
+from tests.test_gpu_kernels import L, P
 
 pytestmark = pytest.mark.gpu
 
@@ -30,3 +34,47 @@ def test_one_round_by_the_rule(mode, M, N, K):
 def test_activations_on_either_side_of_four_rounds(act, M, f, K):
     """Activations over more than four tiles per compute unit take their operands straight into registers."""
     F.test_fused_activations(act, 3, M, f, K)
+
+
+FORWARD, RESID, DGRAD, GELU, SWIGLU, DGELU, DSWIGLU = range(7)
+# (kind, M, N, K): tile and whether its operands go through LDS, on both sides of every line (256 compute units); SwiGLU's N counts gate and up
+RULE = [
+    ((FORWARD, 448, 512, 256), (32, True)), ((FORWARD, 448, 512, 260), (32, False)), ((FORWARD, 448, 512, 1276), (32, False)), ((FORWARD, 448, 512, 1284), (32, True)),
+    ((FORWARD, 512, 1024, 256), (32, True)), ((FORWARD, 516, 1024, 256), (32, False)), ((FORWARD, 516, 1024, 288), (32, True)),
+    ((FORWARD, 448, 2336, 512), (32, True)), ((FORWARD, 448, 2816, 512), (32, False)), ((FORWARD, 700, 3072, 768), (32, True)),
+    ((FORWARD, 1024, 2432, 512), (64, False)), ((FORWARD, 1084, 4032, 448), (64, False)), ((RESID, 448, 512, 1408), (32, True)),
+    ((DGRAD, 516, 1024, 64), (64, False)), ((DGRAD, 1084, 1024, 64), (32, False)), ((SWIGLU, 114, 2040, 1024), (32, False)), ((DGRAD, 516, 1024, 96), (32, True)), ((DGRAD, 512, 1024, 64), (32, True)), ((DGRAD, 448, 512, 504), (32, False)),
+    ((DGRAD, 700, 1024, 1288), (32, True)), ((DGRAD, 171, 4000, 1536), (64, False)), ((DGRAD, 1024, 2432, 1024), (32, True)), ((DGRAD, 1084, 4032, 448), (64, False)),
+    ((GELU, 512, 1024, 512), (32, True)), ((GELU, 516, 1024, 512), (32, False)), ((GELU, 448, 512, 264), (32, False)),
+    ((SWIGLU, 448, 1024, 256), (32, False)), ((SWIGLU, 448, 1024, 288), (32, True)), ((SWIGLU, 448, 1664, 512), (32, True)), ((SWIGLU, 448, 2048, 512), (64, False)), ((SWIGLU, 448, 2816, 512), (32, False)),
+    ((SWIGLU, 900, 2600, 640), (64, False)), ((SWIGLU, 1084, 4032, 448), (64, False)),
+    ((DGELU, 512, 1024, 256), (32, True)), ((DGELU, 516, 1024, 256), (64, False)), ((DGELU, 900, 2600, 640), (32, True)), ((DSWIGLU, 516, 1024, 288), (32, True)),
+    ((DSWIGLU, 451, 1536, 1280), (32, True)), ((DSWIGLU, 171, 4000, 1280), (64, False)), ((DSWIGLU, 195, 1000, 200), (32, False)),
+]
+
+
+@pytest.mark.parametrize("shape,expect", RULE)
+def test_tile_and_form_by_the_rule(shape, expect):
+    """Read off the launched kernel (a capture: nothing runs, so the buffers are only names)."""
+    import torch
+    kind, M, N, K = shape
+    t = P(torch.zeros(256, dtype=torch.uint8, device="cuda:0"))
+    if kind <= DGRAD:
+        (name, _, _), = launches(lambda s: L().stage_kernel_gemm(0, int(kind == DGRAD), M, N, K, t, K, t, K if kind == DGRAD else N, t, N, t if kind == RESID else None, N, 0, 0, s))
+    elif kind <= SWIGLU:
+        f = N // 2 if kind == SWIGLU else N
+        (name, _, _), = launches(lambda s: L().stage_kernel_gemm_act(0, int(kind == SWIGLU), M, f, K, t, K, t, N, t, N, t, f, 0, s))
+    else:
+        (name, _, _), = launches(lambda s: L().stage_kernel_gemm_act_bwd(0, int(kind == DSWIGLU), M, N, K, t, K, t, K, t, (1 + (kind == DSWIGLU)) * N, t, 0, s))
+    m = re.search(r"gemm32_kernelILi\d+ELi(\d+)ELi\d+ELi\d+ELi\d+ELb([01])E", name)
+    assert (16 * int(m[1]), m[2] == "1") == expect
+
+
+@pytest.mark.parametrize("mode,M,N,K", [(0, 516, 1024, 256), (0, 448, 512, 260), (1, 448, 512, 504), (0, 65, 140, 1276)])
+def test_straight_to_registers_by_the_rule(mode, M, N, K):
+    F.test_products(mode, 0, M, N, K)
+
+
+@pytest.mark.parametrize("act,M,f,K", [(0, 516, 1024, 96), (1, 448, 512, 256), (1, 65, 100, 264)])
+def test_activations_straight_to_registers_by_the_rule(act, M, f, K):
+    F.test_fused_activations(act, 0, M, f, K)
