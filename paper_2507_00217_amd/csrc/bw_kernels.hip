@@ -318,7 +318,9 @@ __device__ __forceinline__ void gradient_row_sums(const ColSum& j, int col0, int
   }
 }
 
-__global__ __launch_bounds__(SUM_WAVES * 64) void col_sum_kernel(ColSumList l) {
+// (Two workgroups to a CU: 64 registers.  With 67 more than 256 workgroups took two rounds: a bias gradient of 2048 x 18432 in two
+// steps 17.9 instead of 17.2 us.)
+__global__ __launch_bounds__(SUM_WAVES * 64, 8) void col_sum_kernel(ColSumList l) {
   __shared__ float sums[SUM_WAVES][64];
   int ji = 0;
   while (ji + 1 < l.n && (int)blockIdx.x >= l.first[ji + 1]) ++ji;
@@ -478,17 +480,18 @@ hipError_t norm_bwd_noalloc(DType dt, const NormArgs& n, hipStream_t s) {
 
 // ---------------------------------------------------------------------------
 // Gradient of a linear map's bias: the column sums of its dZ, added to the fp32 accumulator, with a fixed summation order (no
-// atomics).  Up to BIAS_DIRECT_ROWS rows col_sum_kernel sums dZ itself, in the launch that also adds the norms' partial sums.
+// atomics).  Up to a number of rows (bias_grad_direct) col_sum_kernel sums dZ itself, in the launch that also adds the norms' partial sums.
 // Beyond that two steps: BIAS_PARTS row ranges are summed by one workgroup each per 32 x (16 / sizeof(T)) columns -- 8 row
 // lanes per column group, combined through LDS in lane order -- then col_sum_kernel adds the parts.  The four maps of a
 // layer go out together.
 // The line: a workgroup of the one step owns its 64 columns alone, so its time grows with the rows, where the two steps spread
-// them over 64 workgroups but pay a second launch.  us, one step / two, 4928 columns: bf16 400 rows 4.2 / 6.8, 1024 4.4 / 7.0,
-// 2048 6.1 / 8.0, 4096 9.9 / 11.0; 18432 columns: 400 rows 6.9 / 11.5, 2048 18.1 / 18.8, 3072 25.4 / 23.8; fp32, 1920 columns:
-// 400 rows 3.4 / 6.5, 2048 6.1 / 6.5, 3072 9.4 / 7.4.
+// them over 64 workgroups but pay a second launch.  Rows that start on 128-byte lines, up to 16384 columns: 2048 (us, one step / two;
+// bf16, 5120 columns, 1024 rows 4.4 / 6.4, 2048 5.5 / 7.2; 12288 columns, 2048 rows 10.5 / 12.5; fp32, 5120 columns, 2048 rows 9.8 / 11.1, 1920 columns, 1800
+// rows 5.5 / 5.9, 2048 6.2 / 5.9, 3072 9.4 / 7.4).  Others 1024, more than 8192 columns 512: the 128 bytes of a workgroup's columns are then two lines, each fetched twice (bf16, 5144
+// columns, 1024 rows 5.4 / 6.4, 2048 8.7 / 7.6; fp32, 3576 columns, 1024 rows 4.7 / 6.8, 1800 9.3 / 7.5; bf16, 12280 columns,
+// 1024 rows 9.7 / 9.2).  On lines but wider 1024: there are workgroups enough to be past the latency (18432 columns, bf16, 1024 rows 11.5 / 12.0, 2048 18.0 / 17.1; fp32, 2048 rows 27.7 / 26.3).
 // ---------------------------------------------------------------------------
 constexpr int BIAS_PARTS = 64;
-constexpr int BIAS_DIRECT_ROWS = 2048;
 size_t bias_grad_partial_bytes(int n) { return n > 0 ? (size_t)BIAS_PARTS * n * sizeof(float) : 0; }
 
 template <typename T>
@@ -526,11 +529,20 @@ __global__ __launch_bounds__(256) void bias_grad_partial_kernel(BiasGradList l) 
   }
 }
 
-bool bias_grad_direct(int rows) { return rows <= BIAS_DIRECT_ROWS; }
+bool bias_grad_direct(DType dt, const BiasGradList& l) {
+  const int64_t es = dt == DT_F32 ? 4 : 2;
+  bool lines = true;
+  int64_t cols = 0;
+  for (int i = 0; i < l.n; ++i) {
+    lines = lines && ((uintptr_t)l.j[i].dz & 127) == 0 && l.j[i].ld * es % 128 == 0;
+    cols += l.j[i].cols;
+  }
+  return l.rows <= (lines ? cols <= 16384 ? 2048 : 1024 : cols <= 8192 ? 1024 : 512);
+}
 hipError_t bias_grad_rows(DType dt, BiasGradList& l, ColSumList* sums, hipStream_t s) {
   const int V = dt == DT_F32 ? 4 : 8;
   if (l.n == 0) return hipSuccess;
-  const bool direct = bias_grad_direct(l.rows);
+  const bool direct = bias_grad_direct(dt, l);
   int total = 0;
   for (int i = 0; i < l.n; ++i) {
     const BiasGrad& j = l.j[i];

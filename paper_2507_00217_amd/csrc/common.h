@@ -114,7 +114,7 @@ hipError_t norm_bwd(DType dt, const NormArgs& n, hipStream_t s);
 // then col_sums_add of what norm_col_sums (and bias_grad_rows) put on a list
 hipError_t norm_bwd_rows(DType dt, const NormArgs& n, hipStream_t s, int* parts);
 void norm_col_sums(const NormArgs& n, int parts, ColSumList* l);
-bool bias_grad_direct(int rows);     // bias_grad_rows puts the gradient rows themselves on the list and launches nothing
+bool bias_grad_direct(DType dt, const BiasGradList& l);     // bias_grad_rows puts the gradient rows themselves on the list and launches nothing
 hipError_t bias_grad_rows(DType dt, BiasGradList& l, ColSumList* sums, hipStream_t s);
 hipError_t col_sums_add(ColSumList& l, hipStream_t s);
 // the same with the partial sums in a fixed device array of the library (n.partial ignored); d <= norm_bwd_noalloc_max_d()

@@ -504,7 +504,7 @@ int exec_backward_input(stage* st, int mb, const void* dy, void* dx, int l0, int
       };
       add(o.dyb, D.d, STAGE_P_BOUT); add(o.z, D.fin, STAGE_P_BIN); add(o.dx1b, D.d, STAGE_P_BO); add(o.dqkv, D.dq, STAGE_P_BQKV);
       const double bytes = (double)D.T * (2 * D.d + D.fin + D.dq) * D.es;
-      if (bias_grad_direct(D.T)) {                             // no launch of its own
+      if (bias_grad_direct(st->dt, bl)) {                             // no launch of its own
         HIPCHK(bias_grad_rows(st->dt, bl, &sums, st->stream));
         sum_bytes = bytes;
       } else {

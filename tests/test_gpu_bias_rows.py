@@ -3,14 +3,14 @@ import numpy as np
 import pytest
 
 from tests import test_gpu_kernels as T
-from tests.gpu_util import rnd, to_dev, to_np
+from tests.gpu_util import launches, rnd, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("rows,n,ld", [(1, 8, 8), (127, 64, 64), (129, 72, 80), (511, 200, 200), (513, 136, 136), (1023, 64, 72),
-                                       (1025, 1000, 1000), (2047, 192, 192), (2048, 328, 336), (2049, 328, 336)])
+                                       (1025, 1000, 1000), (2047, 192, 192), (2048, 328, 336), (2049, 328, 336), (2048, 320, 320), (2049, 320, 320)])
 def test_direct_and_two_step_sums(dtype, rows, n, ld):
     """Edges of the rows in flight (512 / 1024 per step), of the 64 columns of a workgroup, and of the rule; dbias is added to.
 
@@ -27,3 +27,15 @@ def test_direct_and_two_step_sums(dtype, rows, n, ld):
     ref = start.astype(np.float64) + x[:, :n].astype(np.float64).sum(0)
     bound = (rows / 128 * 2 + 40) * 2.0 ** -24 * (np.abs(x[:, :n]).astype(np.float64).sum(0) + np.abs(start))
     assert np.all(np.abs(to_np(db) - ref) <= bound)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("rows,n,ld,kernels", [(1024, 328, 336, 1), (1025, 328, 336, 2), (2048, 320, 320, 1), (2049, 320, 320, 2),
+                                               (2048, 16384, 16384, 1), (1024, 16448, 16448, 1), (1025, 16448, 16448, 2), (512, 8200, 8200, 1),
+                                               (513, 8200, 8200, 2)])
+def test_launches_on_either_side_of_the_line(dtype, rows, n, ld, kernels):
+    """One launch up to 2048 rows on 128-byte lines and 16384 columns, up to 1024 of others, 512 of more than 8192 columns off the lines (a capture: nothing runs)."""
+    import torch
+    t = torch.zeros(4096, dtype=torch.uint8, device="cuda:0")
+    got = launches(lambda s: T.L().stage_kernel_bias_grad(T.DT[dtype], rows, n, T.P(t), ld, T.P(t), T.P(t), s))
+    assert len(got) == kernels

@@ -50,6 +50,12 @@ def test_two_forward_workgroups_of_head_dim_64_fit_a_compute_unit(resources):
         assert r["vgpr_count"] <= 128 and r["vgpr_spill_count"] == 0 and r["private_segment_fixed_size"] == 0, (n, r)
 
 
+def test_two_column_sum_workgroups_fit_a_compute_unit(resources):
+    """16 wavefronts each, so eight to a SIMD: 512 / 8 registers."""
+    (found,) = [r for n, r in resources.items() if "col_sum_kernel" in n]
+    assert found["vgpr_count"] <= 64
+
+
 def test_loading_wavefronts_wait_by_count(code_objects):
     """The loops of the wavefronts that only load (loads to LDS and a barrier, no MFMA): the one wait in them is the counted one that leaves
     later tiles outstanding."""
