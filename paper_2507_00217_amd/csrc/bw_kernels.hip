@@ -485,11 +485,14 @@ hipError_t norm_bwd_noalloc(DType dt, const NormArgs& n, hipStream_t s) {
 // lanes per column group, combined through LDS in lane order -- then col_sum_kernel adds the parts.  The four maps of a
 // layer go out together.
 // The line: a workgroup of the one step owns its 64 columns alone, so its time grows with the rows, where the two steps spread
-// them over 64 workgroups but pay a second launch.  Rows that start on 128-byte lines, up to 16384 columns: 2048 (us, one step / two;
-// bf16, 5120 columns, 1024 rows 4.4 / 6.4, 2048 5.5 / 7.2; 12288 columns, 2048 rows 10.5 / 12.5; fp32, 5120 columns, 2048 rows 9.8 / 11.1, 1920 columns, 1800
-// rows 5.5 / 5.9, 2048 6.2 / 5.9, 3072 9.4 / 7.4).  Others 1024, more than 8192 columns 512: the 128 bytes of a workgroup's columns are then two lines, each fetched twice (bf16, 5144
-// columns, 1024 rows 5.4 / 6.4, 2048 8.7 / 7.6; fp32, 3576 columns, 1024 rows 4.7 / 6.8, 1800 9.3 / 7.5; bf16, 12280 columns,
-// 1024 rows 9.7 / 9.2).  On lines but wider 1024: there are workgroups enough to be past the latency (18432 columns, bf16, 1024 rows 11.5 / 12.0, 2048 18.0 / 17.1; fp32, 2048 rows 27.7 / 26.3).
+// them over 64 workgroups but pay a second launch (us, one step / two).
+//   rows that start on 128-byte lines, up to 16384 columns: 2048 rows (bf16, 5120 columns, 1024 rows 4.4 / 6.4, 2048 5.5 / 7.2; 12288
+//     columns, 2048 rows 10.5 / 12.5; fp32, 5120 columns, 2048 rows 9.8 / 11.1; 1920 columns, 1800 rows 5.8 / 6.2, 2048 6.2 / 6.3, 3072 9.4 / 7.4)
+//   wider: 1024, there are workgroups enough to be past the latency (18432 columns, bf16, 1024 rows 11.5 / 12.0, 2048 18.0 / 17.1; fp32, 2048
+//     rows 27.7 / 26.3)
+//   off the lines: 1024, and 512 of more than 8192 columns; the 128 bytes of a workgroup's columns are then two lines, each fetched twice
+//     (bf16, 5144 columns, 1024 rows 5.4 / 6.4, 2048 8.7 / 7.6; 12280 columns, 1024 rows 9.7 / 9.2; fp32, 3576 columns, 1024 rows 4.7 / 6.8, 1800 9.3 /
+//     7.5)
 // ---------------------------------------------------------------------------
 constexpr int BIAS_PARTS = 64;
 size_t bias_grad_partial_bytes(int n) { return n > 0 ? (size_t)BIAS_PARTS * n * sizeof(float) : 0; }

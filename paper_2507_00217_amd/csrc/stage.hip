@@ -512,7 +512,8 @@ int exec_backward_input(stage* st, int mb, const void* dy, void* dx, int l0, int
         HIPCHK(bias_grad_rows(st->dt, bl, &sums, st->stream));
       }
     }
-    { ProfScope ps(st, STAGE_K_NORM_BWD, sum_bytes); HIPCHK(col_sums_add(sums, st->stream)); }
+    // (counted with the bias gradients where it reads their rows: the norms' partial sums are little beside them)
+    { ProfScope ps(st, sum_bytes > 0.0 ? STAGE_K_COPY : STAGE_K_NORM_BWD, sum_bytes); HIPCHK(col_sums_add(sums, st->stream)); }
   }
   return STAGE_OK;
 }

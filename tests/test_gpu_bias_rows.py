@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 from tests import test_gpu_kernels as T
-from tests.gpu_util import launches, rnd, to_dev, to_np
+from tests.gpu_util import SMALL, launches, rnd, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -39,3 +39,25 @@ def test_launches_on_either_side_of_the_line(dtype, rows, n, ld, kernels):
     t = torch.zeros(4096, dtype=torch.uint8, device="cuda:0")
     got = launches(lambda s: T.L().stage_kernel_bias_grad(T.DT[dtype], rows, n, T.P(t), ld, T.P(t), T.P(t), s))
     assert len(got) == kernels
+
+
+@pytest.mark.parametrize("seq", [200, 2056])
+def test_profile_counts_bias_gradients_with_the_copies(seq):
+    """One launch or two, the bytes of the bias gradients are not the norms'."""
+    import torch
+    from paper_2507_00217_amd import stage as S
+    from paper_2507_00217_amd import synth
+    cfg, prof = dict(SMALL["cfg4s"], n_layers=1, seq=seq, n_microbatches=2, stash_cap=0, norm="layernorm", act="gelu"), {}
+    ops = synth.schedule_1f1b(2, 1)
+    for b in (0, 1):
+        c = dict(cfg, bias=b)
+        X = to_dev(synth.make_boundary(c, 8), c["dtype"])
+        st = S.Stage(c)
+        st.load_weights(synth.make_weights(c, 7))
+        st.profile(True)
+        st.run_schedule(ops, X, X.clone(), torch.zeros_like(X), torch.zeros_like(X))
+        prof[b] = st.profile_read()
+        st.close()
+    rows, dq = cfg["mb_size"] * seq, cfg["hidden"] // cfg["n_heads"] * (cfg["n_heads"] + 2 * cfg["n_kv_heads"])
+    assert prof[1]["norm_bwd"]["work"] == prof[0]["norm_bwd"]["work"] > 0
+    assert prof[1]["copy"]["work"] - prof[0]["copy"]["work"] == 2 * rows * (2 * cfg["hidden"] + cfg["ffn"] + dq) * 2
