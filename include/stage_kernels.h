@@ -16,7 +16,7 @@
  * shape.  Products (with or without activation, weight gradients one at a time or grouped): 2 = full 256 x 256 tiles only, 3 =
  * half-height tiles only (SwiGLU backward; the normal choice elsewhere), 4 = 128 x 128, 5 = 64 x 64, 6 = 128 x 64 tiles only (SwiGLU
  * forward: 128 x 64 for 5; weight gradients: 64 x 64 for 6), 7 / 8 / 9 = 96 x 64, 192 x 128, 128 x 192
- * (not SwiGLU or weight gradients), 10 = 32 x 64 (not SwiGLU forward or weight gradients); in fp32 2 / 3 / 4 = tiles of 64 x 64 / 32 x 32 / 16 x 16 (weight gradients: 32 x 32 for 4);
+ * (SwiGLU and weight gradients: the normal choice), 10 = 32 x 64 (SwiGLU forward and weight gradients: the normal choice); in fp32 2 / 3 / 4 = tiles of 64 x 64 / 32 x 32 / 16 x 16 (weight gradients: 32 x 32 for 4);
  * attention: 2 / 3 = forward and dQ workgroups of 8 / 4 wavefronts (dK/dV workgroups of 128 keys), 4 = forward and dQ
  * workgroups of 64 queries whose two wavefronts per query block each take half of the keys, dK/dV workgroups of 64 keys, 5 = the
  * same with four wavefronts per query block in the forward and two pairs of wavefronts per key block in dK/dV, 6 / 7 = the backward

@@ -137,7 +137,7 @@ bool gemm_mfma_supported(const GemmArgs& g);
 // tile_shape: 0 = full 256 x 256 tiles for complete rounds of one per compute unit, smaller ones for a short last round or a small
 // product; otherwise (so that tests reach each on any shape) all tiles 1 = full, 2 = half-height (SwiGLU backward; the rule
 // elsewhere), 3 = 128 x 128, 4 = 64 x 64 (SwiGLU forward: 128 x 64), 5 = 128 x 64 (weight gradients: 64 x 64),
-// 6 .. 9 = 96 x 64, 192 x 128, 128 x 192, 32 x 64 (not weight gradients)
+// 6 .. 9 = 96 x 64, 192 x 128, 128 x 192, 32 x 64 (weight gradients, SwiGLU forward and, but for 9, backward: the rule)
 hipError_t gemm_mfma(const GemmArgs& g, hipStream_t s, int tile_shape = 0);
 // several weight-gradient (TN, fp32-accumulating) products together: persistent workgroups over the full tiles of complete
 // rounds, a second launch for a short last round (or list) in small tiles; each product may reduce over nseg operand pairs in

@@ -1114,11 +1114,12 @@ inline bool keeps_pace(const GemmArgs& g, const SmallGrid& t) {
 // against full ones, 2048 x 6144 x 2048: 49 / 48 (60 / 53).  The half-height tile is left to the SwiGLU backward, whose z it
 // rewrites in whole rows through LDS (2048 x 2816 x 2048: 36 / 39).  All give the same bits.
 // `shape`: 0 = this rule, else one tile shape for all: 1 = full, 2 = half-height (SwiGLU backward; elsewhere the rule), 3 = 128 x
-// 128, 4 = 64 x 64 (SwiGLU forward: 128 x 64), 5 = 128 x 64, 6 = 96 x 64, 7 = 192 x 128, 8 = 128 x 192, 9 = 32 x 64 (SwiGLU forward: 128 x 64 for these, backward for 6 to 8).
+// 128, 4 = 64 x 64 (SwiGLU forward: 128 x 64), 5 = 128 x 64, 6 = 96 x 64, 7 = 192 x 128, 8 = 128 x 192, 9 = 32 x 64 (SwiGLU forward: the rule for
+// these, backward for 6 to 8).
 template <bool BKC, int EPI>
 hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
   constexpr bool HALF = EPI == EPI_DSWIGLU;            // where there are half-height tiles
-  if (shape == 2 && !HALF) shape = 0;
+  if ((shape == 2 && !HALF) || (EPI == EPI_SWIGLU && shape > 5) || (HALF && shape > 5 && shape < 9)) shape = 0;      // no such kernel: the rule
   const int tiles_m = (g.M + BM - 1) / BM;
   const int tiles_n = EPI == EPI_SWIGLU ? (g.N / 2 + GLU_BN - 1) / GLU_BN : (g.N + BN - 1) / BN, total = tiles_m * tiles_n;
   int n_half = 0, n_quarter = 0, n_tiny = 0;          // full tiles at the end of the walk order that are split in 2 / 4 / 8 or 16
@@ -1219,6 +1220,7 @@ hipError_t gemm_mfma(const GemmArgs& g, hipStream_t s, int tile_shape) {
       if (g.act_bwd == 2) return launch<true, EPI_DSWIGLU>(g, s, tile_shape);
       return launch<true, EPI_STORE>(g, s, tile_shape);
     case GEMM_TN: {
+      if (tile_shape > 5) tile_shape = 0;
       // One product without a short last round needs no persistent workgroups: a workgroup per tile is 5 % faster (us; 1304 x 5400 x
       // 115 18.3 / 17.2, 6200 x 2552 x 137 26.8 / 25.4, 3224 x 2472 x 6298 128 / 119; but 1688 x 7096 x 5750 128 / 137).  The same bits.
       const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN, total = tiles_m * tiles_n, tail = total % cu_count();
@@ -1244,6 +1246,7 @@ hipError_t gemm_mfma_wgrad_group(const GemmArgs* list, int n, int nseg, const in
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
   if (attr != hipSuccess) return attr;
   const int n_cu = cu_count();
+  if (shape == 2 || shape > 5) shape = 0;
   for (int i0 = 0; i0 < n; i0 += GROUP_MAX) {
     GemmGroup gg;
     gg.n = n - i0 < GROUP_MAX ? n - i0 : GROUP_MAX;
@@ -1263,7 +1266,7 @@ hipError_t gemm_mfma_wgrad_group(const GemmArgs* list, int n, int nseg, const in
     // the time, take 64 x 64 tiles (75 tiles, K 400: 18.1 / 15.2 us; 9 tiles, K 400: 10.2 / 5.6; but 72 tiles, K 1500: 29 / 33).  Measured (us, full tiles against this rule's): 48 tiles, K 128: 22.5 / 9.7;
     // 75 tiles, K 400: 28.9 / 17.7; 64 tiles, K 4096: 91.7 / 42.4; 128 tiles, K 8192: 172 / 159; on fuller rounds the doubled
     // operand traffic loses (196 tiles, K 3000: 86 / 113).
-    // (`shape`: 0 = this rule; 1 = full tiles, 3 = 128 x 128, 4 and 5 = 64 x 64 for the whole list.)
+    // (`shape`: 1 = full tiles, 3 = 128 x 128, 4 and 5 = 64 x 64 for the whole list; otherwise this rule.)
     const int tail = total % n_cu, n_small = shape >= 3 ? total : shape == 1 || 2 * tail > n_cu ? 0 : tail, n_full = total - n_small;
     if (n_full) {
       const int grid = n_full < n_cu ? n_full : n_cu;       // one workgroup per CU (160 KiB of LDS each)

@@ -266,3 +266,20 @@ def test_short_reductions_with_a_plain_store(mode, M, N):
         if mode == 0:
             (name, _, _), = launches(lambda stream: run(outs[0], 0, stream, P(R)))
             assert "gemm_mid_kernel" in name
+
+
+@pytest.mark.parametrize("M,N,K", [(400, 1736, 1088), (1100, 2048, 128), (2048, 4096, 256)])
+def test_shapes_that_a_product_lacks_leave_the_rule(M, N, K):
+    """kernel_set 7 to 10 where there is no such tile: the kernels of kernel_set 0 (captures: nothing runs)."""
+    import torch
+    t = P(torch.zeros(256, dtype=torch.uint8, device="cuda:0"))
+    ints, longs, ptrs = (C.c_int * 1), (C.c_int64 * 1), (C.c_void_p * 1)
+    calls = {
+        "weight gradient": lambda ks, s: L().stage_kernel_gemm(1, 2, M, N, K, t, M, t, N, t, N, None, 0, 1, ks, s),
+        "weight gradients": lambda ks, s: L().stage_kernel_wgrad_group(1, 1, ints(M), ints(N), ints(K), ptrs(t), longs(M), ptrs(t), longs(N), ptrs(t), longs(N), ks, s),
+        "SwiGLU": lambda ks, s: L().stage_kernel_gemm_act(1, 1, M, N, K, t, K, t, 2 * N, t, 2 * N, t, N, ks, s),
+        "SwiGLU backward": lambda ks, s: L().stage_kernel_gemm_act_bwd(1, 1, M, N, K, t, K, t, K, t, 2 * N, None, ks, s),
+    }
+    for name, call in calls.items():
+        for ks in (7, 8, 9) if name == "SwiGLU backward" else (7, 8, 9, 10):
+            assert launches(lambda s: call(ks, s)) == launches(lambda s: call(0, s)), (name, ks)
