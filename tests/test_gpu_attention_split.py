@@ -77,3 +77,35 @@ def test_the_rule_at_its_lines(causal, b, s, h, hkv, hd):
 @pytest.mark.parametrize("b,s,h,hkv,hd", [(1, 392, 8, 1, 128), (2, 300, 12, 2, 64)])
 def test_two_query_parts_with_split_query_heads(kernel_set, b, s, h, hkv, hd):
     K.test_attention_bwd_with_split_query_heads(kernel_set, 1, b, s, h, hkv, hd)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+@pytest.mark.parametrize("part", ["q", "k", "v", "do"])
+@pytest.mark.parametrize("s,hd,causal,at", [(37, 128, 1, 20), (37, 64, 0, 36), (150, 128, 1, 0), (150, 64, 1, 141), (300, 64, 1, 130), (300, 128, 0, 299)])
+def test_infinities_and_nan_spread_as_with_two_parts(part, value, s, hd, causal, at):
+    """An infinity or NaN of one position makes the same elements non-finite, in the same way, whatever the number of key and query parts and
+    whether the backward is one launch, and leaves the others as they were."""
+    import torch
+    h, hkv = 2, 1
+    g = torch.Generator().manual_seed(36)
+    qkv, do = torch.randn((s, (h + 2 * hkv) * hd), generator=g), torch.randn((s, h * hd), generator=g)
+    if part == "do":
+        do[at, hd + 3] = value
+    else:
+        qkv[at, {"q": hd, "k": h * hd, "v": (h + hkv) * hd}[part] + 5] = value
+    qkv, do = qkv.to("cuda:0").bfloat16(), do.to("cuda:0").bfloat16()
+    o, dqkv = {}, {}
+    for ks in (4, 5, 6, 7):
+        o[ks], dqkv[ks] = torch.zeros_like(do), torch.zeros_like(qkv)
+        lse, delta = (torch.zeros((h, s), device="cuda:0") for _ in range(2))
+        assert K.L().stage_kernel_attention_fwd(1, 1, s, h, hkv, hd, causal, K.P(qkv), K.P(o[ks]), K.P(lse), ks, None) == 0
+        assert K.L().stage_kernel_attention_fwd(1, 1, s, h, hkv, hd, causal, K.P(qkv), K.P(o[4]), K.P(lse), 4, None) == 0
+        assert K.L().stage_kernel_attention_bwd(1, 1, s, h, hkv, hd, causal, K.P(qkv), K.P(o[4]), K.P(lse), K.P(do), K.P(dqkv[ks]), K.P(delta), ks, None) == 0
+    for got in (o, dqkv):
+        ref = got[4].float()
+        fin = torch.isfinite(ref)
+        for ks in (5, 6, 7):
+            x = got[ks].float()
+            assert torch.equal(torch.isnan(x), torch.isnan(ref)) and torch.equal(x[torch.isinf(ref)], ref[torch.isinf(ref)]) and torch.equal(torch.isfinite(x), fin), ks
+            if fin.any():
+                assert (x[fin] - ref[fin]).abs().max() <= K.KTOL["bf16"] * ref[fin].abs().max(), ks

@@ -1,12 +1,13 @@
 """The small tiles of the bf16 products at their edges."""
 import ctypes as C
+import re
 
 import numpy as np
 import pytest
 
 from oracle import stage_oracle as so
 from paper_2507_00217_amd import synth
-from tests.gpu_util import launches, rnd, to_dev, to_np
+from tests.gpu_util import SMALL, TOL, launches, rnd, to_dev, to_np
 from tests.test_gpu_kernels import KTOL, L, P
 
 pytestmark = pytest.mark.gpu
@@ -57,7 +58,8 @@ def test_reductions_around_the_ring(mode):
 @pytest.mark.parametrize("M,N,K", [(1, 8, 64), (96, 64, 128), (97, 72, 192), (193, 136, 256), (129, 200, 320), (200, 392, 448), (400, 1736, 1088),
                                    (1000, 1280, 64), (1000, 5120, 192), (4096, 1536, 192)])
 def test_tiles_between_the_powers_of_two(M, N, K):
-    """96 x 64 (7), 192 x 128 (8) and 128 x 192 tiles (9) against full ones (2) and the rule (0), every epilogue they have: one row, one past a
+    """96 x 64 (7), 192 x 128 (8) and 128 x 192 tiles (9) against full ones (2) and the rule (0), every epilogue that an entry
+    point reaches with bf16 operands alone (bias, fp32 residual and fp32 output: test_stage_epilogues_between_the_powers_of_two): one row, one past a
     tile, reductions around the ring's depths of two and four; the last three shapes are what the rule gives to each of them."""
     import torch
     P0, R = P, lambda i, *sh: to_dev(rnd(synth.normal(45, i, sh, std=1.0 if i != 2 else 1.5 * K ** -0.5), "bf16"), "bf16")
@@ -79,7 +81,7 @@ def test_tiles_between_the_powers_of_two(M, N, K):
 
 @pytest.mark.parametrize("M,N,K", [(1, 8, 64), (31, 64, 128), (33, 72, 448), (64, 136, 512), (65, 56, 576), (130, 200, 1088), (512, 1024, 64), (513, 1024, 64)])
 def test_tiles_of_32_rows(M, N, K):
-    """32 x 64 tiles (10) against full ones (2) and the rule (0), every epilogue they have: one row, on either side of a tile, reductions from one
+    """32 x 64 tiles (10) against full ones (2) and the rule (0), every epilogue that an entry point reaches: one row, on either side of a tile, reductions from one
     K tile over the ring's depth of eight to two rounds of it; the last two are the largest that the rule gives to them and one past it."""
     import torch
     P0, R = P, lambda i, *sh: to_dev(rnd(synth.normal(46, i, sh, std=1.0 if i != 2 else 1.5 * K ** -0.5), "bf16"), "bf16")
@@ -283,3 +285,24 @@ def test_shapes_that_a_product_lacks_leave_the_rule(M, N, K):
     for name, call in calls.items():
         for ks in (7, 8, 9) if name == "SwiGLU backward" else (7, 8, 9, 10):
             assert launches(lambda s: call(ks, s)) == launches(lambda s: call(0, s)), (name, ks)
+
+
+@pytest.mark.parametrize("T,mb,hidden,ffn,tiles", [(1000, 2, 1280, 5120, {(1280, 1280): 0, (1280, 5120): 0, (5120, 1280): 1}), (4096, 8, 1536, 512, {(1536, 1536): 2}),
+                                                   (2016, 4, 2560, 512, {(2560, 2560): 1})])
+def test_stage_epilogues_between_the_powers_of_two(T, mb, hidden, ffn, tiles):
+    """Bias, fp32 residual and fp32 output on 96 x 64 (0), 192 x 128 (1) and 128 x 192 tiles (2), which only a stage asks for: one GPT-style layer with
+    biases against the oracle, whose products of (outputs, reduction) over T tokens the rule gives to those tiles."""
+    import torch
+    from tests.test_gpu_stage import compare, inputs, run_gpu, run_oracle
+    for (N, K), shape in tiles.items():
+        t = P(torch.zeros(256, dtype=torch.uint8, device="cuda:0"))
+        # (a residual gives the tiles of both residual products; the product with GELU is launched by its own entry)
+        call = (lambda s: L().stage_kernel_gemm_act(1, 0, T, N, K, t, K, t, N, t, N, t, N, 0, s)) if N == ffn else \
+               (lambda s: L().stage_kernel_gemm(1, 0, T, N, K, t, K, t, N, t, N, t, N, 0, 0, s))
+        (name, _, _), = launches(call)
+        assert re.search(rf"gemm_mid_kernelILb0ELi\d+ELi{shape}E", name), name
+    cfg = dict(SMALL["cfg4s"], n_layers=1, hidden=hidden, n_heads=hidden // 128, n_kv_heads=hidden // 128, ffn=ffn, mb_size=mb, seq=T // mb, n_microbatches=1,
+               stash_cap=1, bias=1, norm="layernorm", act="gelu")
+    params, X, G = inputs(cfg, 4600)
+    ops = [(0, 0), (1, 0), (2, 0)]
+    compare(cfg, run_gpu(cfg, params, X, G, ops), run_oracle(cfg, params, X, G, ops), TOL["bf16"])

@@ -64,7 +64,7 @@ def test_loading_wavefronts_wait_by_count(code_objects):
         text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", str(path)], capture_output=True, text=True, check=True).stdout
         for func in re.split(r"\n(?=[0-9a-f]{16} <)", text):
             name = re.search(r"<(\S+)>:", func)
-            if not name or not re.search(r"gemm_(quarter|tiny|mid)_kernel", name[1]):
+            if not name or not re.search(r"gemm_(quarter|tiny|mid|wgrad_small)_kernel", name[1]):
                 continue
             code = [(int(a, 16), i.strip()) for i, a in re.findall(r"^\s+(.+?)\s*// ([0-9A-F]+):", func, re.M)]
             at, loops = {a: n for n, (a, _) in enumerate(code)}, []
