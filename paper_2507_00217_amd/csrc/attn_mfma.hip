@@ -1176,7 +1176,7 @@ hipError_t bwd_t(const AttnArgs& a, hipStream_t s) {
   const bool long_chains = a.h > a.hkv * ns && n_dkv < RESIDENT / 2;
   const bool two_pairs = 2 * total <= RESIDENT || (a.causal && total <= RESIDENT && (a.s > 320 || (HD == 128 && long_chains)));
   if (a.width == 6 || (a.width == 0 && two_pairs)) return bwd_fused_launch<HD, 4, 2>(a, s);
-  // With one wavefront per SIMD: head_dim 128 those up to 320 positions, two to a CU (100 x 65 17.2 / 13.2, 128 x 111 18.1 / 14.7, 82 x 192 24.0 /
+  // With one wavefront per SIMD: head_dim 128 those up to 320 positions, two to a CU (its kernel spills 9 registers; 100 x 65 17.2 / 13.2, 128 x 111 18.1 / 14.7, 82 x 192 24.0 /
   // 23.0; 51 x 316 29.0 / 28.0); head_dim 64 up to three to a CU, 768, and from three tiles on, which do not all end at once, up to 960 (16 x 1024
   // 32.1 / 26.1, 36 x 777 31.9 / 29.5, 40 x 512 25.7 / 19.0, 160 x 192 without mask 18.8 / 16.9; but 240 x 65 without mask 13.9 / 16.3, 225 x 111
   // 15.6 / 16.6, 16 x 2048 59.7 / 62.6).  Not the long chains (32 x 979 on 4 KV heads without scratch 199.8, as two launches with two pairs,

@@ -901,9 +901,9 @@ __global__ __launch_bounds__(WR * 512 / TN, WR == 1 ? 2 : 1) void gemm_mfma_kern
 // part bid % (1 << (RB + CB)) of full tile number first + bid / (1 << (RB + CB)) of the walk order, and a part that lies outside the
 // matrix has nothing to do (false).  A whole product is counted in its own tiles because empty workgroups are not free: they
 // recur with the period of the parts, and so does the placement of workgroups on the shader engines of an XCD -- 24 rows x
-// 5720 x 1280 in 64 x 64 tiles kept a quarter of the engines busy, 15.1 us instead of 8.  (More than one round of 128 x 128 tiles
-// without empty parts keeps the other order: 4096 x 1536 x 4096 between its neighbours in a layer 60 us, 74 in the order of its own
-// tiles; one round is better off in that, 2048 x 2048 outputs 50 to 53 us, 53 to 55 in the other.)
+// 5720 x 1280 in 64 x 64 tiles 11.2 us instead of 6.4, 100 x 5120 x 1280 10.6, 6.1.  (More than one round of 128 x 128 tiles
+// without empty parts keeps the other order: 2048 x 4096 x 4096 with operands from HBM 72.5 us, 85.1 in the order of its own
+// tiles; one round is better off in that, 2048 x 2048 x 4096 31.0 (47.7), 31.9 (49.1) in the other.)
 template <int RB, int CB, int TB, bool COMPACT>
 __device__ __forceinline__ bool small_tile(int tiles_m, int tiles_n, int first, int rows, int cols, int& m0, int& n0) {
   int bid = blockIdx.x;
@@ -1105,14 +1105,17 @@ inline bool keeps_pace(const GemmArgs& g, const SmallGrid& t) {
 
 // Full tiles for every complete round of one tile per CU; what is left over -- a last round that would keep at most half of
 // the CUs busy, or a whole product with that few tiles -- goes out in smaller tiles, the smallest of which one round is
-// enough: 32 x 64 (whole products), 64 x 64, 128 x 64, 128 x 128, and beyond that 128 x 128 with a shallow ring, two workgroups to a CU.  A tile's time per K
-// tile is what its CU's LDS and load path take (0.19, 0.28, 0.36 us for the first three while few CUs are busy, 0.5 for the third
-// when all are; full 1.05 to 1.4), so a smaller tile always finishes sooner than a larger one, but no two rounds of it do.
-// Measured (us; 64 x 64 / 128 x 64 / 128 x 128): 400 x 640 x 1728: 8.6 / 9.8 / 13.7; 1000 x 1280 x 5120: 36 / 26 / 34; 2048 x 2048 x
-// 4096: 60 / 41 / 32.  Two 128 x 128 workgroups to a CU against the half-height tiles that used to take such shapes: 1000 x 5120 x
-// 1280: 18.3 / 20.1 (operands from HBM: 22 / 28), 4096 x 1536 x 4096: 51 / 51 (59 / 72), and with more than half a tile per CU
-// against full ones, 2048 x 6144 x 2048: 49 / 48 (60 / 53).  The half-height tile is left to the SwiGLU backward, whose z it
-// rewrites in whole rows through LDS (2048 x 2816 x 2048: 36 / 39).  All give the same bits.
+// enough: 32 x 64 (whole products), 64 x 64, 128 x 64, 128 x 128, and beyond that 128 x 128 with a shallow ring, two workgroups to a CU; for
+// whole products the shapes between, see below.  A tile's time per K tile is what its CU's LDS and load path take (us while few CUs are
+// busy / when all are: 32 x 64 0.09 / 0.20, 64 x 64 0.12 / 0.23, 96 x 64 0.14 / 0.29, 128 x 64 0.16 / 0.33, 128 x 128 0.28 / 0.44, 192 x 128 0.37 /
+// 0.60, 128 x 192 0.41 / 0.71, full 1.05 / 1.39), so a smaller tile always finishes sooner than a larger one, but no two rounds of it do.
+// Measured (us, operands from HBM in brackets; 64 x 64, 128 x 64, 128 x 128): 400 x 640 x 1728 6.9 / 8.0 / 11.9 (13.4 / 16.8 / 21.3); 1000 x 1280 x
+// 5120 35.3 / 24.8 / 34.5 (55 / 43 / 56); 2048 x 2048 x 4096 56.3 / 41.0 / 31.2 (86 / 63 / 48).  Two 128 x 128 workgroups to a CU against full
+// tiles: 2048 x 4096 x 2048 31.4 / 43.2 (42 / 57), 2000 x 4096 x 1024 18.5 / 25.8 (25.6 / 33.2); and with more than half a tile per CU, where
+// whole rounds of larger tiles with loading wavefronts do not win either: 2048 x 6144 x 2048 48.6 / 44.6 (69 / 61), 128 x 192 49.0 (70), 192 x 128
+// 63.1 (73); 4096 x 3072 x 4096 90.8 / 81.6 (122 / 107), 128 x 192 89.9 (123); 2048 x 5120 x 2048 46.5 / 42.3 (60 / 60), 192 x 128 43.0 (63).  The
+// half-height tile is left to the SwiGLU backward, whose z it rewrites in whole rows through LDS (2048 x 2816 x 2048 36.5 (55), two 128 x 128
+// 44.9 (59), full 52.7 (74)).  All give the same bits.
 // `shape`: 0 = this rule, else one tile shape for all: 1 = full, 2 = half-height (SwiGLU backward; elsewhere the rule), 3 = 128 x
 // 128, 4 = 64 x 64 (SwiGLU forward: 128 x 64), 5 = 128 x 64, 6 = 96 x 64, 7 = 192 x 128, 8 = 128 x 192, 9 = 32 x 64 (SwiGLU forward: the rule for
 // these, backward for 6 to 8).
