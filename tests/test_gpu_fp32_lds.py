@@ -36,6 +36,27 @@ def test_activations_on_either_side_of_four_rounds(act, M, f, K):
     F.test_fused_activations(act, 3, M, f, K)
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(278, 384, 384), (214, 576, 2720), (819, 128, 2848), (127, 1344, 160)])
+def test_no_further_from_64_bits_than_small_tiles(mode, M, N, K):
+    """A wavefront of a 32 x 32 tile sums no more terms in one register than one of a 16 x 16 tile, which splits the reduction over twice as
+    many: the two are as far from 64 bits (2-norms over at least 1e5 outputs, which repeat themselves to about one in the square root
+    of that; 10 % allowed.  With one sum per wavefront 5 to 36 % further)."""
+    import torch
+    g = torch.Generator(device="cuda:0").manual_seed(M + K + mode)
+    a, b = (torch.randn(s, generator=g, device="cuda:0") for s in ((M, K), (N, K) if mode else (K, N)))
+    exact = a.double() @ (b.double().t().contiguous() if mode else b.double())
+
+    def off(kernel_set):
+        c = torch.empty((M, N), device="cuda:0")
+        assert L().stage_kernel_gemm(0, mode, M, N, K, P(a), K, P(b), b.shape[1], P(c), N, None, 0, 0, kernel_set, None) == 0
+        torch.cuda.synchronize()
+        return float((c.double() - exact).norm() / exact.norm())
+
+    small, through_lds = off(4), off(3)
+    assert through_lds <= 1.1 * small
+
+
 FORWARD, RESID, DGRAD, GELU, SWIGLU, DGELU, DSWIGLU = range(7)
 # (kind, M, N, K): tile and whether its operands go through LDS, on both sides of every line (256 compute units); SwiGLU's N counts gate and up
 RULE = [
