@@ -318,7 +318,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
       // that the fragments of tile t are in registers, which frees both its slots.
       if (nk > DEPTH) { g2s<AKC, LOADERS, CHA>(smem + 2 * DEPTH * SLOT, rsA, offa, g.lda, kA, lw); advanceA(); }
       if (nk > DEPTH) wait_vm(std::integral_constant<int, (DEPTH - 1) * (CHA + CHB) + CHA>{});
-      else __builtin_amdgcn_s_waitcnt(0);
+      else {
+        // (a reduction that is all under way: tile 0 has landed when what is outstanding are the nk - 1 others)
+        auto rest = [&](auto n_c) {
+          constexpr int n = decltype(n_c)::value;
+          if constexpr (n > 0 && n <= DEPTH - 1) { if (nk >= n + 1) { wait_vm(std::integral_constant<int, n * (CHA + CHB)>{}); return true; } }
+          return false;
+        };
+        if (!(rest(std::integral_constant<int, 7>{}) || rest(std::integral_constant<int, 6>{}) || rest(std::integral_constant<int, 5>{}) || rest(std::integral_constant<int, 4>{}) ||
+              rest(std::integral_constant<int, 3>{}) || rest(std::integral_constant<int, 2>{}) || rest(std::integral_constant<int, 1>{})))
+          __builtin_amdgcn_s_waitcnt(0);
+      }
       __syncthreads();
       int slot = 0, kt = 0;
       for (; kt + DEPTH + 1 < nk; ++kt) {

@@ -84,3 +84,24 @@ def test_loading_wavefronts_wait_by_count(code_objects):
             assert len(waits) == 1 and re.search(r"vmcnt\([1-9]", waits[0]), (name[1], waits)
             seen += 1
     assert seen >= 30
+
+
+# (kernel's tile, loads of one K tile per thread that loads, K tiles ahead)
+RINGS = [(r"gemm_quarter_kernelILb[01]ELi\dELi4E", 8, 4), (r"gemm_tiny_kernelILb[01]ELi\dELi0ELi4E", 4, 8), (r"gemm_tiny_kernelILb[01]ELi\dELi1ELi4E", 6, 4),
+         (r"gemm_mid_kernelILb[01]ELi\dELi0E", 5, 4), (r"gemm_mid_kernelILb[01]ELi\dELi[12]E", 10, 2), (r"gemm_mid_kernelILb[01]ELi\dELi3E", 3, 8)]
+
+
+@pytest.mark.parametrize("kernel,loads,ahead", RINGS)
+def test_a_short_reduction_starts_with_its_first_tile(code_objects, kernel, loads, ahead):
+    """A reduction of no more K tiles than the ring holds ahead is loaded whole before the first barrier; that waits for the first tile only: of
+    `ahead` tiles all but one may be outstanding (a count that no other wait of the loading wavefronts has), and so for fewer tiles."""
+    found = 0
+    for path in code_objects:
+        text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", str(path)], capture_output=True, text=True, check=True).stdout
+        for func in re.split(r"\n(?=[0-9a-f]{16} <)", text):
+            name = re.search(r"<(\S+)>:", func)
+            if name and re.search(kernel, name[1]):
+                waits = {int(n) for n in re.findall(r"s_waitcnt vmcnt\((\d+)\)", func)}
+                assert waits >= {n * loads for n in range(1, ahead)}, (name[1], sorted(waits))
+                found += 1
+    assert found
