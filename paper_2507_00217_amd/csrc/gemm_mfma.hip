@@ -319,7 +319,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, lds
       if (nk > DEPTH) { g2s<AKC, LOADERS, CHA>(smem + 2 * DEPTH * SLOT, rsA, offa, g.lda, kA, lw); advanceA(); }
       if (nk > DEPTH) wait_vm(std::integral_constant<int, (DEPTH - 1) * (CHA + CHB) + CHA>{});
       else {
-        // (a reduction that is all under way: tile 0 has landed when what is outstanding are the nk - 1 others)
+        // (a reduction that is all under way: tile 0 has landed when what is outstanding are the nk - 1 others.  us, all waited for / tile 0,
+        // beside the form without loading wavefronts in the same run, 256 terms: 2048 x 2048 7.10 (6.81) / 6.65 (6.68), 4298 x 896 input-gradient
+        // form 7.03 (6.68) / 6.58 (6.53), GELU backward 2048 x 1024 9.15 (8.60) / 8.35 (8.33), SwiGLU 2048 x 2048 8.67 (8.27) / 8.38 (8.32))
         auto rest = [&](auto n_c) {
           constexpr int n = decltype(n_c)::value;
           if constexpr (n > 0 && n <= DEPTH - 1) { if (nk >= n + 1) { wait_vm(std::integral_constant<int, n * (CHA + CHB)>{}); return true; } }
@@ -934,14 +936,15 @@ __device__ __forceinline__ bool small_tile(int tiles_m, int tiles_n, int first, 
   return m0 < rows && n0 < cols;
 }
 
-// one workgroup per 128 x 128 tile (four wavefronts of 64 x 64, and four that load unless two workgroups share the CU)
-template <bool BKC, int EPI, int DEPTH>
-__global__ __launch_bounds__(DEPTH == 2 ? 256 : 512, 2) void gemm_quarter_kernel(   // (register budget: as for the half-height tile)
+// one workgroup per 128 x 128 tile (four wavefronts of 64 x 64, and four that load unless two workgroups share the CU or, LW == 0, the
+// reduction is short, see launch_quarter)
+template <bool BKC, int EPI, int DEPTH, int LW = DEPTH == 2 ? 0 : 4>
+__global__ __launch_bounds__(256 + 64 * LW, 2) void gemm_quarter_kernel(   // (register budget: as for the half-height tile)
     GemmArgs g, int tiles_m, int tiles_n, int first) {
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   int m0, n0;
   if (!small_tile<1, 1, EPI == EPI_SWIGLU ? GLU_BN : BN, true>(tiles_m, tiles_n, first, g.M, EPI == EPI_SWIGLU ? g.N / 2 : g.N, m0, n0)) return;
-  gemm_tile<true, BKC, EPI, 2, 1, 1, DEPTH, DEPTH == 2 ? 0 : 4>(g, m0, n0, (lds_char*)smem_raw);
+  gemm_tile<true, BKC, EPI, 2, 1, 1, DEPTH, LW>(g, m0, n0, (lds_char*)smem_raw);
 }
 
 // one workgroup per 64 x 64 (WR == 0) or 128 x 64 tile (WR == 1); four more wavefronts load (LW == 0: the four that multiply, see keeps_pace)
@@ -1074,13 +1077,13 @@ SmallGrid small_grid(const GemmArgs& g, int RB, int CB, int total, int n) {
   if (n == total && (CB == 2 || tm * tn <= cu_count() || tm * tn < parts)) return SmallGrid{tm, tn, -1, tm * tn};
   return SmallGrid{tiles(g.M, BM), tiles(cols, TB), total - n, parts};
 }
-template <bool BKC, int EPI, int DEPTH>
+template <bool BKC, int EPI, int DEPTH, int LW = DEPTH == 2 ? 0 : 4>
 hipError_t launch_quarter(const GemmArgs& g, hipStream_t s, const SmallGrid& t) {
   constexpr size_t LDS = (size_t)(2 * DEPTH + 1) * (TILE_BYTES / 2);
-  auto kern = gemm_quarter_kernel<BKC, EPI, DEPTH>;
+  auto kern = gemm_quarter_kernel<BKC, EPI, DEPTH, LW>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(t.n), dim3(DEPTH == 2 ? 256 : 512), LDS, s, g, t.tiles_m, t.tiles_n, t.first);
+  hipLaunchKernelGGL(kern, dim3(t.n), dim3(256 + 64 * LW), LDS, s, g, t.tiles_m, t.tiles_n, t.first);
   return hipGetLastError();
 }
 template <bool BKC, int EPI, int WR, int LW = 4>
@@ -1185,6 +1188,11 @@ hipError_t launch(const GemmArgs& g, hipStream_t s, int shape) {
     const SmallGrid t = small_grid<EPI>(g, 1, 1, total, n_quarter);
     if constexpr (!HALF)
       if (t.n > n_cu) return launch_quarter<BKC, EPI, 2>(g, s, t);
+    // GELU's backward, most of whose time is its epilogue, as a whole product of up to 1536 terms without loading wavefronts (us, with / without:
+    // 2048 x 2048 x 256 14.4 / 13.7, x 768 20.4 / 19.7, x 1536 26.5 / 26.3, 4298 x 896 x 1280 24.7 / 24.1; but x 2048 28.2 / 28.6; last rounds
+    // within 1 % either way)
+    if constexpr (EPI == EPI_DGELU)
+      if (shape == 0 && t.first < 0 && g.K <= 1536) return launch_quarter<BKC, EPI, 4, 0>(g, s, t);
     return launch_quarter<BKC, EPI, 4>(g, s, t);
   }
   return hipSuccess;

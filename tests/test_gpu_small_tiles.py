@@ -306,3 +306,21 @@ def test_stage_epilogues_between_the_powers_of_two(T, mb, hidden, ffn, tiles):
     params, X, G = inputs(cfg, 4600)
     ops = [(0, 0), (1, 0), (2, 0)]
     compare(cfg, run_gpu(cfg, params, X, G, ops), run_oracle(cfg, params, X, G, ops), TOL["bf16"])
+
+
+@pytest.mark.parametrize("M,N,K,loaders", [(2048, 2048, 1536, False), (2048, 2048, 1600, True), (1900, 2000, 256, False), (4864, 4096, 64, True)])
+def test_short_reductions_of_the_gelu_backward(M, N, K, loaders):
+    """Whole products in 128 x 128 tiles up to 1536 terms without wavefronts that only load (256 threads, not 512), a last round with them; the
+    bits of full tiles."""
+    import torch
+    torch.manual_seed(48)
+    dY, W, Z = (torch.randn(sh, device="cuda:0").bfloat16() for sh in ((M, K), (N, K), (M, N)))
+
+    def run(z, ks, stream=None):
+        return L().stage_kernel_gemm_act_bwd(1, 0, M, N, K, P(dY), K, P(W), K, P(z), N, None, ks, stream)
+    outs = [Z.clone() for _ in range(3)]
+    for z, ks in zip(outs, (0, 2, 4)):
+        assert run(z, ks) == 0
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    name, _, threads = launches(lambda stream: run(outs[0], 0, stream))[-1]
+    assert "gemm_quarter_kernel" in name and threads == (512 if loaders else 256)

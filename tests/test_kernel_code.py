@@ -87,7 +87,7 @@ def test_loading_wavefronts_wait_by_count(code_objects):
 
 
 # (kernel's tile, loads of one K tile per thread that loads, K tiles ahead)
-RINGS = [(r"gemm_quarter_kernelILb[01]ELi\dELi4E", 8, 4), (r"gemm_tiny_kernelILb[01]ELi\dELi0ELi4E", 4, 8), (r"gemm_tiny_kernelILb[01]ELi\dELi1ELi4E", 6, 4),
+RINGS = [(r"gemm_quarter_kernelILb[01]ELi\dELi4ELi4E", 8, 4), (r"gemm_tiny_kernelILb[01]ELi\dELi0ELi4E", 4, 8), (r"gemm_tiny_kernelILb[01]ELi\dELi1ELi4E", 6, 4),
          (r"gemm_mid_kernelILb[01]ELi\dELi0E", 5, 4), (r"gemm_mid_kernelILb[01]ELi\dELi[12]E", 10, 2), (r"gemm_mid_kernelILb[01]ELi\dELi3E", 3, 8)]
 
 
